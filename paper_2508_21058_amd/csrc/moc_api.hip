@@ -301,7 +301,8 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     std::vector<KvItem> kvitems;
     std::vector<TextTile> ttiles;
     int n_partials = 0;
-    const int nseg = (N + kTextSeg - 1) / kTextSeg;
+    const int seg = ((N + text_segments(N) - 1) / text_segments(N) + 31) / 32 * 32;   // equal segments of whole 32-query tiles
+    const int nseg = (N + seg - 1) / seg;
     for (int j = 0; j < C; ++j)
         if (kind[j])
             for (int k0 = off[j]; k0 < off[j + 1]; k0 += kKeyTile) {
@@ -310,8 +311,9 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
             }
     for (int s = 0; s < nseg; ++s)
         for (const TextTile &tt : ttiles)
-            kvitems.push_back(KvItem{tt.key_start, tt.key_len, s * kTextSeg, std::min(kTextSeg, N - s * kTextSeg), -1,
+            kvitems.push_back(KvItem{tt.key_start, tt.key_len, s * seg, std::min(seg, N - s * seg), -1,
                                      tt.first_partial + s, 0, 0});
+    const int n_kvtext = int(kvitems.size());
     for (int j = 0; j < C; ++j) {
         if (kind[j]) continue;
         for (int k0 = off[j]; k0 < off[j + 1]; k0 += kKeyTile) {
@@ -332,6 +334,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     m->n_atiles = int32_t(atiles.size());
     m->n_ranges = int32_t(aranges.size());
     m->n_kvitems = int32_t(kvitems.size());
+    m->n_kvtext = n_kvtext;
     m->n_text_tiles = int32_t(ttiles.size());
     m->n_partials = n_partials;
     m->h_off.assign(off, off + C + 1);

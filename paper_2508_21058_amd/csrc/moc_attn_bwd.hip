@@ -451,7 +451,7 @@ struct KvArgs {
     float *tpart_k, *tpart_v;
     const KvItem *items;
     const int32_t *list_off, *qlist;
-    int N, C, topk, n_partials, n_items, BH;
+    int N, C, topk, n_partials, n_items, n_text, BH;
     float scale, scale_log2;
 };
 
@@ -539,10 +539,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(KvArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int N = a.N;
-    int logical;
-    if (!xcd_remap((long long)a.n_items * a.BH, logical)) return;
-    const int bh = logical / a.n_items;
-    const KvItem item = a.items[logical - bh * a.n_items];
+    int bh, item_no;
+    if (!kv_item(a.n_items, a.n_text, a.BH, bh, item_no)) return;
+    const KvItem item = a.items[item_no];
 
     const T *qbase = static_cast<const T *>(a.q) + (size_t)bh * N * D;
     const T *kbase = static_cast<const T *>(a.k) + (size_t)bh * N * D;
@@ -901,10 +900,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     const bool grad_role = wave >= 4;
     const int w4 = wave & 3;
     const int N = a.N;
-    int logical;
-    if (!xcd_remap((long long)a.n_items * a.BH, logical)) return;
-    const int bh = logical / a.n_items;
-    const KvItem item = a.items[logical - bh * a.n_items];
+    int bh, item_no;
+    if (!kv_item(a.n_items, a.n_text, a.BH, bh, item_no)) return;
+    const KvItem item = a.items[item_no];
 
     // A tile of <= 32 keys (the ragged tail of a chunk) would leave three score waves
     // idle: instead the four take the same keys and the query tiles round-robin, each
@@ -1378,9 +1376,9 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
                 kv.qlist, kv.list_off, m->N, NK, m->C, reinterpret_cast<const float2 *>(kv.stats2),
                 reinterpret_cast<float2 *>(const_cast<float *>(kv.gstats2)));
         }
-        attn_bwd_dkdv_pipe_kernel<D><<<dim3(xcd_grid((long long)m->n_kvitems * BH)), dim3(512), 0, st>>>(kv);
+        attn_bwd_dkdv_pipe_kernel<D><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(512), 0, st>>>(kv);
     } else
-        attn_bwd_dkdv_kernel<D, T><<<dim3(xcd_grid((long long)m->n_kvitems * BH)), dim3(256), 0, st>>>(kv); }
+        attn_bwd_dkdv_kernel<D, T><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(256), 0, st>>>(kv); }
     if (m->n_text_tiles > 0) { MOC_PROF("text_reduce", st);
         text_reduce_kernel<D, T><<<dim3(m->n_text_tiles, BH), dim3(256), 0, st>>>(
             kv.tpart_k, kv.tpart_v, m->d_text_tiles, m->n_partials, m->N, static_cast<T *>(kv.dk),
@@ -1440,7 +1438,8 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     kv.tpart_v = reinterpret_cast<float *>(ws + L.tpart_v);
     kv.items = m->d_kvitems;
     kv.list_off = a.list_off; kv.qlist = a.qlist;
-    kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = m->n_partials; kv.n_items = m->n_kvitems; kv.BH = BH;
+    kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = m->n_partials; kv.n_items = m->n_kvitems; kv.n_text = m->n_kvtext;
+    kv.BH = BH;
     kv.scale = scale; kv.scale_log2 = a.scale_log2;
     if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, dq, st)
                                            : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, dq, st);

@@ -12,7 +12,16 @@ namespace moc {
 
 constexpr int kBM = 128;         // queries per workgroup in the query-stationary passes
 constexpr int kKeyTile = 128;    // keys per workgroup in the key-stationary pass (4 waves x 32)
-constexpr int kTextSeg = 16384;   // queries per partial of a text key tile in the key-stationary pass
+// Queries per partial of a text key tile in the key-stationary pass. A caption tile is attended by all
+// N queries, so its items are the longest of the pass: a quarter of the stream keeps the longest item
+// well under a compute unit's share of short streams (6,256 tokens: a whole-stream item is 196 steps
+// where a video item is 33 and a unit's share 182), 16384 bounds the partials of long ones (4096, 8192
+// and 16384 take the same time there), 256 keeps a segment's partial cheaper than its products.
+constexpr int kTextSegMin = 256, kTextSegMax = 16384;
+inline int text_segments(int N) {
+    const int target = N / 4 < kTextSegMin ? kTextSegMin : (N / 4 > kTextSegMax ? kTextSegMax : (N + 3) / 4);
+    return (N + target - 1) / target;
+}
 constexpr int kRowsPerBlk = 256; // queries per block of the list builder (one wave and one histogram column each)
 constexpr int kMaxListChunks = 16384;   // chunks the list builder's LDS histogram holds
 
@@ -37,7 +46,7 @@ struct TextTile { int32_t key_start, key_len, first_partial, n_partials; };
 
 struct moc_meta {
     int32_t N = 0, C = 0, T = 0, W = 0;
-    int32_t n_atiles = 0, n_ranges = 0, n_kvitems = 0, n_text_tiles = 0, n_partials = 0;
+    int32_t n_atiles = 0, n_ranges = 0, n_kvitems = 0, n_kvtext = 0, n_text_tiles = 0, n_partials = 0;
     int32_t max_chunk_len = 0;
     void *d_base = nullptr;
     size_t d_bytes = 0;
