@@ -1389,7 +1389,7 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
         MOC_PROF("attn_bwd_dq_routed", st);
         bool chunk_path = false;
         if constexpr (sizeof(T) == 2) {
-            if (m->max_chunk_len <= kChunkRows) {
+            if (m->max_routed_len <= kChunkRows) {
                 chunk_path = true;
                 const int groups = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
                 attn_bwd_dq_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);

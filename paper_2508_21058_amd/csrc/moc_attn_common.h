@@ -35,7 +35,12 @@ struct FwdArgs {
 
 // Chunk-stationary routed items (forward and dQ pass): a workgroup keeps the keys and values of one
 // chunk in LDS and serves a group of that chunk's query tiles from them.
-constexpr int kChunkRows = 288;       // resident keys (K region; the V region holds 32 rows more)
+// Resident keys (K region; the V region holds 32 rows more). Only chunks that can be routed to count:
+// captions are forced links and may be longer (512-token captions kept a 33k-token layer of 260-key
+// chunks off this path: 7.51 -> 7.32 ms a training step with it). With d = 64 the rows take half the
+// LDS, but 576 of them leave one workgroup per compute unit: 1,165 us a step of ragged chunks up to 340
+// keys against 1,058 in the tiled kernels, so the bound is the same.
+constexpr int kChunkRows = 288;
 constexpr int kGroupTiles = 16;       // query tiles (of kBM list entries) per workgroup
 
 // The GPU has 8 XCDs with private L2 caches and hands consecutive workgroups to

@@ -486,7 +486,7 @@ static hipError_t fwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, void *o, f
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;   // upper bound; surplus items exit at once
         MOC_PROF("attn_fwd_routed", st);
         if constexpr (sizeof(T) == 2) {
-            if (m->max_chunk_len <= kChunkRows) {
+            if (m->max_routed_len <= kChunkRows) {
                 const int groups = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
                 attn_fwd_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
             } else {

@@ -31,3 +31,10 @@ def _no_captions(shots, frames, frame):
     per = C // shots
     return mi.Layout("no_captions", offs, (np.arange(C) // per).astype(np.int32), np.arange(C, dtype=np.int32),
                      np.zeros((0, 2), dtype=np.int32))
+
+
+# a caption longer than the resident rows of the chunk-stationary kernels beside chunks that fit (288),
+# and chunks of one key too many
+@pytest.mark.parametrize("chunk", [288, 289])
+def test_routed_chunks_beside_a_long_caption(chunk):
+    run_case(mi.multishot_layout(2, 300, 2, 2 * chunk, chunk, "frame"), 1, 2, 128, 2, torch.bfloat16, seed=41)
