@@ -114,7 +114,7 @@ void prof_end(hipStream_t st) {
     if (!g_prof.empty()) (void)hipEventRecord(g_prof.back().e1, st);
 }
 
-AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, bool with_bwd) {
+AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, bool with_bwd) {
     AttnWs L{};
     size_t off = 0;
     const size_t C = m->C, N = m->N, slots = (size_t)topk + 1;
@@ -128,6 +128,7 @@ AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, bool with_bwd)
     L.qlist = take((size_t)BH * N * std::max(topk, 1) * 4);
     L.plse = take((size_t)BH * N * slots * 4);
     L.po = take((size_t)BH * N * slots * d * 2);
+    if (dtype == MOC_F32) L.cvt = take((size_t)BH * N * d * 2 * (with_bwd ? 4 : 3));   // bf16 copies of q, k, v (and dO)
     if (with_bwd) {
         L.delta = take((size_t)BH * N * 4);
         L.stats2 = take(((size_t)BH * N + 1) * 8);     // (lse2, delta) pairs + one pair holding (+inf, 0)
@@ -771,7 +772,7 @@ int moc_attn_workspace_bytes(const moc_meta *meta, int32_t B, int32_t H, int32_t
     if (!bytes) return fail(MOC_ERR_NULL, "bytes is NULL");
     int rc = check_common(meta, B, H, d, topk, dtype);
     if (rc) return rc;
-    *bytes = moc::attn_ws_layout(meta, B * H, d, topk, with_bwd != 0).total;
+    *bytes = moc::attn_ws_layout(meta, B * H, d, topk, dtype, with_bwd != 0).total;
     return MOC_OK;
 }
 
@@ -789,7 +790,7 @@ int attn_bwd_impl(const moc_meta *meta, int32_t B, int32_t H, int32_t d, int dty
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse) || misaligned(d_o) ||
         misaligned(dq) || misaligned(dk) || misaligned(dv) || misaligned(sel))
         return fail(MOC_ERR_ALIGN, "device pointers must be 16-byte aligned");
-    const moc::AttnWs L = moc::attn_ws_layout(meta, B * H, d, topk, true);
+    const moc::AttnWs L = moc::attn_ws_layout(meta, B * H, d, topk, dtype, true);
     if (!workspace || workspace_bytes < L.total) return fail(MOC_ERR_WORKSPACE, "attention workspace too small (with_bwd)");
     if (misaligned(workspace)) return fail(MOC_ERR_ALIGN, "workspace must be 16-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -817,7 +818,7 @@ int moc_attn_fwd(const moc_meta *meta, int32_t B, int32_t H, int32_t d, int dtyp
     if (!q || !k || !v || !o || !lse || (!sel && topk > 0)) return fail(MOC_ERR_NULL, "a tensor pointer is NULL");
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse) || misaligned(sel))
         return fail(MOC_ERR_ALIGN, "device pointers must be 16-byte aligned");
-    const moc::AttnWs L = moc::attn_ws_layout(meta, B * H, d, topk, false);
+    const moc::AttnWs L = moc::attn_ws_layout(meta, B * H, d, topk, dtype, false);
     if (!workspace || workspace_bytes < L.total) return fail(MOC_ERR_WORKSPACE, "attention workspace too small");
     if (misaligned(workspace)) return fail(MOC_ERR_ALIGN, "workspace must be 16-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -7,9 +7,9 @@
 //   dV_t = sum_i P_it dO_i,  dK_t = scale sum_i dS_it q_i,  dQ_i = scale sum_t dS_it k_t
 //
 // Two passes over the same dense items as the forward, neither uses atomics:
-//   dQ pass    query-stationary (forced-link items and routed items, exactly the
-//              forward's work list); each item writes its partial dQ to the slot
-//              of its (query, link) pair, a merge kernel adds the slots.
+//   dQ pass    query-stationary (routed items and forced-link items, exactly the
+//              forward's work list); a routed item writes its partial dQ to the slot
+//              of its (query, link) pair, the forced-link items add the slots.
 //   dK/dV pass key-stationary: a workgroup owns <= 128 keys of one chunk and
 //              walks every query that attends them - the chunk's window
 //              (contiguous) and the chunk's inverse routing list (gathered) -
@@ -24,7 +24,7 @@ namespace moc {
 template <int D, typename T>
 __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ o, const T *__restrict__ d_o, size_t rows,
                                                     const float *__restrict__ lse, float *__restrict__ delta,
-                                                    float *__restrict__ stats2) {
+                                                    float *__restrict__ stats2, bf16_t *__restrict__ do16) {
     constexpr int TPQ = D / 8, QPW = 256 / TPQ;
     const size_t row = (size_t)blockIdx.x * QPW + threadIdx.x / TPQ;
     const int c8 = threadIdx.x % TPQ;
@@ -35,6 +35,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ o, con
         Io<T>::load8f(d_o + row * D + c8 * 8, b);
 #pragma unroll
         for (int e = 0; e < 8; ++e) s = fmaf(a[e], b[e], s);
+        if constexpr (sizeof(T) == 4) Io<bf16_t>::store8(do16 + row * D + c8 * 8, b);   // what the products read
     }
 #pragma unroll
     for (int w = TPQ / 2; w >= 1; w >>= 1) s += __shfl_xor(s, w, 64);
@@ -122,7 +123,7 @@ __device__ __forceinline__ void dq_half_tile(const char *smem, LaneOffs<D> &lo, 
 // lane owns 8 features of a row, adds the routed partials (16-byte loads, a
 // batch in flight) and stores the final row.
 // `smem` must be free (barrier before); needs 4 * (32 * (D + 4) + 128) * 2 bytes.
-template <int D>
+template <int D, typename OT>
 __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, const f32x16 *acc, float scale,
                                                bool row_valid, int qi, size_t bhN, const FwdArgs &a) {
     constexpr int DB = D / 32, RS = D + 4;
@@ -174,12 +175,14 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o8[e] = fmaf(w[u], f[u][e], o8[e]);
         }
-        Io<bf16_t>::store8(static_cast<bf16_t *>(a.o_out) + row * D + cg * 8, o8);
+        Io<OT>::store8(static_cast<OT *>(a.o_out) + row * D + cg * 8, o8);
     }
 }
 
-template <int D, typename T, int MODE>
+// OT: storage type of dQ (forced-link items only)
+template <int D, int MODE, typename OT>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
+    typedef bf16_t T;
     constexpr int BN = 64;
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int TB = BN * D * 2;
@@ -198,8 +201,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
     const bool row_valid = r < it.q_count;
     const bool wave_active = wave * 32 < it.q_count;
     const int rc = row_valid ? r : it.q_count - 1;
-    int qi, slot;
-    if (MODE == MODE_ANCHOR) { qi = it.q_start + rc; slot = a.topk; }
+    int qi, slot = 0;
+    if (MODE == MODE_ANCHOR) { qi = it.q_start + rc; }
     else { const int e = it.entries[rc]; qi = e >> 5; slot = e & 31; }
 
     const T *qbase = static_cast<const T *>(a.q) + (size_t)bh * N * D;
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
     LaneOffs<D> lo;
     lo.init(lane);
 
-    TileLoader<D, T, BN> kld(tid), vld(tid);
+    TileLoader<D, BN> kld(tid), vld(tid);
     TileIter<BN> ti(it);
     int valid = ti.valid();
     bool more;
@@ -231,10 +234,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
         const size_t st = (size_t)ti.start() * D;
         kld.issue_rows(kbase + st, ti.valid(), reinterpret_cast<bf16_t *>(smem + buf * TB));
         vld.issue_rows(vbase + st, ti.valid(), reinterpret_cast<bf16_t *>(smem + (2 + buf) * TB));
-    };
-    auto commit = [&](int buf) {
-        kld.commit(reinterpret_cast<bf16_t *>(smem + buf * TB));
-        vld.commit(reinterpret_cast<bf16_t *>(smem + (2 + buf) * TB));
     };
     auto stage = [&](auto cur) {
         constexpr int CUR = decltype(cur)::value;
@@ -246,11 +245,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
             if (cur_valid > 32)
                 dq_half_tile<D, CUR * TB, (2 + CUR) * TB, 32>(smem, lo, qf, dof, dqacc, c, lse2, dl, cur_valid, lane);
         }
-        if (more) { commit(CUR ^ 1); __syncthreads(); }
+        if (more) { kld.commit(); __syncthreads(); }
         return more;
     };
     issue(0);
-    commit(0);
+    kld.commit();
     __syncthreads();
     while (true) {
         if (!stage(IC<0>{})) break;
@@ -258,17 +257,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
     }
 
     __syncthreads();      // tile buffers are free: reuse them for the output transpose
-    if constexpr (MODE == MODE_ANCHOR && sizeof(T) == 2) {
-        if (a.o_out) {      // the routed items are done: sum here, no forced-link partial, no merge kernel
-            sum_store_rows<D>(smem, wave, lane, dqacc, a.scale, row_valid, qi, (size_t)bh * N, a);
-            return;
-        }
+    if constexpr (MODE == MODE_ANCHOR) {   // the routed items are done: sum here, no forced-link partial
+        sum_store_rows<D, OT>(smem, wave, lane, dqacc, a.scale, row_valid, qi, (size_t)bh * N, a);
+    } else {
+        const size_t prow = ((size_t)bh * N + qi) * a.slots + slot;
+        store_rows_bf16<D>(smem, wave, lane, dqacc, a.scale, row_valid ? (int)prow : -1, a.po);
     }
-    const size_t prow = ((size_t)bh * N + qi) * a.slots + slot;
-    store_rows_bf16<D>(smem, wave, lane, dqacc, a.scale, row_valid ? (int)prow : -1, a.po);
 }
 
-// Routed dQ items, chunk-stationary (bf16 storage, chunks of at most kChunkRows keys): as in the
+// Routed dQ items, chunk-stationary (chunks of at most kChunkRows keys): as in the
 // forward, K and V of one chunk stay in LDS (K is read both as a row operand for S and transposed
 // for dQ from the same swizzled tile) and the eight waves stream the chunk's inverse list through
 // them independently, 32 list entries at a time: no barrier and no staging inside a chunk, K / V
@@ -287,14 +284,14 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int N = a.N, C = a.C;
-    const int groups_per_head = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
+    const int groups_per_head = (a.items_per_head + a.group - 1) / a.group;
     int logical;
     if (!xcd_remap((long long)groups_per_head * a.BH, logical)) return;
     const int bh = logical / groups_per_head;
     const int32_t *toff = a.tile_off + (size_t)bh * (C + 1);
     const int32_t *loff = a.list_off + (size_t)bh * (C + 1);
-    int t0 = (logical - bh * groups_per_head) * kGroupTiles;
-    const int t1 = min(t0 + kGroupTiles, toff[C]);
+    int t0 = (logical - bh * groups_per_head) * a.group;
+    const int t1 = min(t0 + a.group, toff[C]);
     if (t0 >= t1) return;
     int j;
     {
@@ -408,43 +405,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
     }
 }
 
-template <int D, typename T>
-__global__ __launch_bounds__(256) void dq_merge_kernel(const bf16_t *__restrict__ part,
-                                                       const uint32_t *__restrict__ vmask, int N, int topk,
-                                                       T *__restrict__ dq) {
-    constexpr int TPQ = D / 8, QPW = 256 / TPQ;
-    const int bh = blockIdx.y;
-    const int i = blockIdx.x * QPW + threadIdx.x / TPQ;
-    const int c8 = threadIdx.x % TPQ;
-    if (i >= N) return;
-    const int slots = topk + 1;
-    const size_t row = (size_t)bh * N + i;
-    const uint32_t used = topk > 0 ? vmask[row] : 0u;
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    const bf16_t *pbase = part + row * slots * D + c8 * 8;
-    for (int s0 = 0; s0 < slots; s0 += 4) {
-        float w[4], f[4][8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = s0 + u;
-            const bool ok = s == topk || (s < topk && ((used >> s) & 1u));
-            w[u] = ok ? 1.f : 0.f;
-            Io<bf16_t>::load8f(pbase + (size_t)(ok ? s : topk) * D, f[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = fmaf(w[u], f[u][e], acc[e]);
-    }
-    Io<T>::store8(dq + row * D + c8 * 8, acc);
-}
-
 // ------------------------------------------------------------------ dK/dV pass
 struct KvArgs {
     const void *q, *k, *v, *d_o;
-    const float *lse, *delta;
     const float *stats2;               // per query (lse * log2(e), delta); one extra pair (+inf, 0) at the end
     const float *gstats2;              // the same pairs gathered in the order of the inverse lists
     void *dk, *dv;
@@ -454,242 +417,6 @@ struct KvArgs {
     int N, C, topk, n_partials, n_items, n_text, BH;
     float scale, scale_log2;
 };
-
-// One block of 32 queries (rows ROW0.. of the staged 64-query Q and dO tiles at
-// byte offsets QOFF / DOOFF) against this wave's 32 keys:
-//   S = Q K^T, dP = dO V^T (row reads of Q, dO; K, V fragments in registers)
-//   P, dS (lane owns a key column, registers run over query rows)
-//   dV^T += dO^T P, dK^T += Q^T dS (Q, dO read transposed from the same tiles)
-template <int D, int QOFF, int DOOFF, int ROW0>
-__device__ __forceinline__ void dkdv_block(const char *smem, LaneOffs<D> &lo, const float *lse_s, const float *delta_s,
-                                           const bf16x8 *kf, const bf16x8 *vf, f32x16 *dkacc, f32x16 *dvacc,
-                                           float c, int nv, int lane) {
-    constexpr int KS = D / 16, DB = D / 32;
-    constexpr int RB = ROW0 * D * 2;
-    const int half = lane >> 5;
-    lo.pin();
-    f32x16 sacc, dpacc;
-    {
-        // the dO fragments reuse the registers of the Q fragments as those are consumed
-        bf16x8 fr[KS];
-#pragma unroll
-        for (int s = 0; s < KS; ++s) fr[s] = lo.template frag<QOFF + RB>(smem, s);
-        sacc = zero16();
-        dpacc = zero16();
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            sacc = mfma32(fr[s], kf[s], sacc);
-            fr[s] = lo.template frag<DOOFF + RB>(smem, s);
-        }
-#pragma unroll
-        for (int s = 0; s < KS; ++s) dpacc = mfma32(fr[s], vf[s], dpacc);
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-        for (int u = 0; u < KS - 4; ++u) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < KS; ++u) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int row = ROW0 + g * 8 + half * 4;
-        const f32x4 l4 = *reinterpret_cast<const f32x4 *>(lse_s + row);
-        const f32x4 d4 = *reinterpret_cast<const f32x4 *>(delta_s + row);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 4 * g + e;
-            float p = __builtin_amdgcn_exp2f(fmaf(sacc[i], c, -l4[e]));
-            if (row + e >= nv) p = 0.f;
-            sacc[i] = p;
-            dpacc[i] = p * (dpacc[i] - d4[e]);
-        }
-    }
-#define MOC_KV_STEP(KSTEP)                                                                                   \
-    {                                                                                                        \
-        bf16x8 dot[DB], qt[DB];                                                                              \
-        _Pragma("unroll") for (int b = 0; b < DB; ++b)                                                       \
-            dot[b] = lo.template tfrag<DOOFF + RB + (KSTEP) * 16 * D * 2>(smem, b);                          \
-        _Pragma("unroll") for (int b = 0; b < DB; ++b)                                                       \
-            qt[b] = lo.template tfrag<QOFF + RB + (KSTEP) * 16 * D * 2>(smem, b);                            \
-        const bf16x8 pf = acc_to_frag(sacc, KSTEP);                                                          \
-        const bf16x8 dsf = acc_to_frag(dpacc, KSTEP);                                                        \
-        _Pragma("unroll") for (int b = 0; b < DB; ++b) dvacc[b] = mfma32(dot[b], pf, dvacc[b]);              \
-        _Pragma("unroll") for (int b = 0; b < DB; ++b) dkacc[b] = mfma32(qt[b], dsf, dkacc[b]);              \
-    }
-    MOC_KV_STEP(0) MOC_KV_STEP(1)
-#undef MOC_KV_STEP
-}
-
-// Register-staged, double-buffered variant: used for fp32 storage (which must be
-// converted on the way into LDS).
-template <int D, typename T>
-__global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(KvArgs a) {
-    constexpr int BQ = 64;
-    constexpr int KS = D / 16, DB = D / 32;
-    constexpr int TB = BQ * D * 2;
-    // LDS: Q buffers at 0 and TB, dO buffers at 2 TB and 3 TB
-    __shared__ __attribute__((aligned(1024))) char smem[4 * TB];
-    __shared__ __attribute__((aligned(16))) float lse_s[2][BQ], delta_s[2][BQ];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-    const int N = a.N;
-    int bh, item_no;
-    if (!kv_item(a.n_items, a.n_text, a.BH, bh, item_no)) return;
-    const KvItem item = a.items[item_no];
-
-    const T *qbase = static_cast<const T *>(a.q) + (size_t)bh * N * D;
-    const T *kbase = static_cast<const T *>(a.k) + (size_t)bh * N * D;
-    const T *vbase = static_cast<const T *>(a.v) + (size_t)bh * N * D;
-    const T *dobase = static_cast<const T *>(a.d_o) + (size_t)bh * N * D;
-    const float *lse = a.lse + (size_t)bh * N;
-    const float *delta = a.delta + (size_t)bh * N;
-
-    // this wave's 32 keys (B operands stay in registers for the whole item)
-    // A tile of <= 32 keys (the ragged tail of a chunk) would leave three waves
-    // idle: instead all four waves take the same keys, split the query blocks
-    // among themselves and add their accumulators at the end.
-    const bool split = item.key_len <= 32;
-    const int kblk = split ? 0 : wave;
-    const int nk = min(32, item.key_len - kblk * 32);
-    const bool wave_active = nk > 0;
-    const int key = wave_active ? item.key_start + kblk * 32 + min(l32, nk - 1) : item.key_start;
-    bf16x8 kf[KS], vf[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        kf[s] = Io<T>::load8(kbase + (size_t)key * D + s * 16 + half * 8);
-        vf[s] = Io<T>::load8(vbase + (size_t)key * D + s * 16 + half * 8);
-    }
-    f32x16 dkacc[DB], dvacc[DB];
-#pragma unroll
-    for (int b = 0; b < DB; ++b) { dkacc[b] = zero16(); dvacc[b] = zero16(); }
-    LaneOffs<D> lo;
-    lo.init(lane);
-
-    // query sources: a contiguous range, then (video chunks) the chunk's routed list
-    const int nA = (item.q_len + BQ - 1) / BQ;
-    int cntB = 0;
-    const int32_t *entries = nullptr;
-    if (item.chunk >= 0 && a.topk > 0) {
-        const int32_t *loff = a.list_off + (size_t)bh * (a.C + 1);
-        cntB = loff[item.chunk + 1] - loff[item.chunk];
-        entries = a.qlist + (size_t)bh * N * a.topk + loff[item.chunk];
-    }
-    const int ntiles = nA + (cntB + BQ - 1) / BQ;
-    if (ntiles == 0) return;
-
-    TileLoader<D, T, BQ> qld(tid), dold(tid);
-    float lreg = 0.f, dreg = 0.f;
-    auto tile_valid = [&](int t) { return t < nA ? min(BQ, item.q_len - t * BQ) : min(BQ, cntB - (t - nA) * BQ); };
-    auto issue = [&](int t, int buf) {
-        const int nv = tile_valid(t);
-        bf16_t *qdst = reinterpret_cast<bf16_t *>(smem + buf * TB);
-        bf16_t *dodst = reinterpret_cast<bf16_t *>(smem + (2 + buf) * TB);
-        if (t < nA) {
-            const int q0 = item.q_start + t * BQ;
-            qld.issue_rows(qbase + (size_t)q0 * D, nv, qdst);
-            dold.issue_rows(dobase + (size_t)q0 * D, nv, dodst);
-            if (tid < BQ) { const int i = q0 + min(tid, nv - 1); lreg = lse[i] * kLog2e; dreg = delta[i]; }
-        } else {
-            const int32_t *en = entries + (t - nA) * BQ;
-            auto fn = [=](int r) { return en[min(r, nv - 1)] >> 5; };
-            qld.issue(qbase, fn, qdst);
-            dold.issue(dobase, fn, dodst);
-            if (tid < BQ) { const int i = fn(tid); lreg = lse[i] * kLog2e; dreg = delta[i]; }
-        }
-    };
-    auto commit = [&](int buf) {
-        qld.commit(reinterpret_cast<bf16_t *>(smem + buf * TB));
-        dold.commit(reinterpret_cast<bf16_t *>(smem + (2 + buf) * TB));
-        if (tid < BQ) { lse_s[buf][tid] = lreg; delta_s[buf][tid] = dreg; }
-    };
-    const float c = a.scale_log2;
-    int t = 0;
-    auto stage = [&](auto cur) {
-        constexpr int CUR = decltype(cur)::value;
-        const int nv = tile_valid(t);
-        const bool more = t + 1 < ntiles;
-        if (more) issue(t + 1, CUR ^ 1);
-        // split mode: wave w takes query block (w & 1) of the steps with parity (w >> 1)
-        const bool do0 = wave_active && (!split || (CUR == (wave >> 1) && (wave & 1) == 0));
-        const bool do1 = wave_active && nv > 32 && (!split || (CUR == (wave >> 1) && (wave & 1) == 1));
-        if (do0)
-            dkdv_block<D, CUR * TB, (2 + CUR) * TB, 0>(smem, lo, lse_s[CUR], delta_s[CUR], kf, vf, dkacc, dvacc, c, nv, lane);
-        if (do1)
-            dkdv_block<D, CUR * TB, (2 + CUR) * TB, 32>(smem, lo, lse_s[CUR], delta_s[CUR], kf, vf, dkacc, dvacc, c, nv, lane);
-        if (more) { commit(CUR ^ 1); __syncthreads(); }
-        ++t;
-        return more;
-    };
-    issue(0, 0);
-    commit(0);
-    __syncthreads();
-    while (true) {
-        if (!stage(IC<0>{})) break;
-        if (!stage(IC<1>{})) break;
-    }
-
-    if (split) {
-        // the four waves hold partial sums for the same keys in the same register
-        // layout: exchange them through LDS (16 KB per wave and tensor), wave 0 adds
-        float *xch = reinterpret_cast<float *>(smem);
-        static_assert(4 * DB * 16 * 64 * 4 <= 4 * TB, "exchange buffer must fit the tile buffers");
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            f32x16 *acc = pass == 0 ? dkacc : dvacc;
-            __syncthreads();
-#pragma unroll
-            for (int b = 0; b < DB; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) xch[((wave * DB + b) * 16 + i) * 64 + lane] = acc[b][i];
-            __syncthreads();
-            if (wave == 0) {
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        float v = 0.f;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) v += xch[((w * DB + b) * 16 + i) * 64 + lane];
-                        acc[b][i] = v;
-                    }
-            }
-        }
-        if (wave != 0) return;
-    }
-    if (!wave_active || l32 >= nk) return;
-    const float sc = a.scale;
-    if (item.partial < 0) {
-        T *dk = static_cast<T *>(a.dk) + ((size_t)bh * N + key) * D;
-        T *dv = static_cast<T *>(a.dv) + ((size_t)bh * N + key) * D;
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int x = b * 32 + g * 8 + half * 4;
-                Io<T>::store4(dk + x, dkacc[b][4 * g] * sc, dkacc[b][4 * g + 1] * sc, dkacc[b][4 * g + 2] * sc,
-                              dkacc[b][4 * g + 3] * sc);
-                Io<T>::store4(dv + x, dvacc[b][4 * g], dvacc[b][4 * g + 1], dvacc[b][4 * g + 2], dvacc[b][4 * g + 3]);
-            }
-    } else {
-        const size_t prow = ((size_t)bh * a.n_partials + item.partial) * kKeyTile + kblk * 32 + l32;
-        float *pk = a.tpart_k + prow * D, *pv = a.tpart_v + prow * D;
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int x = b * 32 + g * 8 + half * 4;
-                Io<float>::store4(pk + x, dkacc[b][4 * g] * sc, dkacc[b][4 * g + 1] * sc, dkacc[b][4 * g + 2] * sc,
-                                  dkacc[b][4 * g + 3] * sc);
-                Io<float>::store4(pv + x, dvacc[b][4 * g], dvacc[b][4 * g + 1], dvacc[b][4 * g + 2], dvacc[b][4 * g + 3]);
-            }
-    }
-}
 
 // (lse2, delta) of the queries of every inverse list, in list order, so the
 // key-stationary pass reads them as contiguous vectors
@@ -847,7 +574,7 @@ __device__ __forceinline__ void score_step(const char *smem, const LaneOffs<D> &
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// bf16 storage. Eight waves per workgroup, two per SIMD, in two roles: waves
+// Eight waves per workgroup, two per SIMD, in two roles: waves
 // 0-3 turn a query tile into P and dS for key blocks 0-3 (they hold the K and
 // V fragments and do all the exponentials), waves 4-7 hold the dK / dV
 // accumulators (one block of 32 features each, for all key blocks), consume P
@@ -873,7 +600,7 @@ __device__ __forceinline__ void score_step(const char *smem, const LaneOffs<D> &
 // included, goes through the async path, so no register-destination load
 // forces an early wait; the list words that name the gathered rows are scalar
 // loads issued one step before the copies that use them.
-template <int D>
+template <int D, typename OT>      // OT: storage type of dK and dV
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     typedef bf16_t T;
     constexpr int BQ = 32, NS = 7;
@@ -1313,13 +1040,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
             if (kb * 32 + l32 >= item.key_len) continue;
             if (item.partial < 0) {
                 const size_t row = (size_t)bh * N + item.key_start + kb * 32 + l32;
-                T *dkp = static_cast<T *>(a.dk) + row * D + db * 32, *dvp = static_cast<T *>(a.dv) + row * D + db * 32;
+                OT *dkp = static_cast<OT *>(a.dk) + row * D + db * 32, *dvp = static_cast<OT *>(a.dv) + row * D + db * 32;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int x = g * 8 + half * 4;
-                    Io<T>::store4(dkp + x, dk[j][4 * g] * dks, dk[j][4 * g + 1] * dks, dk[j][4 * g + 2] * dks,
-                                  dk[j][4 * g + 3] * dks);
-                    Io<T>::store4(dvp + x, dv[j][4 * g], dv[j][4 * g + 1], dv[j][4 * g + 2], dv[j][4 * g + 3]);
+                    Io<OT>::store4(dkp + x, dk[j][4 * g] * dks, dk[j][4 * g + 1] * dks, dk[j][4 * g + 2] * dks,
+                                   dk[j][4 * g + 3] * dks);
+                    Io<OT>::store4(dvp + x, dv[j][4 * g], dv[j][4 * g + 1], dv[j][4 * g + 2], dv[j][4 * g + 3]);
                 }
             } else {
                 const size_t prow = ((size_t)bh * a.n_partials + item.partial) * kKeyTile + kb * 32 + l32;
@@ -1359,26 +1086,24 @@ __global__ __launch_bounds__(256) void text_reduce_kernel(const float *__restric
     }
 }
 
+// T: storage type of the caller's tensors; o_in and do_in are the caller's o and dO, a / kv hold bf16 operands
 template <int D, typename T>
-static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv, const void *o, void *dq,
-                               hipStream_t st) {
+static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv, const void *o_in, const void *do_in,
+                               void *dq, hipStream_t st) {
     constexpr int QPW = 256 / (D / 8);
     const size_t rows = (size_t)BH * m->N;
     { MOC_PROF("delta", st);
     delta_kernel<D, T><<<dim3((unsigned)((rows + QPW - 1) / QPW)), dim3(256), 0, st>>>(
-        static_cast<const T *>(o), static_cast<const T *>(a.d_o), rows, a.lse, const_cast<float *>(a.delta),
-        const_cast<float *>(kv.stats2)); }
+        static_cast<const T *>(o_in), static_cast<const T *>(do_in), rows, a.lse, const_cast<float *>(a.delta),
+        const_cast<float *>(kv.stats2), static_cast<bf16_t *>(const_cast<void *>(a.d_o))); }
     { MOC_PROF("attn_bwd_dkdv", st);
-    if constexpr (sizeof(T) == 2) {
-        if (a.topk > 0) {
-            const int NK = m->N * a.topk;
-            gather_stats_kernel<<<dim3((NK + 255) / 256, BH), dim3(256), 0, st>>>(
-                kv.qlist, kv.list_off, m->N, NK, m->C, reinterpret_cast<const float2 *>(kv.stats2),
-                reinterpret_cast<float2 *>(const_cast<float *>(kv.gstats2)));
-        }
-        attn_bwd_dkdv_pipe_kernel<D><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(512), 0, st>>>(kv);
-    } else
-        attn_bwd_dkdv_kernel<D, T><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(256), 0, st>>>(kv); }
+    if (a.topk > 0) {
+        const int NK = m->N * a.topk;
+        gather_stats_kernel<<<dim3((NK + 255) / 256, BH), dim3(256), 0, st>>>(
+            kv.qlist, kv.list_off, m->N, NK, m->C, reinterpret_cast<const float2 *>(kv.stats2),
+            reinterpret_cast<float2 *>(const_cast<float *>(kv.gstats2)));
+    }
+    attn_bwd_dkdv_pipe_kernel<D, T><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(512), 0, st>>>(kv); }
     if (m->n_text_tiles > 0) { MOC_PROF("text_reduce", st);
         text_reduce_kernel<D, T><<<dim3(m->n_text_tiles, BH), dim3(256), 0, st>>>(
             kv.tpart_k, kv.tpart_v, m->d_text_tiles, m->n_partials, m->N, static_cast<T *>(kv.dk),
@@ -1387,26 +1112,18 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     if (a.topk > 0) {
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;
         MOC_PROF("attn_bwd_dq_routed", st);
-        bool chunk_path = false;
-        if constexpr (sizeof(T) == 2) {
-            if (m->max_routed_len <= kChunkRows) {
-                chunk_path = true;
-                const int groups = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
-                attn_bwd_dq_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
-            }
+        if (m->max_routed_len <= kChunkRows) {
+            a.group = group_tiles((long long)a.items_per_head * BH);
+            const int groups = (a.items_per_head + a.group - 1) / a.group;
+            attn_bwd_dq_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
+        } else {
+            attn_bwd_dq_kernel<D, MODE_ROUTED, bf16_t><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
         }
-        if (!chunk_path)
-            attn_bwd_dq_kernel<D, T, MODE_ROUTED><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
     }
-    { MOC_PROF("attn_bwd_dq_forced", st);
+    MOC_PROF("attn_bwd_dq_forced", st);
     a.items_per_head = m->n_atiles;
-    // bf16 storage: the forced-link items run after the routed ones and add the routed partials themselves
-    a.o_out = sizeof(T) == 2 ? dq : nullptr;
-    attn_bwd_dq_kernel<D, T, MODE_ANCHOR><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a); }
-    if (sizeof(T) == 2) return hipGetLastError();
-    MOC_PROF("dq_merge", st);
-    dq_merge_kernel<D, T><<<dim3((m->N + QPW - 1) / QPW, BH), dim3(256), 0, st>>>(a.po, a.vmask, m->N, a.topk,
-                                                                                static_cast<T *>(dq));
+    a.o_out = dq;        // the forced-link items run after the routed ones and add the routed partials themselves
+    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1415,6 +1132,14 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
                            void *dv, char *ws, const AttnWs &L, hipStream_t st) {
     FwdArgs a{};
     a.q = q; a.k = k; a.v = v; a.d_o = d_o;
+    if (dtype == MOC_F32) {
+        const size_t n = (size_t)BH * m->N * d;
+        bf16_t *c = reinterpret_cast<bf16_t *>(ws + L.cvt);
+        const hipError_t e = launch_to_bf16(q, k, v, c, n, st);
+        if (e != hipSuccess) return e;
+        a.q = c; a.k = c + n; a.v = c + 2 * n;
+        a.d_o = c + 3 * n;                      // written by the delta kernel
+    }
     a.po = reinterpret_cast<bf16_t *>(ws + L.po);
     a.plse = nullptr;
     a.N = m->N; a.C = m->C; a.topk = topk; a.slots = topk + 1;
@@ -1429,8 +1154,7 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     a.delta = reinterpret_cast<const float *>(ws + L.delta);
     a.gstats2 = reinterpret_cast<const float *>(ws + L.gstats2);
     KvArgs kv{};
-    kv.q = q; kv.k = k; kv.v = v; kv.d_o = d_o;
-    kv.lse = lse; kv.delta = a.delta;
+    kv.q = a.q; kv.k = a.k; kv.v = a.v; kv.d_o = a.d_o;
     kv.stats2 = reinterpret_cast<const float *>(ws + L.stats2);
     kv.gstats2 = reinterpret_cast<const float *>(ws + L.gstats2);
     kv.dk = dk; kv.dv = dv;
@@ -1441,10 +1165,10 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = m->n_partials; kv.n_items = m->n_kvitems; kv.n_text = m->n_kvtext;
     kv.BH = BH;
     kv.scale = scale; kv.scale_log2 = a.scale_log2;
-    if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, dq, st)
-                                           : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, dq, st);
-    return d == 128 ? bwd_dispatch<128, float>(m, BH, a, kv, o, dq, st)
-                    : bwd_dispatch<64, float>(m, BH, a, kv, o, dq, st);
+    if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, d_o, dq, st)
+                                           : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, d_o, dq, st);
+    return d == 128 ? bwd_dispatch<128, float>(m, BH, a, kv, o, d_o, dq, st)
+                    : bwd_dispatch<64, float>(m, BH, a, kv, o, d_o, dq, st);
 }
 
 }  // namespace moc

@@ -18,6 +18,7 @@ struct FwdArgs {
     float *plse;       // [BH, N, slots]   partial log-sum-exp (forward only)
     int N, C, topk, slots;
     int BH, items_per_head;   // work list of the launch: items_per_head entries per (batch, head)
+    int group;                // entries per workgroup (chunk-stationary kernels)
     float scale, scale_log2;
     const AnchorTile *atiles;
     const int32_t *arange_off;
@@ -29,7 +30,7 @@ struct FwdArgs {
     const float *gstats2;   // [BH, N*topk] pairs (lse * log2 e, delta) in inverse-list order
     // forced-link forward items with the merge fused into their epilogue
     const uint32_t *vmask;  // [BH, N] bit r: routed slot r of the query counts (set by the list builder)
-    void *o_out;            // [BH, N, D] final output
+    void *o_out;            // [BH, N, D] final output, in the caller's storage type
     float *lse_out;         // [BH, N] final log-sum-exp
 };
 
@@ -41,7 +42,14 @@ struct FwdArgs {
 // LDS, but 576 of them leave one workgroup per compute unit: 1,165 us a step of ragged chunks up to 340
 // keys against 1,058 in the tiled kernels, so the bound is the same.
 constexpr int kChunkRows = 288;
-constexpr int kGroupTiles = 16;       // query tiles (of kBM list entries) per workgroup
+// Query tiles (of kBM list entries) per workgroup: sixteen amortise the copy of a chunk's K and V; calls
+// with less than sixteen tiles per compute unit take fewer, so that every unit has a workgroup (1,088
+// tokens of two heads are 68 tiles: 158 us a training step in five groups, 101 in 68).
+constexpr int kGroupTiles = 16, kComputeUnits = 256;
+inline int group_tiles(long long total) {
+    const long long g = total / kComputeUnits;
+    return g < 1 ? 1 : (g > kGroupTiles ? kGroupTiles : (int)g);
+}
 
 // The GPU has 8 XCDs with private L2 caches and hands consecutive workgroups to
 // them round-robin. Work lists are ordered so that neighbours share K/V (or
@@ -145,35 +153,6 @@ template <int BN> struct TileIter {
     }
 };
 
-// Stages ROWS source rows of D features into a swizzled LDS tile (SwTile<D>),
-// 16 bytes per lane and pass, through registers (conversion to bf16 on the way)
-// so the global loads of the next tile overlap the math on the current one.
-// rowfn(r) gives the global row of tile row r (clamped by the caller).
-template <int D, typename T, int ROWS> struct RowStager {
-    static constexpr int CG = D / 8, RPP = 256 / CG, P = (ROWS + RPP - 1) / RPP;
-    int cg, rr;
-    bf16x8 reg[P];
-    __device__ __forceinline__ explicit RowStager(int tid) : cg(tid % CG), rr(tid / CG) {}
-    template <typename F> __device__ __forceinline__ void load_fn(const T *base, F rowfn) {
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const int row = rr + p * RPP;
-            if (ROWS % RPP == 0 || row < ROWS) reg[p] = Io<T>::load8(base + (size_t)rowfn(row) * D + cg * 8);
-        }
-    }
-    __device__ __forceinline__ void load(const T *base, int start, int valid) {
-        load_fn(base, [=](int r) { return start + min(r, valid - 1); });
-    }
-    __device__ __forceinline__ void store_sw(bf16_t *lds) const {
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const int row = rr + p * RPP;
-            if (ROWS % RPP == 0 || row < ROWS)
-                *reinterpret_cast<u32x4 *>(lds + SwTile<D>::off(row, cg)) = __builtin_bit_cast(u32x4, reg[p]);
-        }
-    }
-};
-
 // Epilogue of the query-stationary passes. A transposed accumulator holds, per
 // lane, 4-feature pieces of ONE row; storing those directly scatters 8-byte
 // writes over 32 rows per instruction and the L2 writes partial lines back
@@ -214,16 +193,13 @@ __device__ __forceinline__ void store_rows_bf16(char *smem, int wave, int lane, 
 }
 
 // Moves ROWS source rows of D features into a swizzled LDS tile (SwTile<D>).
-//   issue(base, rowfn, lds)  starts the transfer of a tile into `lds`
-//   commit(lds)              finishes it (before the barrier that publishes `lds`)
-// bf16 storage: asynchronous global->LDS loads (global_load_lds_dwordx4): no
-// staging registers, no LDS store instructions. One wave instruction fills 1 KB
-// of LDS, lane l writing bytes [16 l, 16 l + 16), so each lane fetches the
-// global element that belongs at its swizzled LDS position.
-// fp32 storage needs a conversion, so it goes through registers.
-template <int D, typename T, int ROWS> struct TileLoader;
-
-template <int D, int ROWS> struct TileLoader<D, bf16_t, ROWS> {
+//   issue_rows(tile, valid, lds)  starts the transfer of a tile into `lds`
+//   commit()                      waits for this wave's copies (before the barrier that publishes `lds`)
+// Asynchronous global->LDS loads (global_load_lds_dwordx4): no staging registers, no
+// LDS store instructions. One wave instruction fills 1 KB of LDS, lane l writing
+// bytes [16 l, 16 l + 16), so each lane fetches the global element that belongs at
+// its swizzled LDS position.
+template <int D, int ROWS> struct TileLoader {
     static constexpr int NW = 4;                        // waves of the workgroup that share the loads
     static constexpr int RPI = 512 / D;                 // rows per wave instruction
     static constexpr int NI = ROWS / RPI;               // wave instructions per tile
@@ -233,17 +209,6 @@ template <int D, int ROWS> struct TileLoader<D, bf16_t, ROWS> {
     __device__ __forceinline__ int slot(int p) const { return wave + NW * p; }
     __device__ __forceinline__ explicit TileLoader(int tid)
         : wave(__builtin_amdgcn_readfirstlane(tid >> 6)), rlo((tid & 63) / (D / 8)), cgp((tid & 63) % (D / 8)) {}
-    // arbitrary (gathered) rows: rowfn(r) is the global row of tile row r
-    template <typename F> __device__ __forceinline__ void issue(const bf16_t *base, F rowfn, bf16_t *lds) const {
-        const uint32_t at = lds_address(lds);      // one pointer conversion per tile, not one per copy
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const int n = slot(p);
-            const int row = n * RPI + rlo;
-            const int cg = cgp ^ SwTile<D>::sw(row);
-            async_copy16_at(base + (size_t)rowfn(row) * D + cg * 8, at + n * 1024);
-        }
-    }
     // contiguous rows [0, valid) of a tile whose first row is at `tile` (a
     // wave-uniform pointer): scalar base + one 32-bit lane offset per load
     __device__ __forceinline__ void issue_rows(const bf16_t *tile, int valid, bf16_t *lds) const {
@@ -258,19 +223,7 @@ template <int D, int ROWS> struct TileLoader<D, bf16_t, ROWS> {
         }
     }
     // the tile is complete once this wave's copies have landed (and the workgroup has met at a barrier)
-    __device__ __forceinline__ void commit(bf16_t *) const { wait_vmcnt<0>(); }
-};
-
-template <int D, int ROWS> struct TileLoader<D, float, ROWS> {
-    RowStager<D, float, ROWS> st;
-    __device__ __forceinline__ explicit TileLoader(int tid) : st(tid) {}
-    template <typename F> __device__ __forceinline__ void issue(const float *base, F rowfn, bf16_t *) {
-        st.load_fn(base, rowfn);
-    }
-    __device__ __forceinline__ void issue_rows(const float *tile, int valid, bf16_t *) {
-        st.load_fn(tile, [=](int r) { return min(r, valid - 1); });
-    }
-    __device__ __forceinline__ void commit(bf16_t *lds) const { st.store_sw(lds); }
+    __device__ __forceinline__ void commit() const { wait_vmcnt<0>(); }
 };
 
 }  // namespace moc

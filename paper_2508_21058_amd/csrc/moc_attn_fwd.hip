@@ -4,9 +4,16 @@
 // rows against contiguous key ranges":
 //   forced-link items  queries of one window tile x (all text spans + the window)
 //   routed items       queries gathered through a chunk's inverse list x that chunk
-// Every item produces a normalised partial output and its log-sum-exp in the
-// slot of the (query, link) pair; a merge kernel combines the <= topk+1 partials
-// of a query (the usual split-softmax identity), so no item ever waits on another.
+// The routed items run first and leave a normalised partial output and its
+// log-sum-exp in the slot of the (query, link) pair; the forced-link items combine
+// them with their own result in the epilogue (the usual split-softmax identity).
+//
+// Both kinds work on bf16 operands. fp32 storage is rounded to bf16 copies in the
+// workspace first (one pass over q, k, v; the rounding a load would apply), so tiles
+// travel to LDS asynchronously whatever the storage; outputs are written in the
+// storage type. Against converting on every load, which needs tiles staged through
+// registers and partials merged by kernels of their own, a training step of 13k
+// tokens and six heads went from 1,217 to 820 us (the conversions cost 26 us a pass).
 //
 // Per workgroup: 4 waves x 32 query rows. K and V tiles (64 keys) are staged
 // row-major in swizzled LDS tiles; V is read back through the transposing LDS
@@ -136,8 +143,9 @@ __device__ __forceinline__ void fwd_tile(const char *smem, LaneOffs<D> &lo, cons
 // wave's LDS patch as in store_rows_bf16; then every lane owns 8 features of a
 // row, adds the weighted routed partials (16-byte loads, a batch in flight) and
 // stores the final row. The forced-link partial never goes to memory.
-// `smem` must be free (barrier before); needs 4 * (32 * (D + 4) + 64) * 2 + 4 * 32 * 34 * 4 bytes.
-template <int D>
+// `smem` must be free (barrier before); needs merge_lds(D) bytes.
+constexpr int merge_lds(int D) { return 4 * (32 * (D + 4) + 64) * 2 + 4 * 32 * 34 * 4; }
+template <int D, typename OT>
 __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane, const f32x16 *acc, float m_run,
                                                  float l_tot, bool row_valid, int qi, size_t bhN, const FwdArgs &a) {
     constexpr int DB = D / 32, RS = D + 4, WS = 34;    // WS: floats per row of the weight table (32 weights, lse)
@@ -204,19 +212,21 @@ __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane,
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o8[e] = fmaf(w[u], f[u][e], o8[e]);
         }
-        Io<bf16_t>::store8(static_cast<bf16_t *>(a.o_out) + row * D + cg * 8, o8);
+        Io<OT>::store8(static_cast<OT *>(a.o_out) + row * D + cg * 8, o8);
         if (cg == 0) a.lse_out[row] = wts[r * WS + 32];
     }
 }
 
-template <int D, typename T, int MODE>
+// OT: storage type of the final output (forced-link items only)
+template <int D, int MODE, typename OT>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
+    typedef bf16_t T;
     constexpr int BN = 64;
     constexpr int KS = D / 16;   // feature steps of the QK product
     constexpr int DB = D / 32;   // 32-feature blocks of the output
     constexpr int TB = BN * D * 2;   // bytes per tile
     // LDS: K buffers at 0 and TB, V buffers at 2 TB and 3 TB
-    __shared__ __attribute__((aligned(1024))) char smem[4 * TB];
+    __shared__ __attribute__((aligned(1024))) char smem[MODE == MODE_ANCHOR && merge_lds(D) > 4 * TB ? merge_lds(D) : 4 * TB];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int N = a.N;
@@ -232,8 +242,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
     const bool row_valid = r < it.q_count;
     const bool wave_active = wave * 32 < it.q_count;
     const int rc = row_valid ? r : it.q_count - 1;
-    int qi, slot;
-    if (MODE == MODE_ANCHOR) { qi = it.q_start + rc; slot = a.topk; }
+    int qi, slot = 0;
+    if (MODE == MODE_ANCHOR) { qi = it.q_start + rc; }
     else { const int e = it.entries[rc]; qi = e >> 5; slot = e & 31; }
 
     const T *qbase = static_cast<const T *>(a.q) + (size_t)bh * N * D;
@@ -255,7 +265,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
     // Double-buffered pipeline, one barrier per tile: while tile t is consumed
     // from one LDS buffer, tile t+1 streams from global memory into the other.
     // The loop is unrolled by two so every access has a constant buffer offset.
-    TileLoader<D, T, BN> kld(tid), vld(tid);
+    TileLoader<D, BN> kld(tid), vld(tid);
     TileIter<BN> ti(it);
     int valid = ti.valid();
     bool more;
@@ -264,10 +274,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
         kld.issue_rows(kbase + st, ti.valid(), reinterpret_cast<bf16_t *>(smem + buf * TB));
         vld.issue_rows(vbase + st, ti.valid(), reinterpret_cast<bf16_t *>(smem + (2 + buf) * TB));
     };
-    auto commit = [&](int buf) {
-        kld.commit(reinterpret_cast<bf16_t *>(smem + buf * TB));
-        vld.commit(reinterpret_cast<bf16_t *>(smem + (2 + buf) * TB));
-    };
     auto stage = [&](auto cur) {
         constexpr int CUR = decltype(cur)::value;
         const int cur_valid = valid;
@@ -275,11 +281,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
         if (more) { valid = ti.valid(); issue(CUR ^ 1); }
         if (wave_active)
             fwd_tile<D, CUR * TB, (2 + CUR) * TB>(smem, lo, qf, oacc, m_run, l_run, c, cur_valid, lane);
-        if (more) { commit(CUR ^ 1); __syncthreads(); }
+        if (more) { kld.commit(); __syncthreads(); }
         return more;       // false: that was the last tile
     };
     issue(0);
-    commit(0);
+    kld.commit();
     __syncthreads();
     while (true) {
         if (!stage(IC<0>{})) break;
@@ -288,21 +294,18 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
 
     __syncthreads();      // every wave is done with the tile buffers: reuse them for the output transpose
     const float l_tot = xhalf_sum(l_run);
-    const float inv = 1.f / l_tot;
-    if constexpr (MODE == MODE_ANCHOR && sizeof(T) == 2) {
-        if (a.o_out) {      // the routed items are done: combine here, no forced-link partial, no merge kernel
-            merge_store_rows<D>(smem, wave, lane, oacc, m_run, l_tot, row_valid, qi, (size_t)bh * N, a);
-            return;
-        }
+    if constexpr (MODE == MODE_ANCHOR) {   // the routed items are done: combine here, no forced-link partial
+        merge_store_rows<D, OT>(smem, wave, lane, oacc, m_run, l_tot, row_valid, qi, (size_t)bh * N, a);
+    } else {
+        const size_t prow = ((size_t)bh * N + qi) * a.slots + slot;
+        store_rows_bf16<D>(smem, wave, lane, oacc, 1.f / l_tot, row_valid ? (int)prow : -1, a.po);
+        if (row_valid && half == 0) a.plse[prow] = m_run * a.scale + __logf(l_tot);
     }
-    const size_t prow = ((size_t)bh * N + qi) * a.slots + slot;
-    store_rows_bf16<D>(smem, wave, lane, oacc, inv, row_valid ? (int)prow : -1, a.po);
-    if (row_valid && half == 0) a.plse[prow] = m_run * a.scale + __logf(l_tot);
 }
 
-// Routed items, chunk-stationary (bf16 storage, chunks of at most kChunkRows
+// Routed items, chunk-stationary (chunks of at most kChunkRows
 // keys): the K and V rows of a chunk stay in LDS while the chunk's inverse list
-// streams past. A workgroup takes kGroupTiles consecutive routed items (128
+// streams past. A workgroup takes up to kGroupTiles consecutive routed items (128
 // list entries each, usually of one or two chunks); per chunk it loads K / V
 // once, then its eight waves work through the 32-query blocks on their own:
 // query fragments straight from global memory into registers, the
@@ -324,14 +327,14 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int N = a.N, C = a.C;
-    const int groups_per_head = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
+    const int groups_per_head = (a.items_per_head + a.group - 1) / a.group;
     int logical;
     if (!xcd_remap((long long)groups_per_head * a.BH, logical)) return;
     const int bh = logical / groups_per_head;
     const int32_t *toff = a.tile_off + (size_t)bh * (C + 1);
     const int32_t *loff = a.list_off + (size_t)bh * (C + 1);
-    int t0 = (logical - bh * groups_per_head) * kGroupTiles;
-    const int t1 = min(t0 + kGroupTiles, toff[C]);
+    int t0 = (logical - bh * groups_per_head) * a.group;
+    const int t1 = min(t0 + a.group, toff[C]);
     if (t0 >= t1) return;
     int j;
     {
@@ -432,82 +435,39 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
     }
 }
 
-// o = sum_s exp(lse_s - lse) o_s over the forced-link slot and the used routed slots
-template <int D, typename T>
-__global__ __launch_bounds__(256) void fwd_merge_kernel(const bf16_t *__restrict__ po,
-                                                        const float *__restrict__ plse,
-                                                        const uint32_t *__restrict__ vmask, int N, int topk,
-                                                        T *__restrict__ o, float *__restrict__ lse) {
-    constexpr int TPQ = D / 8, QPW = 256 / TPQ;
-    const int bh = blockIdx.y;
-    const int i = blockIdx.x * QPW + threadIdx.x / TPQ;
-    const int c8 = threadIdx.x % TPQ;
-    if (i >= N) return;
-    const int slots = topk + 1;
-    const size_t row = (size_t)bh * N + i;
-    const float *pl = plse + row * slots;
-    const uint32_t used = topk > 0 ? vmask[row] : 0u;       // the routed slots that count
-    float mx = pl[topk];
-    for (int s = 0; s < topk; ++s)
-        if ((used >> s) & 1u) mx = fmaxf(mx, pl[s]);
-    float z = __expf(pl[topk] - mx);
-    for (int s = 0; s < topk; ++s)
-        if ((used >> s) & 1u) z += __expf(pl[s] - mx);
-    const float tot = mx + __logf(z);
-    // unused slots read the forced-link slot again with weight 0, so all loads
-    // are unconditional and several are in flight
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    const bf16_t *pbase = po + row * slots * D + c8 * 8;
-    for (int s0 = 0; s0 < slots; s0 += 4) {
-        float w[4], f[4][8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = s0 + u;
-            const bool ok = s == topk || (s < topk && ((used >> s) & 1u));
-            const int src = ok ? s : topk;
-            w[u] = ok ? __expf(pl[src] - tot) : 0.f;
-            Io<bf16_t>::load8f(pbase + (size_t)src * D, f[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = fmaf(w[u], f[u][e], acc[e]);
-    }
-    Io<T>::store8(o + row * D + c8 * 8, acc);
-    if (c8 == 0) lse[row] = tot;
+// fp32 -> bf16 copies of three tensors of n elements (n a multiple of 8), 8 elements a lane; bound by HBM
+__global__ __launch_bounds__(256) void to_bf16_kernel(const float *x0, const float *x1, const float *x2, bf16_t *out, size_t n) {
+    const float *x = blockIdx.y == 0 ? x0 : (blockIdx.y == 1 ? x1 : x2);
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (i < n) *reinterpret_cast<bf16x8 *>(out + blockIdx.y * n + i) = Io<float>::load8(x + i);
 }
 
-template <int D, typename T>
+hipError_t launch_to_bf16(const void *q, const void *k, const void *v, void *out, size_t n, hipStream_t st) {
+    MOC_PROF("to_bf16", st);
+    to_bf16_kernel<<<dim3((unsigned)((n / 8 + 255) / 256), 3), dim3(256), 0, st>>>(
+        static_cast<const float *>(q), static_cast<const float *>(k), static_cast<const float *>(v),
+        static_cast<bf16_t *>(out), n);
+    return hipGetLastError();
+}
+
+template <int D, typename OT>
 static hipError_t fwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, void *o, float *lse, hipStream_t st) {
     a.BH = BH;
     if (a.topk > 0) {
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;   // upper bound; surplus items exit at once
         MOC_PROF("attn_fwd_routed", st);
-        if constexpr (sizeof(T) == 2) {
-            if (m->max_routed_len <= kChunkRows) {
-                const int groups = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
-                attn_fwd_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
-            } else {
-                attn_fwd_kernel<D, T, MODE_ROUTED><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
-            }
+        if (m->max_routed_len <= kChunkRows) {
+            a.group = group_tiles((long long)a.items_per_head * BH);
+            const int groups = (a.items_per_head + a.group - 1) / a.group;
+            attn_fwd_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
         } else {
-            attn_fwd_kernel<D, T, MODE_ROUTED><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
+            attn_fwd_kernel<D, MODE_ROUTED, bf16_t><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
         }
     }
-    // bf16 storage: the forced-link items run after the routed ones and merge in their epilogue
-    // (needs the LDS of the tile buffers to hold the transposition patches and the weight table)
-    const bool fuse = sizeof(T) == 2 && 4 * (32 * (D + 4) + 64) * 2 + 4 * 32 * 34 * 4 <= 4 * 64 * D * 2;
-    { MOC_PROF("attn_fwd_forced", st);
+    MOC_PROF("attn_fwd_forced", st);
     a.items_per_head = m->n_atiles;
-    a.o_out = fuse ? o : nullptr; a.lse_out = lse;
-    attn_fwd_kernel<D, T, MODE_ANCHOR><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a); }
-    if (fuse) return hipGetLastError();
-    MOC_PROF("fwd_merge", st);
-    constexpr int QPW = 256 / (D / 8);
-    fwd_merge_kernel<D, T><<<dim3((m->N + QPW - 1) / QPW, BH), dim3(256), 0, st>>>(
-        a.po, a.plse, a.vmask, m->N, a.topk, static_cast<T *>(o), lse);
+    a.o_out = o; a.lse_out = lse;
+    attn_fwd_kernel<D, MODE_ANCHOR, OT><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -515,6 +475,13 @@ hipError_t launch_attn_fwd(const moc_meta *m, int BH, int d, int dtype, const vo
                            int topk, float scale, void *o, float *lse, char *ws, const AttnWs &L, hipStream_t st) {
     FwdArgs a{};
     a.q = q; a.k = k; a.v = v;
+    if (dtype == MOC_F32) {
+        const size_t n = (size_t)BH * m->N * d;
+        bf16_t *c = reinterpret_cast<bf16_t *>(ws + L.cvt);
+        const hipError_t e = launch_to_bf16(q, k, v, c, n, st);
+        if (e != hipSuccess) return e;
+        a.q = c; a.k = c + n; a.v = c + 2 * n;
+    }
     a.po = reinterpret_cast<bf16_t *>(ws + L.po);
     a.plse = reinterpret_cast<float *>(ws + L.plse);
     a.N = m->N; a.C = m->C; a.topk = topk; a.slots = topk + 1;

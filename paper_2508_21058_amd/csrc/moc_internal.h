@@ -102,9 +102,9 @@ hipError_t launch_probe(int kind, void *buf, size_t bytes, int iters, hipStream_
 
 // Layout of the attention workspace (byte offsets); shared by fwd and bwd.
 struct AttnWs {
-    size_t cnt, list_off, tile_off, vmask, gsum, cnt_blk, qlist, plse, po, delta, stats2, gstats2, tpart_k, tpart_v, total;
+    size_t cnt, list_off, tile_off, vmask, gsum, cnt_blk, qlist, plse, po, cvt, delta, stats2, gstats2, tpart_k, tpart_v, total;
 };
-AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, bool with_bwd);
+AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, bool with_bwd);
 
 // Route workspace: pooled keys split into three bf16 planes (hi, mid, lo with
 // hi + mid + lo == the fp32 value), [BH][3][Cpad][d], Cpad = C rounded up to 32, pad rows zero.
@@ -127,6 +127,9 @@ hipError_t fused_wait_flag(int *timed_out);
 // counts -> offsets -> inverse lists (per head and chunk: the queries that routed to it)
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws,
                               const AttnWs &L, hipStream_t st);
+
+// bf16 copies of three fp32 tensors of n elements each, back to back in `out`
+hipError_t launch_to_bf16(const void *q, const void *k, const void *v, void *out, size_t n, hipStream_t st);
 
 // (both read the lists and the slot masks launch_build_lists left in the workspace)
 hipError_t launch_attn_fwd(const moc_meta *m, int BH, int d, int dtype, const void *q, const void *k,

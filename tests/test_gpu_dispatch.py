@@ -38,3 +38,10 @@ def _no_captions(shots, frames, frame):
 @pytest.mark.parametrize("chunk", [288, 289])
 def test_routed_chunks_beside_a_long_caption(chunk):
     run_case(mi.multishot_layout(2, 300, 2, 2 * chunk, chunk, "frame"), 1, 2, 128, 2, torch.bfloat16, seed=41)
+
+
+# fp32 storage through the same kernels as bf16: both head sizes, the chunk-stationary and the tiled
+# routed items, one group per workgroup (small calls) and ragged last tiles; k = 0 leaves forced links alone
+@pytest.mark.parametrize("d,chunk,topk", [(64, 33, 3), (128, 288, 2), (128, 300, 2), (64, 300, 1), (128, 65, 0)])
+def test_fp32_storage(d, chunk, topk):
+    run_case(mi.stream_layout(2, 37, 4 * chunk + 5, chunk, "chunk"), 1, 3, d, topk, torch.float32, seed=51 + chunk)
