@@ -1063,7 +1063,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     }
 }
 
-// sums the per-segment partials of a text key tile in a fixed order
+// Sums the per-segment partials of a text key tile in a fixed order, one float4 of dK and of dV a
+// thread; bound by HBM. A workgroup per 256 of them, not per tile: a call has few caption tiles (48 at
+// 6,256 tokens and 24 heads: 35 us in 48 workgroups, 6.5 in 768).
 template <int D, typename T>
 __global__ __launch_bounds__(256) void text_reduce_kernel(const float *__restrict__ tpart_k,
                                                           const float *__restrict__ tpart_v,
@@ -1072,7 +1074,8 @@ __global__ __launch_bounds__(256) void text_reduce_kernel(const float *__restric
     const TextTile tt = tiles[blockIdx.x];
     const int bh = blockIdx.y;
     constexpr int V4 = D / 4;                       // float4 groups per row
-    for (int u = threadIdx.x; u < tt.key_len * V4; u += 256) {
+    const int u = blockIdx.z * 256 + threadIdx.x;
+    if (u < tt.key_len * V4) {
         const int kr = u / V4, x = (u % V4) * 4;
         f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
         for (int p = 0; p < tt.n_partials; ++p) {
@@ -1105,7 +1108,7 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     }
     attn_bwd_dkdv_pipe_kernel<D, T><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(512), 0, st>>>(kv); }
     if (m->n_text_tiles > 0) { MOC_PROF("text_reduce", st);
-        text_reduce_kernel<D, T><<<dim3(m->n_text_tiles, BH), dim3(256), 0, st>>>(
+        text_reduce_kernel<D, T><<<dim3(m->n_text_tiles, BH, kKeyTile * (D / 4) / 256), dim3(256), 0, st>>>(
             kv.tpart_k, kv.tpart_v, m->d_text_tiles, m->n_partials, m->N, static_cast<T *>(kv.dk),
             static_cast<T *>(kv.dv)); }
     a.BH = BH;
