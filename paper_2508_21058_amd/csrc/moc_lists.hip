@@ -14,10 +14,10 @@
 //          written out whole as row `block` of a [blocks][C] table;
 //   scan   down the blocks of every chunk (a block's first position inside the
 //          chunk's list), then across the chunks (list offsets, tile offsets);
-//   fill   one wave per block walks its queries in order; the lanes hold the
-//          entries of ONE query, whose chunks are distinct, and take their
-//          positions from LDS counters. LDS operations of a wave complete in
-//          program order, so the positions do not depend on scheduling.
+//   fill   one wave per block walks its queries in order and takes their
+//          positions from LDS cursors (see fill_rows), so they do not depend on
+//          scheduling.
+// Calls with few entries do all three in one workgroup per head.
 // An entry packs query and slot as (i << 5) | r (r < MOC_MAX_TOPK = 32).
 //
 // Which entries of a selection row count (Sec. 3.3 pre-routing mask): forced
@@ -26,48 +26,129 @@
 // row and anything outside [0, C). The union M(i) + R(i) is a set. Bit r of
 // vmask[query] says whether slot r counts; the attention epilogues read the
 // same word, so a dropped slot is never merged.
-#include "moc_device.h"
+#include "moc_attn_common.h"
 #include "moc_internal.h"
 
 namespace moc {
 
-// Both passes below walk a block of kRowsPerBlk queries 64 / topk queries at a time: lane L holds
-// entry L of the step's rows (query L / topk, slot L % topk), read with one coalesced load.
+// The passes below walk their queries 64 / topk at a time: lane L holds entry L of the step's rows
+// (query L / topk, slot L % topk), read with one coalesced load. The loads of kListUnroll steps are in
+// flight together: a step is a chain of two dependent loads, and small calls have few waves to cover it.
+constexpr int kListUnroll = 4;
 
-// One wave per block. An entry counts if it names a video chunk (rw >= 0) outside the query's own
-// window that no earlier slot of the row names (the row-mates sit in the neighbouring lanes).
+struct ListLane {
+    int rpb, mu, r;      // queries per step (topk <= 32: at least two), this lane's query of the step and its slot
+    bool on;
+    __device__ __forceinline__ explicit ListLane(int topk, int lane)
+        : rpb(64 / topk), mu(lane / topk), r(lane - lane / topk * topk), on(lane / topk < 64 / topk) {}
+};
+
+// Counts the entries of queries [i0, i0 + nrow) into hist and writes their slot masks. An entry counts
+// if it names a video chunk (rw >= 0) outside the query's own window that no earlier slot of the row
+// names (the row-mates sit in the neighbouring lanes). sel and vmask point at the head's first query.
+__device__ __forceinline__ void count_rows(const int32_t *__restrict__ sel, int i0, int nrow, int topk, int C, int lane,
+                                           const int32_t *__restrict__ chunk_of, const int32_t *__restrict__ win,
+                                           const int32_t *__restrict__ rw, uint32_t *__restrict__ vmask,
+                                           int32_t *hist) {
+    const ListLane L(topk, lane);
+    const int32_t *src = sel + (size_t)i0 * topk;
+    uint32_t *vm = vmask + i0;
+    const uint32_t rowbits = topk >= 32 ? 0xffffffffu : ((1u << topk) - 1u);
+    for (int u0 = 0; u0 < nrow; u0 += kListUnroll * L.rpb) {
+        int j[kListUnroll], wq[kListUnroll], w[kListUnroll];
+#pragma unroll
+        for (int t = 0; t < kListUnroll; ++t) {
+            const int u = u0 + t * L.rpb + L.mu;
+            const bool in = L.on && u < nrow;
+            const int jt = src[in ? u * topk + L.r : 0];       // (plain loads: a load inside a branch is waited for there)
+            wq[t] = chunk_of[i0 + (in ? u : 0)];
+            j[t] = in ? jt : -1;
+        }
+#pragma unroll
+        for (int t = 0; t < kListUnroll; ++t) {
+            wq[t] = win[wq[t]];
+            const bool known = j[t] >= 0 && j[t] < C;
+            const int wt = rw[known ? j[t] : 0];
+            w[t] = known ? wt : -1;
+        }
+#pragma unroll
+        for (int t = 0; t < kListUnroll; ++t) {
+            const int u = u0 + t * L.rpb + L.mu;
+            bool ok = w[t] >= 0 && w[t] != wq[t];
+            for (int p = 0; p + 1 < topk; ++p) {
+                const int other = __shfl(j[t], L.mu * topk + p, 64);
+                if (p < L.r && other == j[t]) ok = false;
+            }
+            if (ok) atomicAdd(&hist[j[t]], 1);
+            const unsigned long long bal = __ballot(ok);
+            if (L.on && u < nrow && L.r == 0) vm[u] = (uint32_t)(bal >> (L.mu * topk)) & rowbits;
+        }
+    }
+}
+
+// Writes the list entries of queries [i0, i0 + nrow); cursor[j] is the next free position of chunk j's
+// list for them. Lanes of one step that name the same chunk belong to different queries (the slots that
+// count name distinct chunks) and take consecutive positions in lane order, that is in query order: the
+// lanes find each other through one ballot per bit of the chunk index, each adds its rank to the
+// cursor, and the last of them moves it. LDS operations of a wave complete in program order, so the
+// next step reads what this one wrote. (One LDS add per query of the step, the obvious way to the same
+// order, waits for LDS up to 64 / topk times a step: 24.3 us against 17.0 at 9k tokens, sixteen heads and k = 6.
+// At 114k tokens the scattered 4-byte stores bound the pass, 200 us either way.)
+__device__ __forceinline__ void fill_rows(const int32_t *__restrict__ sel, int i0, int nrow, int topk, int bits, int lane,
+                                          const uint32_t *__restrict__ vmask, int32_t *cursor,
+                                          int32_t *__restrict__ qlist) {
+    const ListLane L(topk, lane);
+    const int32_t *src = sel + (size_t)i0 * topk;
+    const uint32_t *vm = vmask + i0;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int u0 = 0; u0 < nrow; u0 += kListUnroll * L.rpb) {
+        int j[kListUnroll];
+        uint32_t used[kListUnroll];
+        bool ok[kListUnroll];
+#pragma unroll
+        for (int t = 0; t < kListUnroll; ++t) {
+            const int u = u0 + t * L.rpb + L.mu;
+            const bool in = L.on && u < nrow;
+            j[t] = src[in ? u * topk + L.r : 0];
+            used[t] = vm[in ? u : 0];
+        }
+#pragma unroll
+        for (int t = 0; t < kListUnroll; ++t) {
+            const int u = u0 + t * L.rpb + L.mu;
+            ok[t] = L.on && u < nrow && ((used[t] >> L.r) & 1u);
+        }
+#pragma unroll
+        for (int t = 0; t < kListUnroll; ++t) {
+            unsigned long long same = __ballot(ok[t]);
+            for (int b = 0; b < bits; ++b) {
+                const bool bit = (j[t] >> b) & 1;
+                const unsigned long long bal = __ballot(bit);
+                same &= bit ? bal : ~bal;
+            }
+            if (ok[t]) {
+                const int pos = cursor[j[t]] + __popcll(same & below);
+                if ((same >> lane) == 1ull) cursor[j[t]] = pos + 1;
+                qlist[pos] = ((i0 + u0 + t * L.rpb + L.mu) << 5) | L.r;
+            }
+            asm volatile("" ::: "memory");      // another lane may have moved the cursor this lane reads next
+        }
+    }
+}
+
+// One wave per block of kRowsPerBlk queries.
 __global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restrict__ sel, int N, int topk, int C,
                                                         const int32_t *__restrict__ chunk_of,
                                                         const int32_t *__restrict__ win,
-                                                        const int32_t *__restrict__ rw, int NB,
+                                                        const int32_t *__restrict__ rw, int NB, int BH,
                                                         uint32_t *__restrict__ vmask, int32_t *__restrict__ cnt_blk) {
     extern __shared__ int32_t hist[];    // [C]
-    const int bh = blockIdx.y, blk = blockIdx.x, lane = threadIdx.x;
+    int logical;
+    if (!xcd_remap((long long)NB * BH, logical)) return;
+    const int bh = logical / NB, blk = logical - bh * NB, lane = threadIdx.x;
     const int i0 = blk * kRowsPerBlk, nrow = min(kRowsPerBlk, N - i0);
     for (int b = lane; b < C; b += 64) hist[b] = 0;
     __syncthreads();
-    const int rpb = 64 / topk;                     // queries per step (topk <= 32: at least two)
-    const int mu = lane / topk, r = lane - mu * topk;
-    const bool lane_on = mu < rpb;
-    const int32_t *src = sel + ((size_t)bh * N + i0) * topk;
-    uint32_t *vm = vmask + (size_t)bh * N + i0;
-    const uint32_t rowbits = topk >= 32 ? 0xffffffffu : ((1u << topk) - 1u);
-    for (int u0 = 0; u0 < nrow; u0 += rpb) {
-        const int u = u0 + mu;
-        const bool in = lane_on && u < nrow;
-        const int j = in ? src[(size_t)u * topk + r] : -1;
-        const int wq = in ? win[chunk_of[i0 + u]] : -1;
-        bool ok = j >= 0 && j < C;
-        const int w = ok ? rw[j] : -1;
-        ok = ok && w >= 0 && w != wq;
-        for (int p = 0; p + 1 < topk; ++p) {
-            const int other = __shfl(j, mu * topk + p, 64);
-            if (p < r && other == j) ok = false;
-        }
-        if (ok) atomicAdd(&hist[j], 1);
-        const unsigned long long bal = __ballot(ok);
-        if (in && r == 0) vm[u] = (uint32_t)(bal >> (mu * topk)) & rowbits;
-    }
+    count_rows(sel + (size_t)bh * N * topk, i0, nrow, topk, C, lane, chunk_of, win, rw, vmask + (size_t)bh * N, hist);
     __syncthreads();
     int32_t *out = cnt_blk + ((size_t)bh * NB + blk) * C;
     for (int b = lane; b < C; b += 64) out[b] = hist[b];
@@ -147,47 +228,80 @@ __global__ __launch_bounds__(256) void list_scan_kernel(const int32_t *__restric
     }
 }
 
-// One wave per block. The positions are handed out query by query: one LDS instruction per query,
-// executed by that query's lanes only. The slots that count name distinct chunks, so the lanes of
-// one instruction never meet in a counter, and the instructions of consecutive queries reach the
-// counters in program order. All 64 lanes then store their entries with one instruction.
-__global__ __launch_bounds__(64) void list_fill_kernel(const int32_t *__restrict__ sel, int N, int topk, int C,
-                                                       const uint32_t *__restrict__ vmask, int NB,
+// One wave per block. A block writes a few words into every chunk's list; neighbouring blocks of a head
+// write the words next to them, so they run on one XCD, whose L2 then holds whole lines (203 -> 197 us at
+// 114k tokens, 24 heads, k = 8; 1,034 -> 866 at 457k tokens, six heads, k = 16).
+__global__ __launch_bounds__(64) void list_fill_kernel(const int32_t *__restrict__ sel, int N, int topk, int C, int bits,
+                                                       const uint32_t *__restrict__ vmask, int NB, int BH,
                                                        const int32_t *__restrict__ cnt_blk,
                                                        const int32_t *__restrict__ list_off,
                                                        int32_t *__restrict__ qlist) {
     extern __shared__ int32_t cursor[];  // [C]
-    const int bh = blockIdx.y, blk = blockIdx.x, lane = threadIdx.x;
+    int logical;
+    if (!xcd_remap((long long)NB * BH, logical)) return;
+    const int bh = logical / NB, blk = logical - bh * NB, lane = threadIdx.x;
     const int i0 = blk * kRowsPerBlk, nrow = min(kRowsPerBlk, N - i0);
     const int32_t *base = cnt_blk + ((size_t)bh * NB + blk) * C;
     const int32_t *lo = list_off + (size_t)bh * (C + 1);
     for (int b = lane; b < C; b += 64) cursor[b] = lo[b] + base[b];
     __syncthreads();
-    const int32_t *src = sel + ((size_t)bh * N + i0) * topk;
-    const uint32_t *vm = vmask + (size_t)bh * N + i0;
-    int32_t *ql = qlist + (size_t)bh * N * topk;
-    const int rpb = 64 / topk;
-    const int mu = lane / topk, r = lane - mu * topk;
-    const bool lane_on = mu < rpb;
-    constexpr int U = 4;                           // steps whose loads are in flight together
-    for (int u0 = 0; u0 < nrow; u0 += U * rpb) {
-        int j[U];
-        bool ok[U];
-#pragma unroll
-        for (int t = 0; t < U; ++t) {
-            const int u = u0 + t * rpb + mu;
-            const bool in = lane_on && u < nrow;
-            ok[t] = in && ((vm[in ? u : 0] >> r) & 1u);
-            j[t] = in ? src[(size_t)u * topk + r] : 0;
+    fill_rows(sel + (size_t)bh * N * topk, i0, nrow, topk, bits, lane, vmask + (size_t)bh * N, cursor,
+              qlist + (size_t)bh * N * topk);
+}
+
+// The whole list builder for a head in one workgroup: sixteen waves take consecutive sixteenths of the
+// queries, count into histograms of their own, scan them and fill. Small calls are bound by the five
+// launches of the general path and their few waves, not by work: 52 us of kernels against 28 at 6,256
+// tokens, 24 heads and k = 3, 38 against 7 at 1,088 tokens.
+constexpr int kHeadWaves = 16, kHeadChunks = 1000;      // 62.5 KB of histograms
+constexpr int kHeadEntries = 32768;       // N * topk up to which it is used: 64 steps a wave, where both ways take about as long
+__global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_t *__restrict__ sel, int N, int topk,
+                                                                    int C, int bits,
+                                                                    const int32_t *__restrict__ chunk_of,
+                                                                    const int32_t *__restrict__ win,
+                                                                    const int32_t *__restrict__ rw,
+                                                                    uint32_t *__restrict__ vmask,
+                                                                    int32_t *__restrict__ list_off,
+                                                                    int32_t *__restrict__ tile_off,
+                                                                    int32_t *__restrict__ qlist) {
+    extern __shared__ int32_t hist[];    // [kHeadWaves][C]
+    __shared__ int32_t wsum[2][kHeadWaves];
+    const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (N + kHeadWaves - 1) / kHeadWaves;
+    const int i0 = min(N, wave * per), nrow = min(per, N - i0);
+    for (int b = tid; b < kHeadWaves * C; b += kHeadWaves * 64) hist[b] = 0;
+    __syncthreads();
+    sel += (size_t)bh * N * topk;
+    vmask += (size_t)bh * N;
+    count_rows(sel, i0, nrow, topk, C, lane, chunk_of, win, rw, vmask, hist + wave * C);
+    __syncthreads();
+    // thread j owns chunk j: entries of the earlier waves, then an exclusive scan over the chunks
+    int tot = 0;
+    if (tid < C)
+        for (int w = 0; w < kHeadWaves; ++w) {
+            const int c = hist[w * C + tid];
+            hist[w * C + tid] = tot;
+            tot += c;
         }
+    int a = tot, b = (tot + kBM - 1) / kBM;          // inclusive scans within the wave
+    const int tiles = b;
 #pragma unroll
-        for (int t = 0; t < U; ++t) {
-            int pos = 0;
-            for (int v = 0; v < rpb; ++v)
-                if (ok[t] && mu == v) pos = atomicAdd(&cursor[j[t]], 1);
-            if (ok[t]) ql[pos] = ((i0 + u0 + t * rpb + mu) << 5) | r;
-        }
+    for (int o = 1; o < 64; o <<= 1) {
+        const int xa = __shfl_up(a, o, 64), xb = __shfl_up(b, o, 64);
+        if (lane >= o) { a += xa; b += xb; }
     }
+    if (lane == 63) { wsum[0][wave] = a; wsum[1][wave] = b; }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) { a += wsum[0][w]; b += wsum[1][w]; }
+    if (tid < C) {
+        int32_t *lo = list_off + (size_t)bh * (C + 1), *to = tile_off + (size_t)bh * (C + 1);
+        lo[tid] = a - tot;
+        to[tid] = b - tiles;
+        if (tid == C - 1) { lo[C] = a; to[C] = b; }
+        for (int w = 0; w < kHeadWaves; ++w) hist[w * C + tid] += a - tot;
+    }
+    __syncthreads();
+    fill_rows(sel, i0, nrow, topk, bits, lane, vmask, hist + wave * C, qlist + (size_t)bh * N * topk);
 }
 
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws, const AttnWs &L,
@@ -201,15 +315,22 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     int32_t *tile_off = reinterpret_cast<int32_t *>(ws + L.tile_off);
     int32_t *qlist = reinterpret_cast<int32_t *>(ws + L.qlist);
     MOC_PROF("build_lists", st);
+    int bits = 0;
+    while ((1 << bits) < C) ++bits;
+    if ((long long)N * topk <= kHeadEntries && C <= kHeadChunks) {
+        list_head_kernel<<<dim3(BH), dim3(kHeadWaves * 64), (size_t)kHeadWaves * C * 4, st>>>(
+            sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, vmask, list_off, tile_off, qlist);
+        return hipGetLastError();
+    }
     const size_t shm_fill = (size_t)C * 4, shm_count = (size_t)C * 4;
-    list_count_kernel<<<dim3(NB, BH), dim3(64), shm_count, st>>>(sel, N, topk, C, m->d_chunk_of, m->d_win, m->d_rwin, NB,
+    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm_count, st>>>(sel, N, topk, C, m->d_chunk_of, m->d_win, m->d_rwin, NB, BH,
                                                                  vmask, cnt_blk);
     int32_t *gsum = reinterpret_cast<int32_t *>(ws + L.gsum);
     const dim3 sgrid((C + 255) / 256, kScanGroups, BH);
     list_group_sum_kernel<<<sgrid, dim3(256), 0, st>>>(cnt_blk, NB, C, gsum);
     list_block_scan_kernel<<<sgrid, dim3(256), 0, st>>>(cnt_blk, NB, C, gsum, cnt);
     list_scan_kernel<<<dim3(BH), dim3(256), 0, st>>>(cnt, C, list_off, tile_off);
-    list_fill_kernel<<<dim3(NB, BH), dim3(64), shm_fill, st>>>(sel, N, topk, C, vmask, NB, cnt_blk, list_off, qlist);
+    list_fill_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm_fill, st>>>(sel, N, topk, C, bits, vmask, NB, BH, cnt_blk, list_off, qlist);
     return hipGetLastError();
 }
 

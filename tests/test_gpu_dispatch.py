@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import moc_inputs as mi
+from paper_2508_21058_amd import binding as mb
 from tests.test_gpu_parity import run_case
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +46,45 @@ def test_routed_chunks_beside_a_long_caption(chunk):
 @pytest.mark.parametrize("d,chunk,topk", [(64, 33, 3), (128, 288, 2), (128, 300, 2), (64, 300, 1), (128, 65, 0)])
 def test_fp32_storage(d, chunk, topk):
     run_case(mi.stream_layout(2, 37, 4 * chunk + 5, chunk, "chunk"), 1, 3, d, topk, torch.float32, seed=51 + chunk)
+
+
+# list builder: both sides of the one-workgroup limit (32768 entries a head, 1000 chunks), rows whose
+# slots fill 64 lanes exactly or leave some idle, more chunks than a workgroup has lanes
+@pytest.mark.parametrize("N,chunk,topk", [(4096, 64, 8), (4097, 64, 8), (1000, 1, 5), (1002, 1, 3), (2340, 13, 14), (300, 7, 32),
+                                          (12000, 9, 7), (9000, 60, 11)])
+def test_list_builder_ranges(N, chunk, topk):
+    offs = np.unique(np.r_[np.arange(0, N, chunk), N]).astype(np.int32)
+    C = len(offs) - 1
+    lay = mi.Layout("lists", offs, np.zeros(C, np.int32), np.arange(C, dtype=np.int32),
+                    np.asarray([[0, offs[1]]], dtype=np.int32))
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    H = 3
+    q, k, v = (torch.randn(1, H, N, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    # rows as a caller may write them: repeated, forced and out-of-range entries among them
+    sel = torch.randint(-1, C + 1, (1, H, N, topk), generator=g, device="cuda", dtype=torch.int32)
+    ws = mb.attn_workspace(meta, 1, H, 64, topk, torch.bfloat16, False)
+    mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
+    torch.cuda.synchronize()
+    # the workspace begins with chunk counts, list offsets and tile offsets; the lists come after tables
+    # whose sizes follow from the shape (every part 256-byte aligned)
+    at, parts = 0, {}
+    for name, n in (("cnt", H * C), ("off", H * (C + 1)), ("tile", H * (C + 1)), ("vmask", H * N), ("gsum", H * 32 * C),
+                    ("blk", H * -(-N // 256) * C), ("list", H * N * topk)):
+        parts[name] = ws[at:at + 4 * n].view(torch.int32).cpu().numpy()
+        at += -(-4 * n // 256) * 256
+    chunk_of = np.repeat(np.arange(C), np.diff(offs))
+    s = sel.cpu().numpy()[0]
+    for h in range(H):
+        first = np.ones((N, topk), bool)
+        for r in range(1, topk):
+            first[:, r] = (s[h][:, r:r + 1] != s[h][:, :r]).all(1)
+        ok = first & (s[h] >= 1) & (s[h] < C) & (s[h] != chunk_of[:, None])      # chunk 0 is the caption
+        assert np.array_equal(parts["vmask"].view(np.uint32)[h * N:(h + 1) * N], (ok.astype(np.uint64) << np.arange(topk, dtype=np.uint64)).sum(1).astype(np.uint32))
+        qi, r = np.nonzero(ok)
+        order = np.argsort(s[h][qi, r], kind="stable")
+        cnt = np.bincount(s[h][qi, r], minlength=C)
+        assert np.array_equal(parts["off"][h * (C + 1):(h + 1) * (C + 1)], np.r_[0, np.cumsum(cnt)])
+        assert np.array_equal(parts["tile"][h * (C + 1):(h + 1) * (C + 1)], np.r_[0, np.cumsum(-(-cnt // 128))])
+        assert np.array_equal(parts["list"][h * N * topk:h * N * topk + len(qi)], ((qi << 5) | r)[order])
+    meta.close()
