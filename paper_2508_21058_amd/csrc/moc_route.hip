@@ -10,15 +10,18 @@
 // one query in each lane (two half-waves share a query and own 16 chunks of a
 // tile each); the [N, C] score matrix never exists in memory.
 //
-// Per-lane top-k without a sort and without paying wave divergence per score:
-//   filter  scores >= tau, the lane's k-th best so far (-inf-like until k scores
-//           have been seen), are appended to a per-lane queue in LDS: after the
-//           first tiles only a few per tile pass;
-//   drain   when a queue would overflow (and at the end) it is inserted into a
-//           register-resident sorted list with strict comparisons, in chunk
-//           order, so ties keep the lower index; tau rises to the new k-th best;
-//   merge   the two half-waves exchange their lists.
-// One pass over the chunks; any data (ties, few tiles) stays exact.
+// Per-lane top-k without branches: a candidate is one 64-bit word, (score, chunk), whose
+// order as a double is the order of the selection: higher score first, lower chunk on a
+// tie (see entry()). The 16 words of a tile go through a sorting network and are merged
+// into the lane's sorted list, v_max_f64 / v_min_f64 pairs that run at the full vector
+// rate here; at the end the two half-waves merge their lists. One pass over the chunks;
+// any data (ties, few tiles) stays exact, and the time does not depend on the data.
+//
+// Bound by these vector instructions: about 240 per tile of 32 x 32 scores (k <= 8) beside
+// its 24 matrix instructions. Against queues of the scores above the k-th best so far,
+// inserted entry by entry (divergent, two LDS rows per entry, two waves per SIMD): 1,313
+// -> 684 us at 114k tokens, 24 heads, 440 chunks, k = 8; 7,074 -> 4,552 us at 457k tokens,
+// six heads, 3,488 chunks, k = 16; 26 -> 15 us at 6,256 tokens, k = 3.
 #include "moc_attn_common.h"
 #include "moc_pool_unit.h"
 
@@ -34,52 +37,62 @@ struct RouteArgs {
     int stride;                   // int32 words between consecutive rows of sel (>= topk)
 };
 
-constexpr int kQCap = 15;         // queue entries per lane (plus one spill row: 2 x 16 KB of LDS for 256 lanes)
-
-// sorted insert (descending), strict: an equal score stays behind the entries already there.
-// Position p takes the median of (val[p-1], val[p], x): the shifted neighbour if x passed it, x if it
-// lands here, else what it held; the index follows with one comparison per position.
-template <int KMAX>
-__device__ __forceinline__ void topk_insert(float (&val)[KMAX], int (&idx)[KMAX], float x, int xi) {
-    bool above = false;                 // x > val[p-1]
-    float pv = INFINITY;                // val[p-1] before this insert
-    int pi = -1;
-#pragma unroll
-    for (int p = 0; p < KMAX; ++p) {
-        const bool here = x > val[p];
-        const float tv = val[p];
-        const int ti = idx[p];
-        val[p] = __builtin_amdgcn_fmed3f(pv, tv, x);
-        idx[p] = above ? pi : (here ? xi : ti);
-        above = here; pv = tv; pi = ti;
-    }
+// The entry of a candidate: the score's bits as the high word of a double, which read as one is finite
+// for every score but a NaN (+-inf become exponent 0x7f8) and ordered like the scores; the low word
+// orders equal scores by chunk, ascending (a negative double falls as its low word grows, hence the
+// sign mask). A NaN counts as -inf, which is no candidate. (A score is never -0: its sum starts at +0.)
+__device__ __forceinline__ double entry(float score, uint32_t chunk) {
+    uint32_t hi;        // the larger of score and -inf: of two numbers of which one is a NaN, the other
+    asm("v_max_f32 %0, 0xff800000, %1" : "=v"(hi) : "v"(score));
+    const uint32_t lo = chunk ^ ~(uint32_t)((int32_t)hi >> 31);
+    return __hiloint2double((int)hi, (int)lo);
+}
+// the chunk, or -1 if the entry is no candidate (masked scores are -inf)
+__device__ __forceinline__ int entry_chunk(double e) {
+    const int hi = __double2hiint(e);
+    return __int_as_float(hi) >= -3.0e38f ? __double2loint(e) ^ ~(hi >> 31) : -1;
 }
 
-// sorted insert ordering by (score desc, index asc)
-template <int KMAX>
-__device__ __forceinline__ void topk_insert_tie(float (&val)[KMAX], int (&idx)[KMAX], float x, int xi) {
+// v_max_f64 / v_min_f64 as they are: fmax() would first quiet signalling NaNs, which entries never are
+__device__ __forceinline__ double max64(double a, double b) { double r; asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+__device__ __forceinline__ double min64(double a, double b) { double r; asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+
+__device__ __forceinline__ void order2(double &a, double &b) {      // a >= b
+    const double t = max64(a, b);
+    b = min64(a, b);
+    a = t;
+}
+// Batcher's odd-even merge sort, descending: 5 / 19 / 63 pairs for 4 / 8 / 16 entries
+template <int M> __device__ __forceinline__ void sort_entries(double *x) {
 #pragma unroll
-    for (int p = 0; p < KMAX; ++p) {
-        const bool sw = (x > val[p]) || (x == val[p] && (unsigned)xi < (unsigned)idx[p]);
-        const float tv = val[p];
-        const int ti = idx[p];
-        val[p] = sw ? x : tv;
-        idx[p] = sw ? xi : ti;
-        x = sw ? tv : x;
-        xi = sw ? ti : xi;
-    }
+    for (int p = 1; p < M; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int i = 0; i < M - 1; ++i)       // pairs (i, i + k) inside blocks of 2 p
+                if (i + k < M && i >= k % p && ((i - k % p) / k) % 2 == 0 && i / (2 * p) == (i + k) / (2 * p))
+                    order2(x[i], x[i + k]);
+}
+// the best K of a descending list of K and a descending list of M <= K, descending again: the pairwise
+// maxima of one list against the other reversed are the best K as a bitonic sequence
+template <int K, int M> __device__ __forceinline__ void merge_entries(double (&list)[K], const double *x) {
+#pragma unroll
+    for (int p = 0; p < M; ++p) list[K - 1 - p] = max64(list[K - 1 - p], x[p]);
+#pragma unroll
+    for (int k = K / 2; k >= 1; k /= 2)
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (!(i & k)) order2(list[i], list[i + k]);
 }
 
-// Four waves x 32 queries per workgroup, two workgroups per CU, two staged tiles of pooled keys (one
-// in use, one in flight). The pass is bound by the selection's vector instructions, not by the
-// latency of the tile copies: eight waves with three stages (one workgroup per CU) measured 13 %
-// slower, because a barrier per tile then couples twice as many waves whose queue drains fall on
-// different tiles.
+// Four waves x 32 queries per workgroup, three workgroups per CU, two staged tiles of pooled keys (one
+// in use, one in flight). The pass is bound by the selection's vector instructions, not by the latency
+// of the tile copies.
 constexpr int kRouteThreads = 256;
 constexpr int kRouteStages = 2;
 
 template <int D, typename T, int KMAX>
-__device__ __forceinline__ void route_body(const RouteArgs &a, char *smem, u32x2 (*queue)[kRouteThreads]) {
+__device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
     constexpr int KS = D / 16;
     constexpr int NQ = sizeof(T) == 2 ? 1 : 3;       // query planes
     constexpr int PB = 32 * D * 2;                   // bytes of one plane tile (32 chunks)
@@ -218,72 +231,25 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem, u32x2
         return acc;
     };
 
-    // ---------------- collect scores >= tau (the k-th best so far), keep an exact sorted list
-    const int base = KMAX - topk;
-    float tau = -3.0e38f;      // never let -inf (an ineligible chunk) pass the filter
-    float val[KMAX];
-    int idx[KMAX];
+    // ---------------- the lane's best KMAX candidates so far, best first
+    double list[KMAX];
 #pragma unroll
-    for (int p = 0; p < KMAX; ++p) { val[p] = (p >= base) ? -INFINITY : INFINITY; idx[p] = -1; }
-    int cnt = 0;
-    auto drain = [&]() {
-        int mx = cnt;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
-        for (int e = 0; e < mx; ++e) {
-            const bool has = e < cnt;
-            const u32x2 ent = queue[e][tid];
-            const uint32_t bits = ent[0];
-            const float x = has ? __builtin_bit_cast(float, bits) : -INFINITY;
-            const int xi = has ? (int)ent[1] : -1;
-            topk_insert<KMAX>(val, idx, x, xi);
-        }
-        cnt = 0;
-        tau = fmaxf(tau, val[KMAX - 1]);     // once the list is full its tail bounds the k-th best
-        // The other half-wave holds the other 16 chunks of every tile for the same query: the k-th best
-        // of either half is a lower bound of the k-th best of both, so the larger of the two bounds
-        // serves both halves and about half as many scores reach the queues.
-        tau = fmaxf(tau, xhalf(tau));
-        // With full lists (topk == KMAX) the two sorted lists give more: the k-th best of their union is
-        // the largest of min(mine[p], other[k - 2 - p]) over p (take p + 1 scores from one list and the
-        // rest from the other) and of the two tails above. Both halves see the same terms.
-        if (base == 0) {
-#pragma unroll
-            for (int p = 0; p + 1 < KMAX; ++p) tau = fmaxf(tau, fminf(val[p], xhalf(val[KMAX - 2 - p])));
-        }
-    };
+    for (int p = 0; p < KMAX; ++p) list[p] = entry(-INFINITY, 0xffffffffu);
     auto scan = [&](auto cur, int t) {
         constexpr int CUR = decltype(cur)::value;
+        constexpr int M = KMAX < 16 ? KMAX : 16;       // entries sorted and merged at a time
         const bool more = t + 1 < ntiles;
         if (t + DIST < ntiles) issue(t + DIST, (CUR + DIST) % kRouteStages);
         const f32x16 sc = scores(cur, t);
-        // Branch-free append: every score is written at the lane's cursor and the cursor moves only if
-        // the score passes, so a later score overwrites a rejected one. Entries past the capacity go
-        // to a spill row; if any lane spilled, the appends of that half tile are taken back, the queues
-        // drained (which also raises the bounds) and the half appended again: 8 scores always fit then.
-        const int jb = t * 32 + half * 4;
-        auto append = [&](auto first) {
-            constexpr int R0 = decltype(first)::value;
+        const uint32_t jb = (uint32_t)(t * 32 + half * 4);
+        double x[16];
 #pragma unroll
-            for (int r = R0; r < R0 + 8; ++r) {
-                const int slot = min(cnt, kQCap);
-                const float x = sc[r];      // (a bit cast straight from the vector element picks element 0)
-                const u32x2 ent = {__builtin_bit_cast(uint32_t, x), (uint32_t)(jb + (r >> 2) * 8 + (r & 3))};
-                queue[slot][tid] = ent;
-                cnt += sc[r] >= tau ? 1 : 0;
-            }
-        };
-        auto append_checked = [&](auto first) {
-            const int before = cnt;
-            append(first);
-            if (__any(cnt > kQCap)) {
-                cnt = before;
-                drain();
-                append(first);
-            }
-        };
-        append_checked(IC<0>{});
-        append_checked(IC<8>{});
+        for (int r = 0; r < 16; ++r) x[r] = entry(sc[r], jb ^ (uint32_t)((r >> 2) * 8 + (r & 3)));
+#pragma unroll
+        for (int r = 0; r < 16; r += M) {
+            sort_entries<M>(x + r);
+            merge_entries<KMAX, M>(list, x + r);
+        }
         if (more) { landed(t + 1); __syncthreads(); }
         return more;
     };
@@ -297,30 +263,37 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem, u32x2
         if (!scan(IC<1 % kRouteStages>{}, t++)) break;
         if (kRouteStages > 2 && !scan(IC<2 % kRouteStages>{}, t++)) break;
     }
-    drain();
 
-    // ---------------- merge the two half-waves (score desc, index asc)
-    {
-        float ov[KMAX];
-        int oi[KMAX];
+    // ---------------- the upper half-wave's list into the lower one's
+    double up[KMAX];
 #pragma unroll
-        for (int p = 0; p < KMAX; ++p) { ov[p] = xhalf(val[p]); oi[p] = __shfl_xor(idx[p], 32, 64); }
-#pragma unroll
-        for (int p = 0; p < KMAX; ++p)
-            if (p >= base) topk_insert_tie<KMAX>(val, idx, ov[p], oi[p]);
+    for (int p = 0; p < KMAX; ++p) {
+        const uint32_t h = (uint32_t)__double2hiint(list[p]), l = (uint32_t)__double2loint(list[p]);
+        const auto rh = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+        const auto rl = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+        up[p] = __hiloint2double((int)rh[1], (int)rl[1]);
     }
+    merge_entries<KMAX, KMAX>(list, up);
     if (valid && half == 0) {
+        if ((topk | a.stride) % 4 == 0) {      // rows of whole 16-byte words
 #pragma unroll
-        for (int p = 0; p < KMAX; ++p)
-            if (p >= base) out[p - base] = idx[p];
+            for (int p = 0; p < KMAX; p += 4) {
+                const u32x4 w = {(uint32_t)entry_chunk(list[p]), (uint32_t)entry_chunk(list[p + 1]),
+                                 (uint32_t)entry_chunk(list[p + 2]), (uint32_t)entry_chunk(list[p + 3])};
+                if (p < topk) *reinterpret_cast<u32x4 *>(out + p) = w;
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < KMAX; ++p)
+                if (p < topk) out[p] = entry_chunk(list[p]);
+        }
     }
 }
 
 template <int D, typename T, int KMAX>
 __global__ __launch_bounds__(kRouteThreads, kRouteThreads == 256 ? 2 : 1) void route_kernel(RouteArgs a) {
     __shared__ __attribute__((aligned(1024))) char smem[kRouteStages * 3 * 32 * D * 2];
-    __shared__ u32x2 queue[kQCap + 1][kRouteThreads];    // (score bits, chunk) pairs; row kQCap takes what does not fit
-    route_body<D, T, KMAX>(a, smem, queue);
+    route_body<D, T, KMAX>(a, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -349,7 +322,6 @@ template <int D, typename T, int KMAX>
 __global__ __launch_bounds__(kRouteThreads, 2) void route_fused_kernel(RouteArgs a, FuseArgs f) {
     static_assert(kRouteThreads == 256, "the pooling unit is written for 256 threads");
     __shared__ __attribute__((aligned(1024))) char smem[kRouteStages * 3 * 32 * D * 2];
-    __shared__ u32x2 queue[kQCap + 1][kRouteThreads];
     static_assert(PoolShape<D, T>::kRedFloats * 4 <= kRouteStages * 3 * 32 * D * 2, "pooling scratch fits the tile buffers");
     const unsigned int wg = blockIdx.y * gridDim.x + blockIdx.x, nwg = gridDim.x * gridDim.y;
     const unsigned int npool = min(nwg, (unsigned int)kFusePoolWgs);
@@ -372,7 +344,7 @@ __global__ __launch_bounds__(kRouteThreads, 2) void route_fused_kernel(RouteArgs
         }
     }
     __syncthreads();
-    route_body<D, T, KMAX>(a, smem, queue);
+    route_body<D, T, KMAX>(a, smem);
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned int fin = __hip_atomic_fetch_add(&g_fuse_sync[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -399,7 +371,8 @@ hipError_t launch_route_fused(const moc_meta *m, int BH, int d, const void *q, c
 #define MOC_FUSED(DD, KK) route_fused_kernel<DD, bf16_t, KK><<<grid, block, 0, st>>>(a, f)
 #define MOC_FUSED_K(DD)                         \
     do {                                        \
-        if (topk <= 8) MOC_FUSED(DD, 8);        \
+        if (topk <= 4) MOC_FUSED(DD, 4);        \
+        else if (topk <= 8) MOC_FUSED(DD, 8);   \
         else if (topk <= 16) MOC_FUSED(DD, 16); \
         else MOC_FUSED(DD, 32);                 \
     } while (0)
@@ -437,7 +410,8 @@ hipError_t launch_route(const moc_meta *m, int BH, int d, int dtype, const void 
 #define MOC_ROUTE(DD, TT, KK) route_kernel<DD, TT, KK><<<grid, block, 0, st>>>(a)
 #define MOC_ROUTE_K(DD, TT)                         \
     do {                                            \
-        if (topk <= 8) MOC_ROUTE(DD, TT, 8);        \
+        if (topk <= 4) MOC_ROUTE(DD, TT, 4);        \
+        else if (topk <= 8) MOC_ROUTE(DD, TT, 8);   \
         else if (topk <= 16) MOC_ROUTE(DD, TT, 16); \
         else MOC_ROUTE(DD, TT, 32);                 \
     } while (0)

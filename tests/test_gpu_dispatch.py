@@ -88,3 +88,55 @@ def test_list_builder_ranges(N, chunk, topk):
         assert np.array_equal(parts["tile"][h * (C + 1):(h + 1) * (C + 1)], np.r_[0, np.cumsum(-(-cnt // 128))])
         assert np.array_equal(parts["list"][h * N * topk:h * N * topk + len(qi)], ((qi << 5) | r)[order])
     meta.close()
+
+
+# selection at the list widths the kernel is built for (4, 8, 16, 32) and one past each, over enough
+# chunks that queues fill, drain and merge; scores of both signs, many exact ties (quarter-integer keys,
+# one-hot queries), zeros of both signs. Scores are exact in fp32 here, so the order is pinned: higher
+# score first, lower chunk on a tie.
+@pytest.mark.parametrize("topk", [1, 3, 4, 5, 8, 9, 16, 17, 32])
+@pytest.mark.parametrize("levels,dtype", [(1, torch.bfloat16), (3, torch.bfloat16), (200, torch.float32)])
+def test_selection_order_and_ties(topk, levels, dtype):
+    C, per, H, d = 330, 4, 2, 64
+    N = C * per
+    rng = np.random.default_rng(topk * 7 + levels)
+    kbar = rng.integers(-levels, levels + 1, (H, C, d)) / 4.0
+    kbar[:, ::5] *= np.where(rng.random((H, 66, 1)) < 0.5, -0.0, 1.0)
+    k = np.repeat(kbar, per, axis=1)[None]
+    q = np.zeros((1, H, N, d))
+    q[0, np.arange(H)[:, None], np.arange(N)[None], rng.integers(0, d, (H, N))] = rng.choice([-1.0, 1.0], (H, N))
+    offs = np.arange(0, N + 1, per, dtype=np.int32)
+    meta = mb.chunk_meta(offs, np.zeros(C, np.int32), np.arange(C, dtype=np.int32), None)
+    qd, kd = (torch.from_numpy(x).to("cuda").to(dtype).contiguous() for x in (q, k))
+    _, sel = mb.route(meta, qd, kd, topk, False)
+    sel = sel.cpu().numpy()[0]
+    for h in range(H):
+        s = q[0, h] @ kbar[h].T
+        s[np.arange(N), np.arange(N) // per] = -np.inf                # the own chunk is a forced link
+        want = np.argsort(-s, axis=1, kind="stable")[:, :topk]
+        assert np.array_equal(sel[h], want)
+    meta.close()
+
+
+# a NaN score is no candidate: the chunk never appears, a query of NaN selects nothing
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_nan_scores_are_no_candidates(dtype):
+    C, per, d, topk = 70, 4, 64, 5
+    N = C * per
+    g = torch.Generator().manual_seed(3)
+    q, k = (torch.randn(1, 1, N, d, generator=g).to(torch.bfloat16).float() for _ in range(2))
+    q[0, 0, 9, 3] = float("nan")
+    for c, v in ((2, float("nan")), (40, float("inf")), (69, float("-inf"))):
+        k[0, 0, c * per, 5] = v
+    offs = np.arange(0, N + 1, per, dtype=np.int32)
+    meta = mb.chunk_meta(offs, np.zeros(C, np.int32), np.arange(C, dtype=np.int32), None)
+    _, sel = mb.route(meta, q.cuda().to(dtype).contiguous(), k.cuda().to(dtype).contiguous(), topk, False)
+    sel = sel.cpu().numpy()[0, 0]
+    kbar = k[0, 0].double().numpy().reshape(C, per, d).mean(1)
+    s = q[0, 0].double().numpy() @ np.nan_to_num(kbar, nan=0.0, posinf=0.0, neginf=0.0).T
+    s[:, [2, 40, 69]] = -np.inf
+    s[np.arange(N), np.arange(N) // per] = -np.inf
+    want = np.argsort(-s, axis=1, kind="stable")[:, :topk]
+    want[9] = -1
+    assert np.array_equal(sel, want)
+    meta.close()
