@@ -24,6 +24,67 @@
 
 namespace moc {
 
+// Lazy rescaling: the running maximum is only a reference point (any value cancels in the
+// final normalisation), so it is moved, and the accumulators rescaled, only when some query's
+// maximum has grown by more than 2^8; until then the probabilities may exceed 1 by that factor.
+// mx: the largest new score of this lane's keys.
+template <int D>
+__device__ __forceinline__ void rescale(f32x16 *oacc, float &m_run, float &l_run, float mx, float c) {
+    const float m_new = fmaxf(m_run, xhalf_max(mx));
+    if (__any((m_new - m_run) * c > 8.f)) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+        l_run *= alpha;
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
+        m_run = m_new;
+    }
+}
+
+// The last tile of a key range when at most 32 of its keys exist: one block of scores, and one or two
+// 16-key steps of V instead of four. Chunks rarely are a multiple of 64 keys: of 260 keys the tail's
+// four cost 32 matrix instructions of 160 as a whole tile, 12 of 140 so: 4.80 -> 4.34 ms at 114k tokens, 24
+// heads, k = 8. (In the tiled kernels the second path costs more registers than they have: 50 -> 57 ms on
+// the forced links of a 182k-token stream.)
+template <int D, int KOFF, int VOFF>
+__device__ __forceinline__ void fwd_tail(const char *smem, LaneOffs<D> &lo, const bf16x8 *qf, f32x16 *oacc,
+                                         float &m_run, float &l_run, float c, int valid, int lane) {
+    constexpr int KS = D / 16, DB = D / 32;
+    const int half = lane >> 5;
+    lo.pin();
+    f32x16 sacc = zero16();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) sacc = mfma32(lo.template frag<KOFF>(smem, s), qf[s], sacc);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        if ((i >> 2) * 8 + half * 4 + (i & 3) >= valid) sacc[i] = -INFINITY;
+        mx = fmaxf(mx, sacc[i]);
+    }
+    rescale<D>(oacc, m_run, l_run, mx, c);
+    const float mc = m_run * c;
+    float ls = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        if (ks * 16 >= valid) break;                  // wave-uniform
+        bf16x8 vf[DB];
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+            vf[b] = ks == 0 ? lo.template tfrag<VOFF>(smem, b) : lo.template tfrag<VOFF + 16 * D * 2>(smem, b);
+#pragma unroll
+        for (int i = 8 * ks; i < 8 * ks + 8; ++i) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(sacc[i], c, -mc));
+            sacc[i] = p;
+            ls += p;
+        }
+        const bf16x8 pf = acc_to_frag(sacc, ks);
+#pragma unroll
+        for (int b = 0; b < DB; ++b) oacc[b] = mfma32(vf[b], pf, oacc[b]);
+    }
+    l_run += ls;
+}
+
 // One tile (BN = 64 keys) of the online-softmax recurrence for this wave's 32
 // queries; the K tile sits at byte offset KOFF of the workgroup's LDS, the V
 // tile at VOFF. Rows >= valid of a ragged tile hold copies of the last valid key
@@ -90,19 +151,7 @@ __device__ __forceinline__ void fwd_tile(const char *smem, LaneOffs<D> &lo, cons
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[kb][i]);
-    // Lazy rescaling: the running maximum is only a reference point (any value cancels in the
-    // final normalisation), so it is moved, and the accumulators rescaled, only when some query's
-    // maximum has grown by more than 2^8; until then the probabilities may exceed 1 by that factor.
-    const float m_new = fmaxf(m_run, xhalf_max(mx));
-    if (__any((m_new - m_run) * c > 8.f)) {
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
-        l_run *= alpha;
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-        m_run = m_new;
-    }
+    rescale<D>(oacc, m_run, l_run, mx, c);
     const float mc = m_run * c;
     float ls = 0.f;
     // O^T[feature][query] += V^T P^T, 16 keys at a time; V is read transposed
@@ -357,10 +406,11 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
         while (toff[j + 1] <= t0) ++j;            // chunk of tile t0 (chunks without routed queries have no tiles)
         const int te = min(t1, toff[j + 1]);      // this chunk's tiles in the group: [t0, te)
         const int key0 = a.off[j], len = a.off[j + 1] - key0;
-        const int ntile = (len + 63) >> 6;
+        const int ntile = max(1, (len + 31) >> 6);   // whole tiles; up to 32 keys are left for the tail
+        const int rows = max(ntile * 64, (len + 31) & ~31);
         // ---- K / V of the chunk -> LDS (rows past the end repeat the last row: finite, and masked as keys)
         {
-            const int nk = (min(ntile * 64, kChunkRows) + RPI - 1) / RPI, nv = ntile * 64 / RPI;
+            const int nk = (min(rows, kChunkRows) + RPI - 1) / RPI, nv = rows / RPI;
             for (int i = wave; i < nk + nv; i += 8) {
                 const bool isk = i < nk;
                 const int ii = isk ? i : i - nk;
@@ -401,6 +451,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
             if (more) load_q(e_nxt, qn);
             for (int t = 1; t < ntile; ++t)
                 fwd_tile<D, 0, KBYTES, true>(smem + t * 64 * RB, lo, qf, oacc, m_run, l_run, c, min(64, len - t * 64), lane);
+            if (ntile * 64 < len)
+                fwd_tail<D, 0, KBYTES>(smem + ntile * 64 * RB, lo, qf, oacc, m_run, l_run, c, len - ntile * 64, lane);
             const float l_tot = xhalf_sum(l_run);
             const float inv = 1.f / l_tot;
             const size_t prow = ((size_t)bh * N + (e_cur >> 5)) * a.slots + (e_cur & 31);

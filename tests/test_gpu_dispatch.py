@@ -140,3 +140,11 @@ def test_nan_scores_are_no_candidates(dtype):
     want[9] = -1
     assert np.array_equal(sel, want)
     meta.close()
+
+
+# routed chunks on both sides of the tile and tail counts of the chunk-stationary forward (64-key tiles, a
+# tail of at most 32 keys, one or two 16-key steps of V)
+@pytest.mark.parametrize("chunk", [1, 16, 17, 32, 33, 64, 65, 80, 81, 96, 97, 128, 257, 273, 288])
+@pytest.mark.parametrize("d", [64, 128])
+def test_routed_tile_edges(chunk, d):
+    run_case(mi.stream_layout(2, 20, 5 * chunk + (chunk + 1) // 2, chunk, "chunk"), 1, 2, d, 3, torch.bfloat16, seed=71 + chunk)
