@@ -352,6 +352,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
                  o_ar = take(aranges.size() * sizeof(KeyRange)), o_at = take(atiles.size() * sizeof(AnchorTile)),
                  o_kv = take(kvitems.size() * sizeof(KvItem)), o_tt = take(ttiles.size() * sizeof(TextTile)),
                  o_tm = take(textmask.size() * 4), o_ntb = take((size_t)(C + 1) * 4), o_rw = take((size_t)C * 4),
+                 o_vid = take((size_t)C * 4),
                  o_cof = take((size_t)N * 4);
     const size_t upload = o_cof;  // chunk_of is filled on the device
     std::vector<char> host(upload, 0);
@@ -370,6 +371,10 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     std::vector<int32_t> ntb(C + 1, 0);
     for (int j = 0; j < C; ++j) ntb[j + 1] = ntb[j] + (kind[j] ? 0 : 1);
     put(o_ntb, ntb.data(), (size_t)(C + 1) * 4);
+    std::vector<int32_t> video;
+    for (int j = 0; j < C; ++j)
+        if (!kind[j]) video.push_back(j);
+    put(o_vid, video.data(), video.size() * 4);
     std::vector<int32_t> rwin(C);
     for (int j = 0; j < C; ++j) rwin[j] = kind[j] ? -1 : win[j];
     put(o_rw, rwin.data(), (size_t)C * 4);
@@ -391,6 +396,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     m->d_textmask = reinterpret_cast<uint32_t *>(base + o_tm);
     m->d_ntb = reinterpret_cast<int32_t *>(base + o_ntb);
     m->d_rwin = reinterpret_cast<int32_t *>(base + o_rw);
+    m->d_video = reinterpret_cast<int32_t *>(base + o_vid);
     m->d_chunk_of = reinterpret_cast<int32_t *>(base + o_cof);
 
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -59,6 +59,7 @@ struct moc_meta {
     int32_t *d_chunk_of = nullptr;   // [N]
     uint32_t *d_textmask = nullptr;  // [ceil(C/32)] bit j%32 of word j/32 set: chunk j is text
     int32_t *d_ntb = nullptr;        // [C+1] number of non-text chunks with index < j
+    int32_t *d_video = nullptr;      // the non-text chunks, ascending
     int32_t *d_arange_off = nullptr; // [W+1] into d_aranges
     moc::KeyRange *d_aranges = nullptr;
     moc::AnchorTile *d_atiles = nullptr;

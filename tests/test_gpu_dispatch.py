@@ -148,3 +148,12 @@ def test_nan_scores_are_no_candidates(dtype):
 @pytest.mark.parametrize("d", [64, 128])
 def test_routed_tile_edges(chunk, d):
     run_case(mi.stream_layout(2, 20, 5 * chunk + (chunk + 1) // 2, chunk, "chunk"), 1, 2, d, 3, torch.bfloat16, seed=71 + chunk)
+
+
+# regularised rows at the widths the kernel's lists are sized for (8 + 4, 16 + 4, 32) and one past each,
+# no routed chunk at all, nothing added, more requested than there are candidates
+@pytest.mark.parametrize("topk,max_in", [(8, 4), (8, 5), (7, 5), (16, 4), (16, 5), (0, 3), (20, 12), (32, 0), (1, 31)])
+def test_regularised_row_widths(topk, max_in):
+    from tests.test_gpu_perturb import _case
+    lay = mi.random_layout(90 + topk, n_chunks=45, max_len=31, n_shots=3)
+    _case(lay, H=2, d=64, topk=topk, causal=True, p_max=1.0, lam=6.0, max_in=max_in, seed=topk, dtype=torch.bfloat16)
