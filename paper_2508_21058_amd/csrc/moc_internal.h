@@ -92,9 +92,13 @@ constexpr int kMaxSegments = 4096;
 hipError_t launch_outer(int D, int dtype, const void *x, int P, int max_tiles, int g, int M, const int32_t *d_seg_off,
                         const int32_t *d_tile_base, const int32_t *d_cand, float *partial, float *mean,
                         float *scores, int32_t *d_selected, hipStream_t st);
-// dst[o][..] = rows of src[o] listed by `n_ranges` records (src row, length, dst row, pad) on the device.
+// dst[o][..] = rows of src[o] listed by `n_ranges` host records; d_ranges: device room for them (used when
+// they are too many to travel with the launch; the records must then outlive the copy).
+struct GatherRange { int32_t src, len, dst, pad; };
+constexpr int kGatherArgRanges = 64;
+struct GatherTable { GatherRange r[kGatherArgRanges]; };
 hipError_t launch_gather(int outer, long long n_src_rows, long long n_dst_rows, int row_bytes, const void *src,
-                         void *dst, const void *d_ranges, int n_ranges, hipStream_t st);
+                         void *dst, const GatherRange *ranges, int n_ranges, void *d_ranges, hipStream_t st);
 
 // Machine probes (streaming copy, MFMA loop); see moc_probe.
 constexpr int kProbeMfmaGrid = 256;

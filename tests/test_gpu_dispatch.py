@@ -157,3 +157,19 @@ def test_regularised_row_widths(topk, max_in):
     from tests.test_gpu_perturb import _case
     lay = mi.random_layout(90 + topk, n_chunks=45, max_len=31, n_shots=3)
     _case(lay, H=2, d=64, topk=topk, causal=True, p_max=1.0, lam=6.0, max_in=max_in, seed=topk, dtype=torch.bfloat16)
+
+
+# row gather: tables that travel with the launch (up to 64 ranges) and larger ones, rows of one 16-byte
+# word, of an odd number of them and of more than a workgroup moves, several planes, single-row ranges
+@pytest.mark.parametrize("n_ranges", [1, 12, 64, 65, 300])
+@pytest.mark.parametrize("words", [1, 3, 16, 2500])
+def test_gather_table_sizes(n_ranges, words):
+    N, outer = 1500, 3
+    rng = np.random.default_rng(n_ranges + words)
+    src = torch.randint(0, 1 << 15, (outer, N, words * 8), device="cuda", dtype=torch.int16).view(torch.bfloat16)
+    ranges = [(int(a), int(rng.integers(0, 14 if n_ranges > 12 else 400))) for a in rng.integers(0, N - 400, n_ranges)]
+    rows = np.concatenate([np.arange(a, a + n) for a, n in ranges])
+    if rows.size == 0:
+        ranges[0], rows = (5, 1), np.array([5])
+    got = mb.gather_rows(src, ranges)
+    assert torch.equal(got.view(torch.int16), src.view(torch.int16)[:, torch.from_numpy(rows).cuda()])
