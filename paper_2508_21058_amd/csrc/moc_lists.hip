@@ -43,10 +43,22 @@ struct ListLane {
         : rpb(64 / topk), mu(lane / topk), r(lane - lane / topk * topk), on(lane / topk < 64 / topk) {}
 };
 
+// The lanes among `who` that name the same chunk as this one, by one ballot per bit of the chunk index.
+__device__ __forceinline__ unsigned long long same_chunk(int j, unsigned long long who, int bits) {
+    for (int b = 0; b < bits; ++b) {
+        const bool bit = (j >> b) & 1;
+        const unsigned long long bal = __ballot(bit);
+        who &= bit ? bal : ~bal;
+    }
+    return who;
+}
+
 // Counts the entries of queries [i0, i0 + nrow) into hist and writes their slot masks. An entry counts
 // if it names a video chunk (rw >= 0) outside the query's own window that no earlier slot of the row
-// names (the row-mates sit in the neighbouring lanes). sel and vmask point at the head's first query.
-__device__ __forceinline__ void count_rows(const int32_t *__restrict__ sel, int i0, int nrow, int topk, int C, int lane,
+// names (the row-mates sit in the neighbouring lanes; topk - 1 shuffles, each an LDS round trip, took
+// 97 us at 5,606 tokens, three heads and k = 16, the ballots take 16). sel and vmask point at the
+// head's first query.
+__device__ __forceinline__ void count_rows(const int32_t *__restrict__ sel, int i0, int nrow, int topk, int C, int bits, int lane,
                                            const int32_t *__restrict__ chunk_of, const int32_t *__restrict__ win,
                                            const int32_t *__restrict__ rw, uint32_t *__restrict__ vmask,
                                            int32_t *hist) {
@@ -54,6 +66,7 @@ __device__ __forceinline__ void count_rows(const int32_t *__restrict__ sel, int 
     const int32_t *src = sel + (size_t)i0 * topk;
     uint32_t *vm = vmask + i0;
     const uint32_t rowbits = topk >= 32 ? 0xffffffffu : ((1u << topk) - 1u);
+    const unsigned long long earlier = (unsigned long long)((1u << L.r) - 1u) << (lane - L.r);      // earlier slots of the row
     for (int u0 = 0; u0 < nrow; u0 += kListUnroll * L.rpb) {
         int j[kListUnroll], wq[kListUnroll], w[kListUnroll];
 #pragma unroll
@@ -74,10 +87,15 @@ __device__ __forceinline__ void count_rows(const int32_t *__restrict__ sel, int 
 #pragma unroll
         for (int t = 0; t < kListUnroll; ++t) {
             const int u = u0 + t * L.rpb + L.mu;
-            bool ok = w[t] >= 0 && w[t] != wq[t];
-            for (int p = 0; p + 1 < topk; ++p) {
-                const int other = __shfl(j[t], L.mu * topk + p, 64);
-                if (p < L.r && other == j[t]) ok = false;
+            const bool link = w[t] >= 0 && w[t] != wq[t];
+            bool ok = link;
+            if (topk > 4) {
+                ok = link && !(same_chunk(j[t], __ballot(link), bits) & earlier);
+            } else {                               // at most three neighbours: fewer shuffles than ballots
+                for (int p = 1; p < topk; ++p) {
+                    const int other = __shfl_up(j[t], p, 64);
+                    if (p <= L.r && other == j[t]) ok = false;
+                }
             }
             if (ok) atomicAdd(&hist[j[t]], 1);
             const unsigned long long bal = __ballot(ok);
@@ -88,15 +106,14 @@ __device__ __forceinline__ void count_rows(const int32_t *__restrict__ sel, int 
 
 // Writes the list entries of queries [i0, i0 + nrow); cursor[j] is the next free position of chunk j's
 // list for them. Lanes of one step that name the same chunk belong to different queries (the slots that
-// count name distinct chunks) and take consecutive positions in lane order, that is in query order: the
-// lanes find each other through one ballot per bit of the chunk index, each adds its rank to the
-// cursor, and the last of them moves it. LDS operations of a wave complete in program order, so the
+// count name distinct chunks) and take consecutive positions in lane order, that is in query order: each
+// adds its rank among them to the cursor, and the last of them moves it. LDS operations of a wave complete in program order, so the
 // next step reads what this one wrote. (One LDS add per query of the step, the obvious way to the same
 // order, waits for LDS up to 64 / topk times a step: 24.3 us against 17.0 at 9k tokens, sixteen heads and k = 6.
 // At 114k tokens the scattered 4-byte stores bound the pass, 200 us either way.)
 __device__ __forceinline__ void fill_rows(const int32_t *__restrict__ sel, int i0, int nrow, int topk, int bits, int lane,
                                           const uint32_t *__restrict__ vmask, int32_t *cursor,
-                                          int32_t *__restrict__ qlist) {
+                                          int32_t *qlist) {
     const ListLane L(topk, lane);
     const int32_t *src = sel + (size_t)i0 * topk;
     const uint32_t *vm = vmask + i0;
@@ -119,12 +136,7 @@ __device__ __forceinline__ void fill_rows(const int32_t *__restrict__ sel, int i
         }
 #pragma unroll
         for (int t = 0; t < kListUnroll; ++t) {
-            unsigned long long same = __ballot(ok[t]);
-            for (int b = 0; b < bits; ++b) {
-                const bool bit = (j[t] >> b) & 1;
-                const unsigned long long bal = __ballot(bit);
-                same &= bit ? bal : ~bal;
-            }
+            const unsigned long long same = same_chunk(j[t], __ballot(ok[t]), bits);
             if (ok[t]) {
                 const int pos = cursor[j[t]] + __popcll(same & below);
                 if ((same >> lane) == 1ull) cursor[j[t]] = pos + 1;
@@ -136,7 +148,7 @@ __device__ __forceinline__ void fill_rows(const int32_t *__restrict__ sel, int i
 }
 
 // One wave per block of kRowsPerBlk queries.
-__global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restrict__ sel, int N, int topk, int C,
+__global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restrict__ sel, int N, int topk, int C, int bits,
                                                         const int32_t *__restrict__ chunk_of,
                                                         const int32_t *__restrict__ win,
                                                         const int32_t *__restrict__ rw, int NB, int BH,
@@ -148,7 +160,7 @@ __global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restric
     const int i0 = blk * kRowsPerBlk, nrow = min(kRowsPerBlk, N - i0);
     for (int b = lane; b < C; b += 64) hist[b] = 0;
     __syncthreads();
-    count_rows(sel + (size_t)bh * N * topk, i0, nrow, topk, C, lane, chunk_of, win, rw, vmask + (size_t)bh * N, hist);
+    count_rows(sel + (size_t)bh * N * topk, i0, nrow, topk, C, bits, lane, chunk_of, win, rw, vmask + (size_t)bh * N, hist);
     __syncthreads();
     int32_t *out = cnt_blk + ((size_t)bh * NB + blk) * C;
     for (int b = lane; b < C; b += 64) out[b] = hist[b];
@@ -273,7 +285,7 @@ __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_
     __syncthreads();
     sel += (size_t)bh * N * topk;
     vmask += (size_t)bh * N;
-    count_rows(sel, i0, nrow, topk, C, lane, chunk_of, win, rw, vmask, hist + wave * C);
+    count_rows(sel, i0, nrow, topk, C, bits, lane, chunk_of, win, rw, vmask, hist + wave * C);
     __syncthreads();
     // thread j owns chunk j: entries of the earlier waves, then an exclusive scan over the chunks
     int tot = 0;
@@ -323,7 +335,7 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
         return hipGetLastError();
     }
     const size_t shm_fill = (size_t)C * 4, shm_count = (size_t)C * 4;
-    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm_count, st>>>(sel, N, topk, C, m->d_chunk_of, m->d_win, m->d_rwin, NB, BH,
+    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm_count, st>>>(sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, NB, BH,
                                                                  vmask, cnt_blk);
     int32_t *gsum = reinterpret_cast<int32_t *>(ws + L.gsum);
     const dim3 sgrid((C + 255) / 256, kScanGroups, BH);
