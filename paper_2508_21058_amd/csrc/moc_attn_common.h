@@ -42,13 +42,25 @@ struct FwdArgs {
 // LDS, but 576 of them leave one workgroup per compute unit: 1,165 us a step of ragged chunks up to 340
 // keys against 1,058 in the tiled kernels, so the bound is the same.
 constexpr int kChunkRows = 288;
-// Query tiles (of kBM list entries) per workgroup: sixteen amortise the copy of a chunk's K and V; calls
-// with less than sixteen tiles per compute unit take fewer, so that every unit has a workgroup (1,088
-// tokens of two heads are 68 tiles: 158 us a training step in five groups, 101 in 68).
-constexpr int kGroupTiles = 16, kComputeUnits = 256;
-inline int group_tiles(long long total) {
-    const long long g = total / kComputeUnits;
-    return g < 1 ? 1 : (g > kGroupTiles ? kGroupTiles : (int)g);
+// Query tiles (of kBM list entries) per workgroup. Sixteen amortise the copy of a chunk's K and V; a call
+// of few tiles takes the number whose rounds of one workgroup per compute unit cost least, a workgroup
+// being its tiles two at a time (eight waves of 32 queries) and the copy, about one tile's time. Training
+// steps of 24 heads, 260-key chunks and k = 3: 5,760 tokens 901 us in the tiled kernels, 980 in groups of
+// fourteen (the last ones in a second round), 870 of sixteen; 7,320 tokens 1,117 tiled, 1,202 in groups of
+// sixteen, 1,079 of six; 130-key chunks, k = 2: 1,021 / 1,119 (fifteen) / 1,015 us (sixteen); 1,088 tokens
+// of two heads 158 us in groups of sixteen, 101 of one.
+constexpr int kGroupTiles = 16, kComputeUnits = 256, kGroupRounds = 4;
+inline int group_tiles(int N, int topk, int C, int BH) {
+    const long long tiles = ((long long)N * topk + kBM - 1) / kBM + C / 2;    // a head's, each list's last one half full
+    auto rounds = [&](int g) { return ((tiles + g - 1) / g * BH + kComputeUnits - 1) / kComputeUnits; };
+    int best = kGroupTiles;
+    if (rounds(best) > kGroupRounds) return best;                            // the last round is a small share
+    long long cost = rounds(best) * (best + 1);
+    for (int g = kGroupTiles - 2; g >= 0; g -= 2) {
+        const int t = g ? g : 1;
+        if (rounds(t) * (t + 1) < cost) { cost = rounds(t) * (t + 1); best = t; }
+    }
+    return best;
 }
 
 // The GPU has 8 XCDs with private L2 caches and hands consecutive workgroups to

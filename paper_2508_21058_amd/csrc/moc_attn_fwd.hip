@@ -509,7 +509,7 @@ static hipError_t fwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, void *o, f
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;   // upper bound; surplus items exit at once
         MOC_PROF("attn_fwd_routed", st);
         if (m->max_routed_len <= kChunkRows) {
-            a.group = group_tiles((long long)a.items_per_head * BH);
+            a.group = group_tiles(m->N, a.topk, m->C, BH);
             const int groups = (a.items_per_head + a.group - 1) / a.group;
             attn_fwd_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
         } else {

@@ -41,6 +41,13 @@ def test_routed_chunks_beside_a_long_caption(chunk):
     run_case(mi.multishot_layout(2, 300, 2, 2 * chunk, chunk, "frame"), 1, 2, 128, 2, torch.bfloat16, seed=41)
 
 
+# two, four and twelve query tiles per workgroup of the chunk-stationary kernels: groups that span many
+# short chunks, the last one of a head cut off
+@pytest.mark.parametrize("H", [3, 8, 24])
+def test_query_tiles_per_workgroup(H):
+    run_case(mi.stream_layout(1, 37, 603, 10, "chunk"), 1, H, 64, 16, torch.bfloat16, seed=61 + H)
+
+
 # fp32 storage through the same kernels as bf16: both head sizes, the chunk-stationary and the tiled
 # routed items, one group per workgroup (small calls) and ragged last tiles; k = 0 leaves forced links alone
 @pytest.mark.parametrize("d,chunk,topk", [(64, 33, 3), (128, 288, 2), (128, 300, 2), (64, 300, 1), (128, 65, 0)])
