@@ -41,9 +41,17 @@ struct RouteArgs {
 // for every score but a NaN (+-inf become exponent 0x7f8) and ordered like the scores; the low word
 // orders equal scores by chunk, ascending (a negative double falls as its low word grows, hence the
 // sign mask). A NaN counts as -inf, which is no candidate. (A score is never -0: its sum starts at +0.)
-__device__ __forceinline__ double entry(float score, uint32_t chunk) {
-    uint32_t hi;        // the larger of score and -inf: of two numbers of which one is a NaN, the other
-    asm("v_max_f32 %0, 0xff800000, %1" : "=v"(hi) : "v"(score));
+// The score is read straight from a matrix accumulator, so its first reader is a builtin: the compiler puts
+// the wait states such a read needs in front of instructions it knows, not in front of inline assembly. The
+// infinities come in registers whose values the compiler does not know (see Infinities): of a median with
+// constants it makes a minimum, which turns a NaN into +inf.
+struct Infinities {
+    float neg = -INFINITY, pos = INFINITY;
+    __device__ __forceinline__ Infinities() { asm("" : "+s"(neg)); asm("" : "+v"(pos)); }
+};
+__device__ __forceinline__ double entry(float score, uint32_t chunk, const Infinities &inf) {
+    // median of score, -inf and +inf: the score, or for a NaN the least of the other two
+    const uint32_t hi = __float_as_uint(__builtin_amdgcn_fmed3f(score, inf.neg, inf.pos));
     const uint32_t lo = chunk ^ ~(uint32_t)((int32_t)hi >> 31);
     return __hiloint2double((int)hi, (int)lo);
 }
@@ -232,9 +240,10 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
     };
 
     // ---------------- the lane's best KMAX candidates so far, best first
+    const Infinities inf;
     double list[KMAX];
 #pragma unroll
-    for (int p = 0; p < KMAX; ++p) list[p] = entry(-INFINITY, 0xffffffffu);
+    for (int p = 0; p < KMAX; ++p) list[p] = entry(-INFINITY, 0xffffffffu, inf);
     auto scan = [&](auto cur, int t) {
         constexpr int CUR = decltype(cur)::value;
         constexpr int M = KMAX < 16 ? KMAX : 16;       // entries sorted and merged at a time
@@ -244,7 +253,7 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
         const uint32_t jb = (uint32_t)(t * 32 + half * 4);
         double x[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = entry(sc[r], jb ^ (uint32_t)((r >> 2) * 8 + (r & 3)));
+        for (int r = 0; r < 16; ++r) x[r] = entry(sc[r], jb ^ (uint32_t)((r >> 2) * 8 + (r & 3)), inf);
 #pragma unroll
         for (int r = 0; r < 16; r += M) {
             sort_entries<M>(x + r);

@@ -1,0 +1,154 @@
+"""Wait states around inline assembly, read off the assembly the compiler writes for gfx950 (no GPU needed).
+
+The hardware does not interlock every pair of dependent instructions; the compiler puts the missing wait
+states in front of the instructions it emits itself, but it does not look inside inline assembly. The
+kernels' inline assembly therefore may not be the first to touch the result of a matrix instruction: a
+compiler instruction that reads or overwrites the accumulator, and so waits for it, has to come before it
+on every path."""
+import os
+import re
+import shutil
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+from paper_2508_21058_amd import build
+
+_REG = re.compile(r"(?<![\w.])([vsa])(?:\[(\d+):(\d+)\]|(\d+)(?!\w))")
+
+
+def _regs(text):
+    out = set()
+    for kind, lo, hi, one in _REG.findall(text):
+        out |= {(kind, i) for i in range(int(lo or one), int(hi or one) + 1)}
+    return out
+
+
+def _kernels(text):
+    """{function: [(line, op, args, inside inline assembly)]}; a label is an instruction named "label"."""
+    fns, fn, inline = {}, None, False
+    for no, raw in enumerate(text.splitlines(), 1):
+        line = raw.strip()
+        if line.startswith((";;#ASMSTART", ";;#ASMEND")):
+            inline = line.startswith(";;#ASMSTART")
+            continue
+        line = line.split(";")[0].strip()
+        label = re.match(r"([\w.$]+):$", line)
+        if label and label[1].startswith("_Z"):
+            fn = fns.setdefault(label[1], [])
+        elif label and label[1].startswith(".Lfunc_end"):
+            fn = None
+        elif label and fn is not None:
+            fn.append((no, "label", label[1], False))
+        elif fn is not None and re.match(r"(v|s|ds|global|buffer|flat|scratch)_", line):
+            op, _, args = line.partition(" ")
+            fn.append((no, op, args, inline))
+    return fns
+
+
+def _written_read(op, args):
+    """Registers an instruction writes and reads (the first operand is the destination where there is one)."""
+    if op.startswith(("global_store", "buffer_store", "scratch_store", "flat_store", "ds_write", "global_load_lds", "s_cmp", "s_cbranch")):
+        return set(), _regs(args)
+    if op.startswith("v_permlane"):
+        return _regs(args), _regs(args)
+    parts = re.split(r",(?![^\[]*\])", args)
+    carry = op.startswith(("v_add_co", "v_sub_co", "v_addc_co", "v_subb_co", "v_mad_u64", "v_mad_i64", "v_div_scale"))
+    n = 2 if carry else 1
+    return _regs(",".join(parts[:n])), _regs(",".join(parts[n:]))
+
+
+class _Pending:
+    """What may be outstanding in front of an instruction, over all paths that lead to it."""
+
+    def __init__(self, matrix=()):
+        self.matrix = set(matrix)          # register tuples of matrix results nobody has waited for
+
+    def merge(self, other):
+        return _Pending(self.matrix | other.matrix)
+
+    def __eq__(self, other):
+        return other is not None and self.matrix == other.matrix
+
+    def step(self, op, args, inline):
+        """Moves past one instruction; returns what is wrong with it."""
+        if op == "label":
+            return []
+        written, read = _written_read(op, args)
+        touched = {t for t in self.matrix if (written | read) & set(t)}
+        bad = ["touches a matrix result first"] if inline and touched else []
+        self.matrix -= touched
+        if op.startswith("v_mfma"):
+            self.matrix.add(tuple(sorted(written)))
+        return bad
+
+
+def _violations(ins):
+    """Forward data flow over the instructions of one function."""
+    at = {a: i for i, (_, op, a, _) in enumerate(ins) if op == "label"}
+    succ = []
+    for i, (_, op, args, _) in enumerate(ins):
+        follow = [i + 1] if i + 1 < len(ins) else []
+        if op == "s_branch":
+            follow = [at[args]]
+        elif op.startswith("s_cbranch"):
+            follow = follow + [at[args]]
+        elif op == "s_endpgm":
+            follow = []
+        succ.append(follow)
+    leaders = {0} | set(at.values()) | {j for i, f in enumerate(succ) if f != [i + 1] for j in f + [i + 1]}
+    state, work, bad = {0: _Pending()}, [0], set()
+    while work:
+        i = start = work.pop()
+        cur = _Pending().merge(state[start])
+        while True:
+            no, op, args, inline = ins[i]
+            bad |= {(no, op, args, why) for why in cur.step(op, args, inline)}
+            if succ[i] != [i + 1] or i + 1 in leaders:
+                break
+            i += 1
+        for j in succ[i]:
+            new = cur.merge(state[j]) if j in state else cur
+            if new != state.get(j):
+                state[j] = _Pending().merge(new)
+                work.append(j)
+    return sorted(bad)
+
+
+def _check(text):
+    return {f: v for f, ins in _kernels(text).items() if ins for v in [_violations(ins)] if v}
+
+
+_MFMA = "\tv_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], 0\n"
+_ASM = "\t;;#ASMSTART\n\t%s\n\t;;#ASMEND\n"
+
+
+@pytest.mark.parametrize("body,found", [
+    (_MFMA + _ASM % "v_max_f32 v30, 0xff800000, v3", True),
+    (_MFMA + "\ts_nop 7\n\tv_mov_b32_e32 v31, v3\n" + _ASM % "v_max_f32 v30, 0xff800000, v4", False),
+    (_MFMA + _ASM % "v_max_f32 v30, 0xff800000, v33", False),
+    # a branch around the one instruction that waits
+    (_MFMA + "\ts_cbranch_execz .LBB0_1\n\tv_mov_b32_e32 v31, v3\n.LBB0_1:\n" + _ASM % "v_max_f32 v30, 0xff800000, v4", True),
+    # round a loop
+    ("\ts_mov_b32 s0, 0\n.LBB0_1:\n" + _ASM % "v_max_f32 v30, 0xff800000, v4" + _MFMA + "\ts_cbranch_scc1 .LBB0_1\n", True),
+])
+def test_the_reader_sees_planted_faults(body, found):
+    assert bool(_check("_Zkernel: ; @_Zkernel\n" + body + "\ts_endpgm\n")) == found
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_no_unguarded_inline_assembly(tmp_path):
+    def assemble(unit):
+        out = str(tmp_path / (unit + ".s"))
+        subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, unit + ".hip"), "-o", out],
+                       check=True, capture_output=True)
+        return open(out).read()
+
+    units = [u for u in build.UNITS if u != "moc_api"]         # (no kernels there)
+    with ThreadPoolExecutor(max_workers=6) as ex:
+        texts = dict(zip(units, ex.map(assemble, units)))
+    assert sum(len(_kernels(t)) for t in texts.values()) > 50, "the assembly was not understood"
+    bad = {u: v for u, t in texts.items() for v in [_check(t)] if v}
+    assert not bad, "\n".join(f"{u} {f[:70]} line {no}: {op} {args}: {why}"
+                              for u, fs in bad.items() for f, v in fs.items() for no, op, args, why in v[:3])

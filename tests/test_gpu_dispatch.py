@@ -125,6 +125,42 @@ def test_selection_order_and_ties(topk, levels, dtype):
     meta.close()
 
 
+# scores that differ only in the products added last: pooled keys whose three bf16 planes are all in use
+# and differ only in the third (one-hot queries), and queries whose first two planes cancel and whose third
+# meets integer keys. Every product and sum is exact in fp32, so the order is pinned. 21 distinct scores
+# among 330 chunks: ties throughout.
+@pytest.mark.parametrize("topk", [2, 8, 16, 32])
+@pytest.mark.parametrize("where,dtype", [("keys", torch.bfloat16), ("keys", torch.float32), ("queries", torch.float32)])
+def test_selection_by_the_last_products(topk, where, dtype):
+    C, per, H, d = 330, 4, 2, 128
+    N = C * per
+    rng = np.random.default_rng(topk)
+    t = rng.integers(1, 22, (H, C))
+    hi, mid, lo = 1.0, 3 * 2.0 ** -10, 2.0 ** -23
+    q, k = np.zeros((1, H, N, d)), np.zeros((1, H, N, d))
+    if where == "keys":          # mean of (4 hi, 4 mid, 4 t lo, 0) in every feature; bf16 holds each of them
+        rows = np.stack([np.full((H, C), 4 * hi), np.full((H, C), 4 * mid), 4 * t * lo, np.zeros((H, C))], axis=2)
+        k[0] = rows.reshape(H, N)[..., None]
+        q[0, np.arange(H)[:, None], np.arange(N)[None], rng.integers(0, d, (H, N))] = rng.choice([-1.0, 1.0], (H, N))
+    else:                        # features x and y hold the same integer: score = t * lo
+        x = rng.permutation(d)[:2]
+        k[0, :, :, x] = np.repeat(t, per, axis=1)
+        q[0, :, :, x[0]], q[0, :, :, x[1]] = hi + mid + 5 * lo, -(hi + mid)
+    offs = np.arange(0, N + 1, per, dtype=np.int32)
+    meta = mb.chunk_meta(offs, np.zeros(C, np.int32), np.arange(C, dtype=np.int32), None)
+    qd, kd = (torch.from_numpy(a).to("cuda").to(dtype).contiguous() for a in (q, k))
+    assert torch.equal(qd.double().cpu(), torch.from_numpy(q)) and torch.equal(kd.double().cpu(), torch.from_numpy(k))
+    _, sel = mb.route(meta, qd, kd, topk, False)
+    sel = sel.cpu().numpy()[0]
+    kbar = k[0].reshape(H, C, per, d).mean(2)
+    for h in range(H):
+        s = q[0, h] @ kbar[h].T
+        s[np.arange(N), np.arange(N) // per] = -np.inf
+        assert len(np.unique(s[0])) == 22
+        assert np.array_equal(sel[h], np.argsort(-s, axis=1, kind="stable")[:, :topk])
+    meta.close()
+
+
 # a NaN score is no candidate: the chunk never appears, a query of NaN selects nothing
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_nan_scores_are_no_candidates(dtype):
