@@ -151,7 +151,10 @@ template <int BN> struct TileIter {
     int r, pos;
     KeyRange cur;
     __device__ __forceinline__ explicit TileIter(const ItemDesc &d) : it(d), r(0), pos(0), cur(d.range(0)) {}
-    __device__ __forceinline__ int start() const { return cur.start + pos; }
+    // In a scalar register before any address is made of it: the tile copies (inline assembly, which gets no
+    // wait states from the compiler) take their base from scalar registers, and one that a vector instruction
+    // has just written may only be read five wait states later; scalar results may be read at once.
+    __device__ __forceinline__ int start() const { return __builtin_amdgcn_readfirstlane(cur.start + pos); }
     __device__ __forceinline__ int valid() const { return min(BN, cur.len - pos); }
     __device__ __forceinline__ bool next() {
         pos += BN;

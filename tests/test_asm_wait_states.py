@@ -1,10 +1,13 @@
 """Wait states around inline assembly, read off the assembly the compiler writes for gfx950 (no GPU needed).
 
 The hardware does not interlock every pair of dependent instructions; the compiler puts the missing wait
-states in front of the instructions it emits itself, but it does not look inside inline assembly. The
-kernels' inline assembly therefore may not be the first to touch the result of a matrix instruction: a
-compiler instruction that reads or overwrites the accumulator, and so waits for it, has to come before it
-on every path."""
+states in front of the instructions it emits itself, but it does not look inside inline assembly. On every path
+  - inline assembly is not the first to touch the result of a matrix instruction: a compiler instruction
+    that reads or overwrites the accumulator, and so waits for it, comes before it;
+  - a scalar register that a vector instruction has written is read by a memory instruction of inline
+    assembly five wait states later at the earliest, by a vector instruction of it two;
+  - a vector register that inline assembly has written is read by a lane permute two wait states later at
+    the earliest, by a lane read one."""
 import os
 import re
 import shutil
@@ -62,14 +65,23 @@ def _written_read(op, args):
 class _Pending:
     """What may be outstanding in front of an instruction, over all paths that lead to it."""
 
-    def __init__(self, matrix=()):
+    def __init__(self, matrix=(), scalar=(), vector=()):
         self.matrix = set(matrix)          # register tuples of matrix results nobody has waited for
+        self.scalar = dict(scalar)         # scalar registers a vector instruction wrote: wait states since (< 5)
+        self.vector = dict(vector)         # vector registers inline assembly wrote: wait states since (< 2)
+
+    def copy(self):
+        return _Pending(self.matrix, self.scalar, self.vector)
 
     def merge(self, other):
-        return _Pending(self.matrix | other.matrix)
+        out = _Pending(self.matrix | other.matrix, self.scalar, self.vector)
+        for mine, more in ((out.scalar, other.scalar), (out.vector, other.vector)):
+            for r, age in more.items():
+                mine[r] = min(mine.get(r, age), age)
+        return out
 
     def __eq__(self, other):
-        return other is not None and self.matrix == other.matrix
+        return other is not None and (self.matrix, self.scalar, self.vector) == (other.matrix, other.scalar, other.vector)
 
     def step(self, op, args, inline):
         """Moves past one instruction; returns what is wrong with it."""
@@ -78,9 +90,21 @@ class _Pending:
         written, read = _written_read(op, args)
         touched = {t for t in self.matrix if (written | read) & set(t)}
         bad = ["touches a matrix result first"] if inline and touched else []
+        need = 2 if op.startswith("v_") else 5 if op.startswith(("global_", "buffer_", "flat_", "scratch_")) else 0
+        if inline and any(self.scalar.get(r, 9) < need for r in read):
+            bad.append(f"reads a scalar register less than {need} wait states after a vector instruction wrote it")
+        need = 2 if op.startswith("v_permlane") else 1 if op.startswith(("v_readlane", "v_readfirstlane")) else 0
+        if any(self.vector.get(r, 9) < need for r in read):
+            bad.append(f"reads a register less than {need} wait states after inline assembly wrote it")
+        passed = int(args, 0) + 1 if op == "s_nop" else 1
+        self.scalar = {r: n + passed for r, n in self.scalar.items() if n + passed < 5 and r not in written}
+        self.vector = {r: n + passed for r, n in self.vector.items() if n + passed < 2 and r not in written}
         self.matrix -= touched
         if op.startswith("v_mfma"):
             self.matrix.add(tuple(sorted(written)))
+        if op.startswith("v_"):
+            self.scalar.update({r: 0 for r in written if r[0] == "s"})
+            self.vector.update({r: 0 for r in written if r[0] == "v" and inline})
         return bad
 
 
@@ -101,7 +125,7 @@ def _violations(ins):
     state, work, bad = {0: _Pending()}, [0], set()
     while work:
         i = start = work.pop()
-        cur = _Pending().merge(state[start])
+        cur = state[start].copy()
         while True:
             no, op, args, inline = ins[i]
             bad |= {(no, op, args, why) for why in cur.step(op, args, inline)}
@@ -111,7 +135,7 @@ def _violations(ins):
         for j in succ[i]:
             new = cur.merge(state[j]) if j in state else cur
             if new != state.get(j):
-                state[j] = _Pending().merge(new)
+                state[j] = new.copy()
                 work.append(j)
     return sorted(bad)
 
@@ -122,6 +146,8 @@ def _check(text):
 
 _MFMA = "\tv_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], 0\n"
 _ASM = "\t;;#ASMSTART\n\t%s\n\t;;#ASMEND\n"
+_BASE = "\tv_readfirstlane_b32 s8, v40\n\tv_readfirstlane_b32 s9, v41\n"
+_COPY = "s_mov_b32 m0, s4\n\ts_nop %d\n\tglobal_load_lds_dwordx4 v42, s[8:9]"
 
 
 @pytest.mark.parametrize("body,found", [
@@ -132,6 +158,11 @@ _ASM = "\t;;#ASMSTART\n\t%s\n\t;;#ASMEND\n"
     (_MFMA + "\ts_cbranch_execz .LBB0_1\n\tv_mov_b32_e32 v31, v3\n.LBB0_1:\n" + _ASM % "v_max_f32 v30, 0xff800000, v4", True),
     # round a loop
     ("\ts_mov_b32 s0, 0\n.LBB0_1:\n" + _ASM % "v_max_f32 v30, 0xff800000, v4" + _MFMA + "\ts_cbranch_scc1 .LBB0_1\n", True),
+    (_BASE + _ASM % (_COPY % 0), True),
+    (_BASE + _ASM % (_COPY % 3), False),
+    (_BASE + "\ts_add_u32 s8, s8, s6\n\ts_addc_u32 s9, s9, 0\n" + _ASM % (_COPY % 0), False),
+    (_ASM % "v_max_f64 v[2:3], v[4:5], v[6:7]" + "\tv_permlane32_swap_b32_e32 v2, v3\n", True),
+    (_ASM % "v_max_f64 v[2:3], v[4:5], v[6:7]" + "\ts_nop 1\n\tv_permlane32_swap_b32_e32 v2, v3\n", False),
 ])
 def test_the_reader_sees_planted_faults(body, found):
     assert bool(_check("_Zkernel: ; @_Zkernel\n" + body + "\ts_endpgm\n")) == found
