@@ -216,3 +216,18 @@ def test_gather_table_sizes(n_ranges, words):
         ranges[0], rows = (5, 1), np.array([5])
     got = mb.gather_rows(src, ranges)
     assert torch.equal(got.view(torch.int16), src.view(torch.int16)[:, torch.from_numpy(rows).cuda()])
+
+
+# many short ranges under one workgroup's words: tables on both sides of a round of the 64-wide search (64, 4096
+# entries), more ranges than are walked, one huge range beside single rows; two and eight words a lane
+@pytest.mark.parametrize("n_ranges", [65, 4096, 4097, 9000])
+@pytest.mark.parametrize("words,outer", [(1, 1), (3, 2), (8, 3), (96, 1)])
+def test_gather_of_short_ranges(n_ranges, words, outer):
+    N = 7000
+    rng = np.random.default_rng(n_ranges + words)
+    src = torch.randint(0, 1 << 15, (outer, N, words * 8), device="cuda", dtype=torch.int16).view(torch.bfloat16)
+    ranges = [(int(a), 1 + int(rng.random() < 0.1)) for a in rng.integers(0, N - 2, n_ranges)]
+    ranges[n_ranges // 2] = (5, N - 5)
+    rows = np.concatenate([np.arange(a, a + n) for a, n in ranges])
+    got = mb.gather_rows(src, ranges)
+    assert torch.equal(got.view(torch.int16), src.view(torch.int16)[:, torch.from_numpy(rows).cuda()])
