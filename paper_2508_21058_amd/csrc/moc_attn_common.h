@@ -77,22 +77,40 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
 }
 
 // The key-stationary work list of a head holds its caption items (n_text, the long ones) before its
-// video items. Both kinds are sliced over the XCDs separately, caption items of every head first: a
+// video items. Both kinds are dealt to the XCDs separately, caption items of every head first: a
 // slice of the plain head-major list would give some XCDs the caption items of a head and others none
 // (six heads of a 457k-token stream: 1.30 M against 0.53 M query tiles), and start the caption items of
 // its last head when the rest is nearly done. With the shorter caption segments of text_segments() this
 // took the 32-shot layer of six heads from 104.4 to 99.6 ms, 13k tokens of six fp32 heads from 1,435 to
-// 1,217 us and the 1,088-token fp32 layer from 119 to 104 us. Launch kv_grid() workgroups; returns false
+// 1,217 us and the 1,088-token fp32 layer from 119 to 104 us. Caption items cost alike and go out as one
+// slice per XCD. Video items do not: under the causal mask early chunks are routed to by more queries. Whole
+// heads balance that and share their queries in an XCD's L2 (two samples of eight ragged heads: 367 us, dealt
+// out eight items at a time 408), so XCDs take equal numbers of heads; the BH % 8 heads left are dealt
+// out two neighbours at a time. Slices of those left some XCDs the long lists of a head: dK/dV of one head of
+// 80k tokens in 5,244-key chunks 2,225 us in slices, 976 dealt out; two heads of 311k tokens 41.3 -> 26.7 ms;
+// six heads of 457k tokens 39.4 -> 37.2 ms; six fp32 heads of 13k ragged tokens 247 -> 257 us. (One at a
+// time loses 2.5 ms of the 457k tokens, eight 12 us of the 13k.) Launch kv_grid() workgroups; returns false
 // for padding.
+constexpr int kVideoTurn = 2;
 __host__ __device__ inline int kv_grid(int n_items, int n_text, int BH) {
     return xcd_grid((long long)n_text * BH) + xcd_grid((long long)(n_items - n_text) * BH);
 }
 __device__ __forceinline__ bool kv_item(int n_items, int n_text, int BH, int &bh, int &item) {
     const long long tot_t = (long long)n_text * BH, tot_v = (long long)(n_items - n_text) * BH;
-    const int per_t = (int)((tot_t + kXcds - 1) / kXcds), per_v = (int)((tot_v + kXcds - 1) / kXcds);
+    const int per_t = (int)((tot_t + kXcds - 1) / kXcds);
     const int x = blockIdx.x % kXcds, p = blockIdx.x / kXcds;
     const bool text = p < per_t;
-    const int l = text ? x * per_t + p : x * per_v + (p - per_t);
+    int l = x * per_t + p;
+    if (!text) {
+        const int whole = BH / kXcds * (n_items - n_text);                                        // an XCD's items of whole heads
+        const int left = (BH % kXcds) * (n_items - n_text);                                       // items of the other heads
+        const int turns = left / (kXcds * kVideoTurn) * kVideoTurn;                               // an XCD's of them in whole turns
+        const int rest = (left - turns * kXcds + kXcds - 1) / kXcds;                              // and behind them
+        const int v = p - per_t, u = v - whole;
+        l = u < 0 ? x * whole + v
+                  : whole * kXcds + (u < turns ? (u / kVideoTurn * kXcds + x) * kVideoTurn + u % kVideoTurn
+                                               : turns * kXcds + x * rest + (u - turns));
+    }
     if (l >= (text ? tot_t : tot_v)) return false;
     const int per_head = text ? n_text : n_items - n_text;
     bh = l / per_head;

@@ -26,6 +26,13 @@ def test_key_stationary_work_split(B, H, shots, text, frames, frame):
     run_case(lay, B, H, 64, 2, torch.bfloat16, seed=31 + H)
 
 
+# video items: heads that every XCD takes whole, heads left over and dealt out two items at a time, with none,
+# some and only incomplete turns (16 items) among them
+@pytest.mark.parametrize("H,chunks", [(1, 7), (1, 17), (2, 16), (7, 5), (8, 3), (11, 11), (16, 2)])
+def test_video_items_over_the_xcds(H, chunks):
+    run_case(mi.stream_layout(1, 9, 21 * chunks, 21, "chunk"), 1, H, 64, 2, torch.bfloat16, seed=81 + H)
+
+
 def _no_captions(shots, frames, frame):
     offs = np.arange(0, shots * frames * frame + 1, 48, dtype=np.int32)
     C = len(offs) - 1
