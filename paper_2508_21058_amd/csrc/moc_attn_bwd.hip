@@ -284,14 +284,14 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int N = a.N, C = a.C;
-    const int groups_per_head = (a.items_per_head + a.group - 1) / a.group;
+    const int groups_per_head = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
     int logical;
     if (!xcd_remap((long long)groups_per_head * a.BH, logical)) return;
     const int bh = logical / groups_per_head;
     const int32_t *toff = a.tile_off + (size_t)bh * (C + 1);
     const int32_t *loff = a.list_off + (size_t)bh * (C + 1);
-    int t0 = (logical - bh * groups_per_head) * a.group;
-    const int t1 = min(t0 + a.group, toff[C]);
+    int t0 = (logical - bh * groups_per_head) * kGroupTiles;
+    const int t1 = min(t0 + kGroupTiles, toff[C]);
     if (t0 >= t1) return;
     int j;
     {
@@ -1115,9 +1115,8 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     if (a.topk > 0) {
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;
         MOC_PROF("attn_bwd_dq_routed", st);
-        if (m->max_routed_len <= kChunkRows) {
-            a.group = group_tiles(m->N, a.topk, m->C, BH);
-            const int groups = (a.items_per_head + a.group - 1) / a.group;
+        if (chunk_stationary(m, a.topk, BH)) {
+            const int groups = (a.items_per_head + kGroupTiles - 1) / kGroupTiles;
             attn_bwd_dq_chunk_kernel<D><<<dim3(xcd_grid((long long)groups * BH)), dim3(512), 0, st>>>(a);
         } else {
             attn_bwd_dq_kernel<D, MODE_ROUTED, bf16_t><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);

@@ -18,7 +18,6 @@ struct FwdArgs {
     float *plse;       // [BH, N, slots]   partial log-sum-exp (forward only)
     int N, C, topk, slots;
     int BH, items_per_head;   // work list of the launch: items_per_head entries per (batch, head)
-    int group;                // entries per workgroup (chunk-stationary kernels)
     float scale, scale_log2;
     const AnchorTile *atiles;
     const int32_t *arange_off;
@@ -42,25 +41,24 @@ struct FwdArgs {
 // LDS, but 576 of them leave one workgroup per compute unit: 1,165 us a step of ragged chunks up to 340
 // keys against 1,058 in the tiled kernels, so the bound is the same.
 constexpr int kChunkRows = 288;
-// Query tiles (of kBM list entries) per workgroup. Sixteen amortise the copy of a chunk's K and V; a call
-// of few tiles takes the number whose rounds of one workgroup per compute unit cost least, a workgroup
-// being its tiles two at a time (eight waves of 32 queries) and the copy, about one tile's time. Training
-// steps of 24 heads, 260-key chunks and k = 3: 5,760 tokens 901 us in the tiled kernels, 980 in groups of
-// fourteen (the last ones in a second round), 870 of sixteen; 7,320 tokens 1,117 tiled, 1,202 in groups of
-// sixteen, 1,079 of six; 130-key chunks, k = 2: 1,021 / 1,119 (fifteen) / 1,015 us (sixteen); 1,088 tokens
-// of two heads 158 us in groups of sixteen, 101 of one.
-constexpr int kGroupTiles = 16, kComputeUnits = 256, kGroupRounds = 4;
-inline int group_tiles(int N, int topk, int C, int BH) {
-    const long long tiles = ((long long)N * topk + kBM - 1) / kBM + C / 2;    // a head's, each list's last one half full
-    auto rounds = [&](int g) { return ((tiles + g - 1) / g * BH + kComputeUnits - 1) / kComputeUnits; };
-    int best = kGroupTiles;
-    if (rounds(best) > kGroupRounds) return best;                            // the last round is a small share
-    long long cost = rounds(best) * (best + 1);
-    for (int g = kGroupTiles - 2; g >= 0; g -= 2) {
-        const int t = g ? g : 1;
-        if (rounds(t) * (t + 1) < cost) { cost = rounds(t) * (t + 1); best = t; }
-    }
-    return best;
+constexpr int kGroupTiles = 16;       // query tiles (of kBM list entries) per workgroup: they amortise the copy
+constexpr int kComputeUnits = 256;
+// Which kernels take the routed items. A workgroup of the chunk-stationary ones fills a compute unit and waits
+// for its chunk's copy and its first queries with nothing beside it, and its last round is long: they need many
+// rounds. The tiled kernels run two independent workgroups on a unit, an item each. Forward + dQ of the routed
+// items, chunk-stationary / tiled, at so many query tiles per compute unit (heads of 128 features):
+//   13 tiles  (6k tokens, 24 heads, k = 3)   40-key chunks 268 / 158 us, 260-key 227 / 166
+//   29 tiles  (10k, 16 heads, k = 6)         409 / 307, 407 / 362
+//   66 tiles  (60k, six heads, k = 6)        64-key 871 / 865, 260-key 1,064 / 1,079
+//   88 tiles  (24k, 24 heads, k = 5)         1,049 / 981, 1,408 / 1,348
+//   95 tiles  (130k, two heads, k = 12)      1,076 / 1,098, 1,480 / 1,548
+//   120 tiles (33k, 24 heads, k = 5)         1,416 / 1,365, 1,856 / 1,897
+//   293 tiles (200k, six heads, k = 8)       3,451 / 3,731, 4,629 / 5,011
+// Smaller groups (one to fourteen tiles) gain on sixteen below 60 tiles, but stay behind the tiled kernels.
+constexpr int kStationaryTiles = 92;
+inline bool chunk_stationary(const moc_meta *m, int topk, int BH) {
+    return m->max_routed_len <= kChunkRows &&
+           (long long)m->N * topk * BH >= (long long)kStationaryTiles * kComputeUnits * kBM;
 }
 
 // The GPU has 8 XCDs with private L2 caches and hands consecutive workgroups to

@@ -7,7 +7,8 @@ import torch
 
 import moc_inputs as mi
 from paper_2508_21058_amd import binding as mb
-from tests.test_gpu_parity import run_case
+from tests import bruteforce as bf
+from tests.test_gpu_parity import check_close, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -42,21 +43,20 @@ def _no_captions(shots, frames, frame):
 
 
 # a caption longer than the resident rows of the chunk-stationary kernels beside chunks that fit (288),
-# and chunks of one key too many
+# and chunks of one key too many (a call this small takes the tiled kernels for both)
 @pytest.mark.parametrize("chunk", [288, 289])
 def test_routed_chunks_beside_a_long_caption(chunk):
     run_case(mi.multishot_layout(2, 300, 2, 2 * chunk, chunk, "frame"), 1, 2, 128, 2, torch.bfloat16, seed=41)
 
 
-# two, four and twelve query tiles per workgroup of the chunk-stationary kernels: groups that span many
-# short chunks, the last one of a head cut off
+# routed items of many short chunks (ten keys), the last one of a head cut off
 @pytest.mark.parametrize("H", [3, 8, 24])
 def test_query_tiles_per_workgroup(H):
     run_case(mi.stream_layout(1, 37, 603, 10, "chunk"), 1, H, 64, 16, torch.bfloat16, seed=61 + H)
 
 
-# fp32 storage through the same kernels as bf16: both head sizes, the chunk-stationary and the tiled
-# routed items, one group per workgroup (small calls) and ragged last tiles; k = 0 leaves forced links alone
+# fp32 storage through the same kernels as bf16: both head sizes, ragged last tiles; k = 0 leaves forced
+# links alone
 @pytest.mark.parametrize("d,chunk,topk", [(64, 33, 3), (128, 288, 2), (128, 300, 2), (64, 300, 1), (128, 65, 0)])
 def test_fp32_storage(d, chunk, topk):
     run_case(mi.stream_layout(2, 37, 4 * chunk + 5, chunk, "chunk"), 1, 3, d, topk, torch.float32, seed=51 + chunk)
@@ -192,12 +192,38 @@ def test_nan_scores_are_no_candidates(dtype):
     meta.close()
 
 
-# routed chunks on both sides of the tile and tail counts of the chunk-stationary forward (64-key tiles, a
-# tail of at most 32 keys, one or two 16-key steps of V)
+# routed chunks on both sides of the key tiles, in calls small enough for the tiled kernels
 @pytest.mark.parametrize("chunk", [1, 16, 17, 32, 33, 64, 65, 80, 81, 96, 97, 128, 257, 273, 288])
 @pytest.mark.parametrize("d", [64, 128])
 def test_routed_tile_edges(chunk, d):
     run_case(mi.stream_layout(2, 20, 5 * chunk + (chunk + 1) // 2, chunk, "chunk"), 1, 2, d, 3, torch.bfloat16, seed=71 + chunk)
+
+
+# The chunk-stationary kernels, which take the routed items from 92 query tiles (of 128 entries) per compute
+# unit on: the same edges (64-key tiles, a tail of at most 32 keys, one or two 16-key steps of V), reached by
+# many short heads; with one head less the tiled kernels run. Three heads are checked against dense float64.
+@pytest.mark.parametrize("chunk,caption,less", [(1, 20, 0), (16, 20, 0), (17, 300, 0), (32, 20, 0), (33, 20, 0), (64, 20, 0),
+                                                (65, 20, 1), (80, 20, 0), (96, 20, 0), (97, 20, 0), (128, 300, 1),
+                                                (257, 300, 0), (273, 20, 0), (288, 20, 0), (289, 20, 0)])
+@pytest.mark.parametrize("d,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (128, torch.float32)])
+def test_routed_items_of_many_heads(chunk, caption, less, d, dtype):
+    topk = 4
+    lay = mi.stream_layout(1, caption, max(5 * chunk, 500) + (chunk + 1) // 2, chunk, "chunk")
+    N = lay.N
+    H = -(-92 * 256 * 128 // (N * topk)) - less
+    g = torch.Generator(device="cuda").manual_seed(chunk + d)
+    q, k, v, d_o = (torch.randn(1, H, N, d, generator=g, device="cuda").bfloat16().to(dtype) for _ in range(4))
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    _, sel = mb.route(meta, q, k, topk)
+    ws = mb.attn_workspace(meta, 1, H, d, topk, dtype, True)
+    o, lse = mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
+    dq, dk, dv = mb.attn_bwd(meta, q, k, v, o, lse, d_o, sel, workspace=ws, after_fwd=True)
+    for h in (0, H // 2, H - 1):
+        qn, kn, vn, dn = (x[0, h].double().cpu().numpy() for x in (q, k, v, d_o))
+        ref = bf.dense_masked_attention(qn, kn, vn, bf.token_mask(lay, sel[0, h].cpu().numpy()), dn)
+        for name, x in (("o", o), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv)):
+            check_close(name, x[0, h].double().cpu().numpy(), ref[name])
+    meta.close()
 
 
 # regularised rows at the widths the kernel's lists are sized for (8 + 4, 16 + 4, 32) and one past each,
