@@ -62,6 +62,14 @@ def test_fp32_storage(d, chunk, topk):
     run_case(mi.stream_layout(2, 37, 4 * chunk + 5, chunk, "chunk"), 1, 3, d, topk, torch.float32, seed=51 + chunk)
 
 
+# epilogue of the forced-link items: rows of slots on both sides of the eight that are loaded together, in
+# windows of a few queries, with rows of fewer candidates than slots
+@pytest.mark.parametrize("topk", [7, 8, 9, 17, 32])
+@pytest.mark.parametrize("d", [64, 128])
+def test_merged_slots(topk, d):
+    run_case(mi.stream_layout(1, 11, 300, 7, "chunk"), 1, 2, d, topk, torch.bfloat16, seed=91 + topk)
+
+
 # list builder: both sides of the one-workgroup limit (32768 entries a head, 1000 chunks), rows whose
 # slots fill 64 lanes exactly or leave some idle, more chunks than a workgroup has lanes
 @pytest.mark.parametrize("N,chunk,topk", [(4096, 64, 8), (4097, 64, 8), (1000, 1, 5), (1002, 1, 3), (2340, 13, 14), (300, 7, 32),
