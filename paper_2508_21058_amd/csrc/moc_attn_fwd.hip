@@ -280,8 +280,8 @@ __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane,
     }
 }
 
-// OT: storage type of the final output (forced-link items only)
-template <int D, int MODE, typename OT>
+// OT: storage type of the final output (forced-link items only); QT: storage type of the queries read
+template <int D, int MODE, typename OT, typename QT = bf16_t>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
     typedef bf16_t T;
     constexpr int BN = 64;
@@ -309,13 +309,13 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
     if (MODE == MODE_ANCHOR) { qi = it.q_start + rc; }
     else { const int e = it.entries[rc]; qi = e >> 5; slot = e & 31; }
 
-    const T *qbase = static_cast<const T *>(a.q) + (size_t)bh * N * D;
+    const QT *qbase = static_cast<const QT *>(a.q) + (size_t)bh * N * D;
     const T *kbase = static_cast<const T *>(a.k) + (size_t)bh * N * D;
     const T *vbase = static_cast<const T *>(a.v) + (size_t)bh * N * D;
 
     bf16x8 qf[KS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qf[s] = Io<T>::load8(qbase + (size_t)qi * D + s * 16 + half * 8);
+    for (int s = 0; s < KS; ++s) qf[s] = Io<QT>::load8(qbase + (size_t)qi * D + s * 16 + half * 8);
 
     f32x16 oacc[DB];
 #pragma unroll
@@ -501,17 +501,17 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
     }
 }
 
-// fp32 -> bf16 copies of three tensors of n elements (n a multiple of 8), 8 elements a lane; bound by HBM
+// fp32 -> bf16 copies of up to three tensors of n elements (n a multiple of 8), 8 elements a lane; bound by HBM
 __global__ __launch_bounds__(256) void to_bf16_kernel(const float *x0, const float *x1, const float *x2, bf16_t *out, size_t n) {
     const float *x = blockIdx.y == 0 ? x0 : (blockIdx.y == 1 ? x1 : x2);
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
     if (i < n) *reinterpret_cast<bf16x8 *>(out + blockIdx.y * n + i) = Io<float>::load8(x + i);
 }
 
-hipError_t launch_to_bf16(const void *q, const void *k, const void *v, void *out, size_t n, hipStream_t st) {
+hipError_t launch_to_bf16(const void *x0, const void *x1, const void *x2, void *out, size_t n, hipStream_t st) {
     MOC_PROF("to_bf16", st);
-    to_bf16_kernel<<<dim3((unsigned)((n / 8 + 255) / 256), 3), dim3(256), 0, st>>>(
-        static_cast<const float *>(q), static_cast<const float *>(k), static_cast<const float *>(v),
+    to_bf16_kernel<<<dim3((unsigned)((n / 8 + 255) / 256), x2 ? 3 : 2), dim3(256), 0, st>>>(
+        static_cast<const float *>(x0), static_cast<const float *>(x1), static_cast<const float *>(x2),
         static_cast<bf16_t *>(out), n);
     return hipGetLastError();
 }
@@ -532,7 +532,9 @@ static hipError_t fwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, void *o, f
     MOC_PROF("attn_fwd_forced", st);
     a.items_per_head = m->n_atiles;
     a.o_out = o; a.lse_out = lse;
-    attn_fwd_kernel<D, MODE_ANCHOR, OT><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
+    const dim3 grid(xcd_grid((long long)a.items_per_head * BH));
+    if (sizeof(OT) == 4 && a.topk == 0) attn_fwd_kernel<D, MODE_ANCHOR, OT, OT><<<grid, dim3(256), 0, st>>>(a);
+    else attn_fwd_kernel<D, MODE_ANCHOR, OT><<<grid, dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -543,9 +545,12 @@ hipError_t launch_attn_fwd(const moc_meta *m, int BH, int d, int dtype, const vo
     if (dtype == MOC_F32) {
         const size_t n = (size_t)BH * m->N * d;
         bf16_t *c = reinterpret_cast<bf16_t *>(ws + L.cvt);
-        const hipError_t e = launch_to_bf16(q, k, v, c, n, st);
+        // With no routed links a query is read once, by its forced-link item, which rounds it then: a copy would
+        // cost more than it saves (forward of 12 heads, 40k tokens in 240-token windows: 337 us with it, 294 without).
+        const hipError_t e = topk > 0 ? launch_to_bf16(q, k, v, c, n, st) : launch_to_bf16(k, v, nullptr, c + n, n, st);
         if (e != hipSuccess) return e;
-        a.q = c; a.k = c + n; a.v = c + 2 * n;
+        if (topk > 0) a.q = c;
+        a.k = c + n; a.v = c + 2 * n;
     }
     a.po = reinterpret_cast<bf16_t *>(ws + L.po);
     a.plse = reinterpret_cast<float *>(ws + L.plse);

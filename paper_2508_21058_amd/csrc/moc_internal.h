@@ -133,8 +133,8 @@ hipError_t fused_wait_flag(int *timed_out);
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws,
                               const AttnWs &L, hipStream_t st);
 
-// bf16 copies of three fp32 tensors of n elements each, back to back in `out`
-hipError_t launch_to_bf16(const void *q, const void *k, const void *v, void *out, size_t n, hipStream_t st);
+// bf16 copies of two or three (x2 not NULL) fp32 tensors of n elements each, back to back in `out`
+hipError_t launch_to_bf16(const void *x0, const void *x1, const void *x2, void *out, size_t n, hipStream_t st);
 
 // (both read the lists and the slot masks launch_build_lists left in the workspace)
 hipError_t launch_attn_fwd(const moc_meta *m, int BH, int d, int dtype, const void *q, const void *k,

@@ -62,6 +62,12 @@ def test_fp32_storage(d, chunk, topk):
     run_case(mi.stream_layout(2, 37, 4 * chunk + 5, chunk, "chunk"), 1, 3, d, topk, torch.float32, seed=51 + chunk)
 
 
+# fp32 storage without routed links: the forced-link items read the queries as they are stored
+@pytest.mark.parametrize("d,chunk,captions", [(64, 33, 37), (64, 129, 0), (128, 257, 0), (128, 31, 140)])
+def test_fp32_forced_links_alone(d, chunk, captions):
+    run_case(mi.stream_layout(2, captions, 3 * chunk + 5, chunk, "chunk"), 1, 3, d, 0, torch.float32, seed=101 + chunk)
+
+
 # epilogue of the forced-link items: rows of slots on both sides of the eight that are loaded together, in
 # windows of a few queries, with rows of fewer candidates than slots
 @pytest.mark.parametrize("topk", [7, 8, 9, 17, 32])
