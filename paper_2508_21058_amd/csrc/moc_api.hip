@@ -336,6 +336,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     m->n_ranges = int32_t(aranges.size());
     m->n_kvitems = int32_t(kvitems.size());
     m->n_kvtext = n_kvtext;
+    m->text_seg = seg;
     m->n_text_tiles = int32_t(ttiles.size());
     m->n_partials = n_partials;
     m->h_off.assign(off, off + C + 1);

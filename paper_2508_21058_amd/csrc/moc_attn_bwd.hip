@@ -414,7 +414,9 @@ struct KvArgs {
     float *tpart_k, *tpart_v;
     const KvItem *items;
     const int32_t *list_off, *qlist;
-    int N, C, topk, n_partials, n_items, n_text, BH;
+    int N, C, topk, n_partials, BH;
+    int n_items, n_text;               // work list of a head: items, caption items among them (of `join` segments each)
+    int text_tiles, join, text_seg, video_at;    // caption tiles; queries of `join` segments; first video item of `items`
     float scale, scale_log2;
 };
 
@@ -629,7 +631,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     const int N = a.N;
     int bh, item_no;
     if (!kv_item(a.n_items, a.n_text, a.BH, bh, item_no)) return;
-    const KvItem item = a.items[item_no];
+    const bool caption = item_no < a.n_text;
+    KvItem item = a.items[caption ? item_no + item_no / a.text_tiles * (a.join - 1) * a.text_tiles : item_no - a.n_text + a.video_at];
+    if (caption) item.q_len = min(a.text_seg, a.N - item.q_start);
 
     // A tile of <= 32 keys (the ragged tail of a chunk) would leave three score waves
     // idle: instead the four take the same keys and the query tiles round-robin, each
@@ -1069,7 +1073,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
 template <int D, typename T>
 __global__ __launch_bounds__(256) void text_reduce_kernel(const float *__restrict__ tpart_k,
                                                           const float *__restrict__ tpart_v,
-                                                          const TextTile *__restrict__ tiles, int n_partials, int N,
+                                                          const TextTile *__restrict__ tiles, int n_partials, int join, int N,
                                                           T *__restrict__ dk, T *__restrict__ dv) {
     const TextTile tt = tiles[blockIdx.x];
     const int bh = blockIdx.y;
@@ -1078,7 +1082,7 @@ __global__ __launch_bounds__(256) void text_reduce_kernel(const float *__restric
     if (u < tt.key_len * V4) {
         const int kr = u / V4, x = (u % V4) * 4;
         f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < tt.n_partials; ++p) {
+        for (int p = 0; p < tt.n_partials; p += join) {
             const size_t prow = ((size_t)bh * n_partials + tt.first_partial + p) * kKeyTile + kr;
             sk += *reinterpret_cast<const f32x4 *>(tpart_k + prow * D + x);
             sv += *reinterpret_cast<const f32x4 *>(tpart_v + prow * D + x);
@@ -1106,10 +1110,10 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
             kv.qlist, kv.list_off, m->N, NK, m->C, reinterpret_cast<const float2 *>(kv.stats2),
             reinterpret_cast<float2 *>(const_cast<float *>(kv.gstats2)));
     }
-    attn_bwd_dkdv_pipe_kernel<D, T><<<dim3(kv_grid(m->n_kvitems, m->n_kvtext, BH)), dim3(512), 0, st>>>(kv); }
+    attn_bwd_dkdv_pipe_kernel<D, T><<<dim3(kv_grid(kv.n_items, kv.n_text, BH)), dim3(512), 0, st>>>(kv); }
     if (m->n_text_tiles > 0) { MOC_PROF("text_reduce", st);
         text_reduce_kernel<D, T><<<dim3(m->n_text_tiles, BH, kKeyTile * (D / 4) / 256), dim3(256), 0, st>>>(
-            kv.tpart_k, kv.tpart_v, m->d_text_tiles, m->n_partials, m->N, static_cast<T *>(kv.dk),
+            kv.tpart_k, kv.tpart_v, m->d_text_tiles, m->n_partials, kv.join, m->N, static_cast<T *>(kv.dk),
             static_cast<T *>(kv.dv)); }
     a.BH = BH;
     if (a.topk > 0) {
@@ -1164,8 +1168,12 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     kv.tpart_v = reinterpret_cast<float *>(ws + L.tpart_v);
     kv.items = m->d_kvitems;
     kv.list_off = a.list_off; kv.qlist = a.qlist;
-    kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = m->n_partials; kv.n_items = m->n_kvitems; kv.n_text = m->n_kvtext;
-    kv.BH = BH;
+    kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = m->n_partials; kv.BH = BH;
+    const int nseg = m->n_text_tiles > 0 ? m->n_kvtext / m->n_text_tiles : 0;
+    kv.text_tiles = m->n_text_tiles; kv.join = text_join(m->N, m->n_text_tiles, BH, nseg);
+    kv.text_seg = kv.join * m->text_seg; kv.video_at = m->n_kvtext;
+    kv.n_text = (nseg + kv.join - 1) / kv.join * m->n_text_tiles;
+    kv.n_items = m->n_kvitems - m->n_kvtext + kv.n_text;
     kv.scale = scale; kv.scale_log2 = a.scale_log2;
     if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, d_o, dq, st)
                                            : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, d_o, dq, st);

@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "../../include/moc.h"
@@ -17,10 +18,23 @@ constexpr int kKeyTile = 128;    // keys per workgroup in the key-stationary pas
 // well under a compute unit's share of short streams (6,256 tokens: a whole-stream item is 196 steps
 // where a video item is 33 and a unit's share 182), 16384 bounds the partials of long ones (4096, 8192
 // and 16384 take the same time there), 256 keeps a segment's partial cheaper than its products.
-constexpr int kTextSegMin = 256, kTextSegMax = 16384;
+constexpr int kTextSegMin = 256, kTextSegMax = 16384, kTextItems = 512;
 inline int text_segments(int N) {
     const int target = N / 4 < kTextSegMin ? kTextSegMin : (N / 4 > kTextSegMax ? kTextSegMax : (N + 3) / 4);
     return (N + target - 1) / target;
+}
+// Neighbouring segments of a caption tile that one workgroup walks, leaving one partial for all of them. Segments
+// balance calls of few caption items; where a call has an item per compute unit anyway, more partials (a tile in
+// fp32 each, written and summed) only cost. So a tile keeps as many as leave fewer than two items per unit (but
+// no more than kTextSegMax queries in one). dK/dV and text_reduce with four partials a tile / with this rule (one
+// where not given): 16 heads of 10k tokens with a 2,000-token caption (256 whole-stream items) 576 / 533 us, 32 heads
+// 1,156 / 1,068, eight 300-token captions of 24 heads (576) 1,568 / 1,507; six heads of them (144, four partials)
+// 294, with two 323.
+inline int text_join(int N, int n_tiles, int BH, int nseg) {
+    const long long items = (long long)n_tiles * BH;
+    int want = items > 0 ? (int)std::min<long long>((kTextItems - 1) / items, nseg) : 1;
+    want = std::max(std::max(want, 1), (N + kTextSegMax - 1) / kTextSegMax);
+    return std::max(1, nseg / want);
 }
 constexpr int kRowsPerBlk = 256; // queries per block of the list builder (one wave and one histogram column each)
 constexpr int kMaxListChunks = 16384;   // chunks the list builder's LDS histogram holds
@@ -47,6 +61,7 @@ struct TextTile { int32_t key_start, key_len, first_partial, n_partials; };
 struct moc_meta {
     int32_t N = 0, C = 0, T = 0, W = 0;
     int32_t n_atiles = 0, n_ranges = 0, n_kvitems = 0, n_kvtext = 0, n_text_tiles = 0, n_partials = 0;
+    int32_t text_seg = 0;            // queries per caption item (the last of a tile may have fewer)
     int32_t max_routed_len = 0;      // longest chunk that is not a caption
     void *d_base = nullptr;
     size_t d_bytes = 0;

@@ -27,6 +27,14 @@ def test_key_stationary_work_split(B, H, shots, text, frames, frame):
     run_case(lay, B, H, 64, 2, torch.bfloat16, seed=31 + H)
 
 
+# caption segments of a tile taken by one workgroup: all four where the call has 256 caption items or more, two
+# of four from 171 on, each on its own below; the last segment ragged
+@pytest.mark.parametrize("H,text,shots,video", [(64, 500, 1, 600), (70, 129, 2, 1000), (43, 500, 1, 1000), (42, 500, 1, 1000),
+                                                (64, 130, 1, 301)])
+def test_joined_caption_segments(H, text, shots, video):
+    run_case(mi.stream_layout(shots, text, video, 50, "chunk"), 1, H, 64, 1, torch.bfloat16, seed=111 + H)
+
+
 # video items: heads that every XCD takes whole, heads left over and dealt out two items at a time, with none,
 # some and only incomplete turns (16 items) among them
 @pytest.mark.parametrize("H,chunks", [(1, 7), (1, 17), (2, 16), (7, 5), (8, 3), (11, 11), (16, 2)])
