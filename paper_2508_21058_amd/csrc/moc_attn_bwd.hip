@@ -276,8 +276,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
     typedef bf16_t T;
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int RB = D * 2;                     // bytes per row
-    constexpr int KBYTES = kChunkRows * RB;
-    constexpr int VBYTES = (kChunkRows + 32) * RB;
+    constexpr int KBYTES = kChunkRows * RB, VBYTES = KBYTES;
     constexpr int RPI = 1024 / RB;                // rows per copy instruction
     __shared__ __attribute__((aligned(1024))) char smem[KBYTES + VBYTES];
 
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
         const int nhalf = (len + 31) >> 5;        // 32-key half tiles
         // ---- K / V of the chunk -> LDS (rows past the end repeat the last row: finite, masked as keys)
         {
-            const int nk = (min(nhalf * 32, kChunkRows) + RPI - 1) / RPI;
+            const int nk = nhalf * 32 / RPI;
             for (int i = wave; i < 2 * nk; i += 8) {
                 const bool isk = i < nk;
                 const int ii = isk ? i : i - nk;

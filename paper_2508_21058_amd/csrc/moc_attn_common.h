@@ -35,11 +35,11 @@ struct FwdArgs {
 
 // Chunk-stationary routed items (forward and dQ pass): a workgroup keeps the keys and values of one
 // chunk in LDS and serves a group of that chunk's query tiles from them.
-// Resident keys (K region; the V region holds 32 rows more). Only chunks that can be routed to count:
-// captions are forced links and may be longer (512-token captions kept a 33k-token layer of 260-key
-// chunks off this path: 7.51 -> 7.32 ms a training step with it). With d = 64 the rows take half the
-// LDS, but 576 of them leave one workgroup per compute unit: 1,165 us a step of ragged chunks up to 340
-// keys against 1,058 in the tiled kernels, so the bound is the same.
+// Resident keys, of K and of V: 144 KB of LDS at d = 128. Only chunks that can be routed to count: captions are
+// forced links and may be longer (512-token captions kept a 33k-token layer of 260-key chunks off this path: 7.51 ->
+// 7.32 ms a training step with it). At d = 64 twice the rows would fit, but longer chunks gain nothing over the tiled
+// kernels there: forward / dQ of 340-key chunks, 24 heads of 114k tokens, k = 8, 3,181 / 3,764 us in 576 resident rows,
+// 3,046 / 4,115 tiled; 512-key chunks, 24 heads of 33k, k = 5, 729 / 899 against 593 / 916.
 constexpr int kChunkRows = 288;
 constexpr int kGroupTiles = 16;       // query tiles (of kBM list entries) per workgroup: they amortise the copy
 constexpr int kComputeUnits = 256;
@@ -86,8 +86,9 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
 // out eight items at a time 408), so XCDs take equal numbers of heads; the BH % 8 heads left are dealt
 // out two neighbours at a time. Slices of those left some XCDs the long lists of a head: dK/dV of one head of
 // 80k tokens in 5,244-key chunks 2,225 us in slices, 976 dealt out; two heads of 311k tokens 41.3 -> 26.7 ms;
-// six heads of 457k tokens 39.4 -> 37.2 ms; six fp32 heads of 13k ragged tokens 247 -> 257 us. (One at a
-// time loses 2.5 ms of the 457k tokens, eight 12 us of the 13k.) Launch kv_grid() workgroups; returns false
+// six heads of 457k tokens 39.4 -> 37.2 ms; six fp32 heads of 13k ragged tokens 247 -> 257 us; 226 layers of
+// random layouts and heads that do not divide by eight 0.44 to 1.15 times their time, 0.92 in the mean (three to
+// eight at a time 0.92, twenty-four 0.94; one loses 2.5 ms of the 457k tokens). Launch kv_grid() workgroups; returns false
 // for padding.
 constexpr int kVideoTurn = 2;
 __host__ __device__ inline int kv_grid(int n_items, int n_text, int BH) {

@@ -382,8 +382,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
     typedef bf16_t T;
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int RB = D * 2;                     // bytes per row
-    constexpr int KBYTES = kChunkRows * RB;       // K region; the last 64-key tile may run 32 rows into the V region
-    constexpr int VBYTES = (kChunkRows + 32) * RB;   // (those keys are masked), so the V region is a full tile longer
+    constexpr int KBYTES = kChunkRows * RB, VBYTES = KBYTES;   // K and V regions; tiles and tail end at or before row 288
+    static_assert(kChunkRows % 64 == 32, "the longest chunk is whole 64-key tiles and a 32-key tail");
     constexpr int RPI = 1024 / RB;                // rows per copy instruction
     __shared__ __attribute__((aligned(1024))) char smem[KBYTES + VBYTES];
 
@@ -424,8 +424,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
         const int rows = max(ntile * 64, (len + 31) & ~31);
         // ---- K / V of the chunk -> LDS (rows past the end repeat the last row: finite, and masked as keys)
         {
-            const int nk = (min(rows, kChunkRows) + RPI - 1) / RPI, nv = rows / RPI;
-            for (int i = wave; i < nk + nv; i += 8) {
+            const int nk = rows / RPI;                // whole: rows is a multiple of 32
+            for (int i = wave; i < 2 * nk; i += 8) {
                 const bool isk = i < nk;
                 const int ii = isk ? i : i - nk;
                 const int row = ii * RPI + rlo;
