@@ -265,7 +265,12 @@ int moc_gather_rows(int32_t outer, int32_t n_src_rows, int32_t row_bytes, const 
  *   softmax_scale  finite and > 0 (1/sqrt(d) in Eq. 1 and 2), else MOC_ERR_SHAPE.
  *   topk > 0 needs C <= 16384 (MOC_ERR_SHAPE otherwise).
  *   o         DEVICE out [B,H,N,d] dtype;  lse DEVICE out [B,H,N] fp32.
- *   workspace DEVICE scratch of moc_attn_workspace_bytes(..., with_bwd) bytes.
+ *   workspace DEVICE scratch of moc_attn_workspace_bytes(..., with_bwd) bytes. Its
+ *             size depends on dtype: MOC_F32 adds room for bf16 copies of q, k and v
+ *             (and dO with with_bwd), 6 (8) bytes per element of a [B,H,N,d] tensor.
+ *             With with_bwd a caption key tile of 128 keys holds up to four fp32
+ *             partials of dK and dV per head, in streams beyond 65,536 tokens one per
+ *             16,384 tokens.
  */
 int moc_attn_workspace_bytes(const moc_meta *meta, int32_t B, int32_t H, int32_t d,
                              int32_t topk, int dtype, int with_bwd, size_t *bytes);

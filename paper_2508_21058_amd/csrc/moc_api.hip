@@ -641,6 +641,8 @@ int moc_gather_rows(int32_t outer, int32_t n_src_rows, int32_t row_bytes, const 
     if (!workspace || workspace_bytes < (size_t)n_tab * 16) return fail(MOC_ERR_WORKSPACE, "need 16 bytes per range");
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = moc::launch_gather(outer, n_src_rows, n_dst, row_bytes, src, dst, tab.data(), n_tab, workspace, st);
+    // The call returns after the copy has finished, whatever the table's way to the device: a caller may then read
+    // dst on any stream or give src back. A table that is uploaded lives on this call's stack besides.
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     return e == hipSuccess ? MOC_OK : hip_fail(e, "moc_gather_rows");
 }

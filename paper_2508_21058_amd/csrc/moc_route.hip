@@ -93,8 +93,9 @@ template <int K, int M> __device__ __forceinline__ void merge_entries(double (&l
             if (!(i & k)) order2(list[i], list[i + k]);
 }
 
-// Four waves x 32 queries per workgroup, three workgroups per CU, two staged tiles of pooled keys (one
-// in use, one in flight). The pass is bound by the selection's vector instructions, not by the latency
+// Four waves x 32 queries per workgroup, three workgroups per CU with bf16 queries (132 to 166 registers at d = 128),
+// two with fp32 ones of 128 features (three planes of query fragments, 232 to 256 registers), two staged tiles of
+// pooled keys (one in use, one in flight). The pass is bound by the selection's vector instructions, not by the latency
 // of the tile copies.
 constexpr int kRouteThreads = 256;
 constexpr int kRouteStages = 2;
@@ -177,9 +178,9 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
     LaneOffs<D> lo;
     lo.init(lane);
 
-    // Copies of one staged tile (3 planes x 32 rows), spread over the eight waves: a wave instruction
-    // moves 1 KB (512 / D rows). Every wave issues the same number of copies per tile so that one
-    // vmcnt bound fits all (with D = 64 the last four waves repeat a copy of the first four).
+    // Copies of one staged tile (3 planes x 32 rows), spread over the four waves: a wave instruction moves
+    // 1 KB (512 / D rows). Every wave issues the same number of copies per tile, six or three, so that one
+    // vmcnt bound fits all.
     constexpr int RPI = 512 / D, NI = 32 / RPI, TOT = 3 * NI, PW = (TOT + NWV - 1) / NWV;
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
     const int rlo = lane / (D / 8), cgp = lane % (D / 8);

@@ -126,8 +126,8 @@ def test_list_builder_ranges(N, chunk, topk):
     meta.close()
 
 
-# selection at the list widths the kernel is built for (4, 8, 16, 32) and one past each, over enough
-# chunks that queues fill, drain and merge; scores of both signs, many exact ties (quarter-integer keys,
+# selection at the list widths the kernel is built for (4, 8, 16, 32) and one past each, over eleven tiles
+# of chunks, the last one ragged; scores of both signs, many exact ties (quarter-integer keys,
 # one-hot queries), zeros of both signs. Scores are exact in fp32 here, so the order is pinned: higher
 # score first, lower chunk on a tie.
 @pytest.mark.parametrize("topk", [1, 3, 4, 5, 8, 9, 16, 17, 32])
