@@ -83,14 +83,16 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
 // 1,217 us and the 1,088-token fp32 layer from 119 to 104 us. Caption items cost alike and go out as one
 // slice per XCD. Video items do not: under the causal mask early chunks are routed to by more queries. Whole
 // heads balance that and share their queries in an XCD's L2 (two samples of eight ragged heads: 367 us, dealt
-// out eight items at a time 408), so XCDs take equal numbers of heads; the BH % 8 heads left are dealt
-// out two neighbours at a time. Slices of those left some XCDs the long lists of a head: dK/dV of one head of
-// 80k tokens in 5,244-key chunks 2,225 us in slices, 976 dealt out; two heads of 311k tokens 41.3 -> 26.7 ms;
-// six heads of 457k tokens 39.4 -> 37.2 ms; six fp32 heads of 13k ragged tokens 247 -> 257 us; 226 layers of
-// random layouts and heads that do not divide by eight 0.44 to 1.15 times their time, 0.92 in the mean (three to
-// eight at a time 0.92, twenty-four 0.94; one loses 2.5 ms of the 457k tokens). Launch kv_grid() workgroups; returns false
-// for padding.
-constexpr int kVideoTurn = 2;
+// out eight items at a time 408), so XCDs take equal numbers of heads. The BH % 8 heads left are dealt out two
+// neighbours at a time: slices of those left some XCDs the long lists of a head. dK/dV of one head of 80k tokens
+// in 5,244-key chunks 2,225 us in slices, 976 dealt out; two heads of 311k tokens 41.3 -> 26.7 ms; six heads of 457k
+// tokens 39.4 -> 37.2 ms. But heads shorter than a round of the chip (an item per compute unit) go out in slices when
+// they are more than a few: dealt out, several at a time would pass through every L2 (six fp32 heads of 13k ragged
+// tokens 247 us in slices, 257 dealt out; six heads of 14k 353 / 405; three heads of 25k 1,471 / 1,134). 499 layers of
+// random layouts, all dealt out: 0.84 times their time in slices with one head, 0.88 two, 0.91 three, 0.96 four,
+// 0.99 six and twelve, 0.44 to 1.17 one by one; 363 by this rule 0.91, 0.44 to 1.09. Three to eight items at a time do as well as two, twenty-four 2 %
+// worse, one loses 2.5 ms of the 457k tokens. Launch kv_grid() workgroups; returns false for padding.
+constexpr int kVideoTurn = 2, kFewHeads = 3;
 __host__ __device__ inline int kv_grid(int n_items, int n_text, int BH) {
     return xcd_grid((long long)n_text * BH) + xcd_grid((long long)(n_items - n_text) * BH);
 }
@@ -103,8 +105,9 @@ __device__ __forceinline__ bool kv_item(int n_items, int n_text, int BH, int &bh
     if (!text) {
         const int whole = BH / kXcds * (n_items - n_text);                                        // an XCD's items of whole heads
         const int left = (BH % kXcds) * (n_items - n_text);                                       // items of the other heads
-        const int turns = left / (kXcds * kVideoTurn) * kVideoTurn;                               // an XCD's of them in whole turns
-        const int rest = (left - turns * kXcds + kXcds - 1) / kXcds;                              // and behind them
+        const bool deal = BH % kXcds <= kFewHeads || n_items - n_text >= kComputeUnits;
+        const int turns = deal ? left / (kXcds * kVideoTurn) * kVideoTurn : 0;                    // an XCD's of them in whole turns
+        const int rest = (left - turns * kXcds + kXcds - 1) / kXcds;                              // and in a slice
         const int v = p - per_t, u = v - whole;
         l = u < 0 ? x * whole + v
                   : whole * kXcds + (u < turns ? (u / kVideoTurn * kXcds + x) * kVideoTurn + u % kVideoTurn

@@ -35,9 +35,10 @@ def test_joined_caption_segments(H, text, shots, video):
     run_case(mi.stream_layout(shots, text, video, 50, "chunk"), 1, H, 64, 1, torch.bfloat16, seed=111 + H)
 
 
-# video items: heads that every XCD takes whole, heads left over and dealt out two items at a time, with none,
-# some and only incomplete turns (16 items) among them
-@pytest.mark.parametrize("H,chunks", [(1, 7), (1, 17), (2, 16), (7, 5), (8, 3), (11, 11), (16, 2)])
+# video items: heads that every XCD takes whole, heads left over and dealt out two items at a time (up to three of
+# them, or 256 items a head), with none, some and only incomplete turns (16 items) among them, heads left in slices
+@pytest.mark.parametrize("H,chunks", [(1, 7), (1, 17), (2, 16), (3, 33), (4, 33), (7, 5), (8, 3), (11, 11), (13, 7), (16, 2),
+                                      (5, 255), (5, 256)])
 def test_video_items_over_the_xcds(H, chunks):
     run_case(mi.stream_layout(1, 9, 21 * chunks, 21, "chunk"), 1, H, 64, 2, torch.bfloat16, seed=81 + H)
 
