@@ -127,6 +127,7 @@ template <int D, typename OT>
 __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, const f32x16 *acc, float scale,
                                                bool row_valid, int qi, size_t bhN, const FwdArgs &a) {
     constexpr int DB = D / 32, RS = D + 4;
+    constexpr bool kLast = forced_last<D, OT>();
     const int half = lane >> 5, l32 = lane & 31;
     const int topk = a.topk, slots = topk + 1;
     bf16_t *patch = reinterpret_cast<bf16_t *>(smem) + wave * (32 * RS + 128);
@@ -153,13 +154,15 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
         if (dr < 0) continue;
         const size_t row = bhN + dr;
         const uint32_t mask = used[r];
-        float o8[8];
+        float forced[8], o8[8];
         {
             const u32x2 lo2 = *reinterpret_cast<const u32x2 *>(patch + r * RS + cg * 8);
             const u32x2 hi2 = *reinterpret_cast<const u32x2 *>(patch + r * RS + cg * 8 + 4);
-            o8[0] = bf16_lo(lo2[0]); o8[1] = bf16_hi(lo2[0]); o8[2] = bf16_lo(lo2[1]); o8[3] = bf16_hi(lo2[1]);
-            o8[4] = bf16_lo(hi2[0]); o8[5] = bf16_hi(hi2[0]); o8[6] = bf16_lo(hi2[1]); o8[7] = bf16_hi(hi2[1]);
+            forced[0] = bf16_lo(lo2[0]); forced[1] = bf16_hi(lo2[0]); forced[2] = bf16_lo(lo2[1]); forced[3] = bf16_hi(lo2[1]);
+            forced[4] = bf16_lo(hi2[0]); forced[5] = bf16_hi(hi2[0]); forced[6] = bf16_lo(hi2[1]); forced[7] = bf16_hi(hi2[1]);
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o8[e] = kLast ? 0.f : forced[e];
         const bf16_t *pbase = a.po + row * slots * D + cg * 8;
         for (int s0 = 0; s0 < topk; s0 += 8) {
             float w[8], f[8][8];
@@ -175,6 +178,9 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o8[e] = fmaf(w[u], f[u][e], o8[e]);
         }
+        if (kLast)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o8[e] += forced[e];
         Io<OT>::store8(static_cast<OT *>(a.o_out) + row * D + cg * 8, o8);
     }
 }

@@ -188,6 +188,12 @@ template <int BN> struct TileIter {
     }
 };
 
+// Where the epilogues of the forced-link items put the forced-link part among the routed partials of a query. At
+// d = 128 with bf16 storage it comes first and, in the forward, is weighted before it is rounded to bf16; for d = 64
+// and fp32 storage it comes last and is rounded before it is weighted, as if it had gone through a slot of its own.
+// Both are as exact; either order is kept where it has always been, so that results stay the same.
+template <int D, typename OT> __device__ constexpr bool forced_last() { return D == 64 || sizeof(OT) == 4; }
+
 // Epilogue of the query-stationary passes. A transposed accumulator holds, per
 // lane, 4-feature pieces of ONE row; storing those directly scatters 8-byte
 // writes over 32 rows per instruction and the L2 writes partial lines back

@@ -188,10 +188,11 @@ __device__ __forceinline__ void fwd_tile(const char *smem, LaneOffs<D> &lo, cons
 // merge kernel, the wave combines right here (the split-softmax identity
 // o = sum_s exp(lse_s - lse) o_s over the forced-link slot and the used routed
 // slots). One lane per query turns the <= topk+1 partial log-sum-exps into
-// weights; the forced-link part, already weighted, is transposed through the
-// wave's LDS patch as in store_rows_bf16; then every lane owns 8 features of a
-// row, adds the weighted routed partials (16-byte loads, a batch in flight) and
-// stores the final row. The forced-link partial never goes to memory.
+// weights; the forced-link part is transposed through the wave's LDS patch as in
+// store_rows_bf16; then every lane owns 8 features of a row, adds the weighted
+// routed partials (16-byte loads, a batch in flight) and stores the final row.
+// The forced-link partial never goes to memory. It is rounded to bf16 in the patch:
+// after its weight, or, where forced_last() says so, before it.
 // The partial log-sum-exps are loaded eight at a time and kept in the weight table: fetched one by one,
 // and again for each of the three passes over them, they were most of a workgroup's time where windows
 // are short (sixteen heads of 7,657 tokens in windows of 8 tokens, d = 64: the kernel 168 -> 134 us with
@@ -201,12 +202,13 @@ constexpr int merge_lds(int D) { return 4 * (32 * (D + 4) + 64) * 2 + 4 * 32 * 3
 template <int D, typename OT>
 __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane, const f32x16 *acc, float m_run,
                                                  float l_tot, bool row_valid, int qi, size_t bhN, const FwdArgs &a) {
-    constexpr int DB = D / 32, RS = D + 4, WS = 34;    // WS: floats per row of the weight table (32 weights, lse)
+    constexpr int DB = D / 32, RS = D + 4, WS = 34;    // WS: floats per row of the weight table (32 weights, lse, forced part's weight)
     const int half = lane >> 5, l32 = lane & 31;
     const int topk = a.topk, slots = topk + 1;
     bf16_t *patch = reinterpret_cast<bf16_t *>(smem) + wave * (32 * RS + 64);
     int32_t *rowidx = reinterpret_cast<int32_t *>(patch + 32 * RS);
     float *wts = reinterpret_cast<float *>(smem + 4 * (32 * RS + 64) * 2) + wave * 32 * WS;
+    constexpr bool kLast = forced_last<D, OT>();
     float wf = 0.f;
     if (half == 0) {
         const size_t row = bhN + qi;
@@ -233,10 +235,11 @@ __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane,
         for (int s = 0; s < topk; ++s) wl[s] = __expf(wl[s] - tot);
         wts[l32 * WS + 32] = tot;
         wf = __expf(lf - tot);
+        if (kLast) wts[l32 * WS + 33] = wf;
         rowidx[l32] = row_valid ? qi : -1;
     }
-    wf = xhalf_sum(wf);                                // the other half-wave holds the same query
-    const float scale = wf / l_tot;
+    if (!kLast) wf = xhalf_sum(wf);                    // the other half-wave holds the same query
+    const float scale = (kLast ? 1.f : wf) / l_tot;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
@@ -253,13 +256,15 @@ __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane,
         const int dr = rowidx[r];
         if (dr < 0) continue;
         const size_t row = bhN + dr;
-        float o8[8];
+        float forced[8], o8[8];
         {
             const u32x2 lo2 = *reinterpret_cast<const u32x2 *>(patch + r * RS + cg * 8);
             const u32x2 hi2 = *reinterpret_cast<const u32x2 *>(patch + r * RS + cg * 8 + 4);
-            o8[0] = bf16_lo(lo2[0]); o8[1] = bf16_hi(lo2[0]); o8[2] = bf16_lo(lo2[1]); o8[3] = bf16_hi(lo2[1]);
-            o8[4] = bf16_lo(hi2[0]); o8[5] = bf16_hi(hi2[0]); o8[6] = bf16_lo(hi2[1]); o8[7] = bf16_hi(hi2[1]);
+            forced[0] = bf16_lo(lo2[0]); forced[1] = bf16_hi(lo2[0]); forced[2] = bf16_lo(lo2[1]); forced[3] = bf16_hi(lo2[1]);
+            forced[4] = bf16_lo(hi2[0]); forced[5] = bf16_hi(hi2[0]); forced[6] = bf16_lo(hi2[1]); forced[7] = bf16_hi(hi2[1]);
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o8[e] = kLast ? 0.f : forced[e];
         const bf16_t *pbase = a.po + row * slots * D + cg * 8;
         for (int s0 = 0; s0 < topk; s0 += 8) {
             float w[8], f[8][8];
@@ -274,6 +279,11 @@ __device__ __forceinline__ void merge_store_rows(char *smem, int wave, int lane,
             for (int u = 0; u < 8; ++u)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o8[e] = fmaf(w[u], f[u][e], o8[e]);
+        }
+        if (kLast) {
+            const float w = wts[r * WS + 33];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o8[e] = fmaf(w, forced[e], o8[e]);
         }
         Io<OT>::store8(static_cast<OT *>(a.o_out) + row * D + cg * 8, o8);
         if (cg == 0) a.lse_out[row] = wts[r * WS + 32];

@@ -287,3 +287,36 @@ def test_gather_of_short_ranges(n_ranges, words, outer):
     rows = np.concatenate([np.arange(a, a + n) for a, n in ranges])
     got = mb.gather_rows(src, ranges)
     assert torch.equal(got.view(torch.int16), src.view(torch.int16)[:, torch.from_numpy(rows).cuda()])
+
+
+# The forced-link part of a query among its routed partials, for d = 64 and fp32 storage: rounded to bf16 first, then
+# weighted and added last, like the partials in the workspace. These and the log-sum-exps give o back. The log-sum-exps
+# are fp32 numbers below 16 (half an ulp 5e-7), so weights and o are good to about 1e-6; a part rounded after its weight
+# is 1e-3 off. In bf16 storage an error of 1e-6 crosses a rounding boundary (3e-3 apart) in one value of a thousand.
+@pytest.mark.parametrize("d,dtype", [(64, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
+@pytest.mark.parametrize("topk", [1, 8, 18])
+def test_forced_part_is_rounded_before_its_weight(d, dtype, topk):
+    lay, H = mi.stream_layout(2, 37, 900, 33, "chunk"), 3
+    N, C = lay.N, lay.C
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    g = torch.Generator(device="cuda").manual_seed(topk)
+    q, k, v = (torch.randn(1, H, N, d, generator=g, device="cuda").to(dtype) for _ in range(3))
+    _, sel = mb.route(meta, q, k, topk, True)
+    ws = mb.attn_workspace(meta, 1, H, d, topk, dtype, False)
+    o, lse = mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
+    forced, flse = mb.attn_fwd(meta, q, k, v, sel[..., :0].contiguous())
+    at, slots = 0, topk + 1
+    for n in (H * C, H * (C + 1), H * (C + 1), H * N, H * 32 * C, H * -(-N // 256) * C, H * N * topk):
+        at += -(-4 * n // 256) * 256
+    plse = ws[at:at + 4 * H * N * slots].view(torch.float32).view(H, N, slots)[..., :topk].double()
+    at += -(-4 * H * N * slots // 256) * 256
+    po = ws[at:at + 2 * H * N * slots * d].view(torch.bfloat16).view(H, N, slots, d)[..., :topk, :].double()
+    used = (sel[0] >= 0)[..., None]
+    parts = torch.where(used, po * torch.exp(plse - lse[0].double()[..., None])[..., None], 0.0).sum(2)
+    want = parts + forced[0].double().bfloat16().double() * torch.exp(flse[0].double() - lse[0].double())[..., None]
+    got = o[0].double()
+    if dtype == torch.float32:
+        assert float((got - want).norm() / want.norm()) < 1e-5
+    else:
+        assert float((got != want.bfloat16().double()).double().mean()) < 5e-3
+    meta.close()
