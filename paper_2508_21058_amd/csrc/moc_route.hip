@@ -21,7 +21,9 @@
 // its 24 matrix instructions. Against queues of the scores above the k-th best so far,
 // inserted entry by entry (divergent, two LDS rows per entry, two waves per SIMD): 1,313
 // -> 684 us at 114k tokens, 24 heads, 440 chunks, k = 8; 7,074 -> 4,552 us at 457k tokens,
-// six heads, 3,488 chunks, k = 16; 26 -> 15 us at 6,256 tokens, k = 3.
+// six heads, 3,488 chunks, k = 16; 26 -> 15 us at 6,256 tokens, k = 3. The queues cost less per tile the
+// longer the scan, as ever fewer scores beat the k-th best; without a causal mask they meet the networks near
+// 9,000 chunks (fp32, d = 64, k = 16: 1,260 -> 1,183 us at 5,210 chunks, 3,561 -> 3,720 at 9,418).
 #include "moc_attn_common.h"
 #include "moc_pool_unit.h"
 
@@ -316,6 +318,9 @@ __global__ __launch_bounds__(kRouteThreads, kRouteThreads == 256 ? 2 : 1) void r
 // flag is raised, the workgroup scores whatever the planes hold, and every wave still exits.
 // The words live in a static device array (zero when the module loads); the last workgroup of a
 // launch clears them again, so launches must not overlap on one GPU.
+// Only the pooling workgroups release and only the end of a wait acquires, since both write back or drop whole
+// caches: with an acquire at every look at the count and a release at the end of every workgroup 114k tokens, 24
+// heads and k = 8 took 2,697 us, 14k tokens 357, now 1,557 and 169 (as two launches 778 and 46).
 constexpr int kFusePoolWgs = 256;
 constexpr long long kFuseSpinLimit = 20000000;
 static __device__ unsigned int g_fuse_sync[4];       // [0] chunks pooled, [1] workgroups finished, [2] a wait ran out
@@ -348,19 +353,21 @@ __global__ __launch_bounds__(kRouteThreads, 2) void route_fused_kernel(RouteArgs
     }
     if (threadIdx.x == 0) {
         long long spins = 0;
-        while (__hip_atomic_load(&g_fuse_sync[0], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < f.units) {
+        while (__hip_atomic_load(&g_fuse_sync[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < f.units) {
             if (++spins > kFuseSpinLimit) { g_fuse_sync[2] = 1u; break; }
             __builtin_amdgcn_s_sleep(8);
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // once, not per look: each would drop the L1 of the pooling waves
     }
     __syncthreads();
     route_body<D, T, KMAX>(a, smem);
     __syncthreads();
     if (threadIdx.x == 0) {
-        const unsigned int fin = __hip_atomic_fetch_add(&g_fuse_sync[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        // (no data passes here: the end of the launch publishes the selections)
+        const unsigned int fin = __hip_atomic_fetch_add(&g_fuse_sync[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (fin == nwg - 1) {                                  // the last one out: every workgroup is past its wait
             __hip_atomic_store(&g_fuse_sync[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&g_fuse_sync[1], 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&g_fuse_sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

@@ -320,3 +320,22 @@ def test_forced_part_is_rounded_before_its_weight(d, dtype, topk):
     else:
         assert float((got != want.bfloat16().double()).double().mean()) < 5e-3
     meta.close()
+
+
+# routing in one launch right after another on other keys, with nothing between the launches: the workspace, which the
+# allocator hands back each time, still holds the planes of the keys before when the pooling workgroups rewrite it. More
+# workgroups than are resident, a list width each.
+@pytest.mark.parametrize("d,topk", [(128, 3), (64, 8), (128, 16), (64, 32)])
+def test_fused_routing_of_other_keys_back_to_back(d, topk):
+    lay, H = mi.stream_layout(2, 40, 3000, 21, "chunk"), 24
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    g = torch.Generator(device="cuda").manual_seed(d + topk)
+    q, *keys = (torch.randn(1, H, lay.N, d, generator=g, device="cuda").bfloat16() for _ in range(4))
+    want = [mb.route(meta, q, k, topk) for k in keys]
+    order = [0, 1, 2, 1, 0, 2, 0]
+    torch.cuda.synchronize()
+    got = [mb.route_fused(meta, q, keys[i], topk) for i in order]
+    for i, (pooled, sel) in zip(order, got):
+        assert torch.equal(pooled, want[i][0]) and torch.equal(sel, want[i][1])
+    assert not mb.route_fused_timed_out()
+    meta.close()
