@@ -373,6 +373,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     for (int j = 0; j < C; ++j) ntb[j + 1] = ntb[j] + (kind[j] ? 0 : 1);
     put(o_ntb, ntb.data(), (size_t)(C + 1) * 4);
     std::vector<int32_t> video;
+    video.reserve(C);
     for (int j = 0; j < C; ++j)
         if (!kind[j]) video.push_back(j);
     put(o_vid, video.data(), video.size() * 4);

@@ -90,8 +90,9 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
 // they are more than a few: dealt out, several at a time would pass through every L2 (six fp32 heads of 13k ragged
 // tokens 247 us in slices, 257 dealt out; six heads of 14k 353 / 405; three heads of 25k 1,471 / 1,134). 499 layers of
 // random layouts, all dealt out: 0.84 times their time in slices with one head, 0.88 two, 0.91 three, 0.96 four,
-// 0.99 six and twelve, 0.44 to 1.17 one by one; 363 by this rule 0.91, 0.44 to 1.09. Three to eight items at a time do as well as two, twenty-four 2 %
-// worse, one loses 2.5 ms of the 457k tokens. Launch kv_grid() workgroups; returns false for padding.
+// 0.99 six and twelve, 0.44 to 1.17 one by one; 363 by this rule 0.91, 0.44 to 1.09. Three to eight items at a time
+// do as well as two, twenty-four 2 % worse, one loses 2.5 ms of the 457k tokens. Launch kv_grid() workgroups;
+// returns false for padding.
 constexpr int kVideoTurn = 2, kFewHeads = 3;
 __host__ __device__ inline int kv_grid(int n_items, int n_text, int BH) {
     return xcd_grid((long long)n_text * BH) + xcd_grid((long long)(n_items - n_text) * BH);
