@@ -383,27 +383,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
             if (more) load_qdo(e_next, qf, dof);
             e = e_next;
             st2 = st_next;
-            // 16-byte stores: the two half-waves hold adjacent 4-feature pieces of the same query and
-            // exchange them (lower half: features [16 u, 16 u + 8), upper half: [16 u + 8, 16 u + 16))
-            if (blk * 32 + l32 < nq) {
-                const size_t prow = ((size_t)bh * N + (e_cur >> 5)) * a.slots + (e_cur & 31);
-                T *dst = a.po + prow * D + half * 8;
-                const float sc = a.scale;
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int g = 2 * u;
-                        const uint32_t x0 = pack_bf16(dqacc[b][4 * g] * sc, dqacc[b][4 * g + 1] * sc);
-                        const uint32_t x1 = pack_bf16(dqacc[b][4 * g + 2] * sc, dqacc[b][4 * g + 3] * sc);
-                        const uint32_t y0 = pack_bf16(dqacc[b][4 * g + 4] * sc, dqacc[b][4 * g + 5] * sc);
-                        const uint32_t y1 = pack_bf16(dqacc[b][4 * g + 6] * sc, dqacc[b][4 * g + 7] * sc);
-                        const auto r0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
-                        const auto r1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
-                        const u32x4 w = {r0[0], r1[0], r0[1], r1[1]};
-                        *reinterpret_cast<u32x4 *>(dst + b * 32 + u * 16) = w;
-                    }
-            }
+            const size_t prow = ((size_t)bh * N + (e_cur >> 5)) * a.slots + (e_cur & 31);
+            scatter_rows_bf16<D>(dqacc, a.scale, (int)prow, nq - blk * 32, lane, a.po);
         }
         t0 = te;
         if (t0 < t1) __syncthreads();             // every wave is done with this chunk's K / V

@@ -234,6 +234,45 @@ __device__ __forceinline__ void store_rows_bf16(char *smem, int wave, int lane, 
     }
 }
 
+// A wave's 32 x D transposed accumulator, scaled, to 32 scattered rows of bf16 without a way through LDS. A lane holds
+// 4-feature pieces of one row, its counterpart in the other half-wave the pieces between them: exchanged across the
+// halves they make 16-byte words, and exchanged with the row 16 lanes on, four lanes hold 64 contiguous bytes of a row.
+// Stored after the first exchange already, in 32-byte pieces of 32 rows at a time, the address unit and the L2 saw twice
+// the requests: routed forward / dQ of 457k tokens, six heads, 130-key chunks, k = 16, 7,457 / 9,116 us against 7,229 /
+// 8,648 now; 114k tokens, 24 heads, 260-key chunks, k = 8, 4,300 / 5,636 against 4,247 / 5,584. (Non-temporal stores
+// lose: 4,410 / 5,762.) prow: the lane's row (in rows of D); rows >= valid are not written.
+template <int D>
+__device__ __forceinline__ void scatter_rows_bf16(const f32x16 *acc, float scale, int prow, int valid, int lane, bf16_t *out) {
+    const int l16 = lane & 15, quad = ((lane >> 4) & 1) * 2 + (lane >> 5);       // 16-byte word of the lane within a 64-byte piece
+    const auto rows = __builtin_amdgcn_permlane16_swap((uint32_t)prow, (uint32_t)prow, false, false);
+    bf16_t *d0 = out + (size_t)rows[0] * D + quad * 8, *d1 = out + (size_t)rows[1] * D + quad * 8;
+    const bool ok0 = l16 < valid, ok1 = l16 + 16 < valid;
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b) {
+        u32x4 w[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = 8 * u;
+            const uint32_t x0 = pack_bf16(acc[b][i] * scale, acc[b][i + 1] * scale);
+            const uint32_t x1 = pack_bf16(acc[b][i + 2] * scale, acc[b][i + 3] * scale);
+            const uint32_t y0 = pack_bf16(acc[b][i + 4] * scale, acc[b][i + 5] * scale);
+            const uint32_t y1 = pack_bf16(acc[b][i + 6] * scale, acc[b][i + 7] * scale);
+            const auto r0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+            const auto r1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+            w[u] = u32x4{r0[0], r1[0], r0[1], r1[1]};
+        }
+        u32x4 p0, p1;                     // rows 0 .. 15, rows 16 .. 31
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const auto r = __builtin_amdgcn_permlane16_swap(w[0][e], w[1][e], false, false);
+            p0[e] = r[0];
+            p1[e] = r[1];
+        }
+        if (ok0) *reinterpret_cast<u32x4 *>(d0 + b * 32) = p0;
+        if (ok1) *reinterpret_cast<u32x4 *>(d1 + b * 32) = p1;
+    }
+}
+
 // Moves ROWS source rows of D features into a swizzled LDS tile (SwTile<D>).
 //   issue_rows(tile, valid, lds)  starts the transfer of a tile into `lds`
 //   commit()                      waits for this wave's copies (before the barrier that publishes `lds`)

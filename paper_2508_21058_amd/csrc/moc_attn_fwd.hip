@@ -480,27 +480,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
             const float l_tot = xhalf_sum(l_run);
             const float inv = 1.f / l_tot;
             const size_t prow = ((size_t)bh * N + (e_cur >> 5)) * a.slots + (e_cur & 31);
-            // The two half-waves hold adjacent 4-feature pieces of the same query: exchange them so
-            // that the lower half stores features [16 u, 16 u + 8) and the upper half [16 u + 8, 16 u + 16)
-            // of a 32-feature block as one 16-byte word each.
-            if (blk * 32 + l32 < nq) {
-                T *dst = a.po + prow * D + half * 8;
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int g = 2 * u;
-                        const uint32_t x0 = pack_bf16(oacc[b][4 * g] * inv, oacc[b][4 * g + 1] * inv);
-                        const uint32_t x1 = pack_bf16(oacc[b][4 * g + 2] * inv, oacc[b][4 * g + 3] * inv);
-                        const uint32_t y0 = pack_bf16(oacc[b][4 * g + 4] * inv, oacc[b][4 * g + 5] * inv);
-                        const uint32_t y1 = pack_bf16(oacc[b][4 * g + 6] * inv, oacc[b][4 * g + 7] * inv);
-                        const auto r0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
-                        const auto r1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
-                        const u32x4 w = {r0[0], r1[0], r0[1], r1[1]};
-                        *reinterpret_cast<u32x4 *>(dst + b * 32 + u * 16) = w;
-                    }
-                if (half == 0) a.plse[prow] = m_run * a.scale + __logf(l_tot);
-            }
+            scatter_rows_bf16<D>(oacc, inv, (int)prow, nq - blk * 32, lane, a.po);
+            if (blk * 32 + l32 < nq && half == 0) a.plse[prow] = m_run * a.scale + __logf(l_tot);
             blk += 8;
             e_cur = e_nxt;
 #pragma unroll
