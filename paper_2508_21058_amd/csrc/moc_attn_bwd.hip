@@ -185,6 +185,31 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
     }
 }
 
+// Sums the per-segment partials of a caption key tile in a fixed order, one float4 of dK and of dV a thread, 256 of them a
+// workgroup; bound by HBM. These workgroups are the first of the forced-link dQ launch, which needs nothing of theirs and
+// whose items are bound by other things; as a launch of their own they took 7 us of 675 at 6,256 tokens, 79 us of 41 ms at
+// 114k, 268 us of 93 ms at 457k.
+template <int D> constexpr int reduce_parts() { return kKeyTile * (D / 4) / 256; }
+template <int D, typename T>
+__device__ __forceinline__ void text_reduce(const FwdArgs &a) {
+    constexpr int PARTS = reduce_parts<D>(), V4 = D / 4;            // V4: float4 groups per row
+    const int tile = blockIdx.x / PARTS, u = blockIdx.x % PARTS * 256 + threadIdx.x;
+    const int bh = tile / a.n_text_tiles;
+    if (bh >= a.BH) return;
+    const TextTile tt = a.text_tiles[tile - bh * a.n_text_tiles];
+    if (u >= tt.key_len * V4) return;
+    const int kr = u / V4, x = (u % V4) * 4;
+    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < tt.n_partials; p += a.join) {
+        const size_t prow = ((size_t)bh * a.n_partials + tt.first_partial + p) * kKeyTile + kr;
+        sk += *reinterpret_cast<const f32x4 *>(a.tpart_k + prow * D + x);
+        sv += *reinterpret_cast<const f32x4 *>(a.tpart_v + prow * D + x);
+    }
+    const size_t row = (size_t)bh * a.N + tt.key_start + kr;
+    Io<T>::store4(static_cast<T *>(a.dk) + row * D + x, sk[0], sk[1], sk[2], sk[3]);
+    Io<T>::store4(static_cast<T *>(a.dv) + row * D + x, sv[0], sv[1], sv[2], sv[3]);
+}
+
 // OT: storage type of dQ (forced-link items only)
 template <int D, int MODE, typename OT>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
@@ -197,8 +222,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int N = a.N;
 
+    if (MODE == MODE_ANCHOR && (int)blockIdx.x < a.n_reduce) { text_reduce<D, OT>(a); return; }
     int logical;
-    if (!xcd_remap((long long)a.items_per_head * a.BH, logical)) return;
+    if (!xcd_remap((long long)a.items_per_head * a.BH, logical, MODE == MODE_ANCHOR ? a.n_reduce : 0)) return;
     const int bh = logical / a.items_per_head;
     ItemDesc it;
     if (!decode_item<MODE>(a, bh, logical - bh * a.items_per_head, it)) return;
@@ -1053,32 +1079,6 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     }
 }
 
-// Sums the per-segment partials of a text key tile in a fixed order, one float4 of dK and of dV a
-// thread; bound by HBM. A workgroup per 256 of them, not per tile: a call has few caption tiles (48 at
-// 6,256 tokens and 24 heads: 35 us in 48 workgroups, 6.5 in 768).
-template <int D, typename T>
-__global__ __launch_bounds__(256) void text_reduce_kernel(const float *__restrict__ tpart_k,
-                                                          const float *__restrict__ tpart_v,
-                                                          const TextTile *__restrict__ tiles, int n_partials, int join, int N,
-                                                          T *__restrict__ dk, T *__restrict__ dv) {
-    const TextTile tt = tiles[blockIdx.x];
-    const int bh = blockIdx.y;
-    constexpr int V4 = D / 4;                       // float4 groups per row
-    const int u = blockIdx.z * 256 + threadIdx.x;
-    if (u < tt.key_len * V4) {
-        const int kr = u / V4, x = (u % V4) * 4;
-        f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < tt.n_partials; p += join) {
-            const size_t prow = ((size_t)bh * n_partials + tt.first_partial + p) * kKeyTile + kr;
-            sk += *reinterpret_cast<const f32x4 *>(tpart_k + prow * D + x);
-            sv += *reinterpret_cast<const f32x4 *>(tpart_v + prow * D + x);
-        }
-        const size_t row = (size_t)bh * N + tt.key_start + kr;
-        Io<T>::store4(dk + row * D + x, sk[0], sk[1], sk[2], sk[3]);
-        Io<T>::store4(dv + row * D + x, sv[0], sv[1], sv[2], sv[3]);
-    }
-}
-
 // T: storage type of the caller's tensors; o_in and do_in are the caller's o and dO, a / kv hold bf16 operands
 template <int D, typename T>
 static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv, const void *o_in, const void *do_in,
@@ -1097,10 +1097,6 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
             reinterpret_cast<float2 *>(const_cast<float *>(kv.gstats2)));
     }
     attn_bwd_dkdv_pipe_kernel<D, T><<<dim3(kv_grid(kv.n_items, kv.n_text, BH)), dim3(512), 0, st>>>(kv); }
-    if (m->n_text_tiles > 0) { MOC_PROF("text_reduce", st);
-        text_reduce_kernel<D, T><<<dim3(m->n_text_tiles, BH, kKeyTile * (D / 4) / 256), dim3(256), 0, st>>>(
-            kv.tpart_k, kv.tpart_v, m->d_text_tiles, m->n_partials, kv.join, m->N, static_cast<T *>(kv.dk),
-            static_cast<T *>(kv.dv)); }
     a.BH = BH;
     if (a.topk > 0) {
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;
@@ -1115,7 +1111,8 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     MOC_PROF("attn_bwd_dq_forced", st);
     a.items_per_head = m->n_atiles;
     a.o_out = dq;        // the forced-link items run after the routed ones and add the routed partials themselves
-    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
+    a.n_reduce = xcd_grid((long long)m->n_text_tiles * BH * reduce_parts<D>());
+    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(a.n_reduce + xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1161,6 +1158,9 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     kv.n_text = (nseg + kv.join - 1) / kv.join * m->n_text_tiles;
     kv.n_items = m->n_kvitems - m->n_kvtext + kv.n_text;
     kv.scale = scale; kv.scale_log2 = a.scale_log2;
+    a.tpart_k = kv.tpart_k; a.tpart_v = kv.tpart_v; a.text_tiles = m->d_text_tiles;
+    a.n_text_tiles = m->n_text_tiles; a.n_partials = m->n_partials; a.join = kv.join;
+    a.dk = dk; a.dv = dv;
     if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, d_o, dq, st)
                                            : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, d_o, dq, st);
     return d == 128 ? bwd_dispatch<128, float>(m, BH, a, kv, o, d_o, dq, st)

@@ -27,6 +27,11 @@ struct FwdArgs {
     const void *d_o;
     const float *lse, *delta;
     const float *gstats2;   // [BH, N*topk] pairs (lse * log2 e, delta) in inverse-list order
+    // sums of the caption tiles' partials, which the first workgroups of the forced-link dQ launch make
+    const float *tpart_k, *tpart_v;
+    const TextTile *text_tiles;
+    void *dk, *dv;
+    int n_text_tiles, n_partials, join, n_reduce;
     // forced-link forward items with the merge fused into their epilogue
     const uint32_t *vmask;  // [BH, N] bit r: routed slot r of the query counts (set by the list builder)
     void *o_out;            // [BH, N, D] final output, in the caller's storage type
@@ -67,8 +72,8 @@ inline bool chunk_stationary(const moc_meta *m, int topk, int BH) {
 // Launch ceil(total/8)*8 workgroups on a 1-D grid; returns false for padding.
 constexpr int kXcds = 8;
 __host__ __device__ inline int xcd_grid(long long total) { return (int)((total + kXcds - 1) / kXcds) * kXcds; }
-__device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
-    const int L = blockIdx.x;
+__device__ __forceinline__ bool xcd_remap(long long total, int &logical, int first = 0) {     // first: other workgroups before
+    const int L = blockIdx.x - first;
     const int per = (int)((total + kXcds - 1) / kXcds);
     logical = (L % kXcds) * per + L / kXcds;
     return logical < total;

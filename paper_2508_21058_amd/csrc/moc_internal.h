@@ -26,7 +26,7 @@ inline int text_segments(int N) {
 // Neighbouring segments of a caption tile that one workgroup walks, leaving one partial for all of them. Segments
 // balance calls of few caption items; where a call has an item per compute unit anyway, more partials (a tile in
 // fp32 each, written and summed) only cost. So a tile keeps as many as leave fewer than two items per unit (but
-// no more than kTextSegMax queries in one). dK/dV and text_reduce with four partials a tile / with this rule (one
+// no more than kTextSegMax queries in one). dK/dV and the sums of the partials with four partials a tile / with this rule (one
 // where not given): 16 heads of 10k tokens with a 2,000-token caption (256 whole-stream items) 576 / 533 us, 32 heads
 // 1,156 / 1,068, eight 300-token captions of 24 heads (576) 1,568 / 1,507; six heads of them (144, four partials)
 // 294, with two 323.
