@@ -36,7 +36,7 @@ inline int text_join(int N, int n_tiles, int BH, int nseg) {
     want = std::max(std::max(want, 1), (N + kTextSegMax - 1) / kTextSegMax);
     return std::max(1, nseg / want);
 }
-constexpr int kRowsPerBlk = 256; // queries per block of the list builder (one wave and one histogram column each)
+constexpr int kRowsPerBlk = 256, kRowsPerBlkMin = 64;   // queries per block of the list builder (one wave and one histogram row each)
 constexpr int kMaxListChunks = 16384;   // chunks the list builder's LDS histogram holds
 
 // One query tile of the forced-link pass: queries [q_start, q_start+q_count)
@@ -122,7 +122,7 @@ hipError_t launch_probe(int kind, void *buf, size_t bytes, int iters, hipStream_
 
 // Layout of the attention workspace (byte offsets); shared by fwd and bwd.
 struct AttnWs {
-    size_t cnt, list_off, tile_off, vmask, gsum, cnt_blk, qlist, plse, po, cvt, delta, stats2, gstats2, tpart_k, tpart_v, total;
+    size_t cnt, list_off, tile_off, vmask, gsum, cnt_blk, qlist, plse, po, cnt_fine, cvt, delta, stats2, gstats2, tpart_k, tpart_v, total;
 };
 AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, bool with_bwd);
 
@@ -145,6 +145,8 @@ hipError_t launch_route_fused(const moc_meta *m, int BH, int d, const void *q, c
 hipError_t fused_wait_flag(int *timed_out);
 
 // counts -> offsets -> inverse lists (per head and chunk: the queries that routed to it)
+// room for the histograms of small blocks, where the list builder uses them
+size_t list_fine_bytes(const moc_meta *m, int BH);
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws,
                               const AttnWs &L, hipStream_t st);
 

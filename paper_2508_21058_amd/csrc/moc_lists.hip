@@ -9,7 +9,7 @@
 // A stable counting sort on the device, no host synchronisation, no global
 // atomics, so every list is in ascending query order and the same input gives
 // the same lists (and the same summation order in dK / dV) on every call:
-//   count  one wave per block of kRowsPerBlk queries: which entries of a
+//   count  one wave per block of queries (64 to 256): which entries of a
 //          row count at all (see entry_ok), an LDS histogram over the chunks,
 //          written out whole as row `block` of a [blocks][C] table;
 //   scan   down the blocks of every chunk (a block's first position inside the
@@ -17,7 +17,8 @@
 //   fill   one wave per block walks its queries in order and takes their
 //          positions from LDS cursors (see fill_rows), so they do not depend on
 //          scheduling.
-// Calls with few entries do all three in one workgroup per head.
+// Calls with few entries do all three in one workgroup per head; where the table is small, the workgroups of
+// the fill scan it themselves.
 // An entry packs query and slot as (i << 5) | r (r < MOC_MAX_TOPK = 32).
 //
 // Which entries of a selection row count (Sec. 3.3 pre-routing mask): forced
@@ -147,17 +148,17 @@ __device__ __forceinline__ void fill_rows(const int32_t *__restrict__ sel, int i
     }
 }
 
-// One wave per block of kRowsPerBlk queries.
+// One wave per block of `rows` queries.
 __global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restrict__ sel, int N, int topk, int C, int bits,
                                                         const int32_t *__restrict__ chunk_of,
                                                         const int32_t *__restrict__ win,
-                                                        const int32_t *__restrict__ rw, int NB, int BH,
+                                                        const int32_t *__restrict__ rw, int rows, int NB, int BH,
                                                         uint32_t *__restrict__ vmask, int32_t *__restrict__ cnt_blk) {
     extern __shared__ int32_t hist[];    // [C]
     int logical;
     if (!xcd_remap((long long)NB * BH, logical)) return;
     const int bh = logical / NB, blk = logical - bh * NB, lane = threadIdx.x;
-    const int i0 = blk * kRowsPerBlk, nrow = min(kRowsPerBlk, N - i0);
+    const int i0 = blk * rows, nrow = min(rows, N - i0);
     for (int b = lane; b < C; b += 64) hist[b] = 0;
     __syncthreads();
     count_rows(sel + (size_t)bh * N * topk, i0, nrow, topk, C, bits, lane, chunk_of, win, rw, vmask + (size_t)bh * N, hist);
@@ -261,12 +262,86 @@ __global__ __launch_bounds__(64) void list_fill_kernel(const int32_t *__restrict
               qlist + (size_t)bh * N * topk);
 }
 
+// Scan and fill in one launch, for tables that are cheap to read whole: every workgroup (sixteen blocks of a head, a
+// wave each) sums the head's table itself, thread (g, j) every G-th row of chunk j, instead of three launches that pass
+// the sums on. Counting and this against the launches before (one workgroup a head at 6,256 tokens, else the five of the
+// general way): 29 -> 15 us at 6,256 tokens, 24 heads, k = 3; 57 -> 26 at 15.5k tokens, sixteen ragged heads, k = 6; 47 -> 19
+// at 12.9k, six heads, k = 5; 66 -> 49 at 33k, 24 heads, k = 5; 155 -> 144 at 182k, 24 heads, k = 5. Blocks shrink until
+// the count has some 4,096 waves: with 2,048 the 33k tokens take 52, with 1,024 the 6,256 tokens 18 and the 15.5k 34.
+constexpr int kFillWaves = 16;
+constexpr int kFillSpread = 4096;         // waves of the count kernel up to which smaller blocks gain
+constexpr int kFillChunks = 880;          // its cursors and sums: 64 KB of LDS
+constexpr int kFillTable = 49152;         // words of a head's table up to which it is used (192 KB read by each workgroup)
+__global__ __launch_bounds__(kFillWaves * 64) void list_scan_fill_kernel(const int32_t *__restrict__ sel, int N, int topk, int C,
+                                                                         int bits, const uint32_t *__restrict__ vmask,
+                                                                         int rows, int NB, int BH,
+                                                                         const int32_t *__restrict__ cnt_blk,
+                                                                         int32_t *__restrict__ list_off,
+                                                                         int32_t *__restrict__ tile_off,
+                                                                         int32_t *__restrict__ qlist) {
+    extern __shared__ int32_t cursor[];  // [kFillWaves][C]
+    __shared__ int32_t part[2][kFillWaves * 64];
+    static_assert(kFillWaves * kFillChunks * 4 + 2 * kFillWaves * 65 * 4 <= 65536, "LDS of a launch");
+    __shared__ int32_t wsum[2][kFillWaves];
+    const int groups = (NB + kFillWaves - 1) / kFillWaves;
+    int logical;
+    if (!xcd_remap((long long)groups * BH, logical)) return;
+    const int bh = logical / groups, b0 = (logical - bh * groups) * kFillWaves;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t *tab = cnt_blk + (size_t)bh * NB * C;
+    // ---- per chunk: entries in the blocks before this workgroup's, entries in all
+    const int G = kFillWaves * 64 / C, g = tid / C, j = tid - g * C;
+    int before = 0, tot = 0;
+    if (g < G) {
+#pragma unroll 8
+        for (int b = g; b < NB; b += G) {
+            const int c = tab[(size_t)b * C + j];
+            tot += c;
+            before += b < b0 ? c : 0;
+        }
+        part[0][tid] = before;
+        part[1][tid] = tot;
+    }
+    __syncthreads();
+    before = tot = 0;
+    if (tid < C)
+        for (int u = 0; u < G; ++u) { before += part[0][u * C + tid]; tot += part[1][u * C + tid]; }
+    // ---- thread j owns chunk j: an exclusive scan over the chunks
+    int a = tot, t = (tot + kBM - 1) / kBM;
+    const int tiles = t;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int xa = __shfl_up(a, o, 64), xt = __shfl_up(t, o, 64);
+        if (lane >= o) { a += xa; t += xt; }
+    }
+    if (lane == 63) { wsum[0][wave] = a; wsum[1][wave] = t; }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) { a += wsum[0][w]; t += wsum[1][w]; }
+    if (tid < C) {
+        if (b0 == 0) {
+            int32_t *lo = list_off + (size_t)bh * (C + 1), *to = tile_off + (size_t)bh * (C + 1);
+            lo[tid] = a - tot;
+            to[tid] = t - tiles;
+            if (tid == C - 1) { lo[C] = a; to[C] = t; }
+        }
+        int c[kFillWaves], at = a - tot + before;
+#pragma unroll
+        for (int w = 0; w < kFillWaves; ++w) c[w] = tab[(size_t)min(b0 + w, NB - 1) * C + tid];
+#pragma unroll
+        for (int w = 0; w < kFillWaves; ++w) { cursor[w * C + tid] = at; at += c[w]; }
+    }
+    __syncthreads();
+    const int i0 = (b0 + wave) * rows;
+    if (i0 < N)
+        fill_rows(sel + (size_t)bh * N * topk, i0, min(rows, N - i0), topk, bits, lane, vmask + (size_t)bh * N, cursor + wave * C,
+                  qlist + (size_t)bh * N * topk);
+}
+
 // The whole list builder for a head in one workgroup: sixteen waves take consecutive sixteenths of the
-// queries, count into histograms of their own, scan them and fill. Small calls are bound by the five
-// launches of the general path and their few waves, not by work: 52 us of kernels against 28 at 6,256
-// tokens, 24 heads and k = 3, 38 against 7 at 1,088 tokens.
+// queries, count into histograms of their own, scan them and fill. The smallest calls are bound by their
+// launches, not by work: 38 us in five, 7 in one at 1,088 tokens; at 8,192 entries a head two launches take as long.
 constexpr int kHeadWaves = 16, kHeadChunks = 1000;      // 62.5 KB of histograms
-constexpr int kHeadEntries = 32768;       // N * topk up to which it is used: 64 steps a wave, where both ways take about as long
+constexpr int kHeadEntries = 8192;        // N * topk up to which it is used
 __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_t *__restrict__ sel, int N, int topk,
                                                                     int C, int bits,
                                                                     const int32_t *__restrict__ chunk_of,
@@ -316,10 +391,15 @@ __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_
     fill_rows(sel, i0, nrow, topk, bits, lane, vmask, hist + wave * C, qlist + (size_t)bh * N * topk);
 }
 
+// (a bound that does not ask how many queries a block gets: never more than kFillTable words a head)
+size_t list_fine_bytes(const moc_meta *m, int BH) {
+    const size_t words = (size_t)((m->N + kRowsPerBlkMin - 1) / kRowsPerBlkMin) * m->C;
+    return (size_t)BH * std::min(words, (size_t)kFillTable) * 4;
+}
+
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws, const AttnWs &L,
                               hipStream_t st) {
     const int C = m->C, N = m->N;
-    const int NB = (N + kRowsPerBlk - 1) / kRowsPerBlk;
     int32_t *cnt = reinterpret_cast<int32_t *>(ws + L.cnt);
     int32_t *cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_blk);
     uint32_t *vmask = reinterpret_cast<uint32_t *>(ws + L.vmask);
@@ -334,15 +414,29 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
             sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, vmask, list_off, tile_off, qlist);
         return hipGetLastError();
     }
-    const size_t shm_fill = (size_t)C * 4, shm_count = (size_t)C * 4;
-    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm_count, st>>>(sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, NB, BH,
-                                                                 vmask, cnt_blk);
+    // blocks of fewer queries where that gives the chip more waves and the table stays small
+    int rows = kRowsPerBlk, NB = (N + rows - 1) / rows;
+    const bool two = C <= kFillChunks && (long long)NB * C <= kFillTable;
+    while (two && rows > kRowsPerBlkMin && (long long)NB * BH < kFillSpread && (long long)((N + rows / 2 - 1) / (rows / 2)) * C <= kFillTable) {
+        rows /= 2;
+        NB = (N + rows - 1) / rows;
+    }
+    if (two) cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_fine);
+    const size_t shm = (size_t)C * 4;
+    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm, st>>>(
+        sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, rows, NB, BH, vmask, cnt_blk);
+    if (two) {
+        const long long wgs = (long long)((NB + kFillWaves - 1) / kFillWaves) * BH;
+        list_scan_fill_kernel<<<dim3(xcd_grid(wgs)), dim3(kFillWaves * 64), kFillWaves * shm, st>>>(
+            sel, N, topk, C, bits, vmask, rows, NB, BH, cnt_blk, list_off, tile_off, qlist);
+        return hipGetLastError();
+    }
     int32_t *gsum = reinterpret_cast<int32_t *>(ws + L.gsum);
     const dim3 sgrid((C + 255) / 256, kScanGroups, BH);
     list_group_sum_kernel<<<sgrid, dim3(256), 0, st>>>(cnt_blk, NB, C, gsum);
     list_block_scan_kernel<<<sgrid, dim3(256), 0, st>>>(cnt_blk, NB, C, gsum, cnt);
     list_scan_kernel<<<dim3(BH), dim3(256), 0, st>>>(cnt, C, list_off, tile_off);
-    list_fill_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm_fill, st>>>(sel, N, topk, C, bits, vmask, NB, BH, cnt_blk, list_off, qlist);
+    list_fill_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm, st>>>(sel, N, topk, C, bits, vmask, NB, BH, cnt_blk, list_off, qlist);
     return hipGetLastError();
 }
 

@@ -339,3 +339,12 @@ def test_fused_routing_of_other_keys_back_to_back(d, topk):
         assert torch.equal(pooled, want[i][0]) and torch.equal(sel, want[i][1])
     assert not mb.route_fused_timed_out()
     meta.close()
+
+
+# the list builder's ways at their edges: one workgroup a head up to 8192 entries; scan and fill in one launch up to
+# 880 chunks and a table of 49152 words (blocks of 64, 128 and 256 queries; a last workgroup of one block), past either
+# the general way
+@pytest.mark.parametrize("N,chunk,topk", [(2048, 20, 4), (2049, 20, 4), (880, 1, 10), (881, 1, 10), (65 * 64 + 1, 70, 2), (16 * 64, 30, 9),
+                                          (196608, 768, 1), (196609, 768, 1), (98304, 192, 1), (49152, 96, 1), (49153, 96, 1)])
+def test_list_builder_ways(N, chunk, topk):
+    test_list_builder_ranges(N, chunk, topk)
