@@ -807,7 +807,7 @@ int attn_bwd_impl(const moc_meta *meta, int32_t B, int32_t H, int32_t d, int dty
     hipError_t e = hipSuccess;
     const ListTag tag{meta, sel, B, H, topk, stream};
     if (topk > 0 && !(reuse_lists && tag_matches(workspace, tag))) {
-        e = moc::launch_build_lists(meta, B * H, topk, sel, static_cast<char *>(workspace), L, st);
+        e = moc::launch_build_lists(meta, B * H, topk, sel, static_cast<char *>(workspace), L, moc::CvtArgs{}, st);
         if (e != hipSuccess) { tag_drop(workspace); return hip_fail(e, "list kernels"); }
     }
     tag_drop(workspace);     // the backward leaves the workspace to whoever comes next
@@ -835,7 +835,10 @@ int moc_attn_fwd(const moc_meta *meta, int32_t B, int32_t H, int32_t d, int dtyp
     hipError_t e = hipSuccess;
     tag_drop(workspace);
     if (topk > 0) {
-        e = moc::launch_build_lists(meta, B * H, topk, sel, static_cast<char *>(workspace), L, st);
+        // fp32 storage: its bf16 copies of q, k and v are made beside the lists
+        const moc::CvtArgs cvt = dtype == MOC_F32 ? moc::cvt_args(q, k, v, static_cast<char *>(workspace) + L.cvt, (size_t)B * H * meta->N * d)
+                                                  : moc::CvtArgs{};
+        e = moc::launch_build_lists(meta, B * H, topk, sel, static_cast<char *>(workspace), L, cvt, st);
         if (e != hipSuccess) return hip_fail(e, "list kernels");
     }
     e = moc::launch_attn_fwd(meta, B * H, d, dtype, q, k, v, topk, softmax_scale, o, lse,

@@ -24,7 +24,10 @@ namespace moc {
 template <int D, typename T>
 __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ o, const T *__restrict__ d_o, size_t rows,
                                                     const float *__restrict__ lse, float *__restrict__ delta,
-                                                    float *__restrict__ stats2, bf16_t *__restrict__ do16) {
+                                                    float *__restrict__ stats2, bf16_t *__restrict__ do16, uint32_t n_delta,
+                                                    CvtArgs cvt) {
+    if constexpr (sizeof(T) == 4)       // the copies of q, k and v are the last workgroups
+        if (blockIdx.x >= n_delta) { convert_workgroup<256>(cvt, blockIdx.x - n_delta); return; }
     constexpr int TPQ = D / 8, QPW = 256 / TPQ;
     const size_t row = (size_t)blockIdx.x * QPW + threadIdx.x / TPQ;
     const int c8 = threadIdx.x % TPQ;
@@ -1154,13 +1157,14 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
 // T: storage type of the caller's tensors; o_in and do_in are the caller's o and dO, a / kv hold bf16 operands
 template <int D, typename T>
 static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv, const void *o_in, const void *do_in,
-                               void *dq, hipStream_t st) {
+                               void *dq, CvtArgs cvt, hipStream_t st) {
     constexpr int QPW = 256 / (D / 8);
     const size_t rows = (size_t)BH * m->N;
     { MOC_PROF("delta", st);
-    delta_kernel<D, T><<<dim3((unsigned)((rows + QPW - 1) / QPW)), dim3(256), 0, st>>>(
+    const uint32_t n_delta = (uint32_t)((rows + QPW - 1) / QPW), extra = cvt_grid(cvt, 256);
+    delta_kernel<D, T><<<dim3(n_delta + extra), dim3(256), 0, st>>>(
         static_cast<const T *>(o_in), static_cast<const T *>(do_in), rows, a.lse, const_cast<float *>(a.delta),
-        const_cast<float *>(kv.stats2), static_cast<bf16_t *>(const_cast<void *>(a.d_o))); }
+        const_cast<float *>(kv.stats2), static_cast<bf16_t *>(const_cast<void *>(a.d_o)), n_delta, cvt); }
     { MOC_PROF("attn_bwd_dkdv", st);
     if (a.topk > 0) {
         const int NK = m->N * a.topk;
@@ -1193,11 +1197,11 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
                            void *dv, char *ws, const AttnWs &L, hipStream_t st) {
     FwdArgs a{};
     a.q = q; a.k = k; a.v = v; a.d_o = d_o;
+    CvtArgs cvt;
     if (dtype == MOC_F32) {
         const size_t n = (size_t)BH * m->N * d;
         bf16_t *c = reinterpret_cast<bf16_t *>(ws + L.cvt);
-        const hipError_t e = launch_to_bf16(q, k, v, c, n, st);
-        if (e != hipSuccess) return e;
+        cvt = cvt_args(q, k, v, c, n);          // with the delta kernel
         a.q = c; a.k = c + n; a.v = c + 2 * n;
         a.d_o = c + 3 * n;                      // written by the delta kernel
     }
@@ -1233,10 +1237,10 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     a.tpart_k = kv.tpart_k; a.tpart_v = kv.tpart_v; a.text_tiles = m->d_text_tiles;
     a.n_text_tiles = m->n_text_tiles; a.n_partials = m->n_partials; a.join = kv.join;
     a.dk = dk; a.dv = dv;
-    if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, d_o, dq, st)
-                                           : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, d_o, dq, st);
-    return d == 128 ? bwd_dispatch<128, float>(m, BH, a, kv, o, d_o, dq, st)
-                    : bwd_dispatch<64, float>(m, BH, a, kv, o, d_o, dq, st);
+    if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, d_o, dq, cvt, st)
+                                           : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, d_o, dq, cvt, st);
+    return d == 128 ? bwd_dispatch<128, float>(m, BH, a, kv, o, d_o, dq, cvt, st)
+                    : bwd_dispatch<64, float>(m, BH, a, kv, o, d_o, dq, cvt, st);
 }
 
 }  // namespace moc

@@ -126,6 +126,20 @@ __device__ __forceinline__ bool kv_item(int n_items, int n_text, int BH, int &bh
     return true;
 }
 
+// Workgroup `wg` of the conversions that ride with a launch of THREADS threads; bound by HBM.
+template <int THREADS> __device__ __forceinline__ void convert_workgroup(const CvtArgs &c, uint32_t wg) {
+    const uint32_t t = wg / c.per_tensor;
+    const float *x = t == 0 ? c.x[0] : (t == 1 ? c.x[1] : c.x[2]);
+    bf16_t *out = static_cast<bf16_t *>(c.out) + t * c.n;
+    const size_t i0 = ((size_t)(wg - t * c.per_tensor) * THREADS * kCvtUnroll + threadIdx.x) * 8;
+    bf16x8 v[kCvtUnroll];
+#pragma unroll
+    for (int u = 0; u < kCvtUnroll; ++u) v[u] = Io<float>::load8(x + min(i0 + (size_t)u * THREADS * 8, c.n - 8));
+#pragma unroll
+    for (int u = 0; u < kCvtUnroll; ++u)
+        if (i0 + (size_t)u * THREADS * 8 < c.n) *reinterpret_cast<bf16x8 *>(out + i0 + (size_t)u * THREADS * 8) = v[u];
+}
+
 struct ItemDesc {
     int q_start, q_count;
     const int32_t *entries;   // gathered rows ((query << 5) | slot) or nullptr

@@ -492,18 +492,13 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
     }
 }
 
-// fp32 -> bf16 copies of up to three tensors of n elements (n a multiple of 8), 8 elements a lane; bound by HBM
-__global__ __launch_bounds__(256) void to_bf16_kernel(const float *x0, const float *x1, const float *x2, bf16_t *out, size_t n) {
-    const float *x = blockIdx.y == 0 ? x0 : (blockIdx.y == 1 ? x1 : x2);
-    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
-    if (i < n) *reinterpret_cast<bf16x8 *>(out + blockIdx.y * n + i) = Io<float>::load8(x + i);
-}
+// fp32 -> bf16 copies where no launch takes them along (a forward without routed links builds no lists)
+__global__ __launch_bounds__(256) void to_bf16_kernel(CvtArgs c) { convert_workgroup<256>(c, blockIdx.x); }
 
-hipError_t launch_to_bf16(const void *x0, const void *x1, const void *x2, void *out, size_t n, hipStream_t st) {
+hipError_t launch_to_bf16(CvtArgs c, hipStream_t st) {
     MOC_PROF("to_bf16", st);
-    to_bf16_kernel<<<dim3((unsigned)((n / 8 + 255) / 256), x2 ? 3 : 2), dim3(256), 0, st>>>(
-        static_cast<const float *>(x0), static_cast<const float *>(x1), static_cast<const float *>(x2),
-        static_cast<bf16_t *>(out), n);
+    const uint32_t grid = cvt_grid(c, 256);
+    to_bf16_kernel<<<dim3(grid), dim3(256), 0, st>>>(c);
     return hipGetLastError();
 }
 
@@ -536,10 +531,13 @@ hipError_t launch_attn_fwd(const moc_meta *m, int BH, int d, int dtype, const vo
     if (dtype == MOC_F32) {
         const size_t n = (size_t)BH * m->N * d;
         bf16_t *c = reinterpret_cast<bf16_t *>(ws + L.cvt);
-        // With no routed links a query is read once, by its forced-link item, which rounds it then: a copy would
-        // cost more than it saves (forward of 12 heads, 40k tokens in 240-token windows: 337 us with it, 294 without).
-        const hipError_t e = topk > 0 ? launch_to_bf16(q, k, v, c, n, st) : launch_to_bf16(k, v, nullptr, c + n, n, st);
-        if (e != hipSuccess) return e;
+        // The copies of q, k and v came with the lists. With no routed links there are no lists, and a query is read
+        // once, by its forced-link item, which rounds it then: a copy of it would cost more than it saves (forward of
+        // 12 heads, 40k tokens in 240-token windows: 337 us with it, 294 without).
+        if (topk == 0) {
+            const hipError_t e = launch_to_bf16(cvt_args(k, v, nullptr, c + n, n), st);
+            if (e != hipSuccess) return e;
+        }
         if (topk > 0) a.q = c;
         a.k = c + n; a.v = c + 2 * n;
     }

@@ -144,14 +144,37 @@ hipError_t launch_route_fused(const moc_meta *m, int BH, int d, const void *q, c
                               void *kb_split, int Cpad, int topk, int causal, int32_t *sel, hipStream_t st);
 hipError_t fused_wait_flag(int *timed_out);
 
+// bf16 copies of `count` (0: none) fp32 tensors of n elements each (n a multiple of 8), back to back in `out`. They ride
+// with a launch that does not need them, as its last workgroups: per_tensor of them a tensor.
+struct CvtArgs {
+    const float *x[3] = {};
+    void *out = nullptr;
+    size_t n = 0;
+    int count = 0;
+    uint32_t per_tensor = 0;
+};
+constexpr int kCvtUnroll = 4;           // words of 8 elements a thread
+inline CvtArgs cvt_args(const void *x0, const void *x1, const void *x2, void *out, size_t n) {
+    CvtArgs c;
+    c.x[0] = static_cast<const float *>(x0); c.x[1] = static_cast<const float *>(x1); c.x[2] = static_cast<const float *>(x2);
+    c.out = out; c.n = n; c.count = x2 ? 3 : 2;
+    return c;
+}
+// the workgroups of `threads` threads it adds to a launch
+inline uint32_t cvt_grid(CvtArgs &c, int threads) {
+    const size_t per_wg = (size_t)threads * kCvtUnroll * 8;
+    c.per_tensor = (uint32_t)((c.n + per_wg - 1) / per_wg);
+    return c.per_tensor * c.count;
+}
+// ... in a launch of their own
+hipError_t launch_to_bf16(CvtArgs c, hipStream_t st);
+
 // counts -> offsets -> inverse lists (per head and chunk: the queries that routed to it)
 // room for the histograms of small blocks, where the list builder uses them
 size_t list_fine_bytes(const moc_meta *m, int BH);
+// (cvt: conversions that ride with its first launch)
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws,
-                              const AttnWs &L, hipStream_t st);
-
-// bf16 copies of two or three (x2 not NULL) fp32 tensors of n elements each, back to back in `out`
-hipError_t launch_to_bf16(const void *x0, const void *x1, const void *x2, void *out, size_t n, hipStream_t st);
+                              const AttnWs &L, CvtArgs cvt, hipStream_t st);
 
 // (both read the lists and the slot masks launch_build_lists left in the workspace)
 hipError_t launch_attn_fwd(const moc_meta *m, int BH, int d, int dtype, const void *q, const void *k,

@@ -153,8 +153,11 @@ __global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restric
                                                         const int32_t *__restrict__ chunk_of,
                                                         const int32_t *__restrict__ win,
                                                         const int32_t *__restrict__ rw, int rows, int NB, int BH,
-                                                        uint32_t *__restrict__ vmask, int32_t *__restrict__ cnt_blk) {
+                                                        uint32_t *__restrict__ vmask, int32_t *__restrict__ cnt_blk,
+                                                        CvtArgs cvt) {
     extern __shared__ int32_t hist[];    // [C]
+    const int mine = xcd_grid((long long)NB * BH);
+    if ((int)blockIdx.x >= mine) { convert_workgroup<64>(cvt, blockIdx.x - mine); return; }
     int logical;
     if (!xcd_remap((long long)NB * BH, logical)) return;
     const int bh = logical / NB, blk = logical - bh * NB, lane = threadIdx.x;
@@ -269,6 +272,7 @@ __global__ __launch_bounds__(64) void list_fill_kernel(const int32_t *__restrict
 // at 12.9k, six heads, k = 5; 66 -> 49 at 33k, 24 heads, k = 5; 155 -> 144 at 182k, 24 heads, k = 5. Blocks shrink until
 // the count has some 4,096 waves: with 2,048 the 33k tokens take 52, with 1,024 the 6,256 tokens 18 and the 15.5k 34.
 constexpr int kFillWaves = 16;
+constexpr int kCvtChunks = 1024;          // 4 KB of LDS a wave: 32 waves on a compute unit
 constexpr int kFillSpread = 4096;         // waves of the count kernel up to which smaller blocks gain
 constexpr int kFillChunks = 880;          // its cursors and sums: 64 KB of LDS
 constexpr int kFillTable = 49152;         // words of a head's table up to which it is used (192 KB read by each workgroup)
@@ -350,9 +354,10 @@ __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_
                                                                     uint32_t *__restrict__ vmask,
                                                                     int32_t *__restrict__ list_off,
                                                                     int32_t *__restrict__ tile_off,
-                                                                    int32_t *__restrict__ qlist) {
+                                                                    int32_t *__restrict__ qlist, int BH, CvtArgs cvt) {
     extern __shared__ int32_t hist[];    // [kHeadWaves][C]
     __shared__ int32_t wsum[2][kHeadWaves];
+    if ((int)blockIdx.x >= BH) { convert_workgroup<kHeadWaves * 64>(cvt, blockIdx.x - BH); return; }
     const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int per = (N + kHeadWaves - 1) / kHeadWaves;
     const int i0 = min(N, wave * per), nrow = min(per, N - i0);
@@ -398,7 +403,7 @@ size_t list_fine_bytes(const moc_meta *m, int BH) {
 }
 
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws, const AttnWs &L,
-                              hipStream_t st) {
+                              CvtArgs cvt, hipStream_t st) {
     const int C = m->C, N = m->N;
     int32_t *cnt = reinterpret_cast<int32_t *>(ws + L.cnt);
     int32_t *cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_blk);
@@ -410,8 +415,9 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     int bits = 0;
     while ((1 << bits) < C) ++bits;
     if ((long long)N * topk <= kHeadEntries && C <= kHeadChunks) {
-        list_head_kernel<<<dim3(BH), dim3(kHeadWaves * 64), (size_t)kHeadWaves * C * 4, st>>>(
-            sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, vmask, list_off, tile_off, qlist);
+        const uint32_t extra = cvt_grid(cvt, kHeadWaves * 64);
+        list_head_kernel<<<dim3(BH + extra), dim3(kHeadWaves * 64), (size_t)kHeadWaves * C * 4, st>>>(
+            sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, vmask, list_off, tile_off, qlist, BH, cvt);
         return hipGetLastError();
     }
     // blocks of fewer queries where that gives the chip more waves and the table stays small
@@ -423,8 +429,15 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     }
     if (two) cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_fine);
     const size_t shm = (size_t)C * 4;
-    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH)), dim3(64), shm, st>>>(
-        sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, rows, NB, BH, vmask, cnt_blk);
+    // (the conversions' waves get the count's LDS too: beside large histograms too few would run at once)
+    if (cvt.count && C > kCvtChunks) {
+        const hipError_t e = launch_to_bf16(cvt, st);
+        if (e != hipSuccess) return e;
+        cvt.count = 0;
+    }
+    const uint32_t extra = cvt_grid(cvt, 64);
+    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH) + extra), dim3(64), shm, st>>>(
+        sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, rows, NB, BH, vmask, cnt_blk, cvt);
     if (two) {
         const long long wgs = (long long)((NB + kFillWaves - 1) / kFillWaves) * BH;
         list_scan_fill_kernel<<<dim3(xcd_grid(wgs)), dim3(kFillWaves * 64), kFillWaves * shm, st>>>(
