@@ -227,7 +227,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
 
     if (MODE == MODE_ANCHOR && (int)blockIdx.x < a.n_reduce) { text_reduce<D, OT>(a); return; }
     int logical;
-    if (!xcd_remap((long long)a.items_per_head * a.BH, logical, MODE == MODE_ANCHOR ? a.n_reduce : 0)) return;
+    const long long total = (long long)a.items_per_head * a.BH;
+    if (!(MODE == MODE_ANCHOR ? xcd_remap_back(total, logical, a.n_reduce) : xcd_remap(total, logical))) return;
     const int bh = logical / a.items_per_head;
     ItemDesc it;
     if (!decode_item<MODE>(a, bh, logical - bh * a.items_per_head, it)) return;

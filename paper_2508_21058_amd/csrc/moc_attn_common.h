@@ -78,6 +78,16 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical, int fir
     logical = (L % kXcds) * per + L / kXcds;
     return logical < total;
 }
+// The same slices from their ends, for the forced-link items: the routed launch before them left the partials of an XCD's
+// last heads in its L2, and those are then read first. Forced forward / dQ of six fp32 heads of 12.9k tokens 110 -> 103 /
+// 131 -> 127 us, sixteen heads of 64 features and 15.5k tokens 128 -> 125 / 158 -> 153, 24 heads of 6,256 tokens 98 -> 97 /
+// 117 -> 112; no difference from 33k tokens on.
+__device__ __forceinline__ bool xcd_remap_back(long long total, int &logical, int first = 0) {
+    if (!xcd_remap(total, logical, first)) return false;
+    const int per = (int)((total + kXcds - 1) / kXcds), slice = logical / per * per;
+    logical = slice + (int)min((long long)per, total - slice) - 1 - (logical - slice);
+    return true;
+}
 
 // The key-stationary work list of a head holds its caption items (n_text, the long ones) before its
 // video items. Both kinds are dealt to the XCDs separately, caption items of every head first: a

@@ -305,7 +305,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
     const int N = a.N;
 
     int logical;
-    if (!xcd_remap((long long)a.items_per_head * a.BH, logical)) return;
+    const long long total = (long long)a.items_per_head * a.BH;
+    if (!(MODE == MODE_ANCHOR ? xcd_remap_back(total, logical) : xcd_remap(total, logical))) return;
     const int bh = logical / a.items_per_head;
     ItemDesc it;
     if (!decode_item<MODE>(a, bh, logical - bh * a.items_per_head, it)) return;
