@@ -189,14 +189,16 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
 }
 
 // Sums the per-segment partials of a caption key tile in a fixed order, one float4 of dK and of dV a thread, 256 of them a
-// workgroup; bound by HBM. These workgroups are the first of the forced-link dQ launch, which needs nothing of theirs and
+// workgroup; bound by HBM. These workgroups are the last of the forced-link dQ launch, which needs nothing of theirs and
 // whose items are bound by other things; as a launch of their own they took 7 us of 675 at 6,256 tokens, 79 us of 41 ms at
-// 114k, 268 us of 93 ms at 457k.
+// 114k, 268 us of 93 ms at 457k. Before the items they would leave the compute units unevenly free: where a call has fewer
+// items than units, pairs of them then share a unit while others idle (sixteen heads of 1,320 tokens: the launch takes
+// 68 us with the sums first, 51 with the sums last, and 50 plus 6 for a launch of their own).
 template <int D> constexpr int reduce_parts() { return kKeyTile * (D / 4) / 256; }
 template <int D, typename T>
 __device__ __forceinline__ void text_reduce(const FwdArgs &a) {
     constexpr int PARTS = reduce_parts<D>(), V4 = D / 4;            // V4: float4 groups per row
-    const int tile = blockIdx.x / PARTS, u = blockIdx.x % PARTS * 256 + threadIdx.x;
+    const int part = blockIdx.x - a.reduce_at, tile = part / PARTS, u = part % PARTS * 256 + threadIdx.x;
     const int bh = tile / a.n_text_tiles;
     if (bh >= a.BH) return;
     const TextTile tt = a.text_tiles[tile - bh * a.n_text_tiles];
@@ -225,10 +227,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int N = a.N;
 
-    if (MODE == MODE_ANCHOR && (int)blockIdx.x < a.n_reduce) { text_reduce<D, OT>(a); return; }
+    if (MODE == MODE_ANCHOR && (int)blockIdx.x >= a.reduce_at) { text_reduce<D, OT>(a); return; }
     int logical;
     const long long total = (long long)a.items_per_head * a.BH;
-    if (!(MODE == MODE_ANCHOR ? xcd_remap_back(total, logical, a.n_reduce) : xcd_remap(total, logical))) return;
+    if (!(MODE == MODE_ANCHOR ? xcd_remap_back(total, logical) : xcd_remap(total, logical))) return;
     const int bh = logical / a.items_per_head;
     ItemDesc it;
     if (!decode_item<MODE>(a, bh, logical - bh * a.items_per_head, it)) return;
@@ -1188,8 +1190,8 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     MOC_PROF("attn_bwd_dq_forced", st);
     a.items_per_head = m->n_atiles;
     a.o_out = dq;        // the forced-link items run after the routed ones and add the routed partials themselves
-    a.n_reduce = xcd_grid((long long)m->n_text_tiles * BH * reduce_parts<D>());
-    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(a.n_reduce + xcd_grid((long long)a.items_per_head * BH)), dim3(256), 0, st>>>(a);
+    a.reduce_at = xcd_grid((long long)a.items_per_head * BH);
+    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(a.reduce_at + m->n_text_tiles * BH * reduce_parts<D>()), dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@ struct FwdArgs {
     const float *tpart_k, *tpart_v;
     const TextTile *text_tiles;
     void *dk, *dv;
-    int n_text_tiles, n_partials, join, n_reduce;
+    int n_text_tiles, n_partials, join, reduce_at;
     // forced-link forward items with the merge fused into their epilogue
     const uint32_t *vmask;  // [BH, N] bit r: routed slot r of the query counts (set by the list builder)
     void *o_out;            // [BH, N, D] final output, in the caller's storage type
@@ -72,8 +72,8 @@ inline bool chunk_stationary(const moc_meta *m, int topk, int BH) {
 // Launch ceil(total/8)*8 workgroups on a 1-D grid; returns false for padding.
 constexpr int kXcds = 8;
 __host__ __device__ inline int xcd_grid(long long total) { return (int)((total + kXcds - 1) / kXcds) * kXcds; }
-__device__ __forceinline__ bool xcd_remap(long long total, int &logical, int first = 0) {     // first: other workgroups before
-    const int L = blockIdx.x - first;
+__device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
+    const int L = blockIdx.x;
     const int per = (int)((total + kXcds - 1) / kXcds);
     logical = (L % kXcds) * per + L / kXcds;
     return logical < total;
@@ -82,8 +82,8 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical, int fir
 // last heads in its L2, and those are then read first. Forced forward / dQ of six fp32 heads of 12.9k tokens 110 -> 103 /
 // 131 -> 127 us, sixteen heads of 64 features and 15.5k tokens 128 -> 125 / 158 -> 153, 24 heads of 6,256 tokens 98 -> 97 /
 // 117 -> 112; no difference from 33k tokens on.
-__device__ __forceinline__ bool xcd_remap_back(long long total, int &logical, int first = 0) {
-    if (!xcd_remap(total, logical, first)) return false;
+__device__ __forceinline__ bool xcd_remap_back(long long total, int &logical) {
+    if (!xcd_remap(total, logical)) return false;
     const int per = (int)((total + kXcds - 1) / kXcds), slice = logical / per * per;
     logical = slice + (int)min((long long)per, total - slice) - 1 - (logical - slice);
     return true;
