@@ -167,9 +167,12 @@ template <int D> struct LaneOffs {
             tr[u] = (SwTile<D>::off(r0, x >> 3) + (x & 7)) * 2;
         }
     }
-    __device__ __forceinline__ void pin() {
+    __device__ __forceinline__ void pin_rows() {
 #pragma unroll
         for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(row[s]));
+    }
+    __device__ __forceinline__ void pin() {
+        pin_rows();
 #pragma unroll
         for (int u = 0; u < 2 * DB; ++u) asm volatile("" : "+v"(tr[u]));
     }

@@ -17,8 +17,9 @@
 // rate here; at the end the two half-waves merge their lists. One pass over the chunks;
 // any data (ties, few tiles) stays exact, and the time does not depend on the data.
 //
-// Bound by these vector instructions: about 240 per tile of 32 x 32 scores (k <= 8) beside
-// its 24 matrix instructions. Against queues of the scores above the k-th best so far,
+// Bound by the sum of these vector instructions, about 240 per tile of 32 x 32 scores (k <= 8), and of its 24 matrix
+// instructions, which hardly run side by side (1,770 cycles a tile measured): neither half the LDS reads nor dealing
+// the ones between the others gains more than 5 % (see launch_route). Against queues of the scores above the k-th best so far,
 // inserted entry by entry (divergent, two LDS rows per entry, two waves per SIMD): 1,313
 // -> 684 us at 114k tokens, 24 heads, 440 chunks, k = 8; 7,074 -> 4,552 us at 457k tokens,
 // six heads, 3,488 chunks, k = 16; 26 -> 15 us at 6,256 tokens, k = 3. The queues cost less per tile the
@@ -28,6 +29,11 @@
 #include "moc_pool_unit.h"
 
 namespace moc {
+
+// f(IC<0>), f(IC<1>), ..., f(IC<N - 1>)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F f) {
+    if constexpr (I < N) { f(IC<I>{}); static_for<N, I + 1>(f); }
+}
 
 struct RouteArgs {
     const void *q;
@@ -72,22 +78,11 @@ __device__ __forceinline__ void order2(double &a, double &b) {      // a >= b
     b = min64(a, b);
     a = t;
 }
-// Batcher's odd-even merge sort, descending: 5 / 19 / 63 pairs for 4 / 8 / 16 entries
-template <int M> __device__ __forceinline__ void sort_entries(double *x) {
-#pragma unroll
-    for (int p = 1; p < M; p *= 2)
-#pragma unroll
-        for (int k = p; k >= 1; k /= 2)
-#pragma unroll
-            for (int i = 0; i < M - 1; ++i)       // pairs (i, i + k) inside blocks of 2 p
-                if (i + k < M && i >= k % p && ((i - k % p) / k) % 2 == 0 && i / (2 * p) == (i + k) / (2 * p))
-                    order2(x[i], x[i + k]);
-}
-// the best K of a descending list of K and a descending list of M <= K, descending again: the pairwise
+// the best K of two descending lists of K, descending again: the pairwise
 // maxima of one list against the other reversed are the best K as a bitonic sequence
-template <int K, int M> __device__ __forceinline__ void merge_entries(double (&list)[K], const double *x) {
+template <int K> __device__ __forceinline__ void merge_entries(double (&list)[K], const double *x) {
 #pragma unroll
-    for (int p = 0; p < M; ++p) list[K - 1 - p] = max64(list[K - 1 - p], x[p]);
+    for (int p = 0; p < K; ++p) list[K - 1 - p] = max64(list[K - 1 - p], x[p]);
 #pragma unroll
     for (int k = K / 2; k >= 1; k /= 2)
 #pragma unroll
@@ -95,53 +90,111 @@ template <int K, int M> __device__ __forceinline__ void merge_entries(double (&l
             if (!(i & k)) order2(list[i], list[i + k]);
 }
 
-// Four waves x 32 queries per workgroup, three workgroups per CU with bf16 queries (132 to 166 registers at d = 128),
-// two with fp32 ones of 128 features (three planes of query fragments, 232 to 256 registers), two staged tiles of
-// pooled keys (one in use, one in flight). The pass is bound by the selection's vector instructions, not by the latency
-// of the tile copies.
+// The selection of a tile as a list of steps, known at compile time, so that they can be dealt between the matrix
+// instructions of the next tile. Per M = min(K, 16) scores: their entries are made, sorted by Batcher's odd-even merge
+// network, descending (5 / 19 / 63 pairs for 4 / 8 / 16 entries), and merged into the list, as merge_entries() does.
+struct NetStep { uint8_t op, i, j; };
+enum : uint8_t { NET_ENTRY, NET_SORT, NET_TAKE, NET_MERGE };
+constexpr int net_cost(uint8_t op) { return op == NET_ENTRY ? 3 : (op == NET_TAKE ? 1 : 2); }     // vector instructions
+template <int K> struct Net {
+    static constexpr int M = K < 16 ? K : 16, kMax = 256;
+    NetStep s[kMax];
+    int n, cost;
+    constexpr void add(uint8_t op, int i, int j) {
+        s[n++] = NetStep{op, (uint8_t)i, (uint8_t)j};
+        cost += net_cost(op);
+    }
+    constexpr Net() : s{}, n(0), cost(0) {
+        for (int r = 0; r < 16; r += M) {
+            for (int i = 0; i < M; ++i) add(NET_ENTRY, r + i, 0);
+            for (int p = 1; p < M; p *= 2)
+                for (int k = p; k >= 1; k /= 2)
+                    for (int i = 0; i < M - 1; ++i)       // pairs (i, i + k) inside blocks of 2 p
+                        if (i + k < M && i >= k % p && ((i - k % p) / k) % 2 == 0 && i / (2 * p) == (i + k) / (2 * p))
+                            add(NET_SORT, r + i, r + i + k);
+            for (int p = 0; p < M; ++p) add(NET_TAKE, K - 1 - p, r + p);
+            for (int k = K / 2; k >= 1; k /= 2)
+                for (int i = 0; i < K; ++i)
+                    if (!(i & k)) add(NET_MERGE, i, i + k);
+        }
+    }
+    // the first step that does not belong to the first `part` of `parts` shares of the cost
+    constexpr int cut(int part, int parts) const {
+        int i = 0;
+        for (int c = 0; i < n && c * parts < cost * part; ++i) c += net_cost(s[i].op);
+        return i;
+    }
+};
+template <int K> struct NetOf { static constexpr Net<K> net{}; };
+
+// steps [AT, END) of the network over one lane's scores `sc` of a tile, x being its entries
+template <int K, int AT, int END>
+__device__ __forceinline__ void net_run(double (&list)[K], double (&x)[16], const f32x16 &sc, uint32_t jb, const Infinities &inf) {
+    if constexpr (AT < END) {
+        constexpr NetStep st = NetOf<K>::net.s[AT];
+        if constexpr (st.op == NET_ENTRY) x[st.i] = entry(sc[st.i], jb ^ (uint32_t)((st.i >> 2) * 8 + (st.i & 3)), inf);
+        else if constexpr (st.op == NET_SORT) order2(x[st.i], x[st.j]);
+        else if constexpr (st.op == NET_TAKE) list[st.i] = max64(list[st.i], x[st.j]);
+        else order2(list[st.i], list[st.j]);
+        net_run<K, AT + 1, END>(list, x, sc, jb, inf);
+    }
+}
+
+// Four waves x 32 (or 64) queries per workgroup, three workgroups per CU with bf16 queries (120 to 154 registers at
+// d = 128), two with fp32 ones of 128 features (three planes of query fragments, 236 to 256 registers) or with 64 queries,
+// two staged tiles of pooled keys (one in use, one in flight).
 constexpr int kRouteThreads = 256;
 constexpr int kRouteStages = 2;
 
-template <int D, typename T, int KMAX>
+// QG groups of 32 queries a wave: see launch_route.
+template <int D, typename T, int KMAX, int QG>
 __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
     constexpr int KS = D / 16;
     constexpr int NQ = sizeof(T) == 2 ? 1 : 3;       // query planes
     constexpr int PB = 32 * D * 2;                   // bytes of one plane tile (32 chunks)
     constexpr int TB = 3 * PB;                       // bytes of one staged tile
     constexpr int NWV = kRouteThreads / 64;
-    constexpr int QPW = kRouteThreads / 2;           // queries per workgroup
+    constexpr int QPW = NWV * 32 * QG;               // queries per workgroup
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int bh = blockIdx.y, N = a.N, C = a.C;
-    const int q0 = blockIdx.x * QPW;
-    const int i = q0 + wave * 32 + l32;
-    const bool valid = i < N;
-    const int ic = valid ? i : N - 1;
-    const int cq = a.chunk_of[ic];
-    const int w = a.win[cq];
-    const int wf = a.wfirst[w], wl = a.wlast[w];
-    const int limit = a.causal ? cq : C;                               // candidates have index < limit
-    // queries ascend with the lane, so do chunk, window and limit
+    // under the causal mask the last queries have the most tiles: first, so that a launch ends on short workgroups
+    // (457k tokens, k = 16: 4,373 -> 4,270 us)
+    const int q0 = (int)(a.causal ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * QPW;
+    const int topk = a.topk;
+    int i[QG], limit[QG], wf[QG], wl[QG], lim_lo[QG], wf_lo[QG], wl_hi[QG];
+#pragma unroll
+    for (int g = 0; g < QG; ++g) {
+        i[g] = q0 + (wave * QG + g) * 32 + l32;
+        const int cq = a.chunk_of[min(i[g], N - 1)], w = a.win[cq];
+        wf[g] = a.wfirst[w];
+        wl[g] = a.wlast[w];
+        limit[g] = a.causal ? cq : C;                                   // candidates have index < limit
+        // queries ascend with the lane, so do chunk, window and limit
+        lim_lo[g] = __builtin_amdgcn_readlane(limit[g], 0);             // smallest limit of the 32 queries
+        wf_lo[g] = __builtin_amdgcn_readlane(wf[g], 0);                 // chunks that may be forced links of one of them
+        wl_hi[g] = __builtin_amdgcn_readlane(wl[g], 31);
+    }
     const int lim_wg = __builtin_amdgcn_readfirstlane(a.causal ? a.chunk_of[min(q0 + QPW - 1, N - 1)] : C);  // uniform: largest limit in the workgroup
     const int ntiles = (lim_wg + 31) >> 5;
-    const int lim_lo = __shfl(limit, 0, 64);                            // smallest limit in the wave
-    const int wf_lo = __shfl(wf, 0, 64), wl_hi = __shfl(wl, 31, 64);    // chunks that may be forced links in the wave
-    const int topk = a.topk;
-    int32_t *out = a.sel + ((size_t)bh * N + ic) * a.stride;
+    auto out_row = [&](int g) { return a.sel + ((size_t)bh * N + i[g]) * a.stride; };
     if (ntiles == 0) {                                                  // no candidates at all
-        if (valid && half == 0)
-            for (int r = 0; r < topk; ++r) out[r] = -1;
+#pragma unroll
+        for (int g = 0; g < QG; ++g)
+            if (i[g] < N && half == 0)
+                for (int r = 0; r < topk; ++r) out_row(g)[r] = -1;
         return;
     }
 
     // query operand planes (B operand: lane -> query column)
-    bf16x8 qf[NQ][KS];
-    {
-        const T *qp = static_cast<const T *>(a.q) + ((size_t)bh * N + ic) * D;
+    bf16x8 qf[QG][NQ][KS];
+#pragma unroll
+    for (int g = 0; g < QG; ++g) {
+        const T *qp = static_cast<const T *>(a.q) + ((size_t)bh * N + min(i[g], N - 1)) * D;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             if constexpr (NQ == 1) {
-                qf[0][s] = Io<T>::load8(qp + s * 16 + half * 8);
+                qf[g][0][s] = Io<T>::load8(qp + s * 16 + half * 8);
             } else {
                 float f[8];
                 Io<T>::load8f(qp + s * 16 + half * 8, f);
@@ -160,9 +213,9 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
                     pm[e] = pack_bf16(mid[2 * e], mid[2 * e + 1]);
                     pl[e] = pack_bf16(lo[2 * e], lo[2 * e + 1]);
                 }
-                qf[0][s] = __builtin_bit_cast(bf16x8, ph);
-                qf[NQ > 1 ? 1 : 0][s] = __builtin_bit_cast(bf16x8, pm);
-                qf[NQ > 2 ? 2 : 0][s] = __builtin_bit_cast(bf16x8, pl);
+                qf[g][0][s] = __builtin_bit_cast(bf16x8, ph);
+                qf[g][NQ > 1 ? 1 : 0][s] = __builtin_bit_cast(bf16x8, pm);
+                qf[g][NQ > 2 ? 2 : 0][s] = __builtin_bit_cast(bf16x8, pl);
             }
         }
     }
@@ -170,13 +223,15 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
     // compiler needs for their loads then sit in front of the loop, not inside it, where they would
     // also wait for the tile copies in flight.
 #pragma unroll
-    for (int qa = 0; qa < NQ; ++qa)
+    for (int g = 0; g < QG; ++g)
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            u32x4 w = __builtin_bit_cast(u32x4, qf[qa][s]);
-            asm volatile("" : "+v"(w));
-            qf[qa][s] = __builtin_bit_cast(bf16x8, w);
-        }
+        for (int qa = 0; qa < NQ; ++qa)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                u32x4 w = __builtin_bit_cast(u32x4, qf[g][qa][s]);
+                asm volatile("" : "+v"(w));
+                qf[g][qa][s] = __builtin_bit_cast(bf16x8, w);
+            }
     LaneOffs<D> lo;
     lo.init(lane);
 
@@ -199,113 +254,150 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
             async_copy16_at(src, (uint32_t)(row * D + cg * 8) * 2u, at + plane * PB + sub * 1024);
         }
     };
-    // tile t + 1 has landed once at most the copies of the tiles after it are still in flight
-    constexpr int DIST = kRouteStages - 1;           // tiles issued ahead of the one in use
-    auto landed = [&](int t_next) {
-        if (DIST > 1 && t_next + DIST - 1 < ntiles) wait_vmcnt<(DIST - 1) * PW>(); else wait_vmcnt<0>();
-    };
+    const Infinities inf;
+    double list[QG][KMAX], x[16];        // a lane's best KMAX candidates so far, best first; entries of a tile
+#pragma unroll
+    for (int g = 0; g < QG; ++g)
+#pragma unroll
+        for (int p = 0; p < KMAX; ++p) list[g][p] = entry(-INFINITY, 0xffffffffu, inf);
 
-    // scores of tile t for this lane: 16 chunks, ineligible ones set to -inf
-    auto scores = [&](auto cur, int t) -> f32x16 {
+    // One pass over the products of a staged tile, in the order (query plane, key plane, features); row fragments are
+    // read kAhead products ahead. With SELECT the selection over `sc`, the scores of the tile before (whose first chunk
+    // for this lane is jb), is dealt between the products.
+    struct Scores { f32x16 g[QG]; };
+    constexpr int NM = (NQ == 1 ? 3 : 6) * KS, kAhead = 2;
+    auto plane_of = [](int m) constexpr { return m / KS < 3 ? m / KS : (m / KS < 5 ? m / KS - 3 : 0); };
+    auto qplane_of = [](int m) constexpr { return m / KS < 3 ? 0 : (m / KS < 5 ? 1 : 2); };
+    auto tile_pass = [&](auto cur, auto select, const Scores &sc, uint32_t jb) -> Scores {
         constexpr int CUR = decltype(cur)::value;
-        lo.pin();
-        f32x16 acc = zero16();
+        constexpr bool SELECT = decltype(select)::value != 0;
+        lo.pin_rows();
+        Scores acc;
 #pragma unroll
-        for (int qa = 0; qa < NQ; ++qa)
+        for (int g = 0; g < QG; ++g) acc.g[g] = zero16();
+        bf16x8 kf[kAhead + 1];
+        auto read = [&](auto m) {
+            constexpr int MI = decltype(m)::value;
+            if constexpr (MI < NM) kf[MI % (kAhead + 1)] = lo.template frag<CUR * TB + plane_of(MI) * PB>(smem, MI % KS);
+        };
+        static_for<kAhead>([&](auto m) { read(m); });
+        static_for<NM>([&](auto m) {
+            constexpr int MI = decltype(m)::value;
+            read(IC<MI + kAhead>{});
 #pragma unroll
-            for (int kp = 0; kp < 3; ++kp) {
-                if (qa + kp > 2) continue;
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    bf16x8 kf;
-                    if (kp == 0) kf = lo.template frag<CUR * TB>(smem, s);
-                    else if (kp == 1) kf = lo.template frag<CUR * TB + PB>(smem, s);
-                    else kf = lo.template frag<CUR * TB + 2 * PB>(smem, s);
-                    acc = mfma32(kf, qf[qa][s], acc);
-                }
+            for (int g = 0; g < QG; ++g) acc.g[g] = mfma32(kf[MI % (kAhead + 1)], qf[g][qplane_of(MI)][MI % KS], acc.g[g]);
+            if constexpr (SELECT) {
+                constexpr int PG = NM / QG, G = MI / PG;
+                constexpr int A = NetOf<KMAX>::net.cut(MI % PG, PG), B = NetOf<KMAX>::net.cut(MI % PG + 1, PG);
+                net_run<KMAX, A, B>(list[G], x, sc.g[G], jb, inf);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        const int j0 = t * 32;
-        const uint32_t tm = uniform_load_u32(a.textmask, t);
-        // fast path: the whole tile is a candidate for every query of the wave
-        const bool clean = tm == 0 && j0 + 32 <= lim_lo && (j0 + 32 <= wf_lo || j0 > wl_hi);
-        if (!clean) {
-            // One 32-bit word per lane, bit b = chunk j0 + b is a candidate of this lane's query:
-            // below the causal limit, outside the own window [wf, wl], not text. The lane then
-            // tests its 16 bits, (r >> 2) * 8 + half * 4 + (r & 3), at compile-time positions.
-            auto below = [](int n) { return n >= 32 ? 0xffffffffu : (n <= 0 ? 0u : ((1u << n) - 1u)); };
-            const uint32_t okm = below(limit - j0) & (below(wf - j0) | ~below(wl - j0 + 1)) & ~tm;
-            const uint32_t mine = okm >> (half * 4);
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (!((mine >> ((r >> 2) * 8 + (r & 3))) & 1u)) acc[r] = -INFINITY;
-        }
+        });
         return acc;
     };
-
-    // ---------------- the lane's best KMAX candidates so far, best first
-    const Infinities inf;
-    double list[KMAX];
+    // scores of chunks that are no candidates become -inf
+    auto mask = [&](Scores &acc, int t) {
+        const int j0 = t * 32;
+        const uint32_t tm = uniform_load_u32(a.textmask, t);
 #pragma unroll
-    for (int p = 0; p < KMAX; ++p) list[p] = entry(-INFINITY, 0xffffffffu, inf);
-    auto scan = [&](auto cur, int t) {
-        constexpr int CUR = decltype(cur)::value;
-        constexpr int M = KMAX < 16 ? KMAX : 16;       // entries sorted and merged at a time
-        const bool more = t + 1 < ntiles;
-        if (t + DIST < ntiles) issue(t + DIST, (CUR + DIST) % kRouteStages);
-        const f32x16 sc = scores(cur, t);
-        const uint32_t jb = (uint32_t)(t * 32 + half * 4);
-        double x[16];
+        for (int g = 0; g < QG; ++g) {
+            // fast path: the whole tile is a candidate for every one of the 32 queries
+            const bool clean = tm == 0 && j0 + 32 <= lim_lo[g] && (j0 + 32 <= wf_lo[g] || j0 > wl_hi[g]);
+            if (!clean) {
+                // One 32-bit word per lane, bit b = chunk j0 + b is a candidate of this lane's query:
+                // below the causal limit, outside the own window [wf, wl], not text. The lane then
+                // tests its 16 bits, (r >> 2) * 8 + half * 4 + (r & 3), at compile-time positions.
+                auto below = [](int n) { return n >= 32 ? 0xffffffffu : (n <= 0 ? 0u : ((1u << n) - 1u)); };
+                const uint32_t okm = below(limit[g] - j0) & (below(wf[g] - j0) | ~below(wl[g] - j0 + 1)) & ~tm;
+                const uint32_t mine = okm >> (half * 4);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = entry(sc[r], jb ^ (uint32_t)((r >> 2) * 8 + (r & 3)), inf);
-#pragma unroll
-        for (int r = 0; r < 16; r += M) {
-            sort_entries<M>(x + r);
-            merge_entries<KMAX, M>(list, x + r);
+                for (int r = 0; r < 16; ++r)
+                    if (!((mine >> ((r >> 2) * 8 + (r & 3))) & 1u)) acc.g[g][r] = -INFINITY;
+            }
         }
-        if (more) { landed(t + 1); __syncthreads(); }
-        return more;
     };
-#pragma unroll
-    for (int u = 0; u < DIST; ++u)
-        if (u < ntiles) issue(u, u);
-    landed(0);
-    __syncthreads();
-    for (int t = 0;;) {
-        if (!scan(IC<0>{}, t++)) break;
-        if (!scan(IC<1 % kRouteStages>{}, t++)) break;
-        if (kRouteStages > 2 && !scan(IC<2 % kRouteStages>{}, t++)) break;
+    auto select_all = [&](const Scores &sc, int t) {
+        static_for<QG>([&](auto g) {
+            constexpr int G = decltype(g)::value;
+            net_run<KMAX, 0, NetOf<KMAX>::net.n>(list[G], x, sc.g[G], (uint32_t)(t * 32 + half * 4), inf);
+        });
+    };
+
+    issue(0, 0);
+    if constexpr (QG == 2) {
+        if (ntiles > 1) { issue(1, 1); wait_vmcnt<PW>(); } else wait_vmcnt<0>();
+        __syncthreads();
+        Scores sc = tile_pass(IC<0>{}, IC<0>{}, Scores{}, 0u);
+        mask(sc, 0);
+        wait_vmcnt<0>();
+        __syncthreads();
+        // the scores of tile t are in `sc`, tile t + 1 has landed in the other stage
+        auto step = [&](auto next, int t) {
+            constexpr int NEXT = decltype(next)::value;
+            if (t + 1 == ntiles) { select_all(sc, t); return false; }
+            const bool more = t + 2 < ntiles;
+            if (more) issue(t + 2, NEXT ^ 1);
+            sc = tile_pass(next, IC<1>{}, sc, (uint32_t)(t * 32 + half * 4));
+            mask(sc, t + 1);
+            if (more) { wait_vmcnt<0>(); __syncthreads(); }
+            return true;
+        };
+        for (int t = 0;;) {
+            if (!step(IC<1>{}, t++)) break;
+            if (!step(IC<0>{}, t++)) break;
+        }
+    } else {
+        wait_vmcnt<0>();
+        __syncthreads();
+        auto step = [&](auto cur, int t) {
+            constexpr int CUR = decltype(cur)::value;
+            const bool more = t + 1 < ntiles;
+            if (more) issue(t + 1, CUR ^ 1);
+            Scores sc = tile_pass(cur, IC<0>{}, Scores{}, 0u);
+            mask(sc, t);
+            select_all(sc, t);
+            if (more) { wait_vmcnt<0>(); __syncthreads(); }
+            return more;
+        };
+        for (int t = 0;;) {
+            if (!step(IC<0>{}, t++)) break;
+            if (!step(IC<1>{}, t++)) break;
+        }
     }
 
     // ---------------- the upper half-wave's list into the lower one's
-    double up[KMAX];
 #pragma unroll
-    for (int p = 0; p < KMAX; ++p) {
-        const uint32_t h = (uint32_t)__double2hiint(list[p]), l = (uint32_t)__double2loint(list[p]);
-        const auto rh = __builtin_amdgcn_permlane32_swap(h, h, false, false);
-        const auto rl = __builtin_amdgcn_permlane32_swap(l, l, false, false);
-        up[p] = __hiloint2double((int)rh[1], (int)rl[1]);
-    }
-    merge_entries<KMAX, KMAX>(list, up);
-    if (valid && half == 0) {
+    for (int g = 0; g < QG; ++g) {
+        double up[KMAX];
+#pragma unroll
+        for (int p = 0; p < KMAX; ++p) {
+            const uint32_t h = (uint32_t)__double2hiint(list[g][p]), l = (uint32_t)__double2loint(list[g][p]);
+            const auto rh = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+            const auto rl = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+            up[p] = __hiloint2double((int)rh[1], (int)rl[1]);
+        }
+        merge_entries<KMAX>(list[g], up);
+        if (i[g] >= N || half != 0) continue;
+        int32_t *out = out_row(g);
         if ((topk | a.stride) % 4 == 0) {      // rows of whole 16-byte words
 #pragma unroll
             for (int p = 0; p < KMAX; p += 4) {
-                const u32x4 w = {(uint32_t)entry_chunk(list[p]), (uint32_t)entry_chunk(list[p + 1]),
-                                 (uint32_t)entry_chunk(list[p + 2]), (uint32_t)entry_chunk(list[p + 3])};
+                const u32x4 w = {(uint32_t)entry_chunk(list[g][p]), (uint32_t)entry_chunk(list[g][p + 1]),
+                                 (uint32_t)entry_chunk(list[g][p + 2]), (uint32_t)entry_chunk(list[g][p + 3])};
                 if (p < topk) *reinterpret_cast<u32x4 *>(out + p) = w;
             }
         } else {
 #pragma unroll
             for (int p = 0; p < KMAX; ++p)
-                if (p < topk) out[p] = entry_chunk(list[p]);
+                if (p < topk) out[p] = entry_chunk(list[g][p]);
         }
     }
 }
 
-template <int D, typename T, int KMAX>
-__global__ __launch_bounds__(kRouteThreads, kRouteThreads == 256 ? 2 : 1) void route_kernel(RouteArgs a) {
+template <int D, typename T, int KMAX, int QG>
+__global__ __launch_bounds__(kRouteThreads, 2) void route_kernel(RouteArgs a) {
     __shared__ __attribute__((aligned(1024))) char smem[kRouteStages * 3 * 32 * D * 2];
-    route_body<D, T, KMAX>(a, smem);
+    route_body<D, T, KMAX, QG>(a, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -360,7 +452,7 @@ __global__ __launch_bounds__(kRouteThreads, 2) void route_fused_kernel(RouteArgs
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // once, not per look: each would drop the L1 of the pooling waves
     }
     __syncthreads();
-    route_body<D, T, KMAX>(a, smem);
+    route_body<D, T, KMAX, 1>(a, smem);
     __syncthreads();
     if (threadIdx.x == 0) {
         // (no data passes here: the end of the launch publishes the selections)
@@ -412,6 +504,16 @@ hipError_t fused_wait_flag(int *timed_out) {
     return e;
 }
 
+// Two groups of 32 queries a wave read a tile's fragments once for both and have registers left (227 to 256, two
+// workgroups a compute unit) for the scores of a tile and of the next, so that the selection of one runs between the
+// products of the other. 24 heads, bf16, d = 128, one group / two: 114k tokens, 260-key chunks, k = 8 600 / 593 us, 130-key
+// chunks 1,047 / 1,020, k = 3 554 / 535; 457k tokens, six heads, 3,488 chunks, k = 8 3,729 / 3,548. It needs a chip full
+// several times over with half the workgroups: 33k tokens, k = 5 (3,120 of them) 84 / 86, 32 heads (4,160) 107 / 107, 48 heads
+// (6,240) 359 / 351; 6,256 tokens (600) 15.7 / 18.3. Wider lists spill (k = 16: 4,270 / 15,809), d = 64 gains nothing (375 / 374
+// at k = 8), nor does fp32 there (116 / 165, spills). One group with the selection dealt takes as long as without, or longer
+// (457k tokens, k = 16: 4,380 / 4,547).
+constexpr long long kPairWgs = 4096;
+
 hipError_t launch_route(const moc_meta *m, int BH, int d, int dtype, const void *q, const void *kb_split, int Cpad,
                         int topk, int causal, int32_t *sel, int sel_stride, hipStream_t st) {
     RouteArgs a{};
@@ -422,20 +524,27 @@ hipError_t launch_route(const moc_meta *m, int BH, int d, int dtype, const void 
     a.sel = sel;
     a.N = m->N; a.C = m->C; a.Cpad = Cpad; a.topk = topk; a.causal = causal != 0;
     a.stride = sel_stride;
-    dim3 grid((m->N + kRouteThreads / 2 - 1) / (kRouteThreads / 2), BH), block(kRouteThreads);
     MOC_PROF("route_topk", st);
-#define MOC_ROUTE(DD, TT, KK) route_kernel<DD, TT, KK><<<grid, block, 0, st>>>(a)
-#define MOC_ROUTE_K(DD, TT)                         \
-    do {                                            \
-        if (topk <= 4) MOC_ROUTE(DD, TT, 4);        \
-        else if (topk <= 8) MOC_ROUTE(DD, TT, 8);   \
-        else if (topk <= 16) MOC_ROUTE(DD, TT, 16); \
-        else MOC_ROUTE(DD, TT, 32);                 \
-    } while (0)
-    if (dtype == MOC_BF16) { if (d == 128) MOC_ROUTE_K(128, bf16_t); else MOC_ROUTE_K(64, bf16_t); }
-    else { if (d == 128) MOC_ROUTE_K(128, float); else MOC_ROUTE_K(64, float); }
-#undef MOC_ROUTE_K
-#undef MOC_ROUTE
+    auto run = [&](auto dd, auto kk, auto tt) {
+        constexpr int DD = decltype(dd)::value, KK = decltype(kk)::value;
+        using T = decltype(tt);
+        if constexpr (KK <= 8 && sizeof(T) == 2 && DD == 128) {
+            const int wgs = (m->N + kRouteThreads - 1) / kRouteThreads;
+            if ((long long)wgs * BH >= kPairWgs) {
+                route_kernel<DD, T, KK, 2><<<dim3(wgs, BH), dim3(kRouteThreads), 0, st>>>(a);
+                return;
+            }
+        }
+        route_kernel<DD, T, KK, 1><<<dim3((m->N + kRouteThreads / 2 - 1) / (kRouteThreads / 2), BH), dim3(kRouteThreads), 0, st>>>(a);
+    };
+    auto by_k = [&](auto dd, auto tt) {
+        if (topk <= 4) run(dd, IC<4>{}, tt);
+        else if (topk <= 8) run(dd, IC<8>{}, tt);
+        else if (topk <= 16) run(dd, IC<16>{}, tt);
+        else run(dd, IC<32>{}, tt);
+    };
+    if (dtype == MOC_BF16) { if (d == 128) by_k(IC<128>{}, bf16_t{}); else by_k(IC<64>{}, bf16_t{}); }
+    else { if (d == 128) by_k(IC<128>{}, float{}); else by_k(IC<64>{}, float{}); }
     return hipGetLastError();
 }
 

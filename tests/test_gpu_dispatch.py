@@ -85,7 +85,7 @@ def test_merged_slots(topk, d):
     run_case(mi.stream_layout(1, 11, 300, 7, "chunk"), 1, 2, d, topk, torch.bfloat16, seed=91 + topk)
 
 
-# list builder: both sides of the one-workgroup limit (32768 entries a head, 1000 chunks), rows whose
+# list builder: 8,192 to 99,000 entries a head (one workgroup a head to the general way), rows whose
 # slots fill 64 lanes exactly or leave some idle, more chunks than a workgroup has lanes
 @pytest.mark.parametrize("N,chunk,topk", [(4096, 64, 8), (4097, 64, 8), (1000, 1, 5), (1002, 1, 3), (2340, 13, 14), (300, 7, 32),
                                           (12000, 9, 7), (9000, 60, 11)])
@@ -348,3 +348,24 @@ def test_fused_routing_of_other_keys_back_to_back(d, topk):
                                           (196608, 768, 1), (196609, 768, 1), (98304, 192, 1), (49152, 96, 1), (49153, 96, 1)])
 def test_list_builder_ways(N, chunk, topk):
     test_list_builder_ranges(N, chunk, topk)
+
+
+# two groups of 32 queries a wave, taken from 4,096 workgroups of 256 queries up (bf16, d = 128, k <= 8): the selections of
+# some heads are those of a call of these heads alone, which takes one group a wave (and which the oracle checks); the last
+# workgroup holds one query, one group, one query past a group, or all; one tile of chunks, two, and many with text in them
+@pytest.mark.parametrize("N,chunk,text,topk,causal", [(2049, 100, 0, 8, True), (2080, 33, 60, 3, True), (2209, 17, 90, 8, False),
+                                                      (2304, 70, 0, 5, False), (2303, 70, 300, 4, True), (2050, 7, 20, 8, True)])
+def test_route_pair_of_query_groups(N, chunk, text, topk, causal):
+    lay = mi.stream_layout(1, text, N - text, chunk, "chunk")
+    BH = 4096 // ((N + 255) // 256) + 1
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    q = torch.randn(1, BH, lay.N, 128, generator=g, device="cuda").to(torch.bfloat16)
+    k = torch.randn(1, BH, lay.N, 128, generator=g, device="cuda").to(torch.bfloat16)
+    k[0, :, text:text + 4 * chunk] = k[0, :, text + 4 * chunk:text + 8 * chunk]     # equal means: ties go to the lower chunk
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    pooled, sel = mb.route(meta, q, k, topk, causal)
+    for heads in (slice(0, 100), slice(BH - 100, BH)):
+        want_pooled, want = mb.route(meta, q[:, heads].contiguous(), k[:, heads].contiguous(), topk, causal)
+        assert torch.equal(pooled[:, heads], want_pooled) and torch.equal(sel[:, heads], want)
+    meta.close()
