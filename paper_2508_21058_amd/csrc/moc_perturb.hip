@@ -18,7 +18,9 @@
 // the slowest of 64 lanes. So the lists live in registers with fixed bounds (a
 // sorting network, unrolled inserts) instead of LDS lists walked at run time, and
 // rows travel through LDS only to be read and written in whole lines: 194 -> 118 us at
-// 114k tokens, 24 heads, 8 + 4 slots (45 of it from the table in place of a search).
+// 114k tokens, 24 heads, 8 + 4 slots (45 of it from the table in place of a search). The draws' blocks made once
+// for all picks and the words of a row found without divisions: 116 -> 104, 12 heads with 20 + 12 slots 216 -> 195. (The
+// chunk's tables and the first block ahead of the rows' loads: no difference, latency is not the bound.)
 #include "moc_internal.h"
 #include "moc_device.h"
 
@@ -35,29 +37,20 @@ struct PerturbArgs {
     uint64_t thr[MOC_MAX_TOPK];            // floor(CDF(j) * 2^32) of the Poisson law, j < max_in
 };
 
-struct Philox {
-    uint32_t c0, c1, k0, k1;               // counter words 0, 1 and the key
-    uint32_t w[4];
-    int t = 0;
-    __device__ void block(uint32_t blk) {
-        uint32_t x0 = c0, x1 = c1, x2 = blk, x3 = 0, a = k0, b = k1;
+// block `blk` of the row with counter words c0, c1
+struct Philox { uint32_t w[4]; };
+__device__ __forceinline__ Philox philox(uint32_t c0, uint32_t c1, uint32_t blk, uint32_t k0, uint32_t k1) {
+    uint32_t x0 = c0, x1 = c1, x2 = blk, x3 = 0;
 #pragma unroll
-        for (int r = 0; r < 10; ++r) {
-            const uint64_t m0 = (uint64_t)0xD2511F53u * x0, m1 = (uint64_t)0xCD9E8D57u * x2;
-            const uint32_t h0 = (uint32_t)(m0 >> 32), l0 = (uint32_t)m0;
-            const uint32_t h1 = (uint32_t)(m1 >> 32), l1 = (uint32_t)m1;
-            x0 = h1 ^ x1 ^ a; x1 = l1; x2 = h0 ^ x3 ^ b; x3 = l0;
-            a += 0x9E3779B9u; b += 0xBB67AE85u;
-        }
-        w[0] = x0; w[1] = x1; w[2] = x2; w[3] = x3;
+    for (int r = 0; r < 10; ++r) {
+        const uint64_t m0 = (uint64_t)0xD2511F53u * x0, m1 = (uint64_t)0xCD9E8D57u * x2;
+        const uint32_t h0 = (uint32_t)(m0 >> 32), l0 = (uint32_t)m0;
+        const uint32_t h1 = (uint32_t)(m1 >> 32), l1 = (uint32_t)m1;
+        x0 = h1 ^ x1 ^ k0; x1 = l1; x2 = h0 ^ x3 ^ k1; x3 = l0;
+        k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     }
-    __device__ uint32_t next() {
-        const int word = t & 3;
-        if (word == 0) block((uint32_t)(t >> 2));
-        ++t;
-        return word == 0 ? w[0] : word == 1 ? w[1] : word == 2 ? w[2] : w[3];
-    }
-};
+    return Philox{{x0, x1, x2, x3}};
+}
 
 constexpr int kPerturbThreads = 128;
 
@@ -82,26 +75,40 @@ __device__ __forceinline__ void perturb_row(const PerturbArgs &a, int i, int bh,
         nv += ent[r] >= 0 ? 1 : 0;
     }
 
-    Philox g;
-    g.c0 = (uint32_t)i; g.c1 = (uint32_t)bh; g.k0 = a.key0; g.k1 = a.key1;
-    const uint32_t r_drop = g.next(), r_in = g.next();
+    const Philox first = philox((uint32_t)i, (uint32_t)bh, 0, a.key0, a.key1);
+    const uint32_t r_drop = first.w[0], r_in = first.w[1];
 
     // ---- drop-off: floor(p k) of the routed chunks, p = u p_max, single precision
     const float u = (float)(r_drop >> 8) * 0x1p-24f;
     const float pk = (u * a.p_max) * (float)a.topk;
     const int nd = min((int)floorf(pk), nv);
-    uint32_t alive = nv >= 32 ? 0xffffffffu : ((1u << nv) - 1u);
-    for (int s = 0; s < nd; ++s) {
-        const int t = (int)__umulhi(g.next(), (uint32_t)(nv - s));
-        uint32_t b = alive;
-        for (int x = 0; x < t; ++x) b &= b - 1;            // skip t alive entries
-        alive &= ~(b & (0u - b));                          // clear the lowest remaining one
-    }
-
     // ---- drop-in: m ~ Poisson by inversion, truncated, capped by what is available
     int m = 0;
     for (int j = 0; j < a.max_in; ++j) m += (uint64_t)r_in >= a.thr[j] ? 1 : 0;
     m = min(m, n_elig - nv);
+
+    // The words of all picks are made before the first of them: made as the picks come to a new block, each block would
+    // be evaluated again for every count of removed entries among the 64 rows, six times a wave instead of two or three.
+    // They wait in the row itself, whose entries are in registers: those of the removals at its front, where survivors come
+    // after the last removal, those of the additions at its end, never in front of the place the next addition goes to.
+    // (In LDS of their own, twice the row's, they cost more waves than they gain: 114.9 -> 136.9 us.)
+    const int picks = nd + m, add_at = width - picks;
+    if (picks > 0) row[nd > 0 ? 0 : add_at] = (int32_t)first.w[2];
+    if (picks > 1) row[1 + (nd > 1 ? 0 : add_at)] = (int32_t)first.w[3];
+    for (int j = 2; j < picks; j += 4) {                   // pick j takes draw j + 2
+        const Philox b = philox((uint32_t)i, (uint32_t)bh, (uint32_t)((j + 2) >> 2), a.key0, a.key1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (j + e < picks) row[j + e + (j + e < nd ? 0 : add_at)] = (int32_t)b.w[e];
+    }
+
+    uint32_t alive = nv >= 32 ? 0xffffffffu : ((1u << nv) - 1u);
+    for (int s = 0; s < nd; ++s) {
+        const int t = (int)__umulhi((uint32_t)row[s], (uint32_t)(nv - s));
+        uint32_t b = alive;
+        for (int x = 0; x < t; ++x) b &= b - 1;            // skip t alive entries
+        alive &= ~(b & (0u - b));                          // clear the lowest remaining one
+    }
 
     // ranks (among the query's candidates) that are taken, ascending: the routed chunks first
     int ex[W];
@@ -127,7 +134,7 @@ __device__ __forceinline__ void perturb_row(const PerturbArgs &a, int i, int bh,
     for (int r = 0; r < K; ++r)
         if ((alive >> r) & 1u) row[out++] = ent[r];
     for (int s = 0; s < m; ++s) {
-        int t = (int)__umulhi(g.next(), (uint32_t)(n_elig - nv - s));
+        int t = (int)__umulhi((uint32_t)row[width - m + s], (uint32_t)(n_elig - nv - s));
 #pragma unroll
         for (int p = 0; p < W; ++p) t += ex[p] <= t ? 1 : 0;      // step over excluded ranks
 #pragma unroll
@@ -149,18 +156,21 @@ __global__ __launch_bounds__(kPerturbThreads) void perturb_kernel(PerturbArgs a)
     const int i0 = blockIdx.x * kPerturbThreads, nrow = min(kPerturbThreads, a.N - i0);
     const int bh = blockIdx.y;
     int32_t *rows = a.sel + ((size_t)bh * a.N + i0) * width;
-    if (a.topk > 0)                                            // (with topk == 0 the rows hold nothing yet)
-        for (int e = tid; e < nrow * width; e += kPerturbThreads) {
-            const int r = e / width;
-            lds[r * rs + (e - r * width)] = rows[e];
+    // word e of the rows is word c of row r; a step of a workgroup's width moves both on without a division
+    const int r0 = tid / width, c0 = tid - r0 * width, dr = kPerturbThreads / width, dc = kPerturbThreads - dr * width;
+    auto words = [&](auto f) {
+        for (int e = tid, r = r0, c = c0; e < nrow * width; e += kPerturbThreads) {
+            f(rows[e], lds[r * rs + c]);
+            r += dr;
+            c += dc;
+            if (c >= width) { c -= width; ++r; }
         }
+    };
+    if (a.topk > 0) words([](int32_t &g, int32_t &l) { l = g; });      // (with topk == 0 the rows hold nothing yet)
     __syncthreads();
     if (tid < nrow) perturb_row<K, W>(a, i0 + tid, bh, width, lds + tid * rs);
     __syncthreads();
-    for (int e = tid; e < nrow * width; e += kPerturbThreads) {
-        const int r = e / width;
-        rows[e] = lds[r * rs + (e - r * width)];
-    }
+    words([](int32_t &g, int32_t &l) { g = l; });
 }
 
 hipError_t launch_perturb(const moc_meta *m, int BH, int topk, int max_in, int causal, float p_max,
@@ -174,8 +184,9 @@ hipError_t launch_perturb(const moc_meta *m, int BH, int topk, int max_in, int c
     a.key0 = (uint32_t)seed; a.key1 = (uint32_t)(seed >> 32);
     for (int j = 0; j < max_in; ++j) a.thr[j] = thr[j];
     dim3 grid((m->N + kPerturbThreads - 1) / kPerturbThreads, BH);
-    MOC_PROF("route_perturb", st);
     const int width = topk + max_in;
+    if (width == 0) return hipSuccess;         // no columns
+    MOC_PROF("route_perturb", st);
     const size_t lds_bytes = (size_t)(width | 1) * kPerturbThreads * sizeof(int32_t);   // <= 16.5 KB
     if (topk <= 8 && width <= 12) perturb_kernel<8, 12><<<grid, kPerturbThreads, lds_bytes, st>>>(a);
     else if (topk <= 16 && width <= 20) perturb_kernel<16, 20><<<grid, kPerturbThreads, lds_bytes, st>>>(a);
