@@ -27,7 +27,7 @@ struct FwdArgs {
     const void *d_o;
     const float *lse, *delta;
     const float *gstats2;   // [BH, N*topk] pairs (lse * log2 e, delta) in inverse-list order
-    // sums of the caption tiles' partials, which the first workgroups of the forced-link dQ launch make
+    // sums of the caption tiles' partials, which the last workgroups of the forced-link dQ launch make
     const float *tpart_k, *tpart_v;
     const TextTile *text_tiles;
     void *dk, *dv;
