@@ -17,8 +17,8 @@
 // rate here; at the end the two half-waves merge their lists. One pass over the chunks;
 // any data (ties, few tiles) stays exact, and the time does not depend on the data.
 //
-// Bound by the sum of these vector instructions, about 240 per tile of 32 x 32 scores (k <= 8), and of its 24 matrix
-// instructions, which hardly run side by side (1,770 cycles a tile measured): neither half the LDS reads nor dealing
+// Bound by the sum of these vector instructions, about 190 per tile of 32 x 32 scores (k <= 8), and of its 24 matrix
+// instructions, which hardly run side by side (1,650 cycles a tile measured): neither half the LDS reads nor dealing
 // the ones between the others gains more than 5 % (see launch_route). Against queues of the scores above the k-th best so far,
 // inserted entry by entry (divergent, two LDS rows per entry, two waves per SIMD): 1,313
 // -> 684 us at 114k tokens, 24 heads, 440 chunks, k = 8; 7,074 -> 4,552 us at 457k tokens,
@@ -57,10 +57,13 @@ struct Infinities {
     float neg = -INFINITY, pos = INFINITY;
     __device__ __forceinline__ Infinities() { asm("" : "+s"(neg)); asm("" : "+v"(pos)); }
 };
-__device__ __forceinline__ double entry(float score, uint32_t chunk, const Infinities &inf) {
+// `chunk` comes as two words whose bits do not overlap, the second a constant: one three-way instruction joins them with
+// the sign. Written as operators that took three, 80 of 222 vector instructions a tile at k = 8, now 48: 114k tokens, 24 heads,
+// k = 8 565 -> 540 us; 457k tokens, six heads, k = 16 4,155 -> 4,006; d = 64 365 -> 342; 6,256 tokens, k = 8 28.8 -> 27.2.
+__device__ __forceinline__ double entry(float score, uint32_t chunk, uint32_t low, const Infinities &inf) {
     // median of score, -inf and +inf: the score, or for a NaN the least of the other two
     const uint32_t hi = __float_as_uint(__builtin_amdgcn_fmed3f(score, inf.neg, inf.pos));
-    const uint32_t lo = chunk ^ ~(uint32_t)((int32_t)hi >> 31);
+    const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)((int32_t)hi >> 31), chunk, low, 0x69);    // ~(sign ^ chunk ^ low)
     return __hiloint2double((int)hi, (int)lo);
 }
 // the chunk, or -1 if the entry is no candidate (masked scores are -inf)
@@ -132,7 +135,7 @@ template <int K, int AT, int END>
 __device__ __forceinline__ void net_run(double (&list)[K], double (&x)[16], const f32x16 &sc, uint32_t jb, const Infinities &inf) {
     if constexpr (AT < END) {
         constexpr NetStep st = NetOf<K>::net.s[AT];
-        if constexpr (st.op == NET_ENTRY) x[st.i] = entry(sc[st.i], jb ^ (uint32_t)((st.i >> 2) * 8 + (st.i & 3)), inf);
+        if constexpr (st.op == NET_ENTRY) x[st.i] = entry(sc[st.i], jb, (uint32_t)((st.i >> 2) * 8 + (st.i & 3)), inf);
         else if constexpr (st.op == NET_SORT) order2(x[st.i], x[st.j]);
         else if constexpr (st.op == NET_TAKE) list[st.i] = max64(list[st.i], x[st.j]);
         else order2(list[st.i], list[st.j]);
@@ -259,7 +262,7 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
 #pragma unroll
     for (int g = 0; g < QG; ++g)
 #pragma unroll
-        for (int p = 0; p < KMAX; ++p) list[g][p] = entry(-INFINITY, 0xffffffffu, inf);
+        for (int p = 0; p < KMAX; ++p) list[g][p] = entry(-INFINITY, 0xffffffffu, 0u, inf);
 
     // One pass over the products of a staged tile, in the order (query plane, key plane, features); row fragments are
     // read kAhead products ahead. With SELECT the selection over `sc`, the scores of the tile before (whose first chunk
@@ -506,10 +509,10 @@ hipError_t fused_wait_flag(int *timed_out) {
 
 // Two groups of 32 queries a wave read a tile's fragments once for both and have registers left (227 to 256, two
 // workgroups a compute unit) for the scores of a tile and of the next, so that the selection of one runs between the
-// products of the other. 24 heads, bf16, d = 128, one group / two: 114k tokens, 260-key chunks, k = 8 600 / 593 us, 130-key
-// chunks 1,047 / 1,020, k = 3 554 / 535; 457k tokens, six heads, 3,488 chunks, k = 8 3,729 / 3,548. It needs a chip full
-// several times over with half the workgroups: 33k tokens, k = 5 (3,120 of them) 84 / 86, 32 heads (4,160) 107 / 107, 48 heads
-// (6,240) 359 / 351; 6,256 tokens (600) 15.7 / 18.3. Wider lists spill (k = 16: 4,270 / 15,809), d = 64 gains nothing (375 / 374
+// products of the other. 24 heads, bf16, d = 128, one group / two: 114k tokens, 260-key chunks, k = 8 592 / 579 us, 130-key
+// chunks 1,018 / 972, k = 3 540 / 515; 457k tokens, six heads, 3,488 chunks, k = 8 3,694 / 3,455. It needs a chip full
+// several times over with half the workgroups: 33k tokens, k = 5 (3,120 of them) 82 / 84, 32 heads (4,160) 105 / 105, 48 heads
+// (6,240) 354 / 340; 6,256 tokens (600) 15.2 / 18.2. Wider lists spill (k = 16: 4,270 / 15,809), d = 64 gains nothing (375 / 374
 // at k = 8), nor does fp32 there (116 / 165, spills). One group with the selection dealt takes as long as without, or longer
 // (457k tokens, k = 16: 4,380 / 4,547).
 constexpr long long kPairWgs = 4096;
