@@ -102,16 +102,17 @@ namespace moc {
 
 bool prof_on() { return g_prof_on.load(std::memory_order_relaxed); }
 
-void prof_begin(const char *name, hipStream_t st) {
+hipEvent_t prof_begin(const char *name, hipStream_t st) {
     std::lock_guard<std::mutex> lk(g_prof_mu);
     ProfRec r{name, prof_event(), prof_event()};
     (void)hipEventRecord(r.e0, st);
     g_prof.push_back(r);
+    return r.e1;
 }
 
-void prof_end(hipStream_t st) {
+void prof_end(hipEvent_t end, hipStream_t st) {
     std::lock_guard<std::mutex> lk(g_prof_mu);
-    if (!g_prof.empty()) (void)hipEventRecord(g_prof.back().e1, st);
+    (void)hipEventRecord(end, st);
 }
 
 AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, bool with_bwd) {

@@ -86,15 +86,16 @@ struct moc_meta {
 namespace moc {
 
 // Optional per-kernel timing with HIP events on the launch stream (off by
-// default; switched on through moc_prof_enable). A Scope brackets one launch.
+// default; switched on through moc_prof_enable). A Scope brackets one launch and closes its own record, so scopes
+// may nest or overlap those of another thread.
 bool prof_on();
-void prof_begin(const char *name, hipStream_t st);
-void prof_end(hipStream_t st);
+hipEvent_t prof_begin(const char *name, hipStream_t st);      // -> the event that ends the record
+void prof_end(hipEvent_t end, hipStream_t st);
 struct ProfScope {
     hipStream_t st;
-    bool on;
-    ProfScope(const char *name, hipStream_t s) : st(s), on(prof_on()) { if (on) prof_begin(name, s); }
-    ~ProfScope() { if (on) prof_end(st); }
+    hipEvent_t end;
+    ProfScope(const char *name, hipStream_t s) : st(s), end(prof_on() ? prof_begin(name, s) : nullptr) {}
+    ~ProfScope() { if (end) prof_end(end, st); }
 };
 #define MOC_PROF(name, st) ::moc::ProfScope moc_prof_scope_(name, st)
 

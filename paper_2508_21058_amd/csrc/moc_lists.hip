@@ -411,6 +411,12 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     int32_t *list_off = reinterpret_cast<int32_t *>(ws + L.list_off);
     int32_t *tile_off = reinterpret_cast<int32_t *>(ws + L.tile_off);
     int32_t *qlist = reinterpret_cast<int32_t *>(ws + L.qlist);
+    // (the conversions' waves get the count's LDS too: beside large histograms too few would run at once)
+    if (cvt.count && C > kCvtChunks) {
+        const hipError_t e = launch_to_bf16(cvt, st);
+        if (e != hipSuccess) return e;
+        cvt.count = 0;
+    }
     MOC_PROF("build_lists", st);
     int bits = 0;
     while ((1 << bits) < C) ++bits;
@@ -429,12 +435,6 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     }
     if (two) cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_fine);
     const size_t shm = (size_t)C * 4;
-    // (the conversions' waves get the count's LDS too: beside large histograms too few would run at once)
-    if (cvt.count && C > kCvtChunks) {
-        const hipError_t e = launch_to_bf16(cvt, st);
-        if (e != hipSuccess) return e;
-        cvt.count = 0;
-    }
     const uint32_t extra = cvt_grid(cvt, 64);
     list_count_kernel<<<dim3(xcd_grid((long long)NB * BH) + extra), dim3(64), shm, st>>>(
         sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, rows, NB, BH, vmask, cnt_blk, cvt);

@@ -369,3 +369,23 @@ def test_route_pair_of_query_groups(N, chunk, text, topk, causal):
         want_pooled, want = mb.route(meta, q[:, heads].contiguous(), k[:, heads].contiguous(), topk, causal)
         assert torch.equal(pooled[:, heads], want_pooled) and torch.equal(sel[:, heads], want)
     meta.close()
+
+
+# fp32 storage of more than 1,024 chunks: the conversions go out in a launch of their own, a record of its own beside
+# that of the lists
+def test_fp32_storage_of_many_chunks():
+    lay = mi.stream_layout(1, 20, 1100, 1, "chunk")
+    assert lay.C == 1101
+    run_case(lay, 1, 2, 64, 8, torch.float32, seed=131)
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    q, k, v = (torch.randn(1, 2, lay.N, 64, device="cuda") for _ in range(3))
+    _, sel = mb.route(meta, q, k, 8)
+    mb.prof_enable(True)
+    for _ in range(3):
+        mb.attn_fwd(meta, q, k, v, sel)
+    torch.cuda.synchronize()
+    rec = mb.prof_read()
+    mb.prof_enable(False)
+    assert {"to_bf16", "build_lists"} <= set(rec)
+    assert all(n == 3 and 0 < ms < 1000 for n, ms in rec.values())
+    meta.close()
