@@ -129,7 +129,7 @@ AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, boo
     L.qlist = take((size_t)BH * N * std::max(topk, 1) * 4);
     L.plse = take((size_t)BH * N * slots * 4);
     L.po = take((size_t)BH * N * slots * d * 2);
-    L.cnt_fine = take(topk > 0 ? list_fine_bytes(m, BH) : 0);
+    L.cnt_fine = take(topk > 0 ? list_fine_bytes(m, BH, topk) : 0);
     if (dtype == MOC_F32) L.cvt = take((size_t)BH * N * d * 2 * (with_bwd ? 4 : 3));   // bf16 copies of q, k, v (and dO)
     if (with_bwd) {
         L.delta = take((size_t)BH * N * 4);

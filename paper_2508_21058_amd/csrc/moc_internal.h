@@ -170,8 +170,8 @@ inline uint32_t cvt_grid(CvtArgs &c, int threads) {
 // ... in a launch of their own
 hipError_t launch_to_bf16(CvtArgs c, hipStream_t st);
 
-// room for the histograms of small blocks, where the list builder uses them
-size_t list_fine_bytes(const moc_meta *m, int BH);
+// room for the histograms of the list builder's two launches, in calls that take them
+size_t list_fine_bytes(const moc_meta *m, int BH, int topk);
 // counts -> offsets -> inverse lists (per head and chunk: the queries that routed to it); cvt: conversions that ride
 // with its first launch
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws,

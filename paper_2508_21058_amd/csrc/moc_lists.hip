@@ -269,13 +269,9 @@ __global__ __launch_bounds__(64) void list_fill_kernel(const int32_t *__restrict
 // wave each) sums the head's table itself, thread (g, j) every G-th row of chunk j, instead of three launches that pass
 // the sums on. Counting and this against the launches before (one workgroup a head at 6,256 tokens, else the five of the
 // general way): 29 -> 15 us at 6,256 tokens, 24 heads, k = 3; 57 -> 26 at 15.5k tokens, sixteen ragged heads, k = 6; 47 -> 19
-// at 12.9k, six heads, k = 5; 66 -> 49 at 33k, 24 heads, k = 5; 155 -> 144 at 182k, 24 heads, k = 5. Blocks shrink until
-// the count has some 4,096 waves: with 2,048 the 33k tokens take 52, with 1,024 the 6,256 tokens 18 and the 15.5k 34.
+// at 12.9k, six heads, k = 5; 66 -> 49 at 33k, 24 heads, k = 5; 155 -> 144 at 182k, 24 heads, k = 5.
 constexpr int kFillWaves = 16;
-constexpr int kCvtChunks = 1024;          // 4 KB of LDS a wave: 32 waves on a compute unit
-constexpr int kFillSpread = 4096;         // waves of the count kernel up to which smaller blocks gain
 constexpr int kFillChunks = 880;          // its cursors and sums: 64 KB of LDS
-constexpr int kFillTable = 49152;         // words of a head's table up to which it is used (192 KB read by each workgroup)
 __global__ __launch_bounds__(kFillWaves * 64) void list_scan_fill_kernel(const int32_t *__restrict__ sel, int N, int topk, int C,
                                                                          int bits, const uint32_t *__restrict__ vmask,
                                                                          int rows, int NB, int BH,
@@ -343,9 +339,8 @@ __global__ __launch_bounds__(kFillWaves * 64) void list_scan_fill_kernel(const i
 
 // The whole list builder for a head in one workgroup: sixteen waves take consecutive sixteenths of the
 // queries, count into histograms of their own, scan them and fill. The smallest calls are bound by their
-// launches, not by work: 38 us in five, 7 in one at 1,088 tokens; at 8,192 entries a head two launches take as long.
+// launches, not by work: 38 us in five, 7 in one at 1,088 tokens.
 constexpr int kHeadWaves = 16, kHeadChunks = 1000;      // 62.5 KB of histograms
-constexpr int kHeadEntries = 8192;        // N * topk up to which it is used
 __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_t *__restrict__ sel, int N, int topk,
                                                                     int C, int bits,
                                                                     const int32_t *__restrict__ chunk_of,
@@ -396,12 +391,37 @@ __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_
     fill_rows(sel, i0, nrow, topk, bits, lane, vmask, hist + wave * C, qlist + (size_t)bh * N * topk);
 }
 
-// (a bound that does not ask how many queries a block gets: never more than kFillTable words a head)
-size_t list_fine_bytes(const moc_meta *m, int BH) {
-    const size_t words = (size_t)((m->N + kRowsPerBlkMin - 1) / kRowsPerBlkMin) * m->C;
-    return (size_t)BH * std::min(words, (size_t)kFillTable) * 4;
+// How a call's lists are built: a workgroup a head, count and scan + fill over blocks of `rows` queries, or the five
+// launches of the general way.
+enum ListWay { LIST_HEAD, LIST_TWO, LIST_GENERAL };
+struct ListPlan { ListWay way; int rows, NB; };
+constexpr int kFillTable = 49152;         // words of a head's table up to which two launches are used (192 KB read by each workgroup)
+constexpr int kFillSpread = 4096;         // waves of the count kernel up to which smaller blocks gain
+static ListPlan list_plan(int N, int C, int topk, int BH) {
+    const long long entries = (long long)N * topk;
+    ListPlan p{LIST_GENERAL, kRowsPerBlk, (N + kRowsPerBlk - 1) / kRowsPerBlk};
+    const bool two = C <= kFillChunks && (long long)p.NB * C <= kFillTable;
+    if (two) {
+        // Blocks shrink until the count has some 4,096 waves: with 2,048 of them 33k tokens (24 heads, k = 5) take 52 us for 49,
+        // with 1,024 6,256 tokens (24 heads, k = 3) 18 for 15 and 15.5k tokens (sixteen heads, k = 6) 34 for 26.
+        int rows = p.rows, NB = p.NB;
+        while (rows > kRowsPerBlkMin && (long long)NB * BH < kFillSpread && (long long)((N + rows / 2 - 1) / (rows / 2)) * C <= kFillTable) {
+            rows /= 2;
+            NB = (N + rows - 1) / rows;
+        }
+        p = ListPlan{LIST_TWO, rows, NB};
+    }
+    // one launch for two or more: 16.5 us for 17.7 at 8,192 entries, 20 for 14 at 8,400
+    if (entries <= 8192 && C <= kHeadChunks) p = ListPlan{LIST_HEAD, 0, 0};
+    return p;
 }
 
+size_t list_fine_bytes(const moc_meta *m, int BH, int topk) {
+    const ListPlan p = list_plan(m->N, m->C, topk, BH);
+    return p.way == LIST_TWO ? (size_t)BH * p.NB * m->C * 4 : 0;
+}
+
+constexpr int kCvtChunks = 1024;          // 4 KB of LDS a wave: 32 waves on a compute unit
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws, const AttnWs &L,
                               CvtArgs cvt, hipStream_t st) {
     const int C = m->C, N = m->N;
@@ -420,25 +440,20 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     MOC_PROF("build_lists", st);
     int bits = 0;
     while ((1 << bits) < C) ++bits;
-    if ((long long)N * topk <= kHeadEntries && C <= kHeadChunks) {
+    const ListPlan plan = list_plan(N, C, topk, BH);
+    if (plan.way == LIST_HEAD) {
         const uint32_t extra = cvt_grid(cvt, kHeadWaves * 64);
         list_head_kernel<<<dim3(BH + extra), dim3(kHeadWaves * 64), (size_t)kHeadWaves * C * 4, st>>>(
             sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, vmask, list_off, tile_off, qlist, BH, cvt);
         return hipGetLastError();
     }
-    // blocks of fewer queries where that gives the chip more waves and the table stays small
-    int rows = kRowsPerBlk, NB = (N + rows - 1) / rows;
-    const bool two = C <= kFillChunks && (long long)NB * C <= kFillTable;
-    while (two && rows > kRowsPerBlkMin && (long long)NB * BH < kFillSpread && (long long)((N + rows / 2 - 1) / (rows / 2)) * C <= kFillTable) {
-        rows /= 2;
-        NB = (N + rows - 1) / rows;
-    }
-    if (two) cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_fine);
+    const int rows = plan.rows, NB = plan.NB;
+    if (plan.way == LIST_TWO) cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_fine);
     const size_t shm = (size_t)C * 4;
     const uint32_t extra = cvt_grid(cvt, 64);
     list_count_kernel<<<dim3(xcd_grid((long long)NB * BH) + extra), dim3(64), shm, st>>>(
         sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, rows, NB, BH, vmask, cnt_blk, cvt);
-    if (two) {
+    if (plan.way == LIST_TWO) {
         const long long wgs = (long long)((NB + kFillWaves - 1) / kFillWaves) * BH;
         list_scan_fill_kernel<<<dim3(xcd_grid(wgs)), dim3(kFillWaves * 64), kFillWaves * shm, st>>>(
             sel, N, topk, C, bits, vmask, rows, NB, BH, cnt_blk, list_off, tile_off, qlist);

@@ -85,22 +85,28 @@ def test_merged_slots(topk, d):
     run_case(mi.stream_layout(1, 11, 300, 7, "chunk"), 1, 2, d, topk, torch.bfloat16, seed=91 + topk)
 
 
-# list builder: 8,192 to 99,000 entries a head (one workgroup a head to the general way), rows whose
+# list builder: 3,006 to 99,000 entries a head (one workgroup a head to the general way), rows whose
 # slots fill 64 lanes exactly or leave some idle, more chunks than a workgroup has lanes
 @pytest.mark.parametrize("N,chunk,topk", [(4096, 64, 8), (4097, 64, 8), (1000, 1, 5), (1002, 1, 3), (2340, 13, 14), (300, 7, 32),
                                           (12000, 9, 7), (9000, 60, 11)])
 def test_list_builder_ranges(N, chunk, topk):
+    check_lists(N, chunk, topk)
+
+
+def check_lists(N, chunk, topk, H=3):
+    """The lists of random selections against numpy's; -> how they were built: "head" (a workgroup a head), the queries a
+    block of the two launches had, or "general". The tables tell: each way writes others."""
     offs = np.unique(np.r_[np.arange(0, N, chunk), N]).astype(np.int32)
     C = len(offs) - 1
     lay = mi.Layout("lists", offs, np.zeros(C, np.int32), np.arange(C, dtype=np.int32),
                     np.asarray([[0, offs[1]]], dtype=np.int32))
     meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
     g = torch.Generator(device="cuda").manual_seed(N)
-    H = 3
     q, k, v = (torch.randn(1, H, N, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
     # rows as a caller may write them: repeated, forced and out-of-range entries among them
     sel = torch.randint(-1, C + 1, (1, H, N, topk), generator=g, device="cuda", dtype=torch.int32)
     ws = mb.attn_workspace(meta, 1, H, 64, topk, torch.bfloat16, False)
+    ws.fill_(0x7f)
     mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
     torch.cuda.synchronize()
     # the workspace begins with chunk counts, list offsets and tile offsets; the lists come after tables
@@ -125,6 +131,19 @@ def test_list_builder_ranges(N, chunk, topk):
         assert np.array_equal(parts["tile"][h * (C + 1):(h + 1) * (C + 1)], np.r_[0, np.cumsum(-(-cnt // 128))])
         assert np.array_equal(parts["list"][h * N * topk:h * N * topk + len(qi)], ((qi << 5) | r)[order])
     meta.close()
+    # log-sum-exps and outputs of the slots follow, then the table of the two launches, where a call has one
+    for n in (4 * H * N * (topk + 1), 2 * H * N * (topk + 1) * 64):
+        at += -(-n // 256) * 256
+    untouched = (parts["blk"] == 0x7f7f7f7f).all()
+    if at == ws.numel() * ws.element_size():
+        return "head" if untouched else "general"
+    assert untouched
+    table = ws[at:].view(torch.int32).cpu().numpy()
+    rows = [r for r in (64, 128, 256) if -(-4 * H * -(-N // r) * C // 256) * 256 == 4 * len(table)]
+    assert len(rows) == 1
+    used = table[:H * -(-N // rows[0]) * C].reshape(H, -1, C)
+    assert np.array_equal(used.sum(1), parts["off"].reshape(H, C + 1)[:, 1:] - parts["off"].reshape(H, C + 1)[:, :-1])
+    return rows[0]
 
 
 # selection at the list widths the kernel is built for (4, 8, 16, 32) and one past each, over eleven tiles
@@ -341,13 +360,13 @@ def test_fused_routing_of_other_keys_back_to_back(d, topk):
     meta.close()
 
 
-# the list builder's ways at their edges: one workgroup a head up to 8192 entries; scan and fill in one launch up to
-# 880 chunks and a table of 49152 words (blocks of 64, 128 and 256 queries; a last workgroup of one block), past either
-# the general way
-@pytest.mark.parametrize("N,chunk,topk", [(2048, 20, 4), (2049, 20, 4), (880, 1, 10), (881, 1, 10), (65 * 64 + 1, 70, 2), (16 * 64, 30, 9),
-                                          (196608, 768, 1), (196609, 768, 1), (98304, 192, 1), (49152, 96, 1), (49153, 96, 1)])
-def test_list_builder_ways(N, chunk, topk):
-    test_list_builder_ranges(N, chunk, topk)
+# the list builder's ways on both sides of each edge: 8,192 entries; 880 chunks and a table of 49,152 words, filled to its
+# last word, with blocks of 64, 128 and 256 queries (a last workgroup of one block among them)
+@pytest.mark.parametrize("N,chunk,topk,H,way", [
+    (2048, 20, 4, 3, "head"), (2049, 20, 4, 3, 64), (880, 1, 10, 3, 64), (881, 1, 10, 3, "general"), (65 * 64 + 1, 70, 2, 3, 64),
+    (32768, 256, 1, 3, 128), (49152, 192, 1, 3, 256), (49153, 192, 1, 3, "general"), (32768, 256, 17, 3, 128), (8192, 10, 16, 24, 256)])
+def test_list_builder_ways(N, chunk, topk, H, way):
+    assert check_lists(N, chunk, topk, H) == way
 
 
 # two groups of 32 queries a wave, taken from 4,096 workgroups of 256 queries up (bf16, d = 128, k <= 8): the selections of
