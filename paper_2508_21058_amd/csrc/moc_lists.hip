@@ -304,8 +304,9 @@ __global__ __launch_bounds__(kFillWaves * 64) void list_scan_fill_kernel(const i
     }
     __syncthreads();
     before = tot = 0;
+    const int used = min(G, NB);         // a thread past the last row has summed none
     if (tid < C)
-        for (int u = 0; u < G; ++u) { before += part[0][u * C + tid]; tot += part[1][u * C + tid]; }
+        for (int u = 0; u < used; ++u) { before += part[0][u * C + tid]; tot += part[1][u * C + tid]; }
     // ---- thread j owns chunk j: an exclusive scan over the chunks
     int a = tot, t = (tot + kBM - 1) / kBM;
     const int tiles = t;
@@ -400,7 +401,7 @@ constexpr int kFillSpread = 4096;         // waves of the count kernel up to whi
 static ListPlan list_plan(int N, int C, int topk, int BH) {
     const long long entries = (long long)N * topk;
     ListPlan p{LIST_GENERAL, kRowsPerBlk, (N + kRowsPerBlk - 1) / kRowsPerBlk};
-    const bool two = C <= kFillChunks && (long long)p.NB * C <= kFillTable;
+    bool two = C <= kFillChunks && (long long)p.NB * C <= kFillTable;
     if (two) {
         // Blocks shrink until the count has some 4,096 waves: with 2,048 of them 33k tokens (24 heads, k = 5) take 52 us for 49,
         // with 1,024 6,256 tokens (24 heads, k = 3) 18 for 15 and 15.5k tokens (sixteen heads, k = 6) 34 for 26.
@@ -409,10 +410,23 @@ static ListPlan list_plan(int N, int C, int topk, int BH) {
             rows /= 2;
             NB = (N + rows - 1) / rows;
         }
-        p = ListPlan{LIST_TWO, rows, NB};
+        // Sixteen waves a workgroup fill slower than waves spread over the chip, which shows where each has many steps: with blocks of
+        // 256 queries, k = 16 112 us for 102 (one head, 16k tokens) and 121 for 110 (six, 50k), but 135 for 146 with 24 heads; k = 32
+        // 231 for 208 there; k = 8 63 for 67 (six heads, 8k). With 128 queries k = 32 105 for 164 (one head, 12k).
+        two = rows < kRowsPerBlk || topk <= 8 || (topk <= 16 && BH >= 24);
+        if (two) p = ListPlan{LIST_TWO, rows, NB};
     }
-    // one launch for two or more: 16.5 us for 17.7 at 8,192 entries, 20 for 14 at 8,400
-    if (entries <= 8192 && C <= kHeadChunks) p = ListPlan{LIST_HEAD, 0, 0};
+    if (C > kHeadChunks || entries > 32768) return p;
+    const bool head =
+        // one launch for two, or as long: 24 heads of 4,096 entries 11 us for 14, of 8,192 at k = 8 17 for 19, at k = 1 15 for 15, of
+        // 8,400 20 for 14
+        entries <= 8192
+        // one launch for five: a sixteenth of the head is up to as many steps as the general way's blocks, or the heads are many
+        // (960 chunks: 4,096 tokens, k = 3 28 us for 40; 16k, k = 1 27 for 30; 32k, k = 1 51 for 34 with two heads, 61 for 81 with 64)
+        || (!two && (BH >= 48 || (long long)(N - 4096) * topk <= 12288))
+        // 200 heads fill the chip with one workgroup each (32k tokens, two chunks, k = 1 38 us for 49; 128 heads take as long)
+        || (BH >= 192 && C <= 20);
+    if (head) p = ListPlan{LIST_HEAD, 0, 0};
     return p;
 }
 

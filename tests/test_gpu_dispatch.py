@@ -360,11 +360,16 @@ def test_fused_routing_of_other_keys_back_to_back(d, topk):
     meta.close()
 
 
-# the list builder's ways on both sides of each edge: 8,192 entries; 880 chunks and a table of 49,152 words, filled to its
-# last word, with blocks of 64, 128 and 256 queries (a last workgroup of one block among them)
+# the list builder's ways on both sides of each edge: 8,192 entries; two chunks; 880 chunks and a table of 49,152 words,
+# filled to its last word, with blocks of 64, 128 and 256 queries (a last workgroup of one block among them); k = 8 with
+# blocks of 256 queries, 16 with 24 heads; one workgroup a head where two launches are out of reach; many heads
 @pytest.mark.parametrize("N,chunk,topk,H,way", [
-    (2048, 20, 4, 3, "head"), (2049, 20, 4, 3, 64), (880, 1, 10, 3, 64), (881, 1, 10, 3, "general"), (65 * 64 + 1, 70, 2, 3, 64),
-    (32768, 256, 1, 3, 128), (49152, 192, 1, 3, 256), (49153, 192, 1, 3, "general"), (32768, 256, 17, 3, 128), (8192, 10, 16, 24, 256)])
+    (2048, 20, 4, 3, "head"), (2049, 20, 4, 3, 64), (4100, 2050, 3, 3, 64),
+    (880, 1, 10, 3, 64), (881, 1, 10, 3, "head"), (1000, 1, 10, 3, "head"), (1001, 1, 10, 3, "general"), (65 * 64 + 1, 70, 2, 3, 64),
+    (32768, 256, 1, 3, 128), (49152, 192, 1, 3, 256), (49153, 192, 1, 3, "general"), (32768, 256, 17, 3, 128),
+    (8192, 10, 8, 3, 256), (8192, 10, 9, 3, "general"), (8192, 10, 16, 24, 256), (8192, 10, 17, 24, "general"),
+    (16384, 17, 1, 3, "head"), (16385, 17, 1, 3, "general"), (16385, 17, 1, 48, "head"), (16500, 17, 2, 48, "general"),
+    (1300, 163, 8, 191, 64), (1300, 163, 8, 192, "head"), (1300, 60, 8, 192, 64)])
 def test_list_builder_ways(N, chunk, topk, H, way):
     assert check_lists(N, chunk, topk, H) == way
 
