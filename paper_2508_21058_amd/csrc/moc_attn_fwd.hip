@@ -493,8 +493,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_chunk_kernel(FwdArgs a) {
     }
 }
 
-// fp32 -> bf16 copies where no launch takes them along (a forward without routed links builds no lists; beside the
-// histograms of more than 1,024 chunks they would lose waves)
+// fp32 -> bf16 copies where no launch takes them along (a forward without routed links builds no lists; for lists they
+// would delay see launch_build_lists)
 __global__ __launch_bounds__(256) void to_bf16_kernel(CvtArgs c) { convert_workgroup<256>(c, blockIdx.x); }
 
 hipError_t launch_to_bf16(CvtArgs c, hipStream_t st) {

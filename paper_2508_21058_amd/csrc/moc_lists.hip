@@ -435,7 +435,14 @@ size_t list_fine_bytes(const moc_meta *m, int BH, int topk) {
     return p.way == LIST_TWO ? (size_t)BH * p.NB * m->C * 4 : 0;
 }
 
-constexpr int kCvtChunks = 1024;          // 4 KB of LDS a wave: 32 waves on a compute unit
+// Conversions ride with the first launch, but not
+//   beside the histograms of more chunks than this: their waves get the count's LDS too, 4 KB let 32 run on a compute unit;
+constexpr int kCvtChunks = 1024;
+//   where the selections are large: the fill reads them a second time, and the conversions, which stream behind the count,
+//   have by then pushed them out of the caches. Lists and conversions of 24 heads, d = 64, riding / alone: 101 MB of
+//   selections (66k tokens, k = 16) 841 / 733 us (the fill 480 / 295), 51 MB (33k) 348 / 321, 25 MB (16k) 137 / 133; eight heads
+//   34 MB (66k tokens) 267 / 281; with d = 128 506 / 493, 218 / 220 and 384 / 395 for the last three.
+constexpr long long kCvtEntries = 10000000;
 hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t *sel, char *ws, const AttnWs &L,
                               CvtArgs cvt, hipStream_t st) {
     const int C = m->C, N = m->N;
@@ -445,8 +452,7 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     int32_t *list_off = reinterpret_cast<int32_t *>(ws + L.list_off);
     int32_t *tile_off = reinterpret_cast<int32_t *>(ws + L.tile_off);
     int32_t *qlist = reinterpret_cast<int32_t *>(ws + L.qlist);
-    // (the conversions' waves get the count's LDS too: beside large histograms too few would run at once)
-    if (cvt.count && C > kCvtChunks) {
+    if (cvt.count && (C > kCvtChunks || (long long)BH * N * topk > kCvtEntries)) {
         const hipError_t e = launch_to_bf16(cvt, st);
         if (e != hipSuccess) return e;
         cvt.count = 0;

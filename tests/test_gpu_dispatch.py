@@ -413,3 +413,28 @@ def test_fp32_storage_of_many_chunks():
     assert {"to_bf16", "build_lists"} <= set(rec)
     assert all(n == 3 and 0 < ms < 1000 for n, ms in rec.values())
     meta.close()
+
+
+# more than 10 million selections: the same, in the forward of fp32 storage; the first heads are those of a call of their own,
+# whose conversions ride with the lists
+def test_fp32_storage_of_many_selections():
+    lay = mi.stream_layout(1, 30, 16000, 200, "chunk")
+    H, topk, few = 40, 16, 2
+    assert H * lay.N * topk > 10000000
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    g = torch.Generator(device="cuda").manual_seed(17)
+    q, k, v = (torch.randn(1, H, lay.N, 64, generator=g, device="cuda") for _ in range(3))
+    _, sel = mb.route(meta, q, k, topk)
+    mb.prof_enable(True)
+    o, lse = mb.attn_fwd(meta, q, k, v, sel)
+    torch.cuda.synchronize()
+    large = set(mb.prof_read())
+    mb.prof_enable(True)
+    o2, lse2 = mb.attn_fwd(meta, *(x[:, :few].contiguous() for x in (q, k, v, sel)))
+    torch.cuda.synchronize()
+    small = set(mb.prof_read())
+    mb.prof_enable(False)
+    assert "to_bf16" in large and "to_bf16" not in small
+    check_close("o", o[:, :few].cpu().numpy(), o2.cpu().numpy())
+    check_close("lse", lse[:, :few].cpu().numpy(), lse2.cpu().numpy())
+    meta.close()
