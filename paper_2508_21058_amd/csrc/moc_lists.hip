@@ -148,7 +148,8 @@ __device__ __forceinline__ void fill_rows(const int32_t *__restrict__ sel, int i
     }
 }
 
-// One wave per block of `rows` queries.
+// One wave per block of `rows` queries. CVT: conversions ride (an instance of its own: the code of the others does not grow).
+template <bool CVT>
 __global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restrict__ sel, int N, int topk, int C, int bits,
                                                         const int32_t *__restrict__ chunk_of,
                                                         const int32_t *__restrict__ win,
@@ -157,7 +158,8 @@ __global__ __launch_bounds__(64) void list_count_kernel(const int32_t *__restric
                                                         CvtArgs cvt) {
     extern __shared__ int32_t hist[];    // [C]
     const int mine = xcd_grid((long long)NB * BH);
-    if ((int)blockIdx.x >= mine) { convert_workgroup<64>(cvt, blockIdx.x - mine); return; }
+    if constexpr (CVT)
+        if ((int)blockIdx.x >= mine) { convert_workgroup<64>(cvt, blockIdx.x - mine); return; }
     int logical;
     if (!xcd_remap((long long)NB * BH, logical)) return;
     const int bh = logical / NB, blk = logical - bh * NB, lane = threadIdx.x;
@@ -342,6 +344,7 @@ __global__ __launch_bounds__(kFillWaves * 64) void list_scan_fill_kernel(const i
 // queries, count into histograms of their own, scan them and fill. The smallest calls are bound by their
 // launches, not by work: 38 us in five, 7 in one at 1,088 tokens.
 constexpr int kHeadWaves = 16, kHeadChunks = 1000;      // 62.5 KB of histograms
+template <bool CVT>
 __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_t *__restrict__ sel, int N, int topk,
                                                                     int C, int bits,
                                                                     const int32_t *__restrict__ chunk_of,
@@ -353,7 +356,8 @@ __global__ __launch_bounds__(kHeadWaves * 64) void list_head_kernel(const int32_
                                                                     int32_t *__restrict__ qlist, int BH, CvtArgs cvt) {
     extern __shared__ int32_t hist[];    // [kHeadWaves][C]
     __shared__ int32_t wsum[2][kHeadWaves];
-    if ((int)blockIdx.x >= BH) { convert_workgroup<kHeadWaves * 64>(cvt, blockIdx.x - BH); return; }
+    if constexpr (CVT)
+        if ((int)blockIdx.x >= BH) { convert_workgroup<kHeadWaves * 64>(cvt, blockIdx.x - BH); return; }
     const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int per = (N + kHeadWaves - 1) / kHeadWaves;
     const int i0 = min(N, wave * per), nrow = min(per, N - i0);
@@ -463,7 +467,8 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     const ListPlan plan = list_plan(N, C, topk, BH);
     if (plan.way == LIST_HEAD) {
         const uint32_t extra = cvt_grid(cvt, kHeadWaves * 64);
-        list_head_kernel<<<dim3(BH + extra), dim3(kHeadWaves * 64), (size_t)kHeadWaves * C * 4, st>>>(
+        const auto kernel = cvt.count ? list_head_kernel<true> : list_head_kernel<false>;
+        kernel<<<dim3(BH + extra), dim3(kHeadWaves * 64), (size_t)kHeadWaves * C * 4, st>>>(
             sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, vmask, list_off, tile_off, qlist, BH, cvt);
         return hipGetLastError();
     }
@@ -471,7 +476,8 @@ hipError_t launch_build_lists(const moc_meta *m, int BH, int topk, const int32_t
     if (plan.way == LIST_TWO) cnt_blk = reinterpret_cast<int32_t *>(ws + L.cnt_fine);
     const size_t shm = (size_t)C * 4;
     const uint32_t extra = cvt_grid(cvt, 64);
-    list_count_kernel<<<dim3(xcd_grid((long long)NB * BH) + extra), dim3(64), shm, st>>>(
+    const auto count = cvt.count ? list_count_kernel<true> : list_count_kernel<false>;
+    count<<<dim3(xcd_grid((long long)NB * BH) + extra), dim3(64), shm, st>>>(
         sel, N, topk, C, bits, m->d_chunk_of, m->d_win, m->d_rwin, rows, NB, BH, vmask, cnt_blk, cvt);
     if (plan.way == LIST_TWO) {
         const long long wgs = (long long)((NB + kFillWaves - 1) / kFillWaves) * BH;
