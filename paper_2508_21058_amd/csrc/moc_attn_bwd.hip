@@ -229,11 +229,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(FwdArgs a) {
 
     if (MODE == MODE_ANCHOR && (int)blockIdx.x >= a.reduce_at) { text_reduce<D, OT>(a); return; }
     int logical;
-    const long long total = (long long)a.items_per_head * a.BH;
-    if (!(MODE == MODE_ANCHOR ? xcd_remap_back(total, logical) : xcd_remap(total, logical))) return;
-    const int bh = logical / a.items_per_head;
+    if (!xcd_remap((long long)a.items_per_head * a.BH, logical)) return;
+    int bh = logical / a.items_per_head;
+    const int item = logical - bh * a.items_per_head;
+    if (MODE == MODE_ANCHOR) bh = head_from_last(bh, a.slice_heads);
     ItemDesc it;
-    if (!decode_item<MODE>(a, bh, logical - bh * a.items_per_head, it)) return;
+    if (!decode_item<MODE>(a, bh, item, it)) return;
 
     const int r = wave * 32 + l32;
     const bool row_valid = r < it.q_count;
@@ -1189,6 +1190,7 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     }
     MOC_PROF("attn_bwd_dq_forced", st);
     a.items_per_head = m->n_atiles;
+    a.slice_heads = heads_per_slice(BH);
     a.o_out = dq;        // the forced-link items run after the routed ones and add the routed partials themselves
     a.reduce_at = xcd_grid((long long)a.items_per_head * BH);
     attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(a.reduce_at + m->n_text_tiles * BH * reduce_parts<D>()), dim3(256), 0, st>>>(a);

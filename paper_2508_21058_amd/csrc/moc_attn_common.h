@@ -33,6 +33,7 @@ struct FwdArgs {
     void *dk, *dv;
     int n_text_tiles, n_partials, join, reduce_at;
     // forced-link forward items with the merge fused into their epilogue
+    int slice_heads;        // see heads_per_slice
     const uint32_t *vmask;  // [BH, N] bit r: routed slot r of the query counts (set by the list builder)
     void *o_out;            // [BH, N, D] final output, in the caller's storage type
     float *lse_out;         // [BH, N] final log-sum-exp
@@ -78,15 +79,16 @@ __device__ __forceinline__ bool xcd_remap(long long total, int &logical) {
     logical = (L % kXcds) * per + L / kXcds;
     return logical < total;
 }
-// The same slices from their ends, for the forced-link items: the routed launch before them left the partials of an XCD's
-// last heads in its L2, and those are then read first. Forced forward / dQ of six fp32 heads of 12.9k tokens 110 -> 103 /
-// 131 -> 127 us, sixteen heads of 64 features and 15.5k tokens 128 -> 125 / 158 -> 153, 24 heads of 6,256 tokens 98 -> 97 /
-// 117 -> 112; no difference from 33k tokens on.
-__device__ __forceinline__ bool xcd_remap_back(long long total, int &logical) {
-    if (!xcd_remap(total, logical)) return false;
-    const int per = (int)((total + kXcds - 1) / kXcds), slice = logical / per * per;
-    logical = slice + (int)min((long long)per, total - slice) - 1 - (logical - slice);
-    return true;
+// The forced-link items take the heads of a slice from the last one: the routed launch before them left the partials of an
+// XCD's last heads in its L2, and those are then read first. Only where slices are whole heads, and each head's items stay
+// in their order, so that the items come in the sequence of sizes they had: which of them end a launch of few items decides
+// more than the L2 gives (all items walked backwards: forced forward of sixteen heads of 6,543 tokens in ragged windows
+// 74 -> 82 us, of 24 heads of 7,399 tokens 154 -> 136). Forced forward / dQ of 24 heads of 6,256 tokens, k = 3, 84.6 -> 83.3 /
+// 100.5 -> 94.4 us, of 32 fp32 heads of 3,577 tokens, k = 8, 104.6 -> 94.0 / 103.9 -> 98.1, forward of 48 heads of 64
+// features, 11.6k tokens, k = 11, 286 -> 272; 24 heads of 33k tokens 953 -> 951 / 1,169 -> 1,180, no difference.
+inline int heads_per_slice(int BH) { return BH % kXcds == 0 ? BH / kXcds : 0; }      // 0: slices are not whole heads
+__device__ __forceinline__ int head_from_last(int bh, int per_slice) {
+    return per_slice ? (int)(blockIdx.x % kXcds) * 2 * per_slice + per_slice - 1 - bh : bh;
 }
 
 // The key-stationary work list of a head holds its caption items (n_text, the long ones) before its

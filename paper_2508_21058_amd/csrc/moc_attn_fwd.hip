@@ -305,11 +305,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdArgs a) {
     const int N = a.N;
 
     int logical;
-    const long long total = (long long)a.items_per_head * a.BH;
-    if (!(MODE == MODE_ANCHOR ? xcd_remap_back(total, logical) : xcd_remap(total, logical))) return;
-    const int bh = logical / a.items_per_head;
+    if (!xcd_remap((long long)a.items_per_head * a.BH, logical)) return;
+    int bh = logical / a.items_per_head;
+    const int item = logical - bh * a.items_per_head;
+    if (MODE == MODE_ANCHOR) bh = head_from_last(bh, a.slice_heads);
     ItemDesc it;
-    if (!decode_item<MODE>(a, bh, logical - bh * a.items_per_head, it)) return;
+    if (!decode_item<MODE>(a, bh, item, it)) return;
 
     // ---- this lane's query row
     const int r = wave * 32 + l32;
@@ -519,6 +520,7 @@ static hipError_t fwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, void *o, f
     }
     MOC_PROF("attn_fwd_forced", st);
     a.items_per_head = m->n_atiles;
+    a.slice_heads = heads_per_slice(BH);
     a.o_out = o; a.lse_out = lse;
     const dim3 grid(xcd_grid((long long)a.items_per_head * BH));
     if (sizeof(OT) == 4 && a.topk == 0) attn_fwd_kernel<D, MODE_ANCHOR, OT, OT><<<grid, dim3(256), 0, st>>>(a);
