@@ -42,8 +42,16 @@ struct RouteArgs {
     const uint32_t *textmask;
     int32_t *sel;
     int N, C, Cpad, topk, causal;
+    int turn;                     // blocks of queries from the last one on
     int stride;                   // int32 words between consecutive rows of sel (>= topk)
 };
+
+// Under the causal mask the last queries have the most tiles: first, so that a launch ends on short workgroups (457k tokens,
+// k = 16: 4,373 -> 4,270 us; four heads of 60k tokens, 968 chunks, k = 11 140 -> 126). Not for wide lists over few tiles where
+// a head fills the chip: all of its workgroups then scan at one time and write their rows at another (sixteen heads of
+// 100k tokens, k = 11 in rows of 15 words: 120 chunks 194 us in order, 225 turned round, 248 chunks 268 / 289, 488 chunks
+// 424 / 423; of 80k tokens 154 / 156, 214 / 214, 344 / 339; k = 8 turned round 2 % faster at any of these).
+static int from_last(int N, int C, int topk, int causal) { return causal && (topk <= 8 || C >= 384 || N < 80000); }
 
 // The entry of a candidate: the score's bits as the high word of a double, which read as one is finite
 // for every score but a NaN (+-inf become exponent 0x7f8) and ordered like the scores; the low word
@@ -161,12 +169,11 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int bh = blockIdx.y, N = a.N, C = a.C;
-    // Under the causal mask the last queries have the most tiles: first, so that a launch ends on short workgroups
-    // (457k tokens, k = 16: 4,373 -> 4,270 us). Turned round within every eighth block, so that a block of queries keeps its
-    // XCD: the pooling pass before and the perturbed rows' pass behind have the same blocks there, in its L2 (three heads of
-    // 8,000 tokens, k = 8: routing 9.8 us and perturbed rows 12.2 turned round as a whole, 9.3 and 10.0 so).
+    // From the last queries on (see from_last) within every eighth block, so that a block of queries keeps its XCD: the pooling
+    // pass before and the perturbed rows' pass behind have the same blocks there, in its L2 (three heads of 8,000 tokens,
+    // k = 8: routing 9.8 us and perturbed rows 12.2 turned round as a whole, 9.3 and 10.0 so).
     const int nb = gridDim.x, bx = blockIdx.x, b8 = bx % kXcds;
-    const int q0 = (a.causal ? b8 + kXcds * ((nb - b8 + kXcds - 1) / kXcds - 1 - bx / kXcds) : bx) * QPW;
+    const int q0 = (a.turn ? b8 + kXcds * ((nb - b8 + kXcds - 1) / kXcds - 1 - bx / kXcds) : bx) * QPW;
     const int topk = a.topk;
     int i[QG], limit[QG], wf[QG], wl[QG], lim_lo[QG], wf_lo[QG], wl_hi[QG];
 #pragma unroll
@@ -494,6 +501,7 @@ hipError_t launch_route_fused(const moc_meta *m, int BH, int d, const void *q, c
     a.textmask = m->d_textmask;
     a.sel = sel;
     a.N = m->N; a.C = m->C; a.Cpad = Cpad; a.topk = topk; a.causal = causal != 0;
+    a.turn = from_last(a.N, a.C, topk, a.causal);
     a.stride = topk;
     FuseArgs f{k, m->d_off, kbar, static_cast<bf16_t *>(kb_split), (unsigned int)Cpad * (unsigned int)BH};
     dim3 grid((m->N + kRouteThreads / 2 - 1) / (kRouteThreads / 2), BH), block(kRouteThreads);
@@ -544,6 +552,7 @@ hipError_t launch_route(const moc_meta *m, int BH, int d, int dtype, const void 
     a.textmask = m->d_textmask;
     a.sel = sel;
     a.N = m->N; a.C = m->C; a.Cpad = Cpad; a.topk = topk; a.causal = causal != 0;
+    a.turn = from_last(a.N, a.C, topk, a.causal);
     a.stride = sel_stride;
     MOC_PROF("route_topk", st);
     auto run = [&](auto dd, auto kk, auto tt) {
