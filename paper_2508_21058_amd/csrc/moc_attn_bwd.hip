@@ -619,8 +619,8 @@ __device__ __forceinline__ void score_step(const char *smem, const LaneOffs<D> &
 // of step t a grad wave waits only until its own copies of tile t+1 have landed
 // (vmcnt bound, no drain). Everything the loop loads, per-query lse and delta
 // included, goes through the async path, so no register-destination load
-// forces an early wait; the list words that name the gathered rows are scalar
-// loads issued one step before the copies that use them.
+// forces an early wait; the list words that name the gathered rows come the same way,
+// four tiles ahead of the copies that use them, through a small ring in LDS.
 template <int D, typename OT>      // OT: storage type of dK and dV
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     typedef bf16_t T;
@@ -796,11 +796,10 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
         const int32_t *const entries = a.qlist + lpos;
 
         // ---- copy addressing. This wave's copy p of a tensor covers tile rows (w4 + 4p) * RPI + [0, RPI).
-        // Per tile ("group") a wave issues, in this order: the list words of the tile four groups
-        // ahead (into a small LDS ring; a dummy copy when that tile is not a gathered one), PI copies
-        // of Q, PI of dO, one of lse2 / delta: LPT in all, always, so that a vmcnt bound counts groups.
-        // By the time a gathered tile's copies are issued its list words have landed: they are older
-        // than the three groups that may still be in flight.
+        // Per tile ("group") a wave issues the list words of the tile four groups ahead (into a small LDS ring; a dummy
+        // copy when that tile is not a gathered one), PI copies of Q, PI of dO, one of lse2 / delta: LPT in all, always, in
+        // any order, so that a vmcnt bound counts whole groups. Tile u's words went out with group u - 4: a wait that leaves
+        // the two youngest of the groups up to u - 1 in flight, as the one before its copies does, covers them.
         const int rlo = lane / (D / 8), cgp = lane % (D / 8);
         uint32_t vcol[PI], voff[PI];
         auto trow = [&](int p) { return (w4 + 4 * p) * RPI + rlo; };
@@ -884,6 +883,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
         // instructions with a dozen branches and waits for two list words, in front of a grad wave's products; this is
         // 40. dK/dV of 6,256 tokens 277 -> 272 us, two samples of eight ragged heads of 64 features 412 -> 404, 114k
         // tokens 17.74 -> 17.64 ms, 182k tokens 158.4 -> 157.3: the step is not bound by the grad waves alone.
+        // The rows go out first, the single words behind them: the other way round calls of few items and long contiguous runs
+        // lose (one head of 12,200 tokens in one window 306 us by the general way, 313 so, 305 now; three heads 647, 657, 641).
         // Tile u is whole and contiguous; the words four tiles ahead may be the first gathered ones.
         auto issue_contig = [&](int u) {
             const int v = u + 4;
@@ -892,14 +893,14 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
             const int lim = real ? min(BQ, cntB - (v - nA) * BQ) - 1 : 0;
             const uint32_t qat = smem_at + ist * SB + w4 * 1024, sat = stats_at + ist * (2 * BQ * 4) + w4 * 64;
             ist = next_stage(ist);
-            if (lane < 16) {
-                async_copy4_at(wsrc, (uint32_t)(min(eidx, lim) * 4), ent_at + (v & 7) * 256 + w4 * 64);
-                async_copy4_at(stc, soff, sat);
-            }
 #pragma unroll
             for (int p = 0; p < PI; ++p) {
                 async_copy16_at(qp, voff[p], qat + p * 4096);
                 async_copy16_at(dop, voff[p], qat + TB + p * 4096);
+            }
+            if (lane < 16) {
+                async_copy4_at(wsrc, (uint32_t)(min(eidx, lim) * 4), ent_at + (v & 7) * 256 + w4 * 64);
+                async_copy4_at(stc, soff, sat);
             }
             stc += BQ * 2;
             qp += BQ * D * 2;
@@ -1096,7 +1097,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
             const int end_c = item.q_len / BQ, end_g = nA + cntB / BQ;
             while (t + NS - 2 < end_c) { run_wait(); step([&]() { issue_contig(t + NS - 2); }, nothing); }
             while (t + NS - 2 < nA) { step_wait(t); step([&]() { step_issue(t); }, nothing); }
-            // the words of tile t + 5 landed before the barrier of step t - 1: they are older than its Q and dO copies
+            // the words of tile t + 5 went out with group t + 1, which the wait of step t - 1 covered
             if (t + NS - 2 < end_g) ring_read(t + NS - 2);
             while (t + NS - 2 < end_g) {
                 run_wait();
