@@ -883,8 +883,12 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
         // instructions with a dozen branches and waits for two list words, in front of a grad wave's products; this is
         // 40. dK/dV of 6,256 tokens 277 -> 272 us, two samples of eight ragged heads of 64 features 412 -> 404, 114k
         // tokens 17.74 -> 17.64 ms, 182k tokens 158.4 -> 157.3: the step is not bound by the grad waves alone.
-        // The rows go out first, the single words behind them: the other way round calls of few items and long contiguous runs
-        // lose (one head of 12,200 tokens in one window 306 us by the general way, 313 so, 305 now; three heads 647, 657, 641).
+        // The order of the copies is the general way's: list words, rows, lse / delta. With both words first, calls of long
+        // contiguous runs lost (one head of 12,200 tokens in one window 304 us by the general way, 315 so, 294 now; three heads
+        // 640, 653, 627); with both last less is gained (24 heads of 114k tokens 17.36 ms, 17.20, 17.21 with both last, 16.90).
+        // It is no gain where whole and partly filled key tiles walk one long window: the whole ones now run ahead, and Q and
+        // dO leave L2 between them (eight heads, 30k-token windows, 224-key chunks 13.59 -> 13.85 ms with 2.3 -> 3.8 GB fetched,
+        // 200-key chunks 12.03 -> 12.27; 256-key chunks 16.48 -> 16.04, 2.7 GB either way).
         // Tile u is whole and contiguous; the words four tiles ahead may be the first gathered ones.
         auto issue_contig = [&](int u) {
             const int v = u + 4;
@@ -893,15 +897,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
             const int lim = real ? min(BQ, cntB - (v - nA) * BQ) - 1 : 0;
             const uint32_t qat = smem_at + ist * SB + w4 * 1024, sat = stats_at + ist * (2 * BQ * 4) + w4 * 64;
             ist = next_stage(ist);
+            if (lane < 16) async_copy4_at(wsrc, (uint32_t)(min(eidx, lim) * 4), ent_at + (v & 7) * 256 + w4 * 64);
 #pragma unroll
             for (int p = 0; p < PI; ++p) {
                 async_copy16_at(qp, voff[p], qat + p * 4096);
                 async_copy16_at(dop, voff[p], qat + TB + p * 4096);
             }
-            if (lane < 16) {
-                async_copy4_at(wsrc, (uint32_t)(min(eidx, lim) * 4), ent_at + (v & 7) * 256 + w4 * 64);
-                async_copy4_at(stc, soff, sat);
-            }
+            if (lane < 16) async_copy4_at(stc, soff, sat);
             stc += BQ * 2;
             qp += BQ * D * 2;
             dop += BQ * D * 2;
