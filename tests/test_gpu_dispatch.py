@@ -392,7 +392,19 @@ def test_route_pair_of_query_groups(N, chunk, text, topk, causal):
     for heads in (slice(0, 100), slice(BH - 100, BH)):
         want_pooled, want = mb.route(meta, q[:, heads].contiguous(), k[:, heads].contiguous(), topk, causal)
         assert torch.equal(pooled[:, heads], want_pooled) and torch.equal(sel[:, heads], want)
+    # rows wider than the list, with nothing drawn; scratch of the library's own, where it suffices
+    _, wide = mb.route_perturbed(meta, q, k, topk, causal, 0.0, 0.0, 3, 1)
+    assert torch.equal(wide[..., :topk], sel) and bool((wide[..., topk:] == -1).all())
+    if BH * 3 * -(-lay.C // 32) * 32 * 128 * 2 <= 16 << 20:
+        assert torch.equal(mb.route_static(meta, q, k, topk, causal)[1], sel)
     meta.close()
+
+
+# fp32 storage, conversions that ride with the count of the two launches and of the general way (fewer entries, as in the
+# cases above, take one workgroup a head)
+@pytest.mark.parametrize("video,chunk,topk", [(1380, 5, 8), (1010, 1, 32)])
+def test_fp32_storage_beside_the_count(video, chunk, topk):
+    run_case(mi.stream_layout(1, 20, video, chunk, "chunk"), 1, 2, 64, topk, torch.float32, seed=121 + chunk)
 
 
 # fp32 storage of more than 1,024 chunks: the conversions go out in a launch of their own, a record of its own beside
