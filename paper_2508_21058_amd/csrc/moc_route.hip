@@ -17,9 +17,9 @@
 // rate here; at the end the two half-waves merge their lists. One pass over the chunks;
 // any data (ties, few tiles) stays exact, and the time does not depend on the data.
 //
-// Bound by the sum of these vector instructions, about 190 per tile of 32 x 32 scores (k <= 8), and of its 24 matrix
-// instructions, which hardly run side by side (1,650 cycles a tile measured): neither half the LDS reads nor dealing
-// the ones between the others gains more than 5 % (see launch_route). Against queues of the scores above the k-th best so far,
+// Bound by the sum of these vector instructions, about 260 per tile of 32 x 32 scores (k <= 8, 193 of them the selection), and
+// of its 24 matrix instructions, which hardly run side by side: 1,040 and 768 cycles of the 1,700 that a tile takes. Neither
+// half the LDS reads nor dealing the ones between the others gains more than 7 % (see launch_route). Against queues of the scores above the k-th best so far,
 // inserted entry by entry (divergent, two LDS rows per entry, two waves per SIMD): 1,313
 // -> 684 us at 114k tokens, 24 heads, 440 chunks, k = 8; 7,074 -> 4,552 us at 457k tokens,
 // six heads, 3,488 chunks, k = 16; 26 -> 15 us at 6,256 tokens, k = 3. The queues cost less per tile the
@@ -535,13 +535,24 @@ hipError_t fused_wait_flag(int *timed_out) {
 
 // Two groups of 32 queries a wave read a tile's fragments once for both and have registers left (227 to 256, two
 // workgroups a compute unit) for the scores of a tile and of the next, so that the selection of one runs between the
-// products of the other. 24 heads, bf16, d = 128, one group / two: 114k tokens, 260-key chunks, k = 8 592 / 579 us, 130-key
-// chunks 1,018 / 972, k = 3 540 / 515; 457k tokens, six heads, 3,488 chunks, k = 8 3,694 / 3,455. It needs a chip full
-// several times over with half the workgroups: 33k tokens, k = 5 (3,120 of them) 82 / 84, 32 heads (4,160) 105 / 105, 48 heads
-// (6,240) 354 / 340; 6,256 tokens (600) 15.2 / 18.2. Wider lists spill (k = 16: 4,270 / 15,809), d = 64 gains nothing (375 / 374
-// at k = 8), nor does fp32 there (116 / 165, spills). One group with the selection dealt takes as long as without, or longer
-// (457k tokens, k = 16: 4,380 / 4,547).
+// products of the other. 24 heads, bf16, d = 128, causal, one group / two: 114k tokens, k = 8, 440 chunks 549 / 538 us, 872
+// 962 / 921, k = 3, 440 chunks 502 / 476; 457k tokens, six heads, 3,488 chunks, k = 8 3,466 / 3,253. It needs a chip full
+// several times over with half the workgroups (6,256 tokens, 600 of them: 15 / 18). Below 80,000 tokens it also needs
+// - under the causal mask: workgroups that are short against a head, since they end at their own tile and every eighth
+//   is on one XCD (8,000 tokens, 144 heads, 136 chunks, k = 8 116 / 157; 64 chunks 88 / 93; 424 242 / 327; 16,000 tokens,
+//   72 heads, 440 chunks 241 / 246), and one or two tiles, or a dozen (33k tokens, 48 heads, k = 8: 64 chunks
+//   117 / 118, 136 149 / 157, 264 222 / 224, 328 263 / 264, 440 327 / 324, 696 476 / 468; k = 3: 113 / 109, 140 / 143, 203 / 200, 240 / 237,
+//   299 / 290, 435 / 418; 66k tokens, 24 heads, 136 chunks, k = 8 149 / 156);
+// - without it: not four or five tiles (8,000 tokens, 300 heads, k = 8: 64 chunks 188 / 182, 104 282 / 299, 136 341 / 358;
+//   33k tokens, 48 heads, 136 chunks 223 / 223, 200 300 / 298, 440 564 / 544).
+// Wider lists spill (k = 16: 4,270 / 15,809), d = 64 gains nothing (375 / 374 at k = 8), nor does fp32 there (116 / 165,
+// spills). One group with the selection dealt takes as long as without, or longer (457k tokens, k = 16: 4,380 / 4,547).
 constexpr long long kPairWgs = 4096;
+static bool pair_of_groups(int N, int C, long long wgs, int causal) {
+    if (wgs < kPairWgs) return false;
+    if (N >= 80000) return true;
+    return causal ? N >= 32768 && (C <= 64 || C >= 384) : C <= 96 || C > 160;
+}
 
 hipError_t launch_route(const moc_meta *m, int BH, int d, int dtype, const void *q, const void *kb_split, int Cpad,
                         int topk, int causal, int32_t *sel, int sel_stride, hipStream_t st) {
@@ -560,7 +571,7 @@ hipError_t launch_route(const moc_meta *m, int BH, int d, int dtype, const void 
         using T = decltype(tt);
         if constexpr (KK <= 8 && sizeof(T) == 2 && DD == 128) {
             const int wgs = (m->N + kRouteThreads - 1) / kRouteThreads;
-            if ((long long)wgs * BH >= kPairWgs) {
+            if (pair_of_groups(m->N, m->C, (long long)wgs * BH, causal)) {
                 route_kernel<DD, T, KK, 2><<<dim3(wgs, BH), dim3(kRouteThreads), 0, st>>>(a);
                 return;
             }

@@ -374,11 +374,16 @@ def test_list_builder_ways(N, chunk, topk, H, way):
     assert check_lists(N, chunk, topk, H) == way
 
 
-# two groups of 32 queries a wave, taken from 4,096 workgroups of 256 queries up (bf16, d = 128, k <= 8): the selections of
-# some heads are those of a call of these heads alone, which takes one group a wave (and which the oracle checks); the last
-# workgroup holds one query, one group, one query past a group, or all; one tile of chunks, two, and many with text in them
+# two groups of 32 queries a wave, taken from 4,096 workgroups of 256 queries up (bf16, d = 128, k <= 8) where few or many
+# chunks go with them: without the causal mask to 96 chunks and from 161 on, under it from 32,768 tokens on, to 64 and from 384.
+# The selections of some heads are those of a call of these heads alone, which takes one group a wave (and which the oracle
+# checks); the last workgroup holds one query, one group, one query past a group, or all; one tile of chunks, two, and many
+# with text in them; the first six but the fourth stay with one group
 @pytest.mark.parametrize("N,chunk,text,topk,causal", [(2049, 100, 0, 8, True), (2080, 33, 60, 3, True), (2209, 17, 90, 8, False),
-                                                      (2304, 70, 0, 5, False), (2303, 70, 300, 4, True), (2050, 7, 20, 8, True)])
+                                                      (2304, 70, 0, 5, False), (2303, 70, 300, 4, True), (2050, 7, 20, 8, True),
+                                                      (2209, 12, 90, 8, False), (2080, 33, 60, 3, False), (32769, 600, 0, 8, True),
+                                                      (32800, 80, 60, 3, True), (33025, 85, 300, 4, True), (33024, 1100, 90, 8, True),
+                                                      (80001, 800, 20, 8, True)])
 def test_route_pair_of_query_groups(N, chunk, text, topk, causal):
     lay = mi.stream_layout(1, text, N - text, chunk, "chunk")
     BH = 4096 // ((N + 255) // 256) + 1
@@ -389,7 +394,8 @@ def test_route_pair_of_query_groups(N, chunk, text, topk, causal):
     k[0, :, text:text + 4 * chunk] = k[0, :, text + 4 * chunk:text + 8 * chunk]     # equal means: ties go to the lower chunk
     meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
     pooled, sel = mb.route(meta, q, k, topk, causal)
-    for heads in (slice(0, 100), slice(BH - 100, BH)):
+    few = min(100, BH // 2)
+    for heads in (slice(0, few), slice(BH - few, BH)):
         want_pooled, want = mb.route(meta, q[:, heads].contiguous(), k[:, heads].contiguous(), topk, causal)
         assert torch.equal(pooled[:, heads], want_pooled) and torch.equal(sel[:, heads], want)
     # rows wider than the list, with nothing drawn; scratch of the library's own, where it suffices
