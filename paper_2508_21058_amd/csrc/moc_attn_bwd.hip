@@ -190,10 +190,13 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
 
 // Sums the per-segment partials of a caption key tile in a fixed order, one float4 of dK and of dV a thread, 256 of them a
 // workgroup; bound by HBM. These workgroups are the last of the forced-link dQ launch, which needs nothing of theirs and
-// whose items are bound by other things; as a launch of their own they took 7 us of 675 at 6,256 tokens, 79 us of 41 ms at
-// 114k, 268 us of 93 ms at 457k. Before the items they would leave the compute units unevenly free: where a call has fewer
-// items than units, pairs of them then share a unit while others idle (sixteen heads of 1,320 tokens: the launch takes
-// 68 us with the sums first, 51 with the sums last, and 50 plus 6 for a launch of their own).
+// whose items are bound by other things. Forced dQ and a launch of their own / in one, us: 6,256 tokens 107 / 102 (of 680 a
+// step), a 2,000-token caption 144 / 132, 114k tokens, 24 heads 6,024 / 5,981, 457k, six heads 24,650 / 24,524. Nor do calls of
+// many caption tiles lose, though the sums keep the registers and LDS of the items: 100 shots of 30-token captions 1,313 / 1,308,
+// 200 of 128 16,624 / 16,657, 64 of 16, 48 heads 3,536 / 3,552, 16 of 500, d = 64 2,071 / 2,039.
+// Before the items they would leave the compute units unevenly free: where a call has fewer items than units, pairs of them
+// then share a unit while others idle (sixteen heads of 1,320 tokens: the launch takes 68 us with the sums first, 51 with
+// the sums last, and 50 plus 6 for a launch of their own).
 template <int D> constexpr int reduce_parts() { return kKeyTile * (D / 4) / 256; }
 template <int D, typename T>
 __device__ __forceinline__ void text_reduce(const FwdArgs &a) {
@@ -881,8 +884,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
         };
         // issue_group for the long runs of whole tiles of one kind, with nothing to decide: the general way above is 160
         // instructions with a dozen branches and waits for two list words, in front of a grad wave's products; this is
-        // 40. dK/dV of 6,256 tokens 277 -> 272 us, two samples of eight ragged heads of 64 features 412 -> 404, 114k
-        // tokens 17.74 -> 17.64 ms, 182k tokens 158.4 -> 157.3: the step is not bound by the grad waves alone.
+        // 40. dK/dV of 6,256 tokens 241 -> 233 us, two samples of eight ragged heads of 64 features 368 -> 366, 24 heads of 114k
+        // tokens 17.37 -> 17.04 ms, six of 457k, k = 16 37.3 -> 36.4: the step is not bound by the grad waves alone.
         // The order of the copies is the general way's: list words, rows, lse / delta. With both words first, calls of long
         // contiguous runs lost (one head of 12,200 tokens in one window 304 us by the general way, 315 so, 294 now; three heads
         // 640, 653, 627); with both last less is gained (24 heads of 114k tokens 17.36 ms, 17.20, 17.21 with both last, 16.90).

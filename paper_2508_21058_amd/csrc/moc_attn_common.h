@@ -270,7 +270,7 @@ __device__ __forceinline__ void store_rows_bf16(char *smem, int wave, int lane, 
 // halves they make 16-byte words, and exchanged with the row 16 lanes on, four lanes hold 64 contiguous bytes of a row.
 // Stored after the first exchange already, in 32-byte pieces of 32 rows at a time, the address unit and the L2 saw twice
 // the requests: routed forward / dQ of 457k tokens, six heads, 130-key chunks, k = 16, 7,457 / 9,116 us against 7,229 /
-// 8,648 now; 114k tokens, 24 heads, 260-key chunks, k = 8, 4,300 / 5,636 against 4,247 / 5,584. (Non-temporal stores
+// 8,648 now; 114k tokens, 24 heads, 260-key chunks, k = 8, 4,316 / 5,579 against 4,304 / 5,529. (Non-temporal stores
 // lose: 4,410 / 5,762.) prow: the lane's row (in rows of D); rows >= valid are not written.
 template <int D>
 __device__ __forceinline__ void scatter_rows_bf16(const f32x16 *acc, float scale, int prow, int valid, int lane, bf16_t *out) {

@@ -322,8 +322,9 @@ __device__ __forceinline__ void route_body(const RouteArgs &a, char *smem) {
                 // below the causal limit, outside the own window [wf, wl], not text; it differs from text alone only
                 // where the limit or the window cuts the tile. The lane takes its 16 bits, (r >> 2) * 8 + half * 4 +
                 // (r & 3), at compile-time positions, each as a mask of its score: two instructions where a test and a
-                // choice take three. Both together: 114k tokens, k = 16 175 -> 170 us, 457k 4,117 -> 4,047. (With two
-                // groups, k = 8 and all 256 registers taken, the masks cost 106 spills.)
+                // choice take three. Both together, k = 16: 114k tokens, six heads 177 -> 172 us, 24 heads 647 -> 630, 457k
+                // tokens, six heads, 872 chunks 1,117 -> 1,099. (With two groups, k = 8 and all 256 registers taken, the masks
+                // cost 106 spills.)
                 uint32_t okm = ~tm;
                 if (!inside) {
                     auto below = [](int n) { return n >= 32 ? 0xffffffffu : (n <= 0 ? 0u : ((1u << n) - 1u)); };
