@@ -30,8 +30,8 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 # vector instructions per matrix instruction in the score + top-k pass, from the counter run recorded in
-# profiles/moc_kernels_small_and_ragged_passes.txt (SQ_INSTS_VALU / SQ_INSTS_MFMA)
-ROUTE_VALU_PER_MFMA = 11.8
+# profiles/moc_kernels_small_and_ragged_passes.txt ((SQ_INSTS_VALU - SQ_INSTS_MFMA) / SQ_INSTS_MFMA: the first counts both)
+ROUTE_VALU_PER_MFMA = 10.8
 
 
 def layout_counts(lay, sel, chunk_of_t, topk, causal=True):
