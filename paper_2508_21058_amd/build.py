@@ -17,10 +17,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libmoc.so")
-UNITS = ["moc_api", "moc_pool", "moc_route", "moc_lists", "moc_attn_fwd", "moc_attn_bwd", "moc_probe", "moc_perturb", "moc_outer"]
+UNITS = ["moc_api", "moc_pool", "moc_route", "moc_lists", "moc_attn_fwd", "moc_attn_bwd", "moc_attn_dkdv", "moc_probe", "moc_perturb", "moc_outer"]
 # -Wno-inline-asm: the tile-copy asm lists m0 (which it sets) as clobbered; clang warns that m0 is reserved
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# matrix results in vector registers: the accumulation registers of this unit are its own (see mfma32_acc)
+UNIT_FLAGS = {"moc_attn_dkdv": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _deps():
@@ -35,7 +37,7 @@ def _compile(unit: str, force: bool, hdr_time: float) -> str:
     if (not force and os.path.exists(obj) and os.path.getmtime(obj) >= os.path.getmtime(src)
             and os.path.getmtime(obj) >= hdr_time):
         return obj
-    cmd = ["hipcc", *FLAGS, "-c", src, "-o", obj]
+    cmd = ["hipcc", *FLAGS, *UNIT_FLAGS.get(unit, []), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {unit}:\n{r.stdout}\n{r.stderr}")

@@ -133,10 +133,13 @@ AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, boo
     if (dtype == MOC_F32) L.cvt = take((size_t)BH * N * d * 2 * (with_bwd ? 4 : 3));   // bf16 copies of q, k, v (and dO)
     if (with_bwd) {
         L.delta = take((size_t)BH * N * 4);
-        L.stats2 = take(((size_t)BH * N + 1) * 8);     // (lse2, delta) pairs + one pair holding (+inf, 0)
-        L.gstats2 = take((size_t)BH * N * std::max(topk, 1) * 8);
-        L.tpart_k = take((size_t)BH * m->n_partials * kKeyTile * d * 4);
-        L.tpart_v = take((size_t)BH * m->n_partials * kKeyTile * d * 4);
+        const bool wide = wide_tiles(m, BH, d);
+        const size_t rec = wide ? 16 : 8;              // bytes of a query's statistics (see store_stats)
+        L.stats2 = take(((size_t)BH * N + 1) * rec);
+        L.gstats2 = take((size_t)BH * N * std::max(topk, 1) * rec);
+        const size_t part = (size_t)BH * (wide ? m->tt_wide.n_partials * kWideTile : m->tt_all.n_partials * kKeyTile) * d * 4;
+        L.tpart_k = take(part);
+        L.tpart_v = take(part);
     }
     L.total = off;
     return L;
@@ -301,30 +304,45 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     // key-stationary backward items. Caption key tiles come first, ordered by query segment: the
     // tiles that walk the same segment of queries are neighbours in the list, run at the same time
     // on one XCD and share those Q / dO rows in its L2 instead of each fetching them from HBM.
-    std::vector<KvItem> kvitems;
-    std::vector<TextTile> ttiles;
-    int n_partials = 0;
     const int seg = ((N + text_segments(N) - 1) / text_segments(N) + 31) / 32 * 32;   // equal segments of whole 32-query tiles
     const int nseg = (N + seg - 1) / seg;
-    for (int j = 0; j < C; ++j)
-        if (kind[j])
-            for (int k0 = off[j]; k0 < off[j + 1]; k0 += kKeyTile) {
-                ttiles.push_back(TextTile{k0, std::min(kKeyTile, off[j + 1] - k0), n_partials, nseg});
-                n_partials += nseg;
+    std::vector<KvItem> kvitems[3];            // all, wide, rest
+    std::vector<TextTile> ttiles[2];           // all, wide and rest
+    KvList kv[3];
+    TextTiles tt[2];
+    for (int x = 0; x < 2; ++x) {
+        // the tiles of chunk j: f(first key, keys, list)
+        auto tiles_of = [&](int j, auto f) {
+            for (int k0 = off[j], len; k0 < off[j + 1]; k0 += len) {
+                const int left = off[j + 1] - k0;
+                const bool wide = x == 1 && left >= kWideMin;
+                len = std::min(wide ? kWideTile : kKeyTile, left);
+                f(k0, len, wide ? 1 : 2 * x);
             }
-    for (int s = 0; s < nseg; ++s)
-        for (const TextTile &tt : ttiles)
-            kvitems.push_back(KvItem{tt.key_start, tt.key_len, s * seg, std::min(seg, N - s * seg), -1,
-                                     tt.first_partial + s, 0, 0});
-    const int n_kvtext = int(kvitems.size());
-    for (int j = 0; j < C; ++j) {
-        if (kind[j]) continue;
-        for (int k0 = off[j]; k0 < off[j + 1]; k0 += kKeyTile) {
-            const int klen = std::min(kKeyTile, off[j + 1] - k0);
-            const int w = win[j];
-            const int ws = off[wfirst[w]], we = off[wlast[w] + 1];
-            kvitems.push_back(KvItem{k0, klen, ws, we - ws, j, -1, 0, 0});
+        };
+        std::vector<int> list_of;
+        for (int j = 0; j < C; ++j)
+            if (kind[j])
+                tiles_of(j, [&](int k0, int len, int l) {
+                    ttiles[x].push_back(TextTile{k0, len, tt[x].n_partials, nseg});
+                    list_of.push_back(l);
+                    tt[x].n_partials += nseg;
+                    ++kv[l].n_text_tiles;
+                });
+        tt[x].n = int32_t(ttiles[x].size());
+        for (int s = 0; s < nseg; ++s)
+            for (int t = 0; t < tt[x].n; ++t) {
+                const TextTile &w = ttiles[x][t];
+                kvitems[list_of[t]].push_back(KvItem{w.key_start, w.key_len, s * seg, std::min(seg, N - s * seg), -1,
+                                                     w.first_partial + s, 0, 0});
+            }
+        for (int l = 2 * x; l >= x; --l) kv[l].n_text = int32_t(kvitems[l].size());
+        for (int j = 0; j < C; ++j) {
+            if (kind[j]) continue;
+            const int ws = off[wfirst[win[j]]], we = off[wlast[win[j]] + 1];
+            tiles_of(j, [&](int k0, int len, int l) { kvitems[l].push_back(KvItem{k0, len, ws, we - ws, j, -1, 0, 0}); });
         }
+        for (int l = 2 * x; l >= x; --l) kv[l].n_items = int32_t(kvitems[l].size());
     }
 
     std::vector<uint32_t> textmask((C + 31) / 32, 0u);
@@ -336,11 +354,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     m->N = N; m->C = C; m->T = T; m->W = W;
     m->n_atiles = int32_t(atiles.size());
     m->n_ranges = int32_t(aranges.size());
-    m->n_kvitems = int32_t(kvitems.size());
-    m->n_kvtext = n_kvtext;
     m->text_seg = seg;
-    m->n_text_tiles = int32_t(ttiles.size());
-    m->n_partials = n_partials;
     m->h_off.assign(off, off + C + 1);
     for (int j = 0; j < C; ++j)
         if (!kind[j]) m->max_routed_len = std::max(m->max_routed_len, off[j + 1] - off[j]);
@@ -353,7 +367,9 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     const size_t o_off = take((size_t)(C + 1) * 4), o_kind = take((size_t)C * 4), o_win = take((size_t)C * 4),
                  o_wf = take((size_t)W * 4), o_wl = take((size_t)W * 4), o_aro = take((size_t)(W + 1) * 4),
                  o_ar = take(aranges.size() * sizeof(KeyRange)), o_at = take(atiles.size() * sizeof(AnchorTile)),
-                 o_kv = take(kvitems.size() * sizeof(KvItem)), o_tt = take(ttiles.size() * sizeof(TextTile)),
+                 o_kv[3] = {take(kvitems[0].size() * sizeof(KvItem)), take(kvitems[1].size() * sizeof(KvItem)),
+                            take(kvitems[2].size() * sizeof(KvItem))},
+                 o_tt[2] = {take(ttiles[0].size() * sizeof(TextTile)), take(ttiles[1].size() * sizeof(TextTile))},
                  o_tm = take(textmask.size() * 4), o_ntb = take((size_t)(C + 1) * 4), o_rw = take((size_t)C * 4),
                  o_vid = take((size_t)C * 4),
                  o_cof = take((size_t)N * 4);
@@ -368,8 +384,8 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     put(o_aro, arange_off.data(), (size_t)(W + 1) * 4);
     put(o_ar, aranges.data(), aranges.size() * sizeof(KeyRange));
     put(o_at, atiles.data(), atiles.size() * sizeof(AnchorTile));
-    put(o_kv, kvitems.data(), kvitems.size() * sizeof(KvItem));
-    put(o_tt, ttiles.data(), ttiles.size() * sizeof(TextTile));
+    for (int l = 0; l < 3; ++l) put(o_kv[l], kvitems[l].data(), kvitems[l].size() * sizeof(KvItem));
+    for (int x = 0; x < 2; ++x) put(o_tt[x], ttiles[x].data(), ttiles[x].size() * sizeof(TextTile));
     put(o_tm, textmask.data(), textmask.size() * 4);
     std::vector<int32_t> ntb(C + 1, 0);
     for (int j = 0; j < C; ++j) ntb[j + 1] = ntb[j] + (kind[j] ? 0 : 1);
@@ -395,8 +411,10 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     m->d_arange_off = reinterpret_cast<int32_t *>(base + o_aro);
     m->d_aranges = reinterpret_cast<KeyRange *>(base + o_ar);
     m->d_atiles = reinterpret_cast<AnchorTile *>(base + o_at);
-    m->d_kvitems = reinterpret_cast<KvItem *>(base + o_kv);
-    m->d_text_tiles = reinterpret_cast<TextTile *>(base + o_tt);
+    for (int l = 0; l < 3; ++l) kv[l].d_items = reinterpret_cast<KvItem *>(base + o_kv[l]);
+    for (int x = 0; x < 2; ++x) tt[x].d = reinterpret_cast<TextTile *>(base + o_tt[x]);
+    m->kv_all = kv[0]; m->kv_wide = kv[1]; m->kv_rest = kv[2];
+    m->tt_all = tt[0]; m->tt_wide = tt[1];
     m->d_textmask = reinterpret_cast<uint32_t *>(base + o_tm);
     m->d_ntb = reinterpret_cast<int32_t *>(base + o_ntb);
     m->d_rwin = reinterpret_cast<int32_t *>(base + o_rw);

@@ -16,15 +16,24 @@
 //              so dK and dV of video tokens are written once, final. Text keys
 //              are attended by all N queries; their items split the queries
 //              into segments, write fp32 partials, and a reduce kernel sums them.
-#include "moc_attn_common.h"
+//              Calls with many whole tiles of 256 keys have a kernel of their own for
+//              those (moc_attn_dkdv.hip); the one here takes the rest of them.
+#include "moc_attn_bwd.h"
 
 namespace moc {
+
+// Statistics of a query as the key-stationary pass reads them: the pair (lse * log2(e), delta); beside wide tiles the list
+// word (query << 5 | slot) and a spare one follow.
+__device__ __forceinline__ void store_stats(float *stats, size_t i, float lse2, float delta, int word, bool rec) {
+    if (rec) *reinterpret_cast<f32x4 *>(stats + 4 * i) = f32x4{lse2, delta, __int_as_float(word), 0.f};
+    else *reinterpret_cast<f32x2 *>(stats + 2 * i) = f32x2{lse2, delta};
+}
 
 // ------------------------------------------------------------------ delta
 template <int D, typename T>
 __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ o, const T *__restrict__ d_o, size_t rows,
                                                     const float *__restrict__ lse, float *__restrict__ delta,
-                                                    float *__restrict__ stats2, bf16_t *__restrict__ do16, uint32_t n_delta,
+                                                    float *__restrict__ stats2, bf16_t *__restrict__ do16, int N, bool rec, uint32_t n_delta,
                                                     CvtArgs cvt) {
     if constexpr (sizeof(T) == 4)       // the copies of q, k and v are the last workgroups
         if (blockIdx.x >= n_delta) { convert_workgroup<256>(cvt, blockIdx.x - n_delta); return; }
@@ -42,14 +51,13 @@ __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ o, con
     }
 #pragma unroll
     for (int w = TPQ / 2; w >= 1; w >>= 1) s += __shfl_xor(s, w, 64);
-    // stats2 holds per query the pair (lse * log2(e), delta) the key-stationary pass works with
+    // stats2 holds per query the record the key-stationary pass works with; one past the end holds lse2 = +inf: the
+    // padding rows of ragged query tiles
     if (row < rows && c8 == 0) {
         delta[row] = s;
-        stats2[2 * row] = lse[row] * kLog2e;
-        stats2[2 * row + 1] = s;
+        store_stats(stats2, row, lse[row] * kLog2e, s, rec ? (int)((uint32_t)row % (uint32_t)N) << 5 : 0, rec);
     }
-    // one pair past the end holds lse2 = +inf: the padding rows of ragged query tiles
-    if (blockIdx.x == 0 && threadIdx.x == 0) { stats2[2 * rows] = INFINITY; stats2[2 * rows + 1] = 0.f; }
+    if (blockIdx.x == 0 && threadIdx.x == 0) store_stats(stats2, rows, INFINITY, 0.f, 0, rec);
 }
 
 // ------------------------------------------------------------------ dQ pass
@@ -197,11 +205,11 @@ __device__ __forceinline__ void sum_store_rows(char *smem, int wave, int lane, c
 // Before the items they would leave the compute units unevenly free: where a call has fewer items than units, pairs of them
 // then share a unit while others idle (sixteen heads of 1,320 tokens: the launch takes 68 us with the sums first, 51 with
 // the sums last, and 50 plus 6 for a launch of their own).
-template <int D> constexpr int reduce_parts() { return kKeyTile * (D / 4) / 256; }
 template <int D, typename T>
 __device__ __forceinline__ void text_reduce(const FwdArgs &a) {
-    constexpr int PARTS = reduce_parts<D>(), V4 = D / 4;            // V4: float4 groups per row
-    const int part = blockIdx.x - a.reduce_at, tile = part / PARTS, u = part % PARTS * 256 + threadIdx.x;
+    constexpr int V4 = D / 4;                                       // float4 groups per row
+    const int parts = a.key_tile * V4 / 256;                        // workgroups of a tile
+    const int part = blockIdx.x - a.reduce_at, tile = part / parts, u = part % parts * 256 + threadIdx.x;
     const int bh = tile / a.n_text_tiles;
     if (bh >= a.BH) return;
     const TextTile tt = a.text_tiles[tile - bh * a.n_text_tiles];
@@ -209,7 +217,7 @@ __device__ __forceinline__ void text_reduce(const FwdArgs &a) {
     const int kr = u / V4, x = (u % V4) * 4;
     f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
     for (int p = 0; p < tt.n_partials; p += a.join) {
-        const size_t prow = ((size_t)bh * a.n_partials + tt.first_partial + p) * kKeyTile + kr;
+        const size_t prow = ((size_t)bh * a.n_partials + tt.first_partial + p) * a.key_tile + kr;
         sk += *reinterpret_cast<const f32x4 *>(a.tpart_k + prow * D + x);
         sv += *reinterpret_cast<const f32x4 *>(a.tpart_v + prow * D + x);
     }
@@ -376,7 +384,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
         const int nq = min(cnt, (te - toff[j]) * kBM) - q_first;
         const size_t lbase = (size_t)bh * N * a.topk + loff[j] + q_first;
         const int32_t *entries = a.qlist + lbase;
-        const float2 *stats = reinterpret_cast<const float2 *>(a.gstats2) + lbase;
+        const float2 *stats = reinterpret_cast<const float2 *>(a.gstats2) + (lbase << a.rec);   // the first pair of a record
         // software pipeline over the wave's blocks: the list entry and the statistics of the next
         // block are fetched before the key tiles of the current one; its Q and dO fragments are
         // fetched into the registers of the current ones once the last key tile is done, so their
@@ -394,7 +402,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
         if (wave * 32 < nq) {
             const int pos = min(wave * 32 + l32, nq - 1);
             e = entries[pos];
-            st2 = stats[pos];                                 // (lse * log2 e, delta)
+            st2 = stats[pos << a.rec];                                 // (lse * log2 e, delta)
             load_qdo(e, qf, dof);
         }
         for (int blk = wave; blk * 32 < nq; blk += 8) {
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
             if (more) {
                 const int pn = min((blk + 8) * 32 + l32, nq - 1);
                 e_next = entries[pn];
-                st_next = stats[pn];
+                st_next = stats[pn << a.rec];
             }
             f32x16 dqacc[DB];
 #pragma unroll
@@ -428,31 +436,18 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_chunk_kernel(FwdArgs a) {
 }
 
 // ------------------------------------------------------------------ dK/dV pass
-struct KvArgs {
-    const void *q, *k, *v, *d_o;
-    const float *stats2;               // per query (lse * log2(e), delta); one extra pair (+inf, 0) at the end
-    const float *gstats2;              // the same pairs gathered in the order of the inverse lists
-    void *dk, *dv;
-    float *tpart_k, *tpart_v;
-    const KvItem *items;
-    const int32_t *list_off, *qlist;
-    int N, C, topk, n_partials, BH;
-    int n_items, n_text;               // work list of a head: items, caption items among them (of `join` segments each)
-    int text_tiles, join, text_seg, video_at;    // caption tiles; queries of `join` segments; first video item of `items`
-    float scale, scale_log2;
-};
-
-// (lse2, delta) of the queries of every inverse list, in list order, so the
+// the statistics of the queries of every inverse list, in list order, so the
 // key-stationary pass reads them as contiguous vectors
 __global__ __launch_bounds__(256) void gather_stats_kernel(const int32_t *__restrict__ qlist,
                                                            const int32_t *__restrict__ list_off, int N, int NK, int C,
-                                                           const float2 *__restrict__ stats2,
-                                                           float2 *__restrict__ gstats2) {
+                                                           const float *__restrict__ stats2, float *__restrict__ gstats2,
+                                                           bool rec) {
     const int bh = blockIdx.y;
     const int pos = blockIdx.x * 256 + threadIdx.x;
     if (pos >= list_off[(size_t)bh * (C + 1) + C]) return;
-    const int i = qlist[(size_t)bh * NK + pos] >> 5;
-    gstats2[(size_t)bh * NK + pos] = stats2[(size_t)bh * N + i];
+    const int e = qlist[(size_t)bh * NK + pos];
+    const f32x2 st = *reinterpret_cast<const f32x2 *>(stats2 + (((size_t)bh * N + (e >> 5)) << (rec ? 2 : 1)));
+    store_stats(gstats2, (size_t)bh * NK + pos, st[0], st[1], e, rec);
 }
 
 // The two halves of the 8-wave key-stationary kernel, for one tile of 32 queries
@@ -624,10 +619,11 @@ __device__ __forceinline__ void score_step(const char *smem, const LaneOffs<D> &
 // included, goes through the async path, so no register-destination load
 // forces an early wait; the list words that name the gathered rows come the same way,
 // four tiles ahead of the copies that use them, through a small ring in LDS.
-template <int D, typename OT>      // OT: storage type of dK and dV
+template <int D, typename OT, bool REC>      // OT: storage type of dK and dV; REC: statistics in records (see store_stats)
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     typedef bf16_t T;
     constexpr int BQ = 32, NS = 7;
+    constexpr int SW = REC ? 4 : 2;                // words of a query's statistics
     constexpr int kWide = 3;                       // query tiles per step of a single-key-block item
     static_assert(2 * kWide <= NS && kWide <= 4, "two alternating sets of stages, one P / dS slot per score wave");
     constexpr int KS = D / 16, DB = D / 32;
@@ -794,7 +790,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
         __builtin_amdgcn_s_setprio(1);
         const char *qbase = static_cast<const char *>(a.q) + (size_t)bh * N * D * 2;
         const char *dobase = static_cast<const char *>(a.d_o) + (size_t)bh * N * D * 2;
-        const float *const inf_slot = a.stats2 + (size_t)a.BH * N * 2;   // the pair (+inf, 0)
+        const float *const inf_slot = a.stats2 + (size_t)a.BH * N * SW;  // the pair (+inf, 0)
         const size_t lpos = (size_t)bh * N * a.topk + lbeg;
         const int32_t *const entries = a.qlist + lpos;
 
@@ -812,9 +808,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
             voff[p] = (uint32_t)(trow(p) * D * 2) + vcol[p];
         }
         // lanes 0-7 copy lse2, lanes 8-15 delta, of the wave's 8 queries of a tile (pairs in memory)
-        const uint32_t soff = (uint32_t)(((w4 * 8 + (lane & 7)) * 2 + ((lane >> 3) & 1)) * 4);
-        const float *stc = a.stats2 + ((size_t)bh * N + item.q_start) * 2;    // next contiguous tile
-        const float *stg = a.gstats2 + lpos * 2;                              // next gathered tile
+        const uint32_t soff = (uint32_t)(((w4 * 8 + (lane & 7)) * SW + ((lane >> 3) & 1)) * 4);
+        const float *stc = a.stats2 + ((size_t)bh * N + item.q_start) * SW;   // next contiguous tile
+        const float *stg = a.gstats2 + lpos * SW;                             // next gathered tile
         const uint32_t smem_at = lds_address(smem), stats_at = lds_address(stats_s), ent_at = lds_address(ent_s);
         const uint32_t ent_rd = ent_at + w4 * 64 + rlo * 4;
         auto tile_valid = [&](int t) { return t < nA ? min(BQ, item.q_len - t * BQ) : min(BQ, cntB - (t - nA) * BQ); };
@@ -841,8 +837,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
             // (plain selects: a pointer picked and advanced inside the branches ends up in scratch memory)
             const bool contig = u < nA;
             const float *const st2 = contig ? stc : stg;
-            stc += contig ? BQ * 2 : 0;
-            stg += contig ? 0 : BQ * 2;
+            stc += contig ? BQ * SW : 0;
+            stg += contig ? 0 : BQ * SW;
             if (contig) {
                 if (nv == BQ) {
 #pragma unroll
@@ -876,7 +872,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
                 } else {
                     // ragged tile: rows past the end take lse2 = +inf and the delta of the last row
                     const int srow = w4 * 8 + (lane & 7);
-                    const float *sp = st2 + min(srow, nv - 1) * 2 + ((lane >> 3) & 1);
+                    const float *sp = st2 + min(srow, nv - 1) * SW + ((lane >> 3) & 1);
                     if (lane < 8 && srow >= nv) sp = inf_slot;
                     async_copy4_at(sp, sat);
                 }
@@ -907,7 +903,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
                 async_copy16_at(dop, voff[p], qat + TB + p * 4096);
             }
             if (lane < 16) async_copy4_at(stc, soff, sat);
-            stc += BQ * 2;
+            stc += BQ * SW;
             qp += BQ * D * 2;
             dop += BQ * D * 2;
         };
@@ -937,7 +933,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
                 async_copy4_at(wsrc, (uint32_t)(min(eidx, lim) * 4), ent_at + ((u + 4) & 7) * 256 + w4 * 64);
                 async_copy4_at(stg, soff, sat);
             }
-            stg += BQ * 2;
+            stg += BQ * SW;
         };
         // own copies of tile u landed: at most the copies of the younger tiles may be outstanding
         auto wait_tile = [&](int u) {
@@ -1150,7 +1146,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
                     Io<OT>::store4(dvp + x, dv[j][4 * g], dv[j][4 * g + 1], dv[j][4 * g + 2], dv[j][4 * g + 3]);
                 }
             } else {
-                const size_t prow = ((size_t)bh * a.n_partials + item.partial) * kKeyTile + kb * 32 + l32;
+                const size_t prow = ((size_t)bh * a.n_partials + item.partial) * a.key_tile + kb * 32 + l32;
                 float *dkp = a.tpart_k + prow * D + db * 32, *dvp = a.tpart_v + prow * D + db * 32;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -1164,6 +1160,16 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pipe_kernel(KvArgs a) {
     }
 }
 
+// The items of a list, `join` segments of a caption tile each.
+static void kv_items(KvArgs &kv, const KvList &w, const moc_meta *m, int join) {
+    const int nseg = w.n_text_tiles > 0 ? w.n_text / w.n_text_tiles : 0;
+    kv.items = w.d_items;
+    kv.text_tiles = w.n_text_tiles; kv.join = join;
+    kv.text_seg = join * m->text_seg; kv.video_at = w.n_text;
+    kv.n_text = (nseg + join - 1) / join * w.n_text_tiles;
+    kv.n_items = w.n_items - w.n_text + kv.n_text;
+}
+
 // T: storage type of the caller's tensors; o_in and do_in are the caller's o and dO, a / kv hold bf16 operands
 template <int D, typename T>
 static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv, const void *o_in, const void *do_in,
@@ -1174,15 +1180,27 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     const uint32_t n_delta = (uint32_t)((rows + QPW - 1) / QPW), extra = cvt_grid(cvt, 256);
     delta_kernel<D, T><<<dim3(n_delta + extra), dim3(256), 0, st>>>(
         static_cast<const T *>(o_in), static_cast<const T *>(do_in), rows, a.lse, const_cast<float *>(a.delta),
-        const_cast<float *>(kv.stats2), static_cast<bf16_t *>(const_cast<void *>(a.d_o)), n_delta, cvt); }
+        const_cast<float *>(kv.stats2), static_cast<bf16_t *>(const_cast<void *>(a.d_o)), m->N, a.rec, n_delta, cvt); }
     { MOC_PROF("attn_bwd_dkdv", st);
     if (a.topk > 0) {
         const int NK = m->N * a.topk;
         gather_stats_kernel<<<dim3((NK + 255) / 256, BH), dim3(256), 0, st>>>(
-            kv.qlist, kv.list_off, m->N, NK, m->C, reinterpret_cast<const float2 *>(kv.stats2),
-            reinterpret_cast<float2 *>(const_cast<float *>(kv.gstats2)));
+            kv.qlist, kv.list_off, m->N, NK, m->C, kv.stats2, const_cast<float *>(kv.gstats2), a.rec);
     }
-    attn_bwd_dkdv_pipe_kernel<D, T><<<dim3(kv_grid(kv.n_items, kv.n_text, BH)), dim3(512), 0, st>>>(kv); }
+    if constexpr (D == 128) {
+        if (a.rec) {
+            kv_items(kv, m->kv_wide, m, a.join);
+            const hipError_t e = launch_dkdv_wide(kv, sizeof(T) == 4 ? MOC_F32 : MOC_BF16, st);
+            if (e != hipSuccess) return e;
+            kv_items(kv, m->kv_rest, m, a.join);
+        }
+    }
+    const dim3 grid(kv_grid(kv.n_items, kv.n_text, BH));
+    if (D == 128 && a.rec) {
+        if (kv.n_items > 0) attn_bwd_dkdv_pipe_kernel<128, T, true><<<grid, dim3(512), 0, st>>>(kv);
+    } else {
+        attn_bwd_dkdv_pipe_kernel<D, T, false><<<grid, dim3(512), 0, st>>>(kv);
+    } }
     a.BH = BH;
     if (a.topk > 0) {
         a.items_per_head = (m->N * a.topk + kBM - 1) / kBM + m->C;
@@ -1199,7 +1217,7 @@ static hipError_t bwd_dispatch(const moc_meta *m, int BH, FwdArgs &a, KvArgs &kv
     a.slice_heads = heads_per_slice(BH);
     a.o_out = dq;        // the forced-link items run after the routed ones and add the routed partials themselves
     a.reduce_at = xcd_grid((long long)a.items_per_head * BH);
-    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(a.reduce_at + m->n_text_tiles * BH * reduce_parts<D>()), dim3(256), 0, st>>>(a);
+    attn_bwd_dq_kernel<D, MODE_ANCHOR, T><<<dim3(a.reduce_at + a.n_text_tiles * BH * (a.key_tile * (D / 4) / 256)), dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1236,17 +1254,16 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     kv.dk = dk; kv.dv = dv;
     kv.tpart_k = reinterpret_cast<float *>(ws + L.tpart_k);
     kv.tpart_v = reinterpret_cast<float *>(ws + L.tpart_v);
-    kv.items = m->d_kvitems;
     kv.list_off = a.list_off; kv.qlist = a.qlist;
-    kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = m->n_partials; kv.BH = BH;
-    const int nseg = m->n_text_tiles > 0 ? m->n_kvtext / m->n_text_tiles : 0;
-    kv.text_tiles = m->n_text_tiles; kv.join = text_join(m->N, m->n_text_tiles, BH, nseg);
-    kv.text_seg = kv.join * m->text_seg; kv.video_at = m->n_kvtext;
-    kv.n_text = (nseg + kv.join - 1) / kv.join * m->n_text_tiles;
-    kv.n_items = m->n_kvitems - m->n_kvtext + kv.n_text;
+    const bool wide = wide_tiles(m, BH, d);
+    const TextTiles &tt = wide ? m->tt_wide : m->tt_all;
+    kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = tt.n_partials; kv.BH = BH;
+    a.join = text_join(m->N, tt.n, BH, tt.n > 0 ? tt.n_partials / tt.n : 0);
+    kv_items(kv, m->kv_all, m, a.join);
+    kv.key_tile = wide ? kWideTile : kKeyTile;
     kv.scale = scale; kv.scale_log2 = a.scale_log2;
-    a.tpart_k = kv.tpart_k; a.tpart_v = kv.tpart_v; a.text_tiles = m->d_text_tiles;
-    a.n_text_tiles = m->n_text_tiles; a.n_partials = m->n_partials; a.join = kv.join;
+    a.tpart_k = kv.tpart_k; a.tpart_v = kv.tpart_v; a.text_tiles = tt.d;
+    a.n_text_tiles = tt.n; a.n_partials = tt.n_partials; a.key_tile = kv.key_tile; a.rec = wide;
     a.dk = dk; a.dv = dv;
     if (dtype == MOC_BF16) return d == 128 ? bwd_dispatch<128, bf16_t>(m, BH, a, kv, o, d_o, dq, cvt, st)
                                            : bwd_dispatch<64, bf16_t>(m, BH, a, kv, o, d_o, dq, cvt, st);

@@ -31,7 +31,8 @@ struct FwdArgs {
     const float *tpart_k, *tpart_v;
     const TextTile *text_tiles;
     void *dk, *dv;
-    int n_text_tiles, n_partials, join, reduce_at;
+    int n_text_tiles, n_partials, join, reduce_at, key_tile;
+    bool rec;               // statistics in records of four words (see store_stats)
     // forced-link forward items with the merge fused into their epilogue
     int slice_heads;        // see heads_per_slice
     const uint32_t *vmask;  // [BH, N] bit r: routed slot r of the query counts (set by the list builder)

@@ -12,7 +12,10 @@
 namespace moc {
 
 constexpr int kBM = 128;         // queries per workgroup in the query-stationary passes
-constexpr int kKeyTile = 128;    // keys per workgroup in the key-stationary pass (4 waves x 32)
+// Keys per workgroup in the key-stationary pass: 4 score waves of 32, or, where whole tiles of calls with many of them go
+// to the kernel of their own, 4 waves of 64.
+constexpr int kKeyTile = 128, kWideTile = 256;
+constexpr int kWideMin = 160;    // fewer keys left of a chunk go to the other kernel (two waves of 64 would idle)
 // Queries per partial of a text key tile in the key-stationary pass. A caption tile is attended by all
 // N queries, so its items are the longest of the pass: a quarter of the stream keeps the longest item
 // well under a compute unit's share of short streams (6,256 tokens: a whole-stream item is 196 steps
@@ -47,7 +50,7 @@ struct AnchorTile { int32_t q_start, q_count, win, pad; };
 struct KeyRange { int32_t start, len; };
 
 // One workgroup of the key-stationary backward pass.
-//   keys [key_start, key_start+key_len), key_len <= kKeyTile
+//   keys [key_start, key_start+key_len), key_len <= kKeyTile, or kWideTile in the list of wide tiles
 //   contiguous query source [q_start, q_start+q_len)
 //   chunk >= 0: additionally the routed-query list of that chunk
 //   partial >= 0: write fp32 partial sums to that slot instead of dk/dv
@@ -56,11 +59,22 @@ struct KvItem { int32_t key_start, key_len, q_start, q_len, chunk, partial, pad0
 // A text key tile and the partial slots to sum for it.
 struct TextTile { int32_t key_start, key_len, first_partial, n_partials; };
 
+// A work list of the key-stationary pass: n_text caption items, then the video items.
+struct KvList {
+    int32_t n_items = 0, n_text = 0, n_text_tiles = 0;
+    KvItem *d_items = nullptr;
+};
+// The caption tiles of a pass and the rows of partials they need.
+struct TextTiles {
+    int32_t n = 0, n_partials = 0;
+    TextTile *d = nullptr;
+};
+
 }  // namespace moc
 
 struct moc_meta {
     int32_t N = 0, C = 0, T = 0, W = 0;
-    int32_t n_atiles = 0, n_ranges = 0, n_kvitems = 0, n_kvtext = 0, n_text_tiles = 0, n_partials = 0;
+    int32_t n_atiles = 0, n_ranges = 0;
     int32_t text_seg = 0;            // queries per caption item (the last of a tile may have fewer)
     int32_t max_routed_len = 0;      // longest chunk that is not a caption
     void *d_base = nullptr;
@@ -78,8 +92,8 @@ struct moc_meta {
     int32_t *d_arange_off = nullptr; // [W+1] into d_aranges
     moc::KeyRange *d_aranges = nullptr;
     moc::AnchorTile *d_atiles = nullptr;
-    moc::KvItem *d_kvitems = nullptr;
-    moc::TextTile *d_text_tiles = nullptr;
+    moc::KvList kv_all, kv_wide, kv_rest;      // every tile of kKeyTile keys; tiles of kWideTile, and what they leave
+    moc::TextTiles tt_all, tt_wide;            // caption tiles of kv_all; of kv_wide and kv_rest
     std::vector<int32_t> h_off, h_kind, h_win;
 };
 
@@ -121,6 +135,17 @@ constexpr int kProbeMfmaGrid = 256;
 hipError_t launch_probe(int kind, void *buf, size_t bytes, int iters, hipStream_t st, hipEvent_t e0, hipEvent_t e1,
                         double *units);
 
+// Whether the key-stationary pass takes the wide tiles: only with heads of 128 features, and where the items are many rounds
+// of the chip, since they are twice as long as the others', and more where a second launch has to take what they leave.
+// dK/dV without them / with them, at so many wide items, us. Nothing left: 546 items (23k tokens, six heads, 1,280-key
+// chunks) 3,180 / 3,455, 576 (6k, 24 heads, 256-key) 291 / 312, 1,456 (23k, 16 heads, 256-key) 926 / 912, 1,512 (16k, 24
+// heads, 1,280-key) 1,402 / 1,325, 2,184 (23k, 24 heads, 1,280-key) 11,557 / 10,635. With a rest: 660 (14k, 12 heads,
+// 260-key) 613 / 672, 1,320 (29k, 12 heads, 260-key) 1,698 / 1,774, 2,208 (57k, 12 heads, 312-key) 3,019 / 3,166, 2,976
+// (41k, 24 heads, ragged) 3,322 / 3,219, 7,008 (57k, 24 heads, 195-key) 5,687 / 5,269.
+constexpr int kWideItems = 1408, kWideItemsRest = 2560;
+inline bool wide_tiles(const moc_meta *m, int BH, int d) {
+    return d == 128 && (long long)m->kv_wide.n_items * BH >= (m->kv_rest.n_items > 0 ? kWideItemsRest : kWideItems);
+}
 // Layout of the attention workspace (byte offsets); shared by fwd and bwd.
 struct AttnWs {
     size_t cnt, list_off, tile_off, vmask, gsum, cnt_blk, qlist, plse, po, cnt_fine, cvt, delta, stats2, gstats2, tpart_k, tpart_v, total;

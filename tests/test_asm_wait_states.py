@@ -7,7 +7,10 @@ states in front of the instructions it emits itself, but it does not look inside
   - a scalar register that a vector instruction has written is read by a memory instruction of inline
     assembly five wait states later at the earliest, by a vector instruction of it two;
   - a vector register that inline assembly has written is read by a lane permute two wait states later at
-    the earliest, by a lane read one."""
+    the earliest, by a lane read one;
+  - a matrix instruction of inline assembly continues a sum that a matrix instruction has begun only in the very registers of
+    it, and reads operands that a vector instruction has written two wait states later at the earliest;
+  - where inline assembly names accumulation registers, nothing the compiler emits touches any."""
 import os
 import re
 import shutil
@@ -18,13 +21,13 @@ import pytest
 
 from paper_2508_21058_amd import build
 
-_REG = re.compile(r"(?<![\w.])([vsa])(?:\[(\d+):(\d+)\]|(\d+)(?!\w))")
+_REG = re.compile(r"(?<![\w.])([vsa])(?:\[(0x[0-9a-f]+|\d+)(?::(0x[0-9a-f]+|\d+))?\]|(\d+)(?!\w))")
 
 
 def _regs(text):
     out = set()
     for kind, lo, hi, one in _REG.findall(text):
-        out |= {(kind, i) for i in range(int(lo or one), int(hi or one) + 1)}
+        out |= {(kind, i) for i in range(int(lo or one, 0), int(hi or lo or one, 0) + 1)}
     return out
 
 
@@ -65,23 +68,24 @@ def _written_read(op, args):
 class _Pending:
     """What may be outstanding in front of an instruction, over all paths that lead to it."""
 
-    def __init__(self, matrix=(), scalar=(), vector=()):
+    def __init__(self, matrix=(), scalar=(), vector=(), operand=()):
         self.matrix = set(matrix)          # register tuples of matrix results nobody has waited for
         self.scalar = dict(scalar)         # scalar registers a vector instruction wrote: wait states since (< 5)
         self.vector = dict(vector)         # vector registers inline assembly wrote: wait states since (< 2)
+        self.operand = dict(operand)       # vector registers a vector instruction wrote: wait states since (< 2)
 
     def copy(self):
-        return _Pending(self.matrix, self.scalar, self.vector)
+        return _Pending(self.matrix, self.scalar, self.vector, self.operand)
 
     def merge(self, other):
-        out = _Pending(self.matrix | other.matrix, self.scalar, self.vector)
-        for mine, more in ((out.scalar, other.scalar), (out.vector, other.vector)):
+        out = _Pending(self.matrix | other.matrix, self.scalar, self.vector, self.operand)
+        for mine, more in ((out.scalar, other.scalar), (out.vector, other.vector), (out.operand, other.operand)):
             for r, age in more.items():
                 mine[r] = min(mine.get(r, age), age)
         return out
 
     def __eq__(self, other):
-        return other is not None and (self.matrix, self.scalar, self.vector) == (other.matrix, other.scalar, other.vector)
+        return other is not None and (self.matrix, self.scalar, self.vector, self.operand) == (other.matrix, other.scalar, other.vector, other.operand)
 
     def step(self, op, args, inline):
         """Moves past one instruction; returns what is wrong with it."""
@@ -89,7 +93,10 @@ class _Pending:
             return []
         written, read = _written_read(op, args)
         touched = {t for t in self.matrix if (written | read) & set(t)}
-        bad = ["touches a matrix result first"] if inline and touched else []
+        chained = tuple(sorted(written)) if inline and op.startswith("v_mfma") else None
+        bad = ["touches a matrix result first"] if inline and touched - {chained} else []
+        if chained and any(self.operand.get(r, 9) < 2 for r in read):
+            bad.append("reads an operand less than two wait states after a vector instruction wrote it")
         need = 2 if op.startswith("v_") else 5 if op.startswith(("global_", "buffer_", "flat_", "scratch_")) else 0
         if inline and any(self.scalar.get(r, 9) < need for r in read):
             bad.append(f"reads a scalar register less than {need} wait states after a vector instruction wrote it")
@@ -99,12 +106,17 @@ class _Pending:
         passed = int(args, 0) + 1 if op == "s_nop" else 1
         self.scalar = {r: n + passed for r, n in self.scalar.items() if n + passed < 5 and r not in written}
         self.vector = {r: n + passed for r, n in self.vector.items() if n + passed < 2 and r not in written}
+        self.operand = {r: n + passed for r, n in self.operand.items() if n + passed < 2 and r not in written}
+        if passed > 15:                    # as long as the longest matrix instruction here takes
+            self.matrix.clear()
         self.matrix -= touched
         if op.startswith("v_mfma"):
             self.matrix.add(tuple(sorted(written)))
         if op.startswith("v_"):
             self.scalar.update({r: 0 for r in written if r[0] == "s"})
             self.vector.update({r: 0 for r in written if r[0] == "v" and inline})
+            if not op.startswith("v_mfma"):
+                self.operand.update({r: 0 for r in written if r[0] == "v"})
         return bad
 
 
@@ -140,12 +152,23 @@ def _violations(ins):
     return sorted(bad)
 
 
+def _named_accumulators(ins):
+    """Compiler instructions that touch accumulation registers in a function whose inline assembly names some."""
+    def touches(op, args):
+        return op != "label" and any(r[0] == "a" for r in _regs(args))
+    if not any(inline and touches(op, args) for _, op, args, inline in ins):
+        return []
+    return [(no, op, args, "touches accumulation registers that inline assembly names")
+            for no, op, args, inline in ins if not inline and touches(op, args)]
+
+
 def _check(text):
-    return {f: v for f, ins in _kernels(text).items() if ins for v in [_violations(ins)] if v}
+    return {f: v for f, ins in _kernels(text).items() if ins for v in [_violations(ins) + _named_accumulators(ins)] if v}
 
 
 _MFMA = "\tv_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], 0\n"
 _ASM = "\t;;#ASMSTART\n\t%s\n\t;;#ASMEND\n"
+_SUM = "v_mfma_f32_32x32x16_bf16 a[0:0xf], v[16:19], v[20:23], a[0:0xf]"
 _BASE = "\tv_readfirstlane_b32 s8, v40\n\tv_readfirstlane_b32 s9, v41\n"
 _COPY = "s_mov_b32 m0, s4\n\ts_nop %d\n\tglobal_load_lds_dwordx4 v42, s[8:9]"
 
@@ -158,6 +181,13 @@ _COPY = "s_mov_b32 m0, s4\n\ts_nop %d\n\tglobal_load_lds_dwordx4 v42, s[8:9]"
     (_MFMA + "\ts_cbranch_execz .LBB0_1\n\tv_mov_b32_e32 v31, v3\n.LBB0_1:\n" + _ASM % "v_max_f32 v30, 0xff800000, v4", True),
     # round a loop
     ("\ts_mov_b32 s0, 0\n.LBB0_1:\n" + _ASM % "v_max_f32 v30, 0xff800000, v4" + _MFMA + "\ts_cbranch_scc1 .LBB0_1\n", True),
+    (_ASM % _SUM + _ASM % _SUM, False),
+    (_ASM % _SUM + _ASM % "v_accvgpr_read_b32 v30, a[3]", True),
+    (_ASM % _SUM + _ASM % "s_nop 15" + _ASM % "v_accvgpr_read_b32 v30, a[3]", False),
+    (_ASM % _SUM + _ASM % _SUM.replace("[0:0xf]", "[8:23]"), True),
+    ("\tv_mov_b32_e32 v20, v1\n" + _ASM % _SUM, True),
+    ("\tv_mov_b32_e32 v20, v1\n" + _ASM % ("s_nop 1\n\t" + _SUM), False),
+    (_ASM % _SUM + "\tv_accvgpr_write_b32 a200, v1\n", True),
     (_BASE + _ASM % (_COPY % 0), True),
     (_BASE + _ASM % (_COPY % 3), False),
     (_BASE + "\ts_add_u32 s8, s8, s6\n\ts_addc_u32 s9, s9, 0\n" + _ASM % (_COPY % 0), False),
@@ -172,7 +202,7 @@ def test_the_reader_sees_planted_faults(body, found):
 def test_no_unguarded_inline_assembly(tmp_path):
     def assemble(unit):
         out = str(tmp_path / (unit + ".s"))
-        subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, unit + ".hip"), "-o", out],
+        subprocess.run(["hipcc", *build.FLAGS, *build.UNIT_FLAGS.get(unit, []), "--cuda-device-only", "-S", os.path.join(build.CSRC, unit + ".hip"), "-o", out],
                        check=True, capture_output=True)
         return open(out).read()
 

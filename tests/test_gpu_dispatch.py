@@ -268,6 +268,42 @@ def test_routed_items_of_many_heads(chunk, caption, less, d, dtype):
     meta.close()
 
 
+# The key-stationary kernel of wide tiles (256 keys, or the last 160 to 255 of a chunk), which takes over at 1,408 of them or,
+# where it leaves a rest to the other kernel, 2,560: tiles on both sides of the least size, one to four filled waves, with a
+# rest and without, captions as such tiles, lists and windows of whole, partly filled and of few stages of 16 queries; with one
+# head less the other kernel takes all. Two heads are checked against dense float64.
+@pytest.mark.parametrize("chunk,caption,topk,less", [(159, 300, 2, 0), (160, 20, 2, 0), (193, 256, 3, 0), (256, 256, 2, 0),
+                                                     (256, 512, 2, 1), (257, 161, 2, 0), (415, 20, 1, 0), (416, 300, 2, 0),
+                                                     (512, 256, 0, 0), (700, 40, 3, 0)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_wide_key_tiles(chunk, caption, topk, less, dtype):
+    lay = mi.stream_layout(1, caption, 4 * chunk, chunk, "chunk")
+    N, lens = lay.N, np.diff(lay.offsets)
+    text = np.arange(lay.C) == 0
+    assert lens[0] == caption
+    segments = -(-N // (-(-N // 4))) if N > 1024 else -(-N // 256)
+    wide = [l // 256 + (l % 256 >= 160) for l in lens]
+    rest = [l - 256 * (l // 256) > 0 and not l % 256 >= 160 for l in lens]
+    items = sum(w * (segments if t else 1) for w, t in zip(wide, text))
+    H = -(-(2560 if any(rest) else 1408) // max(items, 8)) - less
+    g = torch.Generator(device="cuda").manual_seed(chunk)
+    q, k, v, d_o = (torch.randn(1, H, N, 128, generator=g, device="cuda").bfloat16().to(dtype) for _ in range(4))
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    _, sel = mb.route(meta, q, k, topk)
+    ws = mb.attn_workspace(meta, 1, H, 128, topk, dtype, True)
+    o, lse = mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
+    dq, dk, dv = mb.attn_bwd(meta, q, k, v, o, lse, d_o, sel, workspace=ws, after_fwd=True)
+    for h in (0, H - 1):
+        qn, kn, vn, dn = (x[0, h].double().cpu().numpy() for x in (q, k, v, d_o))
+        rows = sel[0, h].cpu().numpy() if topk else np.zeros((N, 0), dtype=np.int32)
+        ref = bf.dense_masked_attention(qn, kn, vn, bf.token_mask(lay, rows), dn)
+        for name, x in (("o", o), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv)):
+            check_close(name, x[0, h].double().cpu().numpy(), ref[name])
+    again = mb.attn_bwd(meta, q, k, v, o, lse, d_o, sel, workspace=ws)
+    assert all(torch.equal(x, y) for x, y in zip((dq, dk, dv), again))
+    meta.close()
+
+
 # regularised rows at the widths the kernel's lists are sized for (8 + 4, 16 + 4, 32) and one past each,
 # no routed chunk at all, nothing added, more requested than there are candidates
 @pytest.mark.parametrize("topk,max_in", [(8, 4), (8, 5), (7, 5), (16, 4), (16, 5), (0, 3), (20, 12), (32, 0), (1, 31)])
