@@ -146,11 +146,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_wide_kernel(KvArgs a) {
     };
     // Records, in LDS [stage & 15][group of four queries][lse2, delta, list word, spare: four each]. Every wave copies those of
     // the whole stage, a dword a lane (the four write the same words), so that it may read the list words as soon as its own
-    // copies have landed. Past the last stage the records are those of padding rows (lse2 = +inf: P = dS = 0), which name the
-    // head's first query: rows and records go out in every step, and a vmcnt bound counts whole stages.
+    // copies have landed. Padding rows, past the last stage too, repeat the last record of their window or list with lse2 = +inf
+    // (P = dS = 0): rows and records go out in every step, and a vmcnt bound counts whole stages. Zero times a NaN or an infinity
+    // is not zero, so a padding row may only be one that attends these keys anyway (its own would leave the same NaN there).
     const int rec_row = rlo * 4 + (lane & 3), rec_sel = ((lane >> 2) & 3) * 4;
     const uint32_t rec_off = (uint32_t)(rec_row * 16 + rec_sel);
-    const char *const inf_rec = reinterpret_cast<const char *>(a.stats2) + (size_t)a.BH * N * 16 + rec_sel;
+    const char *const inf_rec = reinterpret_cast<const char *>(a.stats2) + (size_t)a.BH * N * 16;
     const char *rec_ptr = reinterpret_cast<const char *>(a.stats2) + ((size_t)bh * N + item.q_start) * 16;
     const char *const rec_list = reinterpret_cast<const char *>(a.gstats2) + ((size_t)bh * N * a.topk + lbeg) * 16;
     int rec_left = item.q_len, rec_more = n_list;
@@ -162,7 +163,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_wide_kernel(KvArgs a) {
             copy4(rec_ptr, rec_off, dst);
         } else {
             if (rec_left <= 0 && rec_more > 0) { rec_ptr = rec_list; rec_left = rec_more; rec_more = 0; }
-            copy4(rec_row < rec_left ? rec_ptr + rec_off : inf_rec, dst);
+            // (past the last stage rec_left - 1 is negative and leads back to the last record)
+            const char *const at = rec_ptr + (min(rec_row, rec_left - 1) * 16 + rec_sel);
+            copy4(rec_row >= rec_left && rec_sel == 0 ? inf_rec : at, dst);
         }
         rec_ptr += RECB;
         rec_left -= R;

@@ -304,6 +304,35 @@ def test_wide_key_tiles(chunk, caption, topk, less, dtype):
     meta.close()
 
 
+# Padding rows of the wide tiles (the rest of the last stage of a window or a list, and the stages up to a whole turn of the ring):
+# a NaN or an infinity in one query's q or dO reaches the keys which that query attends and no others. The first query of the
+# stream is a caption's, so it attends the caption alone.
+@pytest.mark.parametrize("chunk", [256, 250])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_non_finite_rows_stay_with_their_keys(chunk, dtype):
+    lay = mi.stream_layout(1, 256, 4 * chunk, chunk, "chunk")
+    H, N, topk = 180, lay.N, 2             # eight wide tiles a head (four of them of the caption), no rest
+    g = torch.Generator(device="cuda").manual_seed(chunk)
+    q, k, v, d_o = (torch.randn(1, H, N, 128, generator=g, device="cuda").bfloat16().to(dtype) for _ in range(4))
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    _, sel = mb.route(meta, q, k, topk)
+    assert (sel[:, :, 0] == -1).all()
+
+    def grads(q, d_o):
+        o, lse = mb.attn_fwd(meta, q, k, v, sel)
+        return mb.attn_bwd(meta, q, k, v, o, lse, d_o, sel)[1:]
+
+    clean = grads(q, d_o)
+    for value in (float("nan"), float("inf")):
+        for which in (0, 1):
+            bad = [q.clone(), d_o.clone()]
+            bad[which][:, :, 0, 5] = value
+            for name, x, y in zip(("dk", "dv"), grads(*bad), clean):
+                assert torch.equal(x[:, :, 256:], y[:, :, 256:]), (name, value, which)
+                assert not torch.isfinite(x[:, :, :256]).all()
+    meta.close()
+
+
 # regularised rows at the widths the kernel's lists are sized for (8 + 4, 16 + 4, 32) and one past each,
 # no routed chunk at all, nothing added, more requested than there are candidates
 @pytest.mark.parametrize("topk,max_in", [(8, 4), (8, 5), (7, 5), (16, 4), (16, 5), (0, 3), (20, 12), (32, 0), (1, 31)])
