@@ -137,7 +137,8 @@ AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, boo
         const size_t rec = wide ? 16 : 8;              // bytes of a query's statistics (see store_stats)
         L.stats2 = take(((size_t)BH * N + 1) * rec);
         L.gstats2 = take((size_t)BH * N * std::max(topk, 1) * rec);
-        const size_t part = (size_t)BH * (wide ? m->tt_wide.n_partials * kWideTile : m->tt_all.n_partials * kKeyTile) * d * 4;
+        const size_t rows = wide ? (size_t)m->tt_wide.n_partials * kWideTile : (size_t)m->tt_all.n_partials * kKeyTile;
+        const size_t part = BH * rows * d * 4;
         L.tpart_k = take(part);
         L.tpart_v = take(part);
     }

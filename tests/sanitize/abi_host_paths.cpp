@@ -7,7 +7,7 @@
 #include <cstring>
 #include <vector>
 
-#include "../../include/moc.h"
+#include "../../paper_2508_21058_amd/csrc/moc_internal.h"
 
 static int g_checks = 0;
 #define EXPECT(cond)                                                            \
@@ -150,6 +150,18 @@ int main() {
         int32_t bad_span[2] = {3, 8};
         EXPECT(moc_outer_segments(C, off.data(), shot.data(), bad_span, 1, seg.data(), cap.data(), &P) == MOC_ERR_TEXT_SPAN);
         EXPECT(moc_outer_segments(C, off.data(), shot.data(), nullptr, 0, seg.data(), cap.data(), &P) == MOC_OK && P == 3);
+    }
+    // workspace sizes of very many caption partials, each at least 128 x 128 floats twice: past 2^31 rows nothing wraps
+    for (int rest = 0; rest < 2; ++rest) {
+        moc_meta m;                       // tables are not read
+        m.N = 1 << 20; m.C = 16; m.W = 16;
+        m.tt_all.n_partials = m.tt_wide.n_partials = (1 << 24) + 5;
+        m.kv_wide.n_items = rest ? 1 << 16 : 0;
+        size_t some = 0, more = 0;
+        EXPECT(moc_attn_workspace_bytes(&m, 1, 1, 128, 0, MOC_BF16, 1, &more) == MOC_OK);
+        m.tt_all.n_partials = m.tt_wide.n_partials = 5;
+        EXPECT(moc_attn_workspace_bytes(&m, 1, 1, 128, 0, MOC_BF16, 1, &some) == MOC_OK);
+        EXPECT(more - some >= ((size_t)1 << 24) * 128 * 128 * 4 * 2);
     }
     // profiling switches work without a device
     EXPECT(moc_prof_enable(0) == MOC_OK);

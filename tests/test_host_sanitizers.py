@@ -48,7 +48,8 @@ def test_abi_host_paths_under_address_and_undefined_sanitizers(tmp_path):
     others = [os.path.join(hb.OBJ, u + ".o") for u in hb.UNITS if u != "moc_api"]
     exe, drv = str(tmp_path / "abi_san"), str(tmp_path / "abi_host_paths.o")
     _run(["/opt/rocm/llvm/bin/clang++", "-O1", "-g", "-std=c++17", "-fsanitize=address,undefined",
-          "-fno-sanitize-recover=undefined", "-c", os.path.join(SAN, "abi_host_paths.cpp"), "-o", drv])
+          "-fno-sanitize-recover=undefined", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c",
+          os.path.join(SAN, "abi_host_paths.cpp"), "-o", drv])
     _run(["hipcc", "--offload-arch=gfx950", *san, drv, obj, *others, "-o", exe])
     r = _run([exe], env=ENV)
     _clean(r)
