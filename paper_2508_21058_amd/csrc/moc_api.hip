@@ -281,23 +281,23 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     const int W = int(wfirst.size());
 
     // forced-link key ranges per window: union of all text spans and the window's own tokens
+    std::vector<std::pair<int, int>> text;       // the spans, those that touch as one
+    for (int s = 0; s < T; ++s)
+        if (!text.empty() && spans[2 * s] <= text.back().second) text.back().second = spans[2 * s + 1];
+        else text.emplace_back(spans[2 * s], spans[2 * s + 1]);
     std::vector<int32_t> arange_off(W + 1, 0);
     std::vector<KeyRange> aranges;
     std::vector<AnchorTile> atiles;
+    aranges.reserve((size_t)W * (text.size() + 1));
+    atiles.reserve((size_t)N / kBM + W);
     for (int w = 0; w < W; ++w) {
-        std::vector<std::pair<int, int>> iv;
-        for (int s = 0; s < T; ++s) iv.emplace_back(spans[2 * s], spans[2 * s + 1]);
         const int ws = off[wfirst[w]], we = off[wlast[w] + 1];
-        iv.emplace_back(ws, we);
-        std::sort(iv.begin(), iv.end());
-        std::vector<std::pair<int, int>> merged;
-        for (auto &p : iv) {
-            if (!merged.empty() && p.first <= merged.back().second)
-                merged.back().second = std::max(merged.back().second, p.second);
-            else
-                merged.push_back(p);
-        }
-        for (auto &p : merged) aranges.push_back(KeyRange{p.first, p.second - p.first});
+        int lo = ws, hi = we;                    // the window and the spans that touch it
+        size_t s = 0;
+        for (; s < text.size() && text[s].second < lo; ++s) aranges.push_back(KeyRange{text[s].first, text[s].second - text[s].first});
+        for (; s < text.size() && text[s].first <= hi; ++s) { lo = std::min(lo, text[s].first); hi = std::max(hi, text[s].second); }
+        aranges.push_back(KeyRange{lo, hi - lo});
+        for (; s < text.size(); ++s) aranges.push_back(KeyRange{text[s].first, text[s].second - text[s].first});
         arange_off[w + 1] = int32_t(aranges.size());
         for (int q0 = ws; q0 < we; q0 += kBM) atiles.push_back(AnchorTile{q0, std::min(kBM, we - q0), w, 0});
     }
@@ -307,44 +307,26 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     // on one XCD and share those Q / dO rows in its L2 instead of each fetching them from HBM.
     const int seg = ((N + text_segments(N) - 1) / text_segments(N) + 31) / 32 * 32;   // equal segments of whole 32-query tiles
     const int nseg = (N + seg - 1) / seg;
-    std::vector<KvItem> kvitems[3];            // all, wide, rest
-    std::vector<TextTile> ttiles[2];           // all, wide and rest
-    KvList kv[3];
-    TextTiles tt[2];
-    for (int x = 0; x < 2; ++x) {
-        // the tiles of chunk j: f(first key, keys, list)
-        auto tiles_of = [&](int j, auto f) {
-            for (int k0 = off[j], len; k0 < off[j + 1]; k0 += len) {
-                const int left = off[j + 1] - k0;
-                const bool wide = x == 1 && left >= kWideMin;
-                len = std::min(wide ? kWideTile : kKeyTile, left);
-                f(k0, len, wide ? 1 : 2 * x);
-            }
-        };
-        std::vector<int> list_of;
-        for (int j = 0; j < C; ++j)
-            if (kind[j])
-                tiles_of(j, [&](int k0, int len, int l) {
-                    ttiles[x].push_back(TextTile{k0, len, tt[x].n_partials, nseg});
-                    list_of.push_back(l);
-                    tt[x].n_partials += nseg;
-                    ++kv[l].n_text_tiles;
-                });
-        tt[x].n = int32_t(ttiles[x].size());
-        for (int s = 0; s < nseg; ++s)
-            for (int t = 0; t < tt[x].n; ++t) {
-                const TextTile &w = ttiles[x][t];
-                kvitems[list_of[t]].push_back(KvItem{w.key_start, w.key_len, s * seg, std::min(seg, N - s * seg), -1,
-                                                     w.first_partial + s, 0, 0});
-            }
-        for (int l = 2 * x; l >= x; --l) kv[l].n_text = int32_t(kvitems[l].size());
-        for (int j = 0; j < C; ++j) {
-            if (kind[j]) continue;
-            const int ws = off[wfirst[win[j]]], we = off[wlast[win[j]] + 1];
-            tiles_of(j, [&](int k0, int len, int l) { kvitems[l].push_back(KvItem{k0, len, ws, we - ws, j, -1, 0, 0}); });
-        }
-        for (int l = 2 * x; l >= x; --l) kv[l].n_items = int32_t(kvitems[l].size());
+    // Two families: every tile of kKeyTile keys; tiles of kWideTile and what they leave (none of either where no chunk has a
+    // wide tile). They are counted first and then written where they are uploaded from.
+    KvList kv[3];                              // all, wide, rest
+    TextTiles tt[2];                           // all, wide and rest
+    long long n_text[3] = {}, n_video[3] = {};
+    for (int j = 0; j < C; ++j) {
+        const int len = off[j + 1] - off[j], left = len % kWideTile;
+        const int n[3] = {(len + kKeyTile - 1) / kKeyTile, len / kWideTile + (left >= kWideMin),
+                          left >= kWideMin ? 0 : (left + kKeyTile - 1) / kKeyTile};
+        for (int l = 0; l < 3; ++l) (kind[j] ? n_text : n_video)[l] += n[l];
     }
+    const int families = n_video[1] + n_text[1] > 0 ? 2 : 1;
+    for (int l = 0; l < 2 * families - 1; ++l) {
+        if (n_text[l] * nseg + n_video[l] > INT32_MAX) return fail(MOC_ERR_SHAPE, "too many caption key tiles");
+        kv[l].n_text_tiles = int32_t(n_text[l]);
+        kv[l].n_text = int32_t(n_text[l] * nseg);
+        kv[l].n_items = int32_t(kv[l].n_text + n_video[l]);
+        tt[(l + 1) / 2].n += kv[l].n_text_tiles;
+    }
+    for (TextTiles &t : tt) t.n_partials = t.n * nseg;
 
     std::vector<uint32_t> textmask((C + 31) / 32, 0u);
     for (int j = 0; j < C; ++j)
@@ -368,9 +350,9 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     const size_t o_off = take((size_t)(C + 1) * 4), o_kind = take((size_t)C * 4), o_win = take((size_t)C * 4),
                  o_wf = take((size_t)W * 4), o_wl = take((size_t)W * 4), o_aro = take((size_t)(W + 1) * 4),
                  o_ar = take(aranges.size() * sizeof(KeyRange)), o_at = take(atiles.size() * sizeof(AnchorTile)),
-                 o_kv[3] = {take(kvitems[0].size() * sizeof(KvItem)), take(kvitems[1].size() * sizeof(KvItem)),
-                            take(kvitems[2].size() * sizeof(KvItem))},
-                 o_tt[2] = {take(ttiles[0].size() * sizeof(TextTile)), take(ttiles[1].size() * sizeof(TextTile))},
+                 o_kv[3] = {take(kv[0].n_items * sizeof(KvItem)), take(kv[1].n_items * sizeof(KvItem)),
+                            take(kv[2].n_items * sizeof(KvItem))},
+                 o_tt[2] = {take(tt[0].n * sizeof(TextTile)), take(tt[1].n * sizeof(TextTile))},
                  o_tm = take(textmask.size() * 4), o_ntb = take((size_t)(C + 1) * 4), o_rw = take((size_t)C * 4),
                  o_vid = take((size_t)C * 4),
                  o_cof = take((size_t)N * 4);
@@ -385,8 +367,32 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     put(o_aro, arange_off.data(), (size_t)(W + 1) * 4);
     put(o_ar, aranges.data(), aranges.size() * sizeof(KeyRange));
     put(o_at, atiles.data(), atiles.size() * sizeof(AnchorTile));
-    for (int l = 0; l < 3; ++l) put(o_kv[l], kvitems[l].data(), kvitems[l].size() * sizeof(KvItem));
-    for (int x = 0; x < 2; ++x) put(o_tt[x], ttiles[x].data(), ttiles[x].size() * sizeof(TextTile));
+    for (int x = 0; x < families; ++x) {
+        TextTile *tile = reinterpret_cast<TextTile *>(host.data() + o_tt[x]);
+        KvItem *text[3], *video[3];            // next caption tile (of the first segment), next video item
+        for (int l = 0; l < 3; ++l) {
+            text[l] = reinterpret_cast<KvItem *>(host.data() + o_kv[l]);
+            video[l] = text[l] + kv[l].n_text;
+        }
+        for (int j = 0, n_partials = 0; j < C; ++j) {
+            const int ws = off[wfirst[win[j]]], we = off[wlast[win[j]] + 1];
+            for (int k0 = off[j], len; k0 < off[j + 1]; k0 += len) {
+                const int left = off[j + 1] - k0;
+                const bool wide = x == 1 && left >= kWideMin;
+                const int l = wide ? 1 : 2 * x;
+                len = std::min(wide ? kWideTile : kKeyTile, left);
+                if (!kind[j]) {
+                    *video[l]++ = KvItem{k0, len, ws, we - ws, j, -1, 0, 0};
+                    continue;
+                }
+                *tile++ = TextTile{k0, len, n_partials, nseg};
+                for (int s = 0; s < nseg; ++s)
+                    text[l][s * kv[l].n_text_tiles] = KvItem{k0, len, s * seg, std::min(seg, N - s * seg), -1, n_partials + s, 0, 0};
+                ++text[l];
+                n_partials += nseg;
+            }
+        }
+    }
     put(o_tm, textmask.data(), textmask.size() * 4);
     std::vector<int32_t> ntb(C + 1, 0);
     for (int j = 0; j < C; ++j) ntb[j + 1] = ntb[j] + (kind[j] ? 0 : 1);

@@ -44,6 +44,8 @@ int main() {
     std::vector<int32_t> w1{7, 8, 7}, w2{3, 3};
     EXPECT(meta_rc({0, 4, 9, 12}, {0, 0, 0}, &w1, {}) == MOC_ERR_WINDOW);
     EXPECT(meta_rc({0, 4, 9}, {0, 1}, &w2, {}) == MOC_ERR_WINDOW);
+    // 2^20 caption tiles of 2^13 segments: more items than their 32-bit count holds
+    EXPECT(meta_rc({0, 1 << 27}, {0}, nullptr, {0, 1 << 27}) == MOC_ERR_SHAPE);
     {
         moc_meta *m = nullptr;
         int32_t off[2] = {0, 4}, shot[1] = {0};
