@@ -314,8 +314,8 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     long long n_text[3] = {}, n_video[3] = {};
     for (int j = 0; j < C; ++j) {
         const int len = off[j + 1] - off[j], left = len % kWideTile;
-        const int n[3] = {(len + kKeyTile - 1) / kKeyTile, len / kWideTile + (left >= kWideMin),
-                          left >= kWideMin ? 0 : (left + kKeyTile - 1) / kKeyTile};
+        const bool wide = wide_tile(left, len);
+        const int n[3] = {(len + kKeyTile - 1) / kKeyTile, len / kWideTile + wide, wide ? 0 : (left + kKeyTile - 1) / kKeyTile};
         for (int l = 0; l < 3; ++l) (kind[j] ? n_text : n_video)[l] += n[l];
     }
     const int families = n_video[1] + n_text[1] > 0 ? 2 : 1;
@@ -378,7 +378,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
             const int ws = off[wfirst[win[j]]], we = off[wlast[win[j]] + 1];
             for (int k0 = off[j], len; k0 < off[j + 1]; k0 += len) {
                 const int left = off[j + 1] - k0;
-                const bool wide = x == 1 && left >= kWideMin;
+                const bool wide = x == 1 && wide_tile(left, off[j + 1] - off[j]);
                 const int l = wide ? 1 : 2 * x;
                 len = std::min(wide ? kWideTile : kKeyTile, left);
                 if (!kind[j]) {

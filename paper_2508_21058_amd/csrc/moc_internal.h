@@ -15,7 +15,14 @@ constexpr int kBM = 128;         // queries per workgroup in the query-stationar
 // Keys per workgroup in the key-stationary pass: 4 score waves of 32, or, where whole tiles of calls with many of them go
 // to the kernel of their own, 4 waves of 64.
 constexpr int kKeyTile = 128, kWideTile = 256;
-constexpr int kWideMin = 160;    // fewer keys left of a chunk go to the other kernel (two waves of 64 would idle)
+// Whether `left` keys, all a chunk has or what its earlier tiles left of it, make a wide tile. Alone they have to fill all four
+// waves. dK/dV of 24 heads, k = 4, 250 chunks of 160, 176, 192, 193, 208, 224 keys by the other kernel / as wide tiles: 1,335 / 1,364,
+// 1,464 / 1,458, 1,549 / 1,616, 1,721 / 1,621, 1,832 / 1,767, 1,956 / 1,889 us; 120 of 160, 176, 192, 208, 224 keys in one window, k = 1:
+// 10.4 / 11.9, 12.1 / 12.9, 13.2 / 14.0, 15.8 / 15.4, 16.9 / 16.5 ms; 32 captions of 160 keys and 64-key chunks, 454k tokens, six heads,
+// 18.5 / 20.5 ms. Behind a whole tile three waves do, as the other kernel would have two items for them in a second launch: 125
+// chunks of 416 keys 3,125 / 3,040 us, while 250 of them with the 160 keys left to the other kernel take 6,300 / 6,467.
+constexpr int kWideFirst = 193, kWideMin = 160;
+inline bool wide_tile(int left, int len) { return left >= (left == len ? kWideFirst : kWideMin); }
 // Queries per partial of a text key tile in the key-stationary pass. A caption tile is attended by all
 // N queries, so its items are the longest of the pass: a quarter of the stream keeps the longest item
 // well under a compute unit's share of short streams (6,256 tokens: a whole-stream item is 196 steps

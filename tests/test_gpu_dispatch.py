@@ -1,6 +1,8 @@
 """GPU parity at the edges of the launch rules: sizes where a rule picks another kernel, another split
 of the work list or another tile count. Oracle and tolerances as in test_gpu_parity (bf16 products with
 fp32 sums; the bounds there cover any order of the sums)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -268,27 +270,36 @@ def test_routed_items_of_many_heads(chunk, caption, less, d, dtype):
     meta.close()
 
 
-# The key-stationary kernel of wide tiles (256 keys, or the last 160 to 255 of a chunk), which takes over at 1,408 of them or,
-# where it leaves a rest to the other kernel, 2,560: tiles on both sides of the least size, one to four filled waves, with a
-# rest and without, captions as such tiles, lists and windows of whole, partly filled and of few stages of 16 queries; with one
-# head less the other kernel takes all. Two heads are checked against dense float64.
-@pytest.mark.parametrize("chunk,caption,topk,less", [(159, 300, 2, 0), (160, 20, 2, 0), (193, 256, 3, 0), (256, 256, 2, 0),
-                                                     (256, 512, 2, 1), (257, 161, 2, 0), (415, 20, 1, 0), (416, 300, 2, 0),
-                                                     (512, 256, 0, 0), (700, 40, 3, 0)])
+def _workspace_bytes(meta, H, topk, dtype, with_bwd=True):
+    n = ctypes.c_size_t()
+    assert mb.lib().moc_attn_workspace_bytes(meta.handle, 1, H, 128, topk, int(dtype == torch.float32), int(with_bwd), ctypes.byref(n)) == 0
+    return n.value
+
+
+def _first_wide_heads(meta, topk, dtype):
+    """The number of heads from which the library takes the wide key tiles: there the statistics become records of twice the
+    size, for all heads at once, and the workspace grows by more than one head's share. None: never."""
+    steps = np.diff([_workspace_bytes(meta, H, topk, dtype) for H in range(1, 1500)])
+    jumps = np.nonzero(steps > 1.5 * np.median(steps))[0]
+    assert len(jumps) <= 1
+    return int(jumps[0]) + 2 if len(jumps) else None
+
+
+# The key-stationary kernel of wide tiles (256 keys, or the last 160 to 255 of a chunk, 193 where it has no more): tiles on both
+# sides of the least sizes, of three and four filled waves, with a rest and without, captions as such tiles, lists and windows of
+# whole, partly filled and of few stages of 16 queries, at the least number of heads it takes a call of; with one head less the
+# other kernel takes all. Two heads are checked against dense float64.
+@pytest.mark.parametrize("chunk,caption,topk,less", [(159, 300, 2, 0), (192, 416, 2, 0), (193, 256, 3, 0), (256, 256, 2, 0),
+                                                     (256, 512, 2, 1), (257, 193, 2, 0), (415, 20, 1, 0), (416, 300, 2, 0),
+                                                     (416, 416, 1, 0), (512, 256, 0, 0), (700, 40, 3, 0), (700, 40, 3, 1)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_wide_key_tiles(chunk, caption, topk, less, dtype):
     lay = mi.stream_layout(1, caption, 4 * chunk, chunk, "chunk")
-    N, lens = lay.N, np.diff(lay.offsets)
-    text = np.arange(lay.C) == 0
-    assert lens[0] == caption
-    segments = -(-N // (-(-N // 4))) if N > 1024 else -(-N // 256)
-    wide = [l // 256 + (l % 256 >= 160) for l in lens]
-    rest = [l - 256 * (l // 256) > 0 and not l % 256 >= 160 for l in lens]
-    items = sum(w * (segments if t else 1) for w, t in zip(wide, text))
-    H = -(-(2560 if any(rest) else 1408) // max(items, 8)) - less
+    N = lay.N
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    H = _first_wide_heads(meta, topk, dtype) - less
     g = torch.Generator(device="cuda").manual_seed(chunk)
     q, k, v, d_o = (torch.randn(1, H, N, 128, generator=g, device="cuda").bfloat16().to(dtype) for _ in range(4))
-    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
     _, sel = mb.route(meta, q, k, topk)
     ws = mb.attn_workspace(meta, 1, H, 128, topk, dtype, True)
     o, lse = mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
@@ -301,6 +312,16 @@ def test_wide_key_tiles(chunk, caption, topk, less, dtype):
             check_close(name, x[0, h].double().cpu().numpy(), ref[name])
     again = mb.attn_bwd(meta, q, k, v, o, lse, d_o, sel, workspace=ws)
     assert all(torch.equal(x, y) for x, y in zip((dq, dk, dv), again))
+    meta.close()
+
+
+# A chunk with no more than 192 keys fills three of the kernel's four waves at most and goes to the other one, caption or not.
+@pytest.mark.parametrize("chunk,caption,wide", [(160, 160, False), (192, 192, False), (192, 20, False), (193, 20, True),
+                                                (20, 193, True), (159, 416, True)])
+def test_least_wide_key_tile(chunk, caption, wide):
+    lay = mi.stream_layout(1, caption, 4 * chunk, chunk, "chunk")
+    meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
+    assert (_first_wide_heads(meta, 2, torch.bfloat16) is not None) == wide
     meta.close()
 
 
