@@ -325,6 +325,41 @@ def test_least_wide_key_tile(chunk, caption, wide):
     meta.close()
 
 
+# A head of 4 GiB of rows and more: the wide tiles' copies of Q and dO take 64-bit offsets. The last chunk's queries choose the
+# first chunk and the one before the last in turn; the three, whose keys nobody else attends, are checked against dense float64.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_wide_key_tiles_of_a_long_head(dtype):
+    lens = [512] + [4096] * 4096 + [512, 512]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    C, N = len(lens), int(off[-1])
+    assert int(off[-3]) * 256 >= 1 << 32
+    chunks = np.arange(C, dtype=np.int32)
+    meta = mb.chunk_meta(off, np.zeros(C, np.int32), chunks, None)
+    # wide: a delta and two records of four words a query (and, with fp32 storage, its dO in bf16)
+    assert _workspace_bytes(meta, 1, 1, dtype) - _workspace_bytes(meta, 1, 1, dtype, False) >= N * (36 + 256 * (dtype == torch.float32))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v, d_o = (torch.randn(1, 1, N, 128, generator=g, device="cuda", dtype=torch.bfloat16).to(dtype) for _ in range(4))
+    sel = torch.full((1, 1, N, 1), -1, dtype=torch.int32, device="cuda")
+    sel[0, 0, off[-2]::2, 0] = 0
+    sel[0, 0, off[-2] + 1::2, 0] = C - 2
+    ws = mb.attn_workspace(meta, 1, 1, 128, 1, dtype, True)
+    o, lse = mb.attn_fwd(meta, q, k, v, sel, workspace=ws)
+    dq, dk, dv = mb.attn_bwd(meta, q, k, v, o, lse, d_o, sel, workspace=ws, after_fwd=True)
+
+    def pick(x):
+        return torch.cat([x[0, 0, :512], x[0, 0, off[-3]:]]).double().cpu().numpy()
+
+    lay = mi.Layout("three", np.arange(4, dtype=np.int32) * 512, np.zeros(3, np.int32), np.arange(3, dtype=np.int32), np.zeros((0, 2), np.int32))
+    rows = np.full((3 * 512, 1), -1, np.int32)
+    rows[1024::2], rows[1025::2] = 0, 1
+    ref = bf.dense_masked_attention(*(pick(x) for x in (q, k, v)), bf.token_mask(lay, rows), pick(d_o))
+    for name, x in (("o", o), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv)):
+        check_close(name, pick(x), ref[name])
+    meta.close()
+    del q, k, v, d_o, ws, o, lse, dq, dk, dv
+    torch.cuda.empty_cache()
+
+
 # Padding rows of the wide tiles (the rest of the last stage of a window or a list, and the stages up to a whole turn of the ring):
 # a NaN or an infinity in one query's q or dO reaches the keys which that query attends and no others. The first query of the
 # stream is a caption's, so it attends the caption alone.
