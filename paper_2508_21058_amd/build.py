@@ -26,8 +26,10 @@ UNIT_FLAGS = {"moc_attn_dkdv": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _deps():
+    """The newest of what every object depends on: the headers, and the flags in this file."""
     hdrs = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
     hdrs.append(os.path.join(HERE, "..", "include", "moc.h"))
+    hdrs.append(os.path.abspath(__file__))
     return max(os.path.getmtime(h) for h in hdrs)
 
 

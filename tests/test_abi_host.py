@@ -129,3 +129,21 @@ def test_outer_route_and_gather_reject_bad_arguments_on_the_host():
     assert lib.moc_gather_rows(1, 100, 64, None, 2, empty.ctypes.data, None, None, 0, None) == 0
     neg = np.array([[7, -1]], np.int32)
     assert lib.moc_gather_rows(1, 100, 64, fake, 1, neg.ctypes.data, fake, fake, 64, None) == -3
+
+
+def test_an_object_built_with_other_flags_is_not_reused(tmp_path, monkeypatch):
+    from paper_2508_21058_amd import build
+    (tmp_path / "moc_api.o").write_bytes(b"")
+    compiled = []
+
+    class Done:
+        returncode, stdout, stderr = 0, "", ""
+
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **kw: compiled.append(cmd) or Done)
+    build._compile("moc_api", False, build._deps())
+    assert not compiled
+    flags, mtime = os.path.abspath(build.__file__), os.path.getmtime
+    monkeypatch.setattr(build.os.path, "getmtime", lambda p: mtime(p) + 1e6 * (os.path.abspath(p) == flags))
+    build._compile("moc_api", False, build._deps())
+    assert len(compiled) == 1
