@@ -6,8 +6,9 @@ namespace moc {
 
 struct KvArgs {
     const void *q, *k, *v, *d_o;
-    const float *stats2;               // per query (lse * log2(e), delta); one extra pair (+inf, 0) at the end
-    const float *gstats2;              // the same pairs gathered in the order of the inverse lists
+    // per query (lse * log2(e), delta), an extra pair (+inf, 0) at the end; beside wide tiles records of four words (see store_stats)
+    const float *stats2;
+    const float *gstats2;              // the same gathered in the order of the inverse lists
     void *dk, *dv;
     float *tpart_k, *tpart_v;
     const KvItem *items;

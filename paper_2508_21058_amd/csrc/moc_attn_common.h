@@ -26,7 +26,7 @@ struct FwdArgs {
     // backward only
     const void *d_o;
     const float *lse, *delta;
-    const float *gstats2;   // [BH, N*topk] pairs (lse * log2 e, delta) in inverse-list order
+    const float *gstats2;   // [BH, N*topk] (lse * log2 e, delta) in inverse-list order: pairs, with `rec` the first two words of records
     // sums of the caption tiles' partials, which the last workgroups of the forced-link dQ launch make
     const float *tpart_k, *tpart_v;
     const TextTile *text_tiles;

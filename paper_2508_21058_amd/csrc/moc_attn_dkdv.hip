@@ -11,11 +11,13 @@
 // 260-key chunks (whose last four keys stay with the other kernel) 17.05 / 16.22, 33k tokens 3.20 / 3.04, six heads of 457k
 // tokens in 130-key chunks (captions only) 36.6 / 34.6.
 //
-// What bounds it is the issue of instructions, one every four cycles of a wave at best: 16 queries against 64 keys are 1,024
-// cycles of the matrix pipe and 225 instructions, 48 of them its own. Hence the step is written out in slots, and what
-// is issued in the shadow of which product matters: scheduling left to the compiler within a slot 13 % slower; LDS reads behind
-// the 16-cycle score products instead of the 32-cycle gradient product 3 %; a barrier every 16 queries instead of every 32 1 %.
-// The matrix pipe is busy 62 % of the cycles. Without the exponentials a timing-only build takes 5 % less, without the reads of V 6 %.
+// What bounds it is that a SIMD has one wave to issue from, an instruction every four cycles at best: 16 queries against 64
+// keys are 1,024 cycles of the matrix pipe and 225 instructions (900 cycles of issue), 48 of them its own, and take 1,550. On
+// 181,760 tokens it issues 56 % of its cycles, has an instruction that the pipe or its operands hold back 32 % and waits for copies
+// or a barrier 12 %; the matrix pipe is busy 66 % (63 % on 114k tokens of 260-key chunks, whose items are shorter). Hence the step
+// is written out in slots, and what is issued in the shadow of which product matters: scheduling left to the compiler within a slot
+// 13 % slower; LDS reads behind the 16-cycle score products instead of the 32-cycle gradient product 3 %; a barrier every 16 queries
+// instead of every 32 1 %. Without the exponentials a timing-only build takes 5 % less, without the reads of V 6 %.
 #include "moc_attn_bwd.h"
 
 namespace moc {
@@ -96,7 +98,8 @@ constexpr int AK = KB * DB * 16;                        // dV^T in a[0 ..], dK^T
 constexpr int NF = 2 * DB;                              // transposed fragments of a stage: dO, Q of feature block 0, 1 ..
 constexpr int J = 16;                                   // slots of a step: a gradient product, a pair of score products, a 64th of the exponentials
 constexpr int DG = 3;                                   // slots by which the gradient products of a stage reach into the next step
-constexpr int LA = 4, VA = 4;                           // slots between a transposed read, a read of V, and its first product
+constexpr int LA = 4;                                   // slots between a transposed read and its first product
+constexpr int VA = 4;                                   // fragments of V held: each is read VA - 1 slots ahead
 static_assert(NF * KB == J && NB * KS == J && NB * 4 == J && LDS <= 160 * 1024);
 }  // namespace wide
 

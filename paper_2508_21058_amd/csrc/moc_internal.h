@@ -145,14 +145,19 @@ hipError_t launch_probe(int kind, void *buf, size_t bytes, int iters, hipStream_
 // Whether the key-stationary pass takes the wide tiles: only with heads of 128 features, and where the items are many rounds
 // of the chip, since they are twice as long as the others', and more where a second launch has to take what they leave.
 // dK/dV without them / with them, at so many wide items, us. Nothing left: 546 items (23k tokens, six heads, 1,280-key
-// chunks) 3,180 / 3,455, 576 (6k, 24 heads, 256-key) 291 / 312, 1,456 (23k, 16 heads, 256-key) 926 / 912, 1,512 (16k, 24
-// heads, 1,280-key) 1,402 / 1,325, 2,184 (23k, 24 heads, 1,280-key) 11,557 / 10,635. With a rest: 660 (14k, 12 heads,
-// 260-key) 613 / 672, 1,320 (29k, 12 heads, 260-key) 1,698 / 1,774, 2,208 (57k, 12 heads, 312-key) 3,019 / 3,166, 2,976
-// (41k, 24 heads, ragged) 3,322 / 3,219, 7,008 (57k, 24 heads, 195-key) 5,687 / 5,269.
+// chunks) 3,180 / 3,455, 576 (6k, 24 heads, 256-key) 291 / 312, 720, 996 and 1,248 (15k to 27k, twelve heads, 256-key) 304 / 330,
+// 403 / 462 and 517 / 495, 1,456 (23k, 16 heads, 256-key) 926 / 912, 1,512 (16k, 24 heads, 1,280-key) 1,402 / 1,325, 2,184 (23k, 24
+// heads, 1,280-key) 11,557 / 10,635. With a rest: 660 (14k, 12 heads, 260-key) 613 / 672, 1,320 (29k, 12 heads, 260-key) 1,698 / 1,774,
+// 2,208 (57k, 12 heads, 312-key) 3,019 / 3,166, 2,976 (41k, 24 heads, ragged) 3,322 / 3,219, 7,008 (57k, 24 heads, 195-key) 5,687 / 5,269.
+// The line does not look at how much of the work the rest is. Where that is much, either kernel may be ahead by a part of a round
+// (24 heads, k = 4, own-chunk windows, 2,640 and 6,000 items: chunks of 256 and 128 keys in turn 1,099 / 1,172 and 2,435 / 2,495, of 256
+// and 130 1,642 / 1,436 and 4,288 / 3,316, of 256 and eight times 64 1,819 / 1,859 and 4,186 / 4,284, of 256, 64 and 64 1,071 / 936 and
+// 2,490 / 2,121; 2,640 of them in one window 38,028 / 37,601, 45,354 / 45,405, 202,330 / 187,856 and 43,313 / 42,002).
 constexpr int kWideItems = 1408, kWideItemsRest = 2560;
 inline bool wide_tiles(const moc_meta *m, int BH, int d) {
     return d == 128 && (long long)m->kv_wide.n_items * BH >= (m->kv_rest.n_items > 0 ? kWideItemsRest : kWideItems);
 }
+
 // Layout of the attention workspace (byte offsets); shared by fwd and bwd.
 struct AttnWs {
     size_t cnt, list_off, tile_off, vmask, gsum, cnt_blk, qlist, plse, po, cnt_fine, cvt, delta, stats2, gstats2, tpart_k, tpart_v, total;

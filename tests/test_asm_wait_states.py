@@ -93,6 +93,7 @@ class _Pending:
             return []
         written, read = _written_read(op, args)
         touched = {t for t in self.matrix if (written | read) & set(t)}
+        # (a product into the registers of another goes on with its sum: the ones here name them as their third operand too)
         chained = tuple(sorted(written)) if inline and op.startswith("v_mfma") else None
         bad = ["touches a matrix result first"] if inline and touched - {chained} else []
         if chained and any(self.operand.get(r, 9) < 2 for r in read):
@@ -107,7 +108,7 @@ class _Pending:
         self.scalar = {r: n + passed for r, n in self.scalar.items() if n + passed < 5 and r not in written}
         self.vector = {r: n + passed for r, n in self.vector.items() if n + passed < 2 and r not in written}
         self.operand = {r: n + passed for r, n in self.operand.items() if n + passed < 2 and r not in written}
-        if passed > 15:                    # as long as the longest matrix instruction here takes
+        if passed > 15:                    # outlasts the products here, of eight passes at most (32x32x16 in bf16); not one of sixteen
             self.matrix.clear()
         self.matrix -= touched
         if op.startswith("v_mfma"):
