@@ -133,7 +133,7 @@ AttnWs attn_ws_layout(const moc_meta *m, int BH, int d, int topk, int dtype, boo
     if (dtype == MOC_F32) L.cvt = take((size_t)BH * N * d * 2 * (with_bwd ? 4 : 3));   // bf16 copies of q, k, v (and dO)
     if (with_bwd) {
         L.delta = take((size_t)BH * N * 4);
-        const bool wide = wide_tiles(m, BH, d);
+        const bool wide = wide_tiles(m, BH, d, topk);
         const size_t rec = wide ? 16 : 8;              // bytes of a query's statistics (see store_stats)
         L.stats2 = take(((size_t)BH * N + 1) * rec);
         L.gstats2 = take((size_t)BH * N * std::max(topk, 1) * rec);
@@ -311,12 +311,18 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     // wide tile). They are counted first and then written where they are uploaded from.
     KvList kv[3];                              // all, wide, rest
     TextTiles tt[2];                           // all, wide and rest
-    long long n_text[3] = {}, n_video[3] = {};
+    long long n_text[3] = {}, n_video[3] = {}, wide_queries[2] = {};
+    int32_t wide_video[2] = {};
     for (int j = 0; j < C; ++j) {
         const int len = off[j + 1] - off[j], left = len % kWideTile;
-        const bool wide = wide_tile(left, len);
+        const bool wide = left >= kWideMin;
         const int n[3] = {(len + kKeyTile - 1) / kKeyTile, len / kWideTile + wide, wide ? 0 : (left + kKeyTile - 1) / kKeyTile};
         for (int l = 0; l < 3; ++l) (kind[j] ? n_text : n_video)[l] += n[l];
+        const int ragged = wide && left < kWideFull;       // the last wide tile fills three waves
+        const long long queries = kind[j] ? N : off[wlast[win[j]] + 1] - off[wfirst[win[j]]];
+        wide_queries[0] += (n[1] - ragged) * queries;
+        wide_queries[1] += ragged * queries;
+        if (!kind[j]) { wide_video[0] += n[1] - ragged; wide_video[1] += ragged; }
     }
     const int families = n_video[1] + n_text[1] > 0 ? 2 : 1;
     for (int l = 0; l < 2 * families - 1; ++l) {
@@ -378,7 +384,7 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
             const int ws = off[wfirst[win[j]]], we = off[wlast[win[j]] + 1];
             for (int k0 = off[j], len; k0 < off[j + 1]; k0 += len) {
                 const int left = off[j + 1] - k0;
-                const bool wide = x == 1 && wide_tile(left, off[j + 1] - off[j]);
+                const bool wide = x == 1 && left >= kWideMin;
                 const int l = wide ? 1 : 2 * x;
                 len = std::min(wide ? kWideTile : kKeyTile, left);
                 if (!kind[j]) {
@@ -422,6 +428,8 @@ int moc_chunk_meta(int32_t N, int32_t C, const int32_t *off, const int32_t *shot
     for (int x = 0; x < 2; ++x) tt[x].d = reinterpret_cast<TextTile *>(base + o_tt[x]);
     m->kv_all = kv[0]; m->kv_wide = kv[1]; m->kv_rest = kv[2];
     m->tt_all = tt[0]; m->tt_wide = tt[1];
+    for (int i = 0; i < 2; ++i) { m->wide_queries[i] = wide_queries[i]; m->wide_video[i] = wide_video[i]; }
+    m->n_video = ntb[C];
     m->d_textmask = reinterpret_cast<uint32_t *>(base + o_tm);
     m->d_ntb = reinterpret_cast<int32_t *>(base + o_ntb);
     m->d_rwin = reinterpret_cast<int32_t *>(base + o_rw);

@@ -1255,7 +1255,7 @@ hipError_t launch_attn_bwd(const moc_meta *m, int BH, int d, int dtype, const vo
     kv.tpart_k = reinterpret_cast<float *>(ws + L.tpart_k);
     kv.tpart_v = reinterpret_cast<float *>(ws + L.tpart_v);
     kv.list_off = a.list_off; kv.qlist = a.qlist;
-    const bool wide = wide_tiles(m, BH, d);
+    const bool wide = wide_tiles(m, BH, d, topk);
     const TextTiles &tt = wide ? m->tt_wide : m->tt_all;
     kv.N = m->N; kv.C = m->C; kv.topk = topk; kv.n_partials = tt.n_partials; kv.BH = BH;
     a.join = text_join(m->N, tt.n, BH, tt.n > 0 ? tt.n_partials / tt.n : 0);

@@ -1,4 +1,4 @@
-// dK / dV of whole key tiles (256 keys of one chunk, or its last 160 to 255; see wide_tile), heads of 128 features: the key-stationary pass for calls with
+// dK / dV of whole key tiles (256 keys of one chunk, or its last 160 to 255), heads of 128 features: the key-stationary pass for calls with
 // many of them. The ragged rest of such calls, heads of 64 features and small calls take attn_bwd_dkdv_pipe_kernel.
 //
 // A workgroup is four waves, one per SIMD with all 512 of its registers: a wave owns 64 keys, holds their dK^T and dV^T

@@ -15,14 +15,8 @@ constexpr int kBM = 128;         // queries per workgroup in the query-stationar
 // Keys per workgroup in the key-stationary pass: 4 score waves of 32, or, where whole tiles of calls with many of them go
 // to the kernel of their own, 4 waves of 64.
 constexpr int kKeyTile = 128, kWideTile = 256;
-// Whether `left` keys, all a chunk has or what its earlier tiles left of it, make a wide tile. Alone they have to fill all four
-// waves. dK/dV of 24 heads, k = 4, 250 chunks of 160, 176, 192, 193, 208, 224 keys by the other kernel / as wide tiles: 1,335 / 1,364,
-// 1,464 / 1,458, 1,549 / 1,616, 1,721 / 1,621, 1,832 / 1,767, 1,956 / 1,889 us; 120 of 160, 176, 192, 208, 224 keys in one window, k = 1:
-// 10.4 / 11.9, 12.1 / 12.9, 13.2 / 14.0, 15.8 / 15.4, 16.9 / 16.5 ms; 32 captions of 160 keys and 64-key chunks, 454k tokens, six heads,
-// 18.5 / 20.5 ms. Behind a whole tile three waves do, as the other kernel would have two items for them in a second launch: 125
-// chunks of 416 keys 3,125 / 3,040 us, while 250 of them with the 160 keys left to the other kernel take 6,300 / 6,467.
-constexpr int kWideFirst = 193, kWideMin = 160;
-inline bool wide_tile(int left, int len) { return left >= (left == len ? kWideFirst : kWideMin); }
+constexpr int kWideMin = 160;    // fewer keys left of a chunk go to the other kernel (one of four waves of 64 would idle, another be half empty)
+constexpr int kWideFull = 193;   // from here on a wide tile fills all four waves
 // Queries per partial of a text key tile in the key-stationary pass. A caption tile is attended by all
 // N queries, so its items are the longest of the pass: a quarter of the stream keeps the longest item
 // well under a compute unit's share of short streams (6,256 tokens: a whole-stream item is 196 steps
@@ -101,6 +95,9 @@ struct moc_meta {
     moc::AnchorTile *d_atiles = nullptr;
     moc::KvList kv_all, kv_wide, kv_rest;      // every tile of kKeyTile keys; tiles of kWideTile, and what they leave
     moc::TextTiles tt_all, tt_wide;            // caption tiles of kv_all; of kv_wide and kv_rest
+    int64_t wide_queries[2] = {};              // forced queries of the wide tiles of kWideFull keys and more, and of the others
+    int32_t wide_video[2] = {};                // ... and how many of them are not captions'
+    int32_t n_video = 0;                       // chunks that are not captions
     std::vector<int32_t> h_off, h_kind, h_win;
 };
 
@@ -154,8 +151,17 @@ hipError_t launch_probe(int kind, void *buf, size_t bytes, int iters, hipStream_
 // and 130 1,642 / 1,436 and 4,288 / 3,316, of 256 and eight times 64 1,819 / 1,859 and 4,186 / 4,284, of 256, 64 and 64 1,071 / 936 and
 // 2,490 / 2,121; 2,640 of them in one window 38,028 / 37,601, 45,354 / 45,405, 202,330 / 187,856 and 43,313 / 42,002).
 constexpr int kWideItems = 1408, kWideItemsRest = 2560;
-inline bool wide_tiles(const moc_meta *m, int BH, int d) {
-    return d == 128 && (long long)m->kv_wide.n_items * BH >= (m->kv_rest.n_items > 0 ? kWideItemsRest : kWideItems);
+// A tile of three filled waves costs what a full one does. On long contiguous streams of queries that is more than the two items of the
+// other kernel it stands for: 24 heads, 120 chunks of 160, 176, 192 keys in one window, k = 1, 10.3 / 11.6, 11.8 / 12.6, 13.1 / 13.9 ms (208 and
+// 224 keys 15.8 / 15.4, 16.9 / 16.5); 32 captions of 160 keys and 130-key chunks, 454k tokens, six heads, 19.8 / 21.7. On gathered lists it is
+// less: windows of a chunk, k = 4, 250 chunks of them 1,353 / 1,322, 1,489 / 1,419, 1,565 / 1,564 us. So the queries that full tiles stream,
+// and half of those in the lists of the others, have to be as many as there are in the windows of the others. With 16 captions of 256 keys,
+// 229k tokens, twelve heads, 160-, 180- and 192-key chunks 14.0 / 13.0, 13.9 / 12.9, 13.8 / 12.8 ms, k = 16 20.7 / 20.7, 21.3 / 20.6, 21.2 / 20.6; in
+// windows of 14k tokens, which the line leaves to the other kernel, 55.8 / 57.0, 54.3 / 53.1, 51.8 / 50.7.
+inline bool wide_tiles(const moc_meta *m, int BH, int d, int topk) {
+    if (d != 128 || (long long)m->kv_wide.n_items * BH < (m->kv_rest.n_items > 0 ? kWideItemsRest : kWideItems)) return false;
+    const long long list = m->n_video > 0 ? (long long)m->N * topk / m->n_video : 0;        // of a chunk, on average
+    return 2 * (m->wide_queries[0] + m->wide_video[0] * list) + m->wide_video[1] * list >= 2 * m->wide_queries[1];
 }
 
 // Layout of the attention workspace (byte offsets); shared by fwd and bwd.

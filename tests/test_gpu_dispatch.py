@@ -285,12 +285,12 @@ def _first_wide_heads(meta, topk, dtype):
     return int(jumps[0]) + 2 if len(jumps) else None
 
 
-# The key-stationary kernel of wide tiles (256 keys, or the last 160 to 255 of a chunk, 193 where it has no more): tiles on both
-# sides of the least sizes, of three and four filled waves, with a rest and without, captions as such tiles, lists and windows of
-# whole, partly filled and of few stages of 16 queries, at the least number of heads it takes a call of; with one head less the
-# other kernel takes all. Two heads are checked against dense float64.
-@pytest.mark.parametrize("chunk,caption,topk,less", [(159, 300, 2, 0), (192, 416, 2, 0), (193, 256, 3, 0), (256, 256, 2, 0),
-                                                     (256, 512, 2, 1), (257, 193, 2, 0), (415, 20, 1, 0), (416, 300, 2, 0),
+# The key-stationary kernel of wide tiles (256 keys, or the last 160 to 255 of a chunk): tiles on both sides of the least size, of
+# three and four filled waves, with a rest and without, captions as such tiles, lists and windows of whole, partly filled and of few
+# stages of 16 queries, at the least number of heads it takes a call of; with one head less the other kernel takes all. Two heads
+# are checked against dense float64.
+@pytest.mark.parametrize("chunk,caption,topk,less", [(159, 300, 2, 0), (160, 20, 2, 0), (192, 512, 1, 0), (193, 256, 3, 0), (256, 256, 2, 0),
+                                                     (256, 512, 2, 1), (257, 161, 2, 0), (415, 20, 1, 0), (416, 300, 2, 0),
                                                      (416, 416, 1, 0), (512, 256, 0, 0), (700, 40, 3, 0), (700, 40, 3, 1)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_wide_key_tiles(chunk, caption, topk, less, dtype):
@@ -315,13 +315,16 @@ def test_wide_key_tiles(chunk, caption, topk, less, dtype):
     meta.close()
 
 
-# A chunk with no more than 192 keys fills three of the kernel's four waves at most and goes to the other one, caption or not.
-@pytest.mark.parametrize("chunk,caption,wide", [(160, 160, False), (192, 192, False), (192, 20, False), (193, 20, True),
-                                                (20, 193, True), (159, 416, True)])
-def test_least_wide_key_tile(chunk, caption, wide):
+# Tiles of 160 to 192 keys fill three of the kernel's four waves: it takes a call only if fuller ones, or half of their own lists, stream as many
+# queries as their windows have (a caption's is the stream of N = 4 * chunk + caption queries; the lists have N * topk in all).
+@pytest.mark.parametrize("chunk,caption,topk,wide", [(160, 160, 0, False), (192, 192, 2, False), (160, 20, 1, False), (160, 20, 2, True),
+                                                     (192, 20, 1, False), (192, 20, 2, True), (193, 20, 0, True), (20, 192, 2, False),
+                                                     (20, 193, 2, True), (159, 416, 2, True), (192, 256, 0, True), (416, 20, 3, True),
+                                                     (256, 192, 0, False), (256, 192, 1, True), (193, 192, 0, False), (193, 192, 1, True)])
+def test_three_filled_waves_beside_four(chunk, caption, topk, wide):
     lay = mi.stream_layout(1, caption, 4 * chunk, chunk, "chunk")
     meta = mb.chunk_meta(lay.offsets, lay.shot, lay.window, lay.text_spans)
-    assert (_first_wide_heads(meta, 2, torch.bfloat16) is not None) == wide
+    assert (_first_wide_heads(meta, topk, torch.bfloat16) is not None) == wide
     meta.close()
 
 
