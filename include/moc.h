@@ -55,7 +55,7 @@ typedef enum moc_dtype {
 typedef enum moc_status {
     MOC_OK = 0,
     MOC_ERR_NULL = -1,      /* a required pointer is NULL */
-    MOC_ERR_SHAPE = -2,     /* N, C, B, H <= 0; d not in {64,128}; topk out of range; N*topk overflow */
+    MOC_ERR_SHAPE = -2,     /* N, C, B, H <= 0; d not in {64,128}; topk out of range; N*topk overflow; 2^31 work items of captions */
     MOC_ERR_OFFSETS = -3,   /* chunk_offsets not strictly increasing from 0 to N */
     MOC_ERR_TEXT_SPAN = -4, /* a text span is empty, out of range, overlapping, unsorted or not chunk-aligned */
     MOC_ERR_WINDOW = -5,    /* equal window ids not contiguous, or a window spans two shots */
